@@ -29,8 +29,9 @@ def listed():
     return [
         # the 2x5 ladder workload as it stands: the smallest call, one state on one compute unit
         {"name": "ladder_2x5_c64", "kind": "evolve", "net": "ladder", "M": 10, "prec": "c64", "dt": 0.05, "steps": 400},
-        # the dipolar star of the Fig. 3(b) check (every pair, I^z I^z phases, 14 sites) over its 250 steps
-        {"name": "dipolar_star14_c64", "kind": "evolve", "net": "dipolar", "M": 14, "prec": "c64", "dt": 0.02, "steps": 250},
+        # the dipolar star of the Fig. 3(b) check (every pair, I^z I^z phases, 14 sites), its first steps: over all 250
+        # the rounding of the single-precision phases adds up to 2.5e-5 of the state, too much to compare two runs by
+        {"name": "dipolar_star14_c64", "kind": "evolve", "net": "dipolar", "M": 14, "prec": "c64", "dt": 0.02, "steps": 40},
         # one disorder realisation of the star in double precision, a size between the tested ones
         {"name": "star17_c128", "kind": "evolve", "net": "star", "M": 17, "prec": "c128", "dt": 0.02, "steps": 100},
         # the 2x9 ladder whose random-phase curve is compared with the ensemble
@@ -78,6 +79,9 @@ def draw(rng):
         M -= M % 2
     # long runs of small states, short runs of large ones
     most = max(3, min(400, 2 ** (29 - M) if dense else 2 ** (33 - M)))
+    if net in ("chain", "dipolar"):
+        # I^z I^z phases: single-precision rounding grows with the number of factors (see the listed dipolar star)
+        most = max(3, min(most, 7500 // (M * (M - 1) if dense else 2 * M)))
     return {"kind": kind, "net": net, "M": M, "prec": prec, "dt": 0.02 if dense else 0.05, "steps": _log(rng, max(2, most // 16), most)}
 
 
