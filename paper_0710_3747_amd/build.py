@@ -15,8 +15,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(OUT_DIR, "libspinqp.so")
-SOURCES = ["kernels.hip", "noalloc.hip", "planner.cpp", "abi.cpp", "batch.cpp", "autotune.cpp",
-           "ensemble.cpp"]
+# kernels.hip is compiled once per part (template families), in parallel
+KERNEL_PARTS = 8
+SOURCES = [f"kernels.hip:{n}" for n in range(KERNEL_PARTS)] + [
+    "noalloc.hip", "planner.cpp", "abi.cpp", "batch.cpp", "autotune.cpp", "ensemble.cpp"]
 ARCH = os.environ.get("SPINQP_ARCH", "gfx950")
 
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -36,10 +38,12 @@ def build(verbose: bool = False) -> str:
     os.makedirs(OUT_DIR, exist_ok=True)
     objs = []
     procs = []
-    for src in SOURCES:
-        obj = os.path.join(OUT_DIR, os.path.splitext(src)[0] + ".o")
+    for entry in SOURCES:
+        src, _, part = entry.partition(":")
+        obj = os.path.join(OUT_DIR, os.path.splitext(src)[0] + (f"_{part}" if part else "") + ".o")
         if src.endswith(".hip"):
-            cmd = [hipcc(), *HIP_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+            defs = [f"-DSPIN_PART={part}"] if part else []
+            cmd = [hipcc(), *HIP_FLAGS, *defs, "-c", os.path.join(CSRC, src), "-o", obj]
         else:   # host-only C++ (HIP runtime API, no device code)
             cmd = [hipcc(), "-O2", "-std=c++17", "-fPIC", "-Wall", "-c", os.path.join(CSRC, src),
                    "-o", obj]

@@ -239,6 +239,7 @@ static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, const 
             pp.c = sh.c;
             pp.profile = key.profile != 0;
             pp.half = sh.half;
+            pp.gates = sh.half ? kMaxGates : 0;
             if (pp.profile) pp.max_meas = kMaxMeasProfile;
             dp->sp = plan_stream_best(key.M, J, key.dt, key.n_steps, key.observed, key.merge != 0, pp);
             dp->shape = PassShape{sh.r, sh.nt};
@@ -842,6 +843,7 @@ int host_plan(int32_t prec, int32_t M, const std::vector<Coupling>& Jv, double d
             pp.c = hp->sh.c;
             pp.profile = profile;
             pp.half = hp->sh.half;
+            pp.gates = hp->sh.half ? kMaxGates : 0;
             if (profile) pp.max_meas = kMaxMeasProfile;
             hp->sp = plan_stream_best(M, Jv, dt, n_steps, observed, merge, pp);
         }

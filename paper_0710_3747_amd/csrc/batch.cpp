@@ -304,6 +304,7 @@ static int batch_build(const spin_problem* probs, const std::vector<int>& sel,
             // variant (plan_stream), not the single path's variant search
             pp.c = 4;
             pp.half = half;
+            pp.gates = half ? kMaxGates : 0;
             StreamPlan sp = plan_stream(pr.M, Js[p], dt, n_steps, pr.observed_site, true, pp);
             b.pass0 = int(tb.passes.size());
             for (const HostPass& hp : sp.passes) encode_pass<T>(hp, pr.M, pr.observed_site, tb);

@@ -22,8 +22,15 @@ constexpr int kMaxMeasProfile = 64; // per-site observables one pass can hold (a
 // Op codes.  A two-spin factor on register bits (qa < qb) of a stage has
 // code qa*8 + qb; kOpZZ is or-ed in when the factor carries an I^z I^z
 // phase.  kOpMeas accumulates the observable of the state at that point.
+// Code (6 + g)*8 + q exchanges register bit q with lane bit 4 + g (g = 0, 1):
+// register q = 1 of the lanes with the lane bit clear trades places with
+// register q = 0 of the lanes with it set, so the site on the lane bit
+// becomes a register site and the other way round, without LDS.
 constexpr int32_t kOpZZ = 64;
 constexpr int32_t kOpMeas = 255;
+// Ends every stage's ops (not counted in DevStage::nop).
+constexpr int32_t kOpEnd = 253;
+constexpr int kMaxGates = 2;        // lane bits 4 and 5
 // kOpMat (matrix engine, 32 registers per lane): multiply the lane's
 // registers by a dense 32 x 32 complex matrix, the product of consecutive
 // factors of the stage, on MFMA.  aux = index of the matrix in the matrix
@@ -37,34 +44,41 @@ constexpr int kMatFloats = 64 * 64;
 // (A, B) = (sum a*tau, sum b*tau) over the merged two-spin propagators:
 //   theta = B/2, t = tan(theta/2), s = sin(theta)     (three-shear rotation)
 //   (pr, pi) = exp(+i A/4)                             (anti-aligned phase)
-// For kOpMeas, aux is the measurement slot of the pass (resident kernels:
-// unused).  In all-site profile plans every site has its own kOpMeas and
-// aux = slot | kind << 6 | index << 8 | (norm slot + 1) << 14 | site << 17:
-// the site's bit is thread bit `index` of the stage (kind 0), register bit
-// `index` (kind 1) or global address bit `index` of the tile base (kind 2);
-// norm slot + 1 = 0 when this observable does not also carry the norm.
+// For kOpMeas, aux = slot | kind << 6 | index << 8: the observed site's bit is
+// thread bit `index` (kind 0), register bit `index` (kind 1) or global address
+// bit `index` of the tile base (kind 2) at that point of the stage; slot is
+// the pass's measurement slot (one-workgroup kernels: unused).  In all-site
+// profile plans every site has its own kOpMeas and aux also holds
+// (norm slot + 1) << 14 | site << 17; norm slot + 1 = 0 when this observable
+// does not also carry the norm.
+// 32 (48) bytes, so that a record is one aligned scalar load.
 template <typename T>
-struct DevOp {
+struct alignas(sizeof(T) == 4 ? 32 : 16) DevOp {
+    T t, s, pr, pi;
     int32_t code;
     int32_t aux;
-    T t, s, pr, pi;
 };
 
 // One stage: the amplitudes of a tile are gathered from LDS into registers
-// with register bit q <-> tile-local position rpos[q], the stage's ops run
-// on registers, and the registers are scattered back.
+// (thread bit q and register bit q of a lane hold one tile-local position
+// each), the stage's ops run on registers, and the registers are scattered
+// back.  Ops that exchange a register bit with lane bit 4 or 5 leave other
+// positions there: gw/gr and gt_in/gr_in describe the stage's entry,
+// gt_out/gr_out its exit.  tmask/rbit are the layout of whole-tile passes and
+// of the one-workgroup kernel (bits xor-ed).
 struct DevStage {
     int32_t op0, nop;         // op range
-    int32_t ntb;              // number of thread bits (tile bits - register bits)
-    int32_t obs_tq;           // thread bit holding the observed site, or -1
-    int32_t obs_mask;         // register-index mask of the observed site (0 if none)
     int32_t xnext;            // 1: the exchange after this stage moves amplitudes between
                               // waves (workgroup barrier); 0: within each wave only
-    uint32_t tmask[16];       // LDS byte offset of thread bit q (zero past ntb)
+    int32_t pad_;
+    uint32_t tmask[16];       // LDS byte offset of thread bit q (zero past the last)
     uint32_t rbit[8];         // LDS byte offset of register bit q
+    // Half-tile passes: LDS byte weight of thread bit q / register bit q at
+    // entry, in the exchange from the stage before (see exchange_row_slots).
+    uint32_t gw[10], gr[6];
     // Global element offsets of thread bit q / register bit q, for the first
-    // stage of a pass (loaded straight from HBM, input layout) and the last
-    // (stored straight to HBM, output layout).
+    // stage of a pass (loaded straight from HBM, input layout, entry) and the
+    // last (stored straight to HBM, output layout, exit).
     int64_t gt_in[16], gr_in[8], gt_out[16], gr_out[8];
 };
 
@@ -74,12 +88,10 @@ struct DevPass {
     int32_t stage0, nstage;   // stage range (at least one stage)
     int32_t writes;           // 0: read-only pass (observable only)
     int32_t nfree;            // number of non-tile bits
-    int32_t obs_free_bit;     // global bit of the observed site if it is not a tile bit, else -1
     int32_t nmeas;            // measurements in this pass
     int32_t tile_barrier;     // 1: workgroup barrier after each tile's stores
     int32_t half;             // 1: half-tile exchanges (the top register bit of every stage
                               // is the same tile position, which has no LDS image)
-    int32_t pad_;
     int64_t meas_step[kMaxMeas];   // step label of measurement slot m (plus launch offset)
     int64_t free_mask;        // mask of the global bits not in the tile
     int32_t tbit[16];         // global bit of tile-local position p (input layout)
@@ -90,6 +102,26 @@ struct DevPass {
     int8_t pmeas_site[kMaxMeasProfile];    // site of slot m
     int32_t pnorm_meas[kMaxMeas];          // measurement slot whose step the norm slot carries
 };
+
+// LDS slots of a half-tile exchange.  The amplitude that lane `tid` holds in
+// register j (of the half's registers) goes to slot
+//     j * exchange_row_slots + tid + (tid >> P),
+// P = 5 for 8-byte and 4 for 16-byte amplitudes: an address of the lane's own
+// plus a constant per register, so the scatter needs no address arithmetic.
+// The next stage's lanes gather with one weight per thread and register bit,
+// added up.  Modulo the 2^P slots of a 256-byte bank row, lane bits 0 to 3 (3
+// are enough at P = 4) and register bits 0, 1, 2, .. weigh 1, 2, 4, 8, .., lane
+// and wave bits from P on start again at 1: any four positions get distinct
+// weights by ordering the registers and lanes of the stage before, which makes
+// the gather's groups of 16 lanes conflict-free.
+SPIN_HD constexpr int exchange_pad_shift(int elem_bytes) { return elem_bytes == 8 ? 5 : 4; }
+SPIN_HD constexpr int exchange_slot(int tid, int elem_bytes) {
+    return tid + (tid >> exchange_pad_shift(elem_bytes));
+}
+SPIN_HD constexpr int exchange_row_slots(int nt, int elem_bytes) {
+    const int n = 1 << exchange_pad_shift(elem_bytes);
+    return (exchange_slot(nt - 1, elem_bytes) + n - 1) / n * n + 1;
+}
 
 // Fixed LDS swizzle of the one-workgroup kernel (tiled passes use a layout
 // searched per pass, see encode_pass): xor a band of higher local-index bits into the lowest bits

@@ -19,6 +19,12 @@
 #include "device_plan.hpp"
 #include "kernels.hpp"
 
+// The file is compiled once per part, in parallel: part 0 holds the small
+// kernels and the launchers, the others one family of template kernels each.
+#ifndef SPIN_PART
+#error "compile with -DSPIN_PART=0..7 (see build.py)"
+#endif
+
 namespace spinqp {
 
 template <typename T> struct CT;
@@ -155,6 +161,7 @@ __global__ __launch_bounds__(256) void k_init_members(typename CT<T>::c* __restr
     }
 }
 
+#if SPIN_PART == 0
 // acc[i] = (acc[i] + add[i]) * scale (add may be null), i < n.
 __global__ void k_accumulate(double* __restrict__ acc, const double* __restrict__ add, int64_t n,
                              double scale) {
@@ -162,6 +169,7 @@ __global__ void k_accumulate(double* __restrict__ acc, const double* __restrict_
          i += int64_t(gridDim.x) * blockDim.x)
         acc[i] = (acc[i] + (add ? add[i] : 0.0)) * scale;
 }
+#endif
 
 // ---------------------------------------------------------- reductions
 __device__ __forceinline__ double wave_sum(double v) {
@@ -207,6 +215,7 @@ __device__ __forceinline__ double block_sum1(double v, double* red) {
     return s;
 }
 
+#if SPIN_PART == 0
 // Profile partials [slot][nwg][M + 1] -> Pall[s * M + site], N[s]; one
 // workgroup per (step, site or norm).
 __global__ __launch_bounds__(256) void k_reduce_profile(const double* __restrict__ partials, int nwg,
@@ -244,6 +253,7 @@ __global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ parti
         if (N) N[s] = n;
     }
 }
+#endif
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_observe(const typename CT<T>::c* __restrict__ psi, int M,
@@ -325,21 +335,93 @@ __device__ __forceinline__ void reg_xy(C (&v)[1 << R], T t, T s) {
     }
 }
 
+// a <- (pr + i pim) a for two amplitudes and b <- (pr - i pim) b for two
+// others.  In asm so that each result lands in the register of its input: left
+// to itself the compiler computes the 2^R amplitudes into other registers and
+// copies them back, half as many instructions again.  Four at a time because
+// the compiler puts a wait state between two blocks.
+template <typename C>
+__device__ __forceinline__ void phase_quad(C& a0, C& a1, C& b0, C& b1, float pr, float pim) {
+    float w, u;
+    asm("v_mul_f32 %8, %11, %1\n\tv_mul_f32 %9, %11, %0\n\t"
+        "v_fma_f32 %0, %10, %0, -%8\n\tv_fma_f32 %1, %10, %1, %9\n\t"
+        "v_mul_f32 %8, %11, %3\n\tv_mul_f32 %9, %11, %2\n\t"
+        "v_fma_f32 %2, %10, %2, -%8\n\tv_fma_f32 %3, %10, %3, %9\n\t"
+        "v_mul_f32 %8, %11, %5\n\tv_mul_f32 %9, %11, %4\n\t"
+        "v_fma_f32 %4, %10, %4, %8\n\tv_fma_f32 %5, %10, %5, -%9\n\t"
+        "v_mul_f32 %8, %11, %7\n\tv_mul_f32 %9, %11, %6\n\t"
+        "v_fma_f32 %6, %10, %6, %8\n\tv_fma_f32 %7, %10, %7, -%9"
+        : "+v"(a0.x), "+v"(a0.y), "+v"(a1.x), "+v"(a1.y), "+v"(b0.x), "+v"(b0.y), "+v"(b1.x), "+v"(b1.y),
+          "=&v"(w), "=&v"(u)
+        : "s"(pr), "s"(pim));
+}
+template <typename C>
+__device__ __forceinline__ void phase_quad(C& a0, C& a1, C& b0, C& b1, double pr, double pim) {
+    double w, u;
+    asm("v_mul_f64 %8, %11, %1\n\tv_mul_f64 %9, %11, %0\n\t"
+        "v_fma_f64 %0, %10, %0, -%8\n\tv_fma_f64 %1, %10, %1, %9\n\t"
+        "v_mul_f64 %8, %11, %3\n\tv_mul_f64 %9, %11, %2\n\t"
+        "v_fma_f64 %2, %10, %2, -%8\n\tv_fma_f64 %3, %10, %3, %9\n\t"
+        "v_mul_f64 %8, %11, %5\n\tv_mul_f64 %9, %11, %4\n\t"
+        "v_fma_f64 %4, %10, %4, %8\n\tv_fma_f64 %5, %10, %5, -%9\n\t"
+        "v_mul_f64 %8, %11, %7\n\tv_mul_f64 %9, %11, %6\n\t"
+        "v_fma_f64 %6, %10, %6, %8\n\tv_fma_f64 %7, %10, %7, -%9"
+        : "+v"(a0.x), "+v"(a0.y), "+v"(a1.x), "+v"(a1.y), "+v"(b0.x), "+v"(b0.y), "+v"(b1.x), "+v"(b1.y),
+          "=&v"(w), "=&v"(u)
+        : "s"(pr), "s"(pim));
+}
+
 // I^z I^z phase: anti-aligned amplitudes times (pr + i pi), aligned times
 // its conjugate.
 template <int R, int A, int B, typename C, typename T>
 __device__ __forceinline__ void reg_zz(C (&v)[1 << R], T pr, T pim) {
+    constexpr int a = 1 << A, b = 1 << B;
+#pragma unroll
+    for (int j = 0; j < (1 << R); ++j)
+        if ((j & (a | b)) == 0) phase_quad(v[j | a], v[j | b], v[j], v[j | a | b], pr, pim);
+}
+
+// Exchange of register bit Q with lane bit 4 (G = 0) or 5 (G = 1): one
+// v_permlane16_swap / v_permlane32_swap per register pair and component, which
+// trades the rows of the first operand that have the lane bit set for the
+// rows of the second that have it clear.
+template <int G>
+__device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {
+    const auto r = G == 0 ? __builtin_amdgcn_permlane16_swap(a, b, false, false)
+                          : __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+template <int G>
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+    uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+    swap_rows<G>(x, y);
+    a = __uint_as_float(x);
+    b = __uint_as_float(y);
+}
+template <int G>
+__device__ __forceinline__ void swap_rows(double& a, double& b) {
+    const uint64_t x = uint64_t(__double_as_longlong(a)), y = uint64_t(__double_as_longlong(b));
+    uint32_t xl = uint32_t(x), xh = uint32_t(x >> 32), yl = uint32_t(y), yh = uint32_t(y >> 32);
+    swap_rows<G>(xl, yl);
+    swap_rows<G>(xh, yh);
+    a = __longlong_as_double(int64_t((uint64_t(xh) << 32) | xl));
+    b = __longlong_as_double(int64_t((uint64_t(yh) << 32) | yl));
+}
+template <int R, int Q, int G, typename C>
+__device__ __forceinline__ void reg_gate(C (&v)[1 << R]) {
 #pragma unroll
     for (int j = 0; j < (1 << R); ++j) {
-        const bool anti = ((j >> A) & 1) != ((j >> B) & 1);
-        const T q = anti ? pim : -pim;
-        const T x = v[j].x, y = v[j].y;
-        v[j].x = fma(pr, x, -q * y);
-        v[j].y = fma(pr, y, q * x);
+        if (((j >> Q) & 1) == 0) {
+            const int k = j | (1 << Q);
+            swap_rows<G>(v[j].x, v[k].x);
+            swap_rows<G>(v[j].y, v[k].y);
+        }
     }
 }
 
-template <int R, typename C, typename T>
+// GATES: the stage may hold register/lane exchanges.
+template <int R, bool GATES, typename C, typename T>
 __device__ __forceinline__ void reg_op(C (&v)[1 << R], int code, T t, T s, T pr, T pim) {
 #define SPIN_CASE(A, B)                                        \
     case A * 8 + B:                                            \
@@ -348,13 +430,22 @@ __device__ __forceinline__ void reg_op(C (&v)[1 << R], int code, T t, T s, T pr,
             if (code & kOpZZ) reg_zz<R, A, B>(v, pr, pim);     \
         }                                                      \
         break;
+#define SPIN_GATE(Q)                                           \
+    case 48 + Q:                                               \
+        if constexpr (GATES && Q < R) reg_gate<R, Q, 0>(v);    \
+        break;                                                 \
+    case 56 + Q:                                               \
+        if constexpr (GATES && Q < R) reg_gate<R, Q, 1>(v);    \
+        break;
     switch (code & 63) {
         SPIN_CASE(0, 1) SPIN_CASE(0, 2) SPIN_CASE(1, 2) SPIN_CASE(0, 3) SPIN_CASE(1, 3)
         SPIN_CASE(2, 3) SPIN_CASE(0, 4) SPIN_CASE(1, 4) SPIN_CASE(2, 4) SPIN_CASE(3, 4)
         SPIN_CASE(0, 5) SPIN_CASE(1, 5) SPIN_CASE(2, 5) SPIN_CASE(3, 5) SPIN_CASE(4, 5)
+        SPIN_GATE(0) SPIN_GATE(1) SPIN_GATE(2) SPIN_GATE(3) SPIN_GATE(4) SPIN_GATE(5)
         default: break;
     }
 #undef SPIN_CASE
+#undef SPIN_GATE
 }
 
 // sum of (sign * |psi|^2, |psi|^2) over the lane's registers, FP64
@@ -370,13 +461,24 @@ __device__ __forceinline__ void reg_observe(const C (&v)[1 << R], int sign, int 
     }
 }
 
-// LDS byte address of the lane's register 0 in stage S (thread bits only;
-// entries past the stage's thread bits are zero).
+// LDS byte address of the lane's register 0 at the entry of stage S, over its
+// NTB thread bits (offsets past the stage's own thread bits are zero).
+template <int NTB>
 __device__ __forceinline__ uint32_t stage_base(const DevStage& S, int tid) {
     uint32_t b = 0;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) b ^= S.tmask[q] & (0u - ((uint32_t(tid) >> q) & 1u));
+    for (int q = 0; q < NTB; ++q) b ^= S.tmask[q] & (0u - ((uint32_t(tid) >> q) & 1u));
     return b;
+}
+
+// LDS byte address from which the lane gathers register 0 at the entry of
+// stage S in a half-tile exchange (weights added up, see exchange_row_slots).
+template <int NTB>
+__device__ __forceinline__ uint32_t gather_base(const DevStage& S, int tid) {
+    uint32_t a = 0;
+#pragma unroll
+    for (int q = 0; q < NTB; ++q) a += S.gw[q] & (0u - ((uint32_t(tid) >> q) & 1u));
+    return a;
 }
 
 // Barrier for LDS traffic only: global loads in flight (the next tile's
@@ -441,33 +543,28 @@ __device__ __forceinline__ void scatter(const C (&v)[1 << R], char* lds, uint32_
     }
 }
 
-// Gather / scatter of the half of a lane's registers whose top register bit
-// is H (the split position's value in a half-tile exchange), Gray-code order
-// over the lower R - 1 register bits.  The split position has no LDS image:
-// both halves use the same slots, one after the other.
-template <int R, int H, typename C, typename Stage>
-__device__ __forceinline__ void gather_half(C (&v)[1 << R], const char* lds, uint32_t pb,
-                                            const Stage& S) {
+// Exchange of the half of a lane's registers whose top register bit is H
+// (the split position's value).  Scatter: register i of the half goes to row
+// i, a constant offset from the lane's own slot.  Gather: Gray-code order over
+// the lower R - 1 register bits, one add or subtract per register.  Both
+// halves use the same slots, one after the other.
+template <int R, int H, int ROW, typename C>
+__device__ __forceinline__ void scatter_half(const C (&v)[1 << R], char* own) {
     constexpr int B = 1 << (R - 1);
-    uint32_t a = pb;
+#pragma unroll
+    for (int i = 0; i < B; ++i) *reinterpret_cast<C*>(own + i * ROW) = v[H * B + i];
+}
+
+template <int R, int H, typename C>
+__device__ __forceinline__ void gather_half(C (&v)[1 << R], const char* lds, uint32_t a,
+                                            const uint32_t (&w)[R - 1]) {
+    constexpr int B = 1 << (R - 1);
     v[H * B] = *reinterpret_cast<const C*>(lds + a);
 #pragma unroll
     for (int i = 1; i < B; ++i) {
-        a ^= S.rbit[__builtin_ctz(i)];
-        v[H * B + (i ^ (i >> 1))] = *reinterpret_cast<const C*>(lds + a);
-    }
-}
-
-template <int R, int H, typename C, typename Stage>
-__device__ __forceinline__ void scatter_half(const C (&v)[1 << R], char* lds, uint32_t pb,
-                                             const Stage& S) {
-    constexpr int B = 1 << (R - 1);
-    uint32_t a = pb;
-    *reinterpret_cast<C*>(lds + a) = v[H * B];
-#pragma unroll
-    for (int i = 1; i < B; ++i) {
-        a ^= S.rbit[__builtin_ctz(i)];
-        *reinterpret_cast<C*>(lds + a) = v[H * B + (i ^ (i >> 1))];
+        const int b = __builtin_ctz(i), j = i ^ (i >> 1);
+        a = (j >> b) & 1 ? a + w[b] : a - w[b];
+        v[H * B + j] = *reinterpret_cast<const C*>(lds + a);
     }
 }
 
@@ -478,23 +575,41 @@ struct RegBits {
     uint32_t rbit[R];
 };
 
-// Runs ops from index o up to the stage end o1 or the next observable op
-// (whichever comes first) on the lane's registers; returns the index of
-// the first op not run.  Each op's record is loaded one op ahead.
-template <int R, typename C, typename T>
-__device__ __forceinline__ int run_factors(C (&v)[1 << R], const DevOp<T>* __restrict__ ops, int o,
-                                           int o1) {
-    if (o >= o1) return o;
-    DevOp<T> cur = ops[o];
-    while (cur.code != kOpMeas) {
-        const int on = o + 1;
-        const DevOp<T> nxt = ops[on < o1 ? on : o];
-        reg_op<R>(v, cur.code, cur.t, cur.s, cur.pr, cur.pi);
-        o = on;
-        if (o >= o1) break;
-        cur = nxt;
+// An op record in the constant address space: with a pointer that steps
+// through the table the compiler would otherwise use vector loads.
+template <typename T>
+using ConstOp = const __attribute__((address_space(4))) DevOp<T>;
+
+template <typename T>
+__device__ __forceinline__ ConstOp<T>* const_ops(const DevOp<T>* p) {
+    return (ConstOp<T>*)(p);
+}
+
+// Runs a stage's ops from `op` up to the next observable or the end record;
+// returns that record and its code.  Each record is loaded one op ahead: the
+// scalar load's latency hides behind the current op's arithmetic, and the loop
+// itself is a pointer step, the load and a branch tree.
+template <int R, bool GATES, typename C, typename T>
+__device__ __forceinline__ ConstOp<T>* run_factors(C (&v)[1 << R], ConstOp<T>* op, int& code) {
+    int c = op->code;
+    T t = op->t, s = op->s, pr = op->pr, pi = op->pi;
+    // The first record and the gathered registers have arrived before the loop:
+    // otherwise every op waits for them there, and so for the next record's
+    // load too.
+    asm volatile("" ::"s"(t), "s"(s), "s"(pr), "s"(pi));
+    while (c < kOpEnd) {
+        ++op;
+        const int cn = op->code;
+        const T tn = op->t, sn = op->s, prn = op->pr, pin = op->pi;
+        reg_op<R, GATES>(v, c, t, s, pr, pi);
+        c = cn;
+        t = tn;
+        s = sn;
+        pr = prn;
+        pi = pin;
     }
-    return o;
+    code = c;
+    return op;
 }
 
 // ------------------------------------------------------- matrix engine
@@ -578,32 +693,41 @@ __device__ __forceinline__ C& lds_at(char* lds, uint32_t byte) {
 // layout).  The next tile is prefetched into registers while
 // the current one is worked on.  Observables accumulate into accP/accN per
 // measurement slot of the pass.
+// A lane's global accesses in Gray-code order over its register bits: the bits
+// are disjoint, so a step adds or subtracts one (scalar) byte offset.
 template <int R, typename C>
 __device__ __forceinline__ void load_direct(C (&v)[1 << R], const C* __restrict__ psi, int64_t g,
                                             const int64_t* gr) {
-    v[0] = psi[g];
+    const char* a = reinterpret_cast<const char*>(psi + g);
+    v[0] = *reinterpret_cast<const C*>(a);
 #pragma unroll
     for (int i = 1; i < (1 << R); ++i) {
-        g ^= gr[__builtin_ctz(i)];
-        v[i ^ (i >> 1)] = psi[g];
+        const int b = __builtin_ctz(i), j = i ^ (i >> 1);
+        const int64_t d = gr[b] * int64_t(sizeof(C));
+        a += (j >> b) & 1 ? d : -d;
+        v[j] = *reinterpret_cast<const C*>(a);
     }
 }
 
 template <int R, typename C>
 __device__ __forceinline__ void store_direct(const C (&v)[1 << R], C* __restrict__ psi, int64_t g,
                                              const int64_t* gr) {
-    psi[g] = v[0];
+    char* a = reinterpret_cast<char*>(psi + g);
+    *reinterpret_cast<C*>(a) = v[0];
 #pragma unroll
     for (int i = 1; i < (1 << R); ++i) {
-        g ^= gr[__builtin_ctz(i)];
-        psi[g] = v[i ^ (i >> 1)];
+        const int b = __builtin_ctz(i), j = i ^ (i >> 1);
+        const int64_t d = gr[b] * int64_t(sizeof(C));
+        a += (j >> b) & 1 ? d : -d;
+        *reinterpret_cast<C*>(a) = v[j];
     }
 }
 
+template <int NTB>
 __device__ __forceinline__ int64_t lane_offset(const int64_t* gt, int tid) {
     int64_t o = 0;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) o ^= gt[q] & (int64_t(0) - int64_t((uint32_t(tid) >> q) & 1u));
+    for (int q = 0; q < NTB; ++q) o ^= gt[q] & (int64_t(0) - int64_t((uint32_t(tid) >> q) & 1u));
     return o;
 }
 
@@ -668,21 +792,46 @@ __device__ __forceinline__ double wave_sum_last(double v) {
     return v;
 }
 
-// One per-site observable (profile kOpMeas) of the lane's registers: the
-// sign of each amplitude follows the site's bit (thread bit, register bit or
-// a bit of the tile base).
+// Observable of one site on the lane's registers: the sign of each amplitude
+// follows the site's bit (thread bit, register bit or a bit of the tile base;
+// see kOpMeas).
 template <int R, typename C>
-__device__ __forceinline__ void prof_observe(const C (&v)[1 << R], int aux, int64_t base,
-                                             double& p, double& n, int& slot, int& nslot) {
-    slot = aux & 63;
+__device__ __forceinline__ void site_observe(const C (&v)[1 << R], int aux, int64_t base, double& p,
+                                             double& n) {
     const int kind = (aux >> 6) & 3, idx = (aux >> 8) & 63;
-    nslot = ((aux >> 14) & 7) - 1;
     const int sign = kind == 0 ? ((int(threadIdx.x) >> idx) & 1)
                    : kind == 2 ? int((base >> idx) & 1) : 0;
     const int mask = kind == 1 ? (1 << idx) : 0;
     p = 0.0;
     n = 0.0;
     reg_observe<R>(v, sign, mask, p, n);
+}
+
+// Brings a pass's stage headers and ops into the scalar cache, several lines
+// in flight.  Read in order they miss it once per stage and once per few ops,
+// one miss after the other: on a one-tile workgroup (M <= 22) that is a
+// microsecond of every pass.
+template <typename T>
+__device__ __forceinline__ void warm_tables(const DevPass& P, const DevStage* __restrict__ stages,
+                                            const DevOp<T>* __restrict__ ops) {
+    constexpr int kLine = 16;     // words per 64-byte line
+    const DevStage* S = stages + P.stage0;
+    const DevStage& L = S[P.nstage - 1];
+    const int* w = reinterpret_cast<const int*>(ops + S->op0);
+    const int words = (L.op0 + L.nop + 1 - S->op0) * int(sizeof(DevOp<T>) / 4);
+    for (int si = 0; si < P.nstage; si += 2) {
+        // the first 3 lines of a stage hold what the stage loop reads
+        const int* p = reinterpret_cast<const int*>(S + si);
+        const int* q = reinterpret_cast<const int*>(S + (si + 1 < P.nstage ? si + 1 : si));
+        const int a = p[0], b = p[kLine], c = p[2 * kLine], d = q[0], e = q[kLine], f = q[2 * kLine];
+        asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
+    }
+    for (int i = 0; i < words; i += 6 * kLine) {
+        const int last = words - 1;
+        auto at = [&](int n) { return w[i + n * kLine < last ? i + n * kLine : last]; };
+        const int a = at(0), b = at(1), c = at(2), d = at(3), e = at(4), f = at(5);
+        asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
+    }
 }
 
 template <typename T, int R, int NT, bool WRITES, int ENGINE = 0, bool PROFILE = false,
@@ -698,8 +847,12 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
     const int tid = threadIdx.x;
     const DevStage& S0 = stages[P.stage0];
     const DevStage& SL = stages[P.stage0 + P.nstage - 1];
-    const int64_t gin_t = lane_offset(S0.gt_in, tid);
-    const int64_t gout_t = lane_offset(SL.gt_out, tid);
+    constexpr int NTB = __builtin_ctz(NT);
+    constexpr int EB = sizeof(C), ROW = exchange_row_slots(NT, EB) * EB;
+    char* own = ldsb + exchange_slot(tid, EB) * EB;
+    bool prev_cross = false;
+    const int64_t gin_t = lane_offset<NTB>(S0.gt_in, tid);
+    const int64_t gout_t = lane_offset<NTB>(SL.gt_out, tid);
 
     // Tile bases: tile = wperm + i * G, so base = deposit(wperm) | (i-th
     // submask of the free bits above the lowest log2(G) ones).
@@ -720,7 +873,6 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
 
     auto tile_body = [&](int64_t it_tile) {
         const int64_t base = base_w | hi;
-        const int tile_sign = P.obs_free_bit >= 0 ? int((base >> P.obs_free_bit) & 1) : 0;
         C v[1 << R];
         if constexpr (HALF) {
             load_direct<R>(v, psi, base + gin_t, S0.gr_in);
@@ -734,114 +886,117 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
 
         for (int si = 0; si < P.nstage; ++si) {
             const DevStage& S = stages[P.stage0 + si];
+            uint32_t pb = 0;      // lane's LDS address (whole tiles)
             RegBits<R> rb;
+            if constexpr (!HALF) {
+                pb = stage_base<NTB>(S, tid);
 #pragma unroll
-            for (int b = 0; b < R; ++b) rb.rbit[b] = S.rbit[b];
-            const uint32_t pb = stage_base(S, tid);
-            if constexpr (!HALF)
+                for (int b = 0; b < R; ++b) rb.rbit[b] = S.rbit[b];
                 if (si > 0) gather<R>(v, ldsb, pb, rb);
-            const int sign = tile_sign ^ (S.obs_tq >= 0 ? ((tid >> S.obs_tq) & 1) : 0);
-            const int o1 = S.op0 + S.nop;
-            int o = S.op0;
-            while (o < o1) {
+            }
+            ConstOp<T>* op = const_ops<T>(ops + S.op0);
+            while (true) {
+                int code;
                 if constexpr (ENGINE == 1) {
-                    const DevOp<T> op = ops[o];
-                    if (op.code == kOpMat) {
-                        if constexpr (sizeof(T) == 4 && R == 5) mfma_stage(v, mats + size_t(op.aux) * kMatFloats);
-                        ++o;
+                    if (op->code == kOpMat) {
+                        if constexpr (sizeof(T) == 4 && R == 5) mfma_stage(v, mats + size_t(op->aux) * kMatFloats);
+                        ++op;
                         continue;
                     }
+                    code = op->code;
                 } else {
-                    o = run_factors<R>(v, ops, o, o1);
+                    op = run_factors<R, HALF>(v, op, code);
                 }
-                if (o < o1) {    // observable of the state at this point
-                    if constexpr (PROFILE) {
-                        // Every per-site observable at this point from the
-                        // lane's total weight and its register-bit half sums,
-                        // each squared once; wave sums go to the wave's LDS
-                        // row (pacc / nacc), one row per wave.
-                        double tot, half[R];
-                        if constexpr (HALF) reg_half_sums_seq<R>(v, tot, half);
-                        else reg_half_sums<R>(v, tot, half);
-                        const bool last = (tid & 63) == 63;
-                        while (o < o1 && ops[o].code == kOpMeas) {
-                            const int aux = ops[o].aux;
-                            const int slot = aux & 63, kind = (aux >> 6) & 3, idx = (aux >> 8) & 63;
-                            const int nslot = ((aux >> 14) & 7) - 1;
-                            double p;
-                            if (kind == 1) {
-                                double h = half[0];
+                if (code == kOpEnd) break;
+                // observable of the state at this point
+                if constexpr (PROFILE) {
+                    // Every per-site observable at this point from the
+                    // lane's total weight and its register-bit half sums,
+                    // each squared once; wave sums go to the wave's LDS
+                    // row (pacc / nacc), one row per wave.
+                    double tot, half[R];
+                    if constexpr (HALF) reg_half_sums_seq<R>(v, tot, half);
+                    else reg_half_sums<R>(v, tot, half);
+                    const bool last = (tid & 63) == 63;
+                    while (op->code == kOpMeas) {
+                        const int aux = op->aux;
+                        const int slot = aux & 63, kind = (aux >> 6) & 3, idx = (aux >> 8) & 63;
+                        const int nslot = ((aux >> 14) & 7) - 1;
+                        double p;
+                        if (kind == 1) {
+                            double h = half[0];
 #pragma unroll
-                                for (int b = 1; b < R; ++b)
-                                    if (b == idx) h = half[b];
-                                p = tot - 2.0 * h;
-                            } else {
-                                const int neg = kind == 0 ? ((tid >> idx) & 1) : int((base >> idx) & 1);
-                                p = neg ? -tot : tot;
-                            }
-                            p = wave_sum_last(p);
-                            if (last) pacc[slot] += p;
-                            if (nslot >= 0) {
-                                const double n = wave_sum_last(tot);
-                                if (last) nacc[nslot] += n;
-                            }
-                            ++o;
+                            for (int b = 1; b < R; ++b)
+                                if (b == idx) h = half[b];
+                            p = tot - 2.0 * h;
+                        } else {
+                            const int neg = kind == 0 ? ((tid >> idx) & 1) : int((base >> idx) & 1);
+                            p = neg ? -tot : tot;
                         }
-                        continue;
-                    } else if constexpr (HALF) {
-                        // wave sums into the wave's own LDS row (pacc: slot
-                        // m holds P at 2m, N at 2m + 1), no accumulator
-                        // registers
-                        const int slot = ops[o].aux;
-                        double p = 0.0, n = 0.0;
-                        reg_observe<R>(v, sign, S.obs_mask, p, n);
                         p = wave_sum_last(p);
-                        n = wave_sum_last(n);
-                        if ((tid & 63) == 63) {
-                            pacc[2 * slot] += p;
-                            pacc[2 * slot + 1] += n;
+                        if (last) pacc[slot] += p;
+                        if (nslot >= 0) {
+                            const double n = wave_sum_last(tot);
+                            if (last) nacc[nslot] += n;
                         }
-                    } else {
-                        const int slot = ops[o].aux;
-                        double p = 0.0, n = 0.0;
-                        reg_observe<R>(v, sign, S.obs_mask, p, n);
-#pragma unroll
-                        for (int m = 0; m < kMaxMeas; ++m)
-                            if (m == slot) { accP[m] += p; accN[m] += n; }
+                        ++op;
                     }
-                    ++o;
+                } else if constexpr (HALF) {
+                    // wave sums into the wave's own LDS row (pacc: slot
+                    // m holds P at 2m, N at 2m + 1), no accumulator
+                    // registers
+                    const int slot = op->aux & 63;
+                    double p, n;
+                    site_observe<R>(v, op->aux, base, p, n);
+                    p = wave_sum_last(p);
+                    n = wave_sum_last(n);
+                    if ((tid & 63) == 63) {
+                        pacc[2 * slot] += p;
+                        pacc[2 * slot + 1] += n;
+                    }
+                    ++op;
+                } else {
+                    const int slot = op->aux & 63;
+                    double p, n;
+                    site_observe<R>(v, op->aux, base, p, n);
+#pragma unroll
+                    for (int m = 0; m < kMaxMeas; ++m)
+                        if (m == slot) { accP[m] += p; accN[m] += n; }
+                    ++op;
                 }
             }
             if (si + 1 < P.nstage) {
-                // A lane scatters to exactly the LDS slots the next stage's
-                // lanes gather after the barrier.  When both stages keep the
-                // same positions on the wave bits, those slots belong to the
-                // wave's own lanes and only the wave is ordered.
+                // When both stages keep the same positions on the wave bits
+                // the exchange moves amplitudes only within each wave and
+                // only the wave is ordered.
                 const bool xw = S.xnext != 0;
                 auto sync = [&]() {
                     if (xw) lds_barrier();
                     else wave_lds_sync();
                 };
                 if constexpr (HALF) {
-                    // The split position stays on the top register bit:
-                    // half 0 through the LDS, then half 1 through the same
-                    // slots.  A lane's gather slots in the next stage are its
-                    // scatter slots there, so the next exchange needs no
-                    // ordering before its first scatter; inside this one the
-                    // second scatter waits for every first gather.
+                    // Half 0 through the LDS, then half 1 through the same
+                    // slots.  A lane scatters to slots of its own; after an
+                    // exchange that crossed waves (the last one of the tile
+                    // before included) other waves may still be gathering
+                    // from them.
                     const DevStage& S2 = stages[P.stage0 + si + 1];
-                    RegBits<R> rb2;
+                    uint32_t w[R - 1];
 #pragma unroll
-                    for (int b = 0; b < R; ++b) rb2.rbit[b] = S2.rbit[b];
-                    const uint32_t pb2 = stage_base(S2, tid);
-                    scatter_half<R, 0>(v, ldsb, pb, rb);
+                    for (int b = 0; b + 1 < R; ++b) w[b] = S2.gr[b];
+                    const uint32_t ga = gather_base<NTB>(S2, tid);
+                    if (prev_cross) lds_barrier();
+                    prev_cross = xw;
+                    scatter_half<R, 0, ROW>(v, own);
                     sync();
-                    gather_half<R, 0>(v, ldsb, pb2, rb2);
+                    gather_half<R, 0>(v, ldsb, ga, w);
                     sync();
-                    scatter_half<R, 1>(v, ldsb, pb, rb);
+                    scatter_half<R, 1, ROW>(v, own);
                     sync();
-                    gather_half<R, 1>(v, ldsb, pb2, rb2);
+                    gather_half<R, 1>(v, ldsb, ga, w);
                 } else {
+                    // the lanes scatter to exactly the slots that the next
+                    // stage's lanes gather
                     scatter<R>(v, ldsb, pb, rb);
                     sync();
                 }
@@ -850,8 +1005,10 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
         if constexpr (WRITES) store_direct<R>(v, psi, base + gout_t, SL.gr_out);
         // the last gathers are done before the next tile's scatters, unless
         // the last and first stages keep the same wave positions (then every
-        // wave's slots are its own across the tile boundary)
-        if (P.tile_barrier) lds_barrier();
+        // wave's slots are its own across the tile boundary); half tiles have
+        // their barrier at the next scatter
+        if constexpr (!HALF)
+            if (P.tile_barrier) lds_barrier();
     };
     tile_body(0);
     for (int64_t it_tile = 1; it_tile < tiles_per_member; ++it_tile) tile_body(it_tile);
@@ -879,8 +1036,12 @@ __device__ __forceinline__ void slot_sum(const double (&accP)[kMaxMeas],
 // CU when their half-tile LDS buffers fit the CU's 160 KiB together (with
 // room for the small arrays), else one (complex128 tiles of 2^14).
 template <typename T, int R, int NT>
+__host__ __device__ constexpr int half_slots() {
+    return exchange_row_slots(NT, sizeof(typename CT<T>::c)) << (R - 1);
+}
+template <typename T, int R, int NT>
 __host__ __device__ constexpr int half_waves_per_eu() {
-    return ((sizeof(typename CT<T>::c) << (R + __builtin_ctz(NT) - 1)) <= 72 * 1024 ? 2 : 1) * NT / 256;
+    return (half_slots<T, R, NT>() * sizeof(typename CT<T>::c) <= 78 * 1024 ? 2 : 1) * NT / 256;
 }
 
 template <typename T, int R, int NT, bool WRITES, int ENGINE, bool PROFILE, bool HALF>
@@ -893,7 +1054,7 @@ __global__ __launch_bounds__(NT, (HALF ? half_waves_per_eu<T, R, NT>() : 1)) voi
                                              const float* __restrict__ mats) {
     using C = typename CT<T>::c;
     constexpr int K = R + __builtin_ctz(NT);
-    __shared__ C lds[HALF ? (1 << (K - 1)) : (1 << K)];
+    __shared__ C lds[HALF ? half_slots<T, R, NT>() : (1 << K)];
     __shared__ double red[2 * (NT / 64)];
     const DevPass& P = passes[pass_index];
     double accP[kMaxMeas], accN[kMaxMeas];
@@ -906,6 +1067,7 @@ __global__ __launch_bounds__(NT, (HALF ? half_waves_per_eu<T, R, NT>() : 1)) voi
     // line.
     const unsigned G = gridDim.x, w = blockIdx.x;
     const unsigned wperm = (G >= 8) ? (w % 8u) * (G / 8u) + w / 8u : w;
+    warm_tables<T>(P, stages, ops);
     if constexpr (PROFILE) {
         // Per-wave accumulator rows; lane 63 of each wave owns its row.
         constexpr int NW = NT / 64;
@@ -1017,40 +1179,34 @@ __device__ __forceinline__ void resident_run(const ResidentJob& J, const DevStag
             // slots) so that the op loop below stays free of divergence;
             // they never scatter and contribute nothing to observables.
             const bool act = tid < nact;
-            const uint32_t pb = stage_base(S, tid & (nact - 1));
+            const uint32_t pb = stage_base<__builtin_ctz(NT)>(S, tid & (nact - 1));
             C v[1 << R];
             gather<R>(v, ldsb, pb, S);
-            const int sign = S.obs_tq >= 0 ? ((tid >> S.obs_tq) & 1) : 0;
-            const int o1 = S.op0 + S.nop;
-            int o = S.op0;
-            while (o < o1) {
-                o = run_factors<R>(v, ops, o, o1);
-                if (o < o1) {    // observable: reduce over the workgroup now
-                    if constexpr (PROFILE) {
-                        const int aux = ops[o].aux;
-                        double p, n;
-                        int slot, nslot;
-                        prof_observe<R>(v, aux, 0, p, n, slot, nslot);
-                        p = act ? p : 0.0;
-                        n = act ? n : 0.0;
-                        block_sum2<NT>(p, n, red);
-                        if (tid == 0) {
-                            J.Pall[step * M + ((aux >> 17) & 63)] = p;
-                            if (nslot >= 0 && J.N) J.N[step] = n;
-                        }
-                    } else {
-                        double p = 0.0, n = 0.0;
-                        reg_observe<R>(v, sign, S.obs_mask, p, n);
-                        p = act ? p : 0.0;
-                        n = act ? n : 0.0;
-                        block_sum2<NT>(p, n, red);
-                        if (tid == 0) {
-                            J.P[step] = p;
-                            if (J.N) J.N[step] = n;
-                        }
+            ConstOp<T>* op = const_ops<T>(ops + S.op0);
+            while (true) {
+                int code;
+                op = run_factors<R, false>(v, op, code);
+                if (code == kOpEnd) break;
+                // observable: reduce over the workgroup now
+                const int aux = op->aux;
+                double p, n;
+                site_observe<R>(v, aux, 0, p, n);
+                p = act ? p : 0.0;
+                n = act ? n : 0.0;
+                block_sum2<NT>(p, n, red);
+                if constexpr (PROFILE) {
+                    const int nslot = ((aux >> 14) & 7) - 1;
+                    if (tid == 0) {
+                        J.Pall[step * M + ((aux >> 17) & 63)] = p;
+                        if (nslot >= 0 && J.N) J.N[step] = n;
                     }
-                    ++o;
+                } else {
+                    if (tid == 0) {
+                        J.P[step] = p;
+                        if (J.N) J.N[step] = n;
+                    }
                 }
+                ++op;
             }
             __syncthreads();    // every shadow lane has gathered
             if (act) scatter<R>(v, ldsb, pb, S);
@@ -1131,7 +1287,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
     constexpr int K = R + __builtin_ctz(NT);
     constexpr int KL = HALF ? K - 1 : K;    // largest problem held in LDS
     constexpr int NW = NT / 64;
-    __shared__ C lds[1 << KL];
+    __shared__ C lds[HALF ? half_slots<T, R, NT>() : (1 << KL)];
     __shared__ double red[2 * NW];
     __shared__ double wacc[HALF ? NW : 1][2 * kMaxMeas];
     const int tid = threadIdx.x;
@@ -1247,6 +1403,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
     }
 }
 
+#if SPIN_PART == 0
 __global__ void k_fill_int(int* p, int n, int v) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = v;
 }
@@ -1256,6 +1413,30 @@ __global__ void k_status_or(const int* err, int* status) {
     if (threadIdx.x == 0 && *err != 0) atomicOr(status, *err);
 }
 
+void launch_fill_int(int* p, int n, int grid, hipStream_t st) {
+    hipLaunchKernelGGL(k_fill_int, dim3(grid), dim3(256), 0, st, p, n, 0);
+}
+
+void launch_status_or(const int* err, int* status, hipStream_t st) {
+    hipLaunchKernelGGL(k_status_or, dim3(1), dim3(64), 0, st, err, status);
+}
+#else
+void launch_fill_int(int* p, int n, int grid, hipStream_t st);
+void launch_status_or(const int* err, int* status, hipStream_t st);
+#endif
+
+// Pass launches by kernel family (half-tile or whole-tile exchanges), each
+// compiled in its own part.
+template <typename T>
+hipError_t launch_pass_half(const PassShape& sh, void* psi, const DevPass* passes, const DevStage* stages, const DevOp<T>* ops,
+               int pass_index, int64_t tiles_per_wg, int nwg, double* partials, int64_t step_offset, int ch,
+               hipStream_t st);
+template <typename T>
+hipError_t launch_pass_whole(const PassShape& sh, void* psi, const DevPass* passes, const DevStage* stages, const DevOp<T>* ops,
+               int pass_index, int64_t tiles_per_wg, int nwg, double* partials, int64_t step_offset, int ch,
+               hipStream_t st);
+
+#if SPIN_PART == 0
 // ------------------------------------------------------------- launchers
 static inline int grid_for(uint64_t n, int per_block, int cap) {
     uint64_t g = (n + per_block - 1) / per_block;
@@ -1332,22 +1513,6 @@ hipError_t launch_factor(void* psi, int M, int lo, int hi, double t, double s, d
     return hipGetLastError();
 }
 
-template <typename T, int R, int NT, int ENGINE = 0, bool PROFILE = false, bool HALF = false>
-static hipError_t pass_one(bool writes, void* psi, const DevPass* passes, const DevStage* stages,
-                           const DevOp<T>* ops, int pass_index, int64_t tiles_per_wg, int nwg,
-                           double* partials, int64_t step_offset, int ch, const float* mats,
-                           hipStream_t st) {
-    if (writes)
-        hipLaunchKernelGGL((k_pass<T, R, NT, true, ENGINE, PROFILE, HALF>), dim3(nwg), dim3(NT), 0, st,
-                           reinterpret_cast<typename CT<T>::c*>(psi), passes, stages, ops,
-                           pass_index, tiles_per_wg, partials, step_offset, ch, nwg, mats);
-    else
-        hipLaunchKernelGGL((k_pass<T, R, NT, false, ENGINE, PROFILE, HALF>), dim3(nwg), dim3(NT), 0, st,
-                           reinterpret_cast<typename CT<T>::c*>(psi), passes, stages, ops,
-                           pass_index, tiles_per_wg, partials, step_offset, ch, nwg, mats);
-    return hipGetLastError();
-}
-
 bool pass_half_exists(bool f32, int r, int nt) {
     if (f32) return (r == 5 && nt == 512) || (r == 6 && nt == 256);
     return (r == 4 && nt == 512) || (r == 5 && nt == 256) || (r == 5 && nt == 512);
@@ -1363,20 +1528,74 @@ bool pass_shape_exists(bool f32, int r, int nt, int engine) {
 }
 
 template <typename T>
+int batch_occupancy(bool half);
+
+int batch_tile_bits(bool f32) { return f32 ? 14 : 13; }
+
+// Launch shapes of the batch kernel: whole tiles 2^R x 512 lanes (one
+// workgroup per CU); half tiles 2^(R+1) x 256 lanes (two per CU), whose
+// larger register stages take fewer LDS exchanges on dense coupling graphs.
+BatchShape batch_shape(bool f32, bool half) {
+    if (half) return BatchShape{true, f32 ? 6 : 5, 256};
+    return BatchShape{false, f32 ? 5 : 4, 512};
+}
+
+template hipError_t launch_init<float>(void*, int, int, uint64_t, hipStream_t);
+template hipError_t launch_init<double>(void*, int, int, uint64_t, hipStream_t);
+template hipError_t launch_init_product<float>(void*, int, int, uint64_t, hipStream_t);
+template hipError_t launch_init_product<double>(void*, int, int, uint64_t, hipStream_t);
+template hipError_t launch_init_members<float>(void*, int, int, int, uint64_t, uint64_t, hipStream_t);
+template hipError_t launch_init_members<double>(void*, int, int, int, uint64_t, uint64_t, hipStream_t);
+template hipError_t launch_observe<float>(const void*, int, int, double*, int, hipStream_t);
+template hipError_t launch_observe<double>(const void*, int, int, double*, int, hipStream_t);
+template hipError_t launch_factor<float>(void*, int, int, int, double, double, double, double, int,
+                                         hipStream_t);
+template hipError_t launch_factor<double>(void*, int, int, int, double, double, double, double,
+                                          int, hipStream_t);
+
+template <typename T>
 hipError_t launch_pass(const PassShape& sh, void* psi, const DevPass* passes,
                        const DevStage* stages, const DevOp<T>* ops, int pass_index,
                        int64_t tiles_per_wg, int nwg, double* partials, int64_t step_offset,
                        int ch, hipStream_t st) {
-    if constexpr (sizeof(T) == 4) {
-        if (sh.engine == 1) {
-            if (sh.r == 5 && sh.nt == 512 && sh.mats)
-                return pass_one<T, 5, 512, 1>(sh.writes, psi, passes, stages, ops, pass_index,
-                                              tiles_per_wg, nwg, partials, step_offset, ch, sh.mats, st);
-            return hipErrorInvalidValue;
-        }
-    }
-    if (sh.engine != 0) return hipErrorInvalidValue;
-    if (sh.half) {
+    return (sh.half ? launch_pass_half<T> : launch_pass_whole<T>)(sh, psi, passes, stages, ops, pass_index,
+                                                                 tiles_per_wg, nwg, partials, step_offset, ch, st);
+}
+template hipError_t launch_pass<float>(const PassShape&, void*, const DevPass*, const DevStage*,
+                                       const DevOp<float>*, int, int64_t, int, double*, int64_t,
+                                       int, hipStream_t);
+template hipError_t launch_pass<double>(const PassShape&, void*, const DevPass*, const DevStage*,
+                                        const DevOp<double>*, int, int64_t, int, double*, int64_t,
+                                        int, hipStream_t);
+
+int batch_blocks_per_cu(bool f32, bool half) {
+    return f32 ? batch_occupancy<float>(half) : batch_occupancy<double>(half);
+}
+#endif
+
+#if SPIN_PART >= 2 && SPIN_PART <= 5
+template <typename T, int R, int NT, int ENGINE = 0, bool PROFILE = false, bool HALF = false>
+static hipError_t pass_one(bool writes, void* psi, const DevPass* passes, const DevStage* stages,
+                           const DevOp<T>* ops, int pass_index, int64_t tiles_per_wg, int nwg,
+                           double* partials, int64_t step_offset, int ch, const float* mats,
+                           hipStream_t st) {
+    if (writes)
+        hipLaunchKernelGGL((k_pass<T, R, NT, true, ENGINE, PROFILE, HALF>), dim3(nwg), dim3(NT), 0, st,
+                           reinterpret_cast<typename CT<T>::c*>(psi), passes, stages, ops,
+                           pass_index, tiles_per_wg, partials, step_offset, ch, nwg, mats);
+    else
+        hipLaunchKernelGGL((k_pass<T, R, NT, false, ENGINE, PROFILE, HALF>), dim3(nwg), dim3(NT), 0, st,
+                           reinterpret_cast<typename CT<T>::c*>(psi), passes, stages, ops,
+                           pass_index, tiles_per_wg, partials, step_offset, ch, nwg, mats);
+    return hipGetLastError();
+}
+#endif
+
+#if SPIN_PART == 2 || SPIN_PART == 3
+template <typename T>
+hipError_t launch_pass_half(const PassShape& sh, void* psi, const DevPass* passes, const DevStage* stages, const DevOp<T>* ops,
+               int pass_index, int64_t tiles_per_wg, int nwg, double* partials, int64_t step_offset, int ch,
+               hipStream_t st) {
 #define SPIN_HALF(RR, NTT)                                                                        \
     if (sh.r == RR && sh.nt == NTT)                                                               \
         return sh.profile                                                                         \
@@ -1392,8 +1611,24 @@ hipError_t launch_pass(const PassShape& sh, void* psi, const DevPass* passes,
             SPIN_HALF(4, 512) SPIN_HALF(5, 256) SPIN_HALF(5, 512)
         }
 #undef SPIN_HALF
-        return hipErrorInvalidValue;
+    return hipErrorInvalidValue;
+}
+#endif
+
+#if SPIN_PART == 4 || SPIN_PART == 5
+template <typename T>
+hipError_t launch_pass_whole(const PassShape& sh, void* psi, const DevPass* passes, const DevStage* stages, const DevOp<T>* ops,
+               int pass_index, int64_t tiles_per_wg, int nwg, double* partials, int64_t step_offset, int ch,
+               hipStream_t st) {
+    if constexpr (sizeof(T) == 4) {
+        if (sh.engine == 1) {
+            if (sh.r == 5 && sh.nt == 512 && sh.mats)
+                return pass_one<T, 5, 512, 1>(sh.writes, psi, passes, stages, ops, pass_index,
+                                              tiles_per_wg, nwg, partials, step_offset, ch, sh.mats, st);
+            return hipErrorInvalidValue;
+        }
     }
+    if (sh.engine != 0) return hipErrorInvalidValue;
 #define SPIN_PASS(RR, NTT)                                                                   \
     if (sh.r == RR && sh.nt == NTT)                                                          \
         return sh.profile                                                                    \
@@ -1411,7 +1646,9 @@ hipError_t launch_pass(const PassShape& sh, void* psi, const DevPass* passes,
 #undef SPIN_PASS
     return hipErrorInvalidValue;
 }
+#endif
 
+#if SPIN_PART == 0 || SPIN_PART == 1
 template <typename T, int R, int NT>
 static hipError_t res_one(const ResidentJob& job0, const ResidentJob* jobs, int njobs,
                           const DevStage* stages, const DevOp<T>* ops, int64_t n_steps,
@@ -1442,26 +1679,16 @@ hipError_t launch_resident(int r, int nt, const ResidentJob& job0, const Residen
 #undef SPIN_RES
     return hipErrorInvalidValue;
 }
+#endif
 
-int batch_tile_bits(bool f32) { return f32 ? 14 : 13; }
-
-// Launch shapes of the batch kernel: whole tiles 2^R x 512 lanes (one
-// workgroup per CU); half tiles 2^(R+1) x 256 lanes (two per CU), whose
-// larger register stages take fewer LDS exchanges on dense coupling graphs.
-BatchShape batch_shape(bool f32, bool half) {
-    if (half) return BatchShape{true, f32 ? 6 : 5, 256};
-    return BatchShape{false, f32 ? 5 : 4, 512};
-}
-
-int batch_blocks_per_cu(bool f32, bool half) {
+#if SPIN_PART >= 6
+template <typename T>
+int batch_occupancy(bool half) {
+    constexpr bool F = sizeof(T) == 4;
     int n = 0;
-    hipError_t e;
-    if (f32)
-        e = half ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch<float, 6, 256, true>, 256, 0)
-                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch<float, 5, 512, false>, 512, 0);
-    else
-        e = half ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch<double, 5, 256, true>, 256, 0)
-                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch<double, 4, 512, false>, 512, 0);
+    const hipError_t e =
+        half ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch<T, F ? 6 : 5, 256, true>, 256, 0)
+             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch<T, F ? 5 : 4, 512, false>, 512, 0);
     return e == hipSuccess ? n : 0;
 }
 
@@ -1472,8 +1699,8 @@ hipError_t launch_batch(int nslots, bool half, const BatchProblem* probs, const 
                         int ncounters, int* err, int* status, int64_t n_steps, hipStream_t st) {
     // counters and the error flag start at zero (a fill kernel, not a
     // memset node, so the pair can sit in a captured graph)
-    hipLaunchKernelGGL(k_fill_int, dim3(64), dim3(256), 0, st, counters, ncounters, 0);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, err, 1, 0);
+    launch_fill_int(counters, ncounters, 64, st);
+    launch_fill_int(err, 1, 1, st);
     constexpr bool F = sizeof(T) == 4;
     if (half)
         hipLaunchKernelGGL((k_batch<T, F ? 6 : 5, 256, true>), dim3(nslots), dim3(256), 0, st, probs,
@@ -1483,41 +1710,39 @@ hipError_t launch_batch(int nslots, bool half, const BatchProblem* probs, const 
         hipLaunchKernelGGL((k_batch<T, F ? 5 : 4, 512, false>), dim3(nslots), dim3(512), 0, st, probs,
                            jobs, job_start, passes, stages, ops, launches, partials, counters, err,
                            n_steps);
-    hipLaunchKernelGGL(k_status_or, dim3(1), dim3(64), 0, st, err, status);
+    launch_status_or(err, status, st);
     return hipGetLastError();
 }
+#endif
 
-template hipError_t launch_batch<float>(int, bool, const BatchProblem*, const BatchJob*, const int*,
-                                        const DevPass*, const DevStage*, const DevOp<float>*,
-                                        const int2*, double*, int*, int, int*, int*, int64_t,
-                                        hipStream_t);
-template hipError_t launch_batch<double>(int, bool, const BatchProblem*, const BatchJob*, const int*,
-                                         const DevPass*, const DevStage*, const DevOp<double>*,
-                                         const int2*, double*, int*, int, int*, int*, int64_t,
-                                         hipStream_t);
-template hipError_t launch_init<float>(void*, int, int, uint64_t, hipStream_t);
-template hipError_t launch_init<double>(void*, int, int, uint64_t, hipStream_t);
-template hipError_t launch_init_product<float>(void*, int, int, uint64_t, hipStream_t);
-template hipError_t launch_init_product<double>(void*, int, int, uint64_t, hipStream_t);
-template hipError_t launch_init_members<float>(void*, int, int, int, uint64_t, uint64_t, hipStream_t);
-template hipError_t launch_init_members<double>(void*, int, int, int, uint64_t, uint64_t, hipStream_t);
-template hipError_t launch_observe<float>(const void*, int, int, double*, int, hipStream_t);
-template hipError_t launch_observe<double>(const void*, int, int, double*, int, hipStream_t);
-template hipError_t launch_factor<float>(void*, int, int, int, double, double, double, double, int,
-                                         hipStream_t);
-template hipError_t launch_factor<double>(void*, int, int, int, double, double, double, double,
-                                          int, hipStream_t);
-template hipError_t launch_pass<float>(const PassShape&, void*, const DevPass*, const DevStage*,
-                                       const DevOp<float>*, int, int64_t, int, double*, int64_t,
-                                       int, hipStream_t);
-template hipError_t launch_pass<double>(const PassShape&, void*, const DevPass*, const DevStage*,
-                                        const DevOp<double>*, int, int64_t, int, double*, int64_t,
-                                        int, hipStream_t);
-template hipError_t launch_resident<float>(int, int, const ResidentJob&, const ResidentJob*, int,
-                                           const DevStage*, const DevOp<float>*, int64_t,
-                                           hipStream_t);
-template hipError_t launch_resident<double>(int, int, const ResidentJob&, const ResidentJob*, int,
-                                            const DevStage*, const DevOp<double>*, int64_t,
-                                            hipStream_t);
+// Instantiations of the template families of this part.
+#define SPIN_INST_PASS(NAME, T)                                                                            \
+    template hipError_t NAME<T>(const PassShape&, void*, const DevPass*, const DevStage*, const DevOp<T>*, \
+                                int, int64_t, int, double*, int64_t, int, hipStream_t);
+#define SPIN_INST_RESIDENT(T)                                                                             \
+    template hipError_t launch_resident<T>(int, int, const ResidentJob&, const ResidentJob*, int,         \
+                                           const DevStage*, const DevOp<T>*, int64_t, hipStream_t);
+#define SPIN_INST_BATCH(T)                                                                                \
+    template int batch_occupancy<T>(bool);                                                                \
+    template hipError_t launch_batch<T>(int, bool, const BatchProblem*, const BatchJob*, const int*,      \
+                                        const DevPass*, const DevStage*, const DevOp<T>*, const int2*,    \
+                                        double*, int*, int, int*, int*, int64_t, hipStream_t);
+#if SPIN_PART == 0
+SPIN_INST_RESIDENT(float)
+#elif SPIN_PART == 1
+SPIN_INST_RESIDENT(double)
+#elif SPIN_PART == 2
+SPIN_INST_PASS(launch_pass_half, float)
+#elif SPIN_PART == 3
+SPIN_INST_PASS(launch_pass_half, double)
+#elif SPIN_PART == 4
+SPIN_INST_PASS(launch_pass_whole, float)
+#elif SPIN_PART == 5
+SPIN_INST_PASS(launch_pass_whole, double)
+#elif SPIN_PART == 6
+SPIN_INST_BATCH(float)
+#elif SPIN_PART == 7
+SPIN_INST_BATCH(double)
+#endif
 
 }  // namespace spinqp

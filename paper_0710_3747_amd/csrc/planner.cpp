@@ -476,16 +476,155 @@ std::vector<Op> gen_sequence(int M, const std::vector<Coupling>& J, double dt, i
 }  // namespace
 
 // ----------------------------------------------------------------- stages
-void plan_stages_coalesced(HostPass& pass, int r, int c, int beam, bool half) {
+// Gates usable by a pass of k positions with r register bits: the lane bits
+// below them hold the c coalescing positions of the first and last stage, and
+// the workgroup must have whole waves.
+static int usable_gates(int gates, int k, int r, int c) {
+    if (k - r < 6 || r < 2) return 0;
+    return std::max(0, std::min(std::min(gates, kMaxGates), 6 - std::max(4, c)));
+}
+
+// Execution order of a stage's ops when `ng` of its positions start on lane
+// bits (gates) and the other r in registers: a factor runs when both its
+// positions are in registers, an exchange of a register bit with a gate costs
+// one op.  Breadth-first over the number of exchanges, keeping the states
+// that ran the most ops (every choice of starting gates is a start state).
+// `split` (or -1) never leaves its register bit, the top one.
+static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int split) {
+    std::vector<int> local(kMaxSites, -1);
+    for (size_t p = 0; p < pass.sites.size(); ++p) local[pass.sites[p]] = int(p);
+    const int n = int(st.ops.size());
+    // positions as masks; an observable outside the tile waits on no position
+    // but on earlier observables (a virtual position)
+    const uint32_t kOutside = 1u << 31;
+    std::vector<uint32_t> need(n);
+    std::vector<char> meas(n);
+    for (int i = 0; i < n; ++i) {
+        const Op& op = pass.ops[st.ops[i]];
+        meas[i] = op.kind == 1;
+        if (meas[i]) need[i] = local[op.i] >= 0 ? 1u << local[op.i] : kOutside;
+        else need[i] = (1u << local[op.i]) | (1u << local[op.j]);
+    }
+    struct Done {        // ops run; the first 64 inline
+        uint64_t w = 0;
+        std::vector<uint64_t> more;
+        bool get(int i) const { return (i < 64 ? w >> i : more[i / 64 - 1] >> (i % 64)) & 1u; }
+        void set(int i) { (i < 64 ? w : more[i / 64 - 1]) |= uint64_t(1) << (i % 64); }
+        bool operator==(const Done& o) const { return w == o.w && more == o.more; }
+    };
+    struct State {
+        uint32_t gates = 0;       // positions on the gates
+        Done done;
+        int ndone = 0;
+        int parent = -1;          // state it came from, by exchanging
+        int in = 0, out = 0;      // position `in` from a gate with position `out`
+    };
+    // Runs everything that can run; observables after the factors before
+    // them, so that they form groups.
+    auto close = [&](State& s, std::vector<StageItem>* prog) {
+        for (bool any = true; any;) {
+            any = false;
+            for (int kind = 0; kind < 2; ++kind) {
+                uint32_t blocked = 0;
+                for (int i = 0; i < n; ++i) {
+                    if (s.done.get(i)) continue;
+                    if ((need[i] & blocked) || meas[i] != kind || (!meas[i] && (need[i] & s.gates))) {
+                        blocked |= need[i];
+                        continue;
+                    }
+                    s.done.set(i);
+                    ++s.ndone;
+                    if (prog) prog->push_back(StageItem{st.ops[i], 0, 0});
+                    any = true;
+                }
+            }
+        }
+    };
+    uint32_t movable = 0;
+    for (int p : st.regs)
+        if (p != split) movable |= 1u << p;
+    std::vector<std::vector<State>> levels(1);
+    for (uint32_t g = movable;; g = (g - 1) & movable) {     // submasks with ng bits
+        if (__builtin_popcount(g) == ng) {
+            State s;
+            s.gates = g;
+            s.done.more.assign(n > 64 ? (n - 1) / 64 : 0, 0);
+            close(s, nullptr);
+            levels[0].push_back(std::move(s));
+        }
+        if (g == 0) break;
+    }
+    constexpr int kWidth = 16;
+    while (true) {
+        std::vector<State>& level = levels.back();
+        std::stable_sort(level.begin(), level.end(),
+                         [](const State& a, const State& b) { return a.ndone > b.ndone; });
+        if (level.front().ndone == n) break;
+        if (int(levels.size()) > 2 * n + 4) throw std::runtime_error("planner: stage order not found");
+        if (int(level.size()) > kWidth) level.resize(kWidth);
+        std::vector<State> next;
+        for (size_t f = 0; f < level.size(); ++f)
+            for (uint32_t gs = level[f].gates; gs; gs &= gs - 1)
+                for (uint32_t rs = movable & ~level[f].gates; rs; rs &= rs - 1) {
+                    State t = level[f];
+                    t.parent = int(f);
+                    t.in = __builtin_ctz(gs);
+                    t.out = __builtin_ctz(rs);
+                    t.gates ^= (1u << t.in) | (1u << t.out);
+                    close(t, nullptr);
+                    bool dup = false;
+                    for (const State& o : next) dup |= o.gates == t.gates && o.done == t.done;
+                    if (!dup) next.push_back(std::move(t));
+                }
+        levels.push_back(std::move(next));
+    }
+    // the path to the best state, then its ops from the start
+    std::vector<const State*> path;
+    for (int d = int(levels.size()) - 1, f = 0; d >= 0; f = path.back()->parent, --d)
+        path.push_back(&levels[d][f]);
+    State s;
+    s.gates = path.back()->gates;
+    s.done.more.assign(n > 64 ? (n - 1) / 64 : 0, 0);
+    std::vector<int> regs, gates;
+    for (int p : st.regs)
+        if (p != split) (s.gates >> p & 1u ? gates : regs).push_back(p);
+    st.regs = regs;
+    st.gates = gates;
+    st.prog.clear();
+    close(s, &st.prog);
+    for (size_t d = path.size() - 1; d-- > 0;) {
+        const int g = int(std::find(gates.begin(), gates.end(), path[d]->in) - gates.begin());
+        const int q = int(std::find(regs.begin(), regs.end(), path[d]->out) - regs.begin());
+        std::swap(regs[q], gates[g]);
+        s.gates = path[d]->gates;
+        st.prog.push_back(StageItem{-1, q, g});
+        close(s, &st.prog);
+    }
+    st.ops.clear();
+    for (const StageItem& it : st.prog)
+        if (it.op >= 0) st.ops.push_back(it.op);
+    st.regs_out = regs;
+    st.gates_out = gates;
+    if (split >= 0) {
+        st.regs.push_back(split);
+        st.regs_out.push_back(split);
+    }
+}
+
+void plan_stages_coalesced(HostPass& pass, int r, int c, int beam, bool half, int gates, bool rank) {
     uint32_t af = 0, al = 0;
     const int k = int(pass.sites.size());
     for (int p = 0; p < k; ++p) {
         if (pass.bit_in[p] < c) af |= 1u << p;
         if (pass.bit_out[p] < c) al |= 1u << p;
     }
+    const int ng = usable_gates(gates, k, r, c);
+    const int rx = r + ng;      // positions a stage's ops can reach
     pass.split = -1;
     if (!half || k < 2 || r < 2) {
-        plan_stages(pass, r, af, al, beam);
+        plan_stages(pass, rx, af, al, beam);
+        if (!rank)
+            for (HostStage& st : pass.stages) plan_exchanges(pass, st, ng, -1);
         return;
     }
     // split position: the one whose greedy staging is shortest (ties: the
@@ -503,7 +642,7 @@ void plan_stages_coalesced(HostPass& pass, int r, int c, int beam, bool half) {
         if (((af | al) >> h) & 1u) continue;
         HostPass t = pass;
         try {
-            plan_stages(t, r, af, al, 1, 1u << h);
+            plan_stages(t, rx, af, al, 1, 1u << h);
         } catch (const std::runtime_error&) {
             continue;
         }
@@ -514,16 +653,13 @@ void plan_stages_coalesced(HostPass& pass, int r, int c, int beam, bool half) {
         }
     }
     if (best < 0) throw std::runtime_error("planner: no split position for a half-tile pass");
-    plan_stages(pass, r, af, al, beam, 1u << best);
+    plan_stages(pass, rx, af, al, beam, 1u << best);
     pass.split = best;
     // the split position on the top register bit of every stage
     for (HostStage& st : pass.stages) {
-        std::vector<int> regs;
-        for (int q : st.regs)
-            if (q != best) regs.push_back(q);
-        if (int(regs.size()) + 1 != int(st.regs.size())) throw std::runtime_error("planner: split position lost");
-        regs.push_back(best);
-        st.regs = regs;
+        if (std::find(st.regs.begin(), st.regs.end(), best) == st.regs.end())
+            throw std::runtime_error("planner: split position lost");
+        plan_exchanges(pass, st, ng, best);
     }
 }
 
@@ -759,7 +895,7 @@ static StreamPlan plan_stream_per_step(int M, const std::vector<Coupling>& J, do
         auto ap = sc.next_pass(forced, &T);
         plan.passes.push_back(make_pass(sb.ops, ap, T, M));
     }
-    for (auto& p : plan.passes) plan_stages_coalesced(p, std::min(pp.r, int(p.sites.size())), pp.c, 1, pp.half);
+    for (auto& p : plan.passes) plan_stages_coalesced(p, std::min(pp.r, int(p.sites.size())), pp.c, 1, pp.half, pp.gates, pp.rank);
     for (int t = 0; t < nobs0; ++t) {
         plan.launch_tmpl.push_back(t);
         plan.launch_offset.push_back(0);
@@ -794,9 +930,13 @@ HostPass schedule_one(Sched& sc, Relabel& rl, const std::vector<Op>& ops, int M,
     uint32_t af = 0;
     for (size_t p = 0; p < tmp.sites.size(); ++p)
         if (tmp.bit_in[p] < rl.c) af |= 1u << p;
+    auto reach = [&](const HostPass& p) {
+        const int k = int(p.sites.size()), r = std::min(pp.r, k);
+        return r + usable_gates(pp.gates, k, r, rl.c);
+    };
     Mask last_regs = 0;
     try {
-        if (pp.low_policy >= 1) plan_stages(tmp, std::min(pp.r, int(tmp.sites.size())), af, 0);
+        if (pp.low_policy >= 1) plan_stages(tmp, reach(tmp), af, 0);
         if (pp.low_policy >= 1)
             for (int q : tmp.stages.back().regs) last_regs |= bit(tmp.sites[q]);
     } catch (const std::runtime_error&) {
@@ -812,7 +952,7 @@ HostPass schedule_one(Sched& sc, Relabel& rl, const std::vector<Op>& ops, int M,
         HostPass nx = make_pass(ops, nap, T_next, M);
         rl.keep(nx, T_next);
         try {
-            plan_stages(nx, std::min(pp.r, int(nx.sites.size())), 0, 0);
+            plan_stages(nx, reach(nx), 0, 0);
             for (int q : nx.stages.front().regs) next_first |= bit(nx.sites[q]);
         } catch (const std::runtime_error&) {
             next_first = 0;
@@ -913,7 +1053,7 @@ std::vector<HostPass> plan_block(int M, const std::vector<Coupling>& J, double d
 
 void finish_stages(StreamPlan& plan, const PassParams& pp) {
     for (auto& p : plan.passes)
-        plan_stages_coalesced(p, std::min(pp.r, int(p.sites.size())), pp.c, 1, pp.half);
+        plan_stages_coalesced(p, std::min(pp.r, int(p.sites.size())), pp.c, 1, pp.half, pp.gates, pp.rank);
 }
 
 // Blocks of `W` steps repeated verbatim: the first carries the step-0
@@ -1108,6 +1248,7 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
                 if (window == 5 && policy != 2) continue;
                 PassParams v = pp;
                 v.half = false;
+                v.rank = pp.half;
                 v.window = window;
                 v.low_policy = policy;
                 v.rotate = rotate % std::max(M, 1);
@@ -1131,11 +1272,11 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
     // position.
     if (pp.half) {
         for (HostPass& hp : best.passes)
-            plan_stages_coalesced(hp, std::min(pp.r, int(hp.sites.size())), pp.c, nv > 1 ? 32 : 1, true);
+            plan_stages_coalesced(hp, std::min(pp.r, int(hp.sites.size())), pp.c, nv > 1 ? 32 : 1, true, pp.gates);
     } else if (nv > 1) {
         for (HostPass& hp : best.passes) {
             HostPass alt = hp;
-            plan_stages_coalesced(alt, std::min(pp.r, int(alt.sites.size())), pp.c, 32);
+            plan_stages_coalesced(alt, std::min(pp.r, int(alt.sites.size())), pp.c, 32, false, pp.gates);
             if (alt.stages.size() < hp.stages.size()) hp.stages = std::move(alt.stages);
         }
     }
@@ -1161,8 +1302,10 @@ ResidentPlan plan_resident(int M, const std::vector<Coupling>& J, double dt, int
     sb.emit_step(1);
     rp.step.ops = sb.ops;
     rp.step.writes = true;
-    plan_stages(rp.prologue, std::min(r, M));
-    plan_stages(rp.step, std::min(r, M));
+    for (HostPass* hp : {&rp.prologue, &rp.step}) {
+        plan_stages(*hp, std::min(r, M));
+        for (HostStage& st : hp->stages) plan_exchanges(*hp, st, 0, -1);
+    }
     return rp;
 }
 
@@ -1288,9 +1431,9 @@ void choose_lanes(std::vector<int>& tp, const std::vector<uint32_t>& img, int el
 // masks of tile-local positions; zero where the workgroup is one wave).
 // The stages are cut into maximal runs whose register positions leave at
 // least `nw` positions free; a run's wave positions are free in all its
-// stages.  The first stage keeps its 6 lowest-input-bit thread positions on
-// the lane bits and the last stage its 6 lowest-output-bit ones, so global
-// accesses keep their contiguous runs.  The first run's wave positions are
+// stages.  The first stage keeps its lowest-input-bit thread positions on
+// the lane bits below the gates and the last stage its lowest-output-bit ones,
+// so global accesses keep their contiguous runs; gates stay on their lanes.  The first run's wave positions are
 // also the last run's when both allow it (no barrier at the tile end), and
 // positions that keep their address bit are preferred.
 std::vector<uint32_t> wave_bits_plan(const HostPass& hp) {
@@ -1301,18 +1444,21 @@ std::vector<uint32_t> wave_bits_plan(const HostPass& hp) {
     if (nw <= 0 || nst == 1) return w;
     const uint32_t all = (1u << k) - 1;
     std::vector<uint32_t> forbid(nst, 0);
-    for (int si = 0; si < nst; ++si)
+    for (int si = 0; si < nst; ++si) {
         for (int p : hp.stages[si].regs) forbid[si] |= 1u << p;
-    auto low6 = [&](int si, const std::vector<int>& bit) {
+        for (int p : hp.stages[si].gates) forbid[si] |= 1u << p;
+    }
+    auto low_lanes = [&](int si, const std::vector<int>& bit) {
         std::vector<int> tp;
         for (int p = 0; p < k; ++p)
             if (!((forbid[si] >> p) & 1u)) tp.push_back(p);
         std::stable_sort(tp.begin(), tp.end(), [&](int a, int b) { return bit[a] < bit[b]; });
         uint32_t m = 0;
-        for (int q = 0; q < 6 && q < int(tp.size()); ++q) m |= 1u << tp[q];
+        const int nl = 6 - int(hp.stages[si].gates.size());
+        for (int q = 0; q < nl && q < int(tp.size()); ++q) m |= 1u << tp[q];
         return m;
     };
-    const uint32_t lo_first = low6(0, hp.bit_in), lo_last = low6(nst - 1, hp.bit_out);
+    const uint32_t lo_first = low_lanes(0, hp.bit_in), lo_last = low_lanes(nst - 1, hp.bit_out);
     forbid[0] |= lo_first;
     forbid[nst - 1] |= lo_last;
     // maximal runs
@@ -1407,10 +1553,95 @@ struct StageMatrix {
 
 }  // namespace
 
+namespace {
+
+// Reorders a stage's movable register bits (new bit of old bit q is perm[q])
+// and, with swap_gates, its two gates; the ops follow.
+HostStage reorder_stage(const HostStage& st, const std::vector<int>& perm, bool swap_gates) {
+    HostStage o = st;
+    for (size_t q = 0; q < perm.size(); ++q) {
+        o.regs[perm[q]] = st.regs[q];
+        o.regs_out[perm[q]] = st.regs_out[q];
+    }
+    if (swap_gates) {
+        std::swap(o.gates[0], o.gates[1]);
+        std::swap(o.gates_out[0], o.gates_out[1]);
+    }
+    for (StageItem& it : o.prog)
+        if (it.op < 0) {
+            it.q = perm[it.q];
+            if (swap_gates) it.g = 1 - it.g;
+        }
+    return o;
+}
+
+// Orders the register bits, gates and lanes of half-tile stages so that the
+// next stage's gather is free of bank conflicts: the LDS slots of the 16
+// lanes 0..15 must differ modulo the bank row.  `lanes` (positions on the
+// lane bits below the gates) of the first and last stage keep their order.
+void order_for_gathers(std::vector<HostStage>& stages, std::vector<std::vector<int>>& lanes,
+                       const std::vector<std::vector<int>>& waves, int eb, int nt) {
+    const int nst = int(stages.size());
+    const int mod = 1 << exchange_pad_shift(eb);
+    const int row = exchange_row_slots(nt, eb);
+    for (int si = 0; si + 1 < nst; ++si) {
+        const int rr = int(stages[si].regs.size()), ng = int(stages[si].gates.size());
+        const std::vector<int>& nl = lanes[si + 1];
+        const int n = std::min<int>(4, int(nl.size()));
+        // residues of the next stage's lanes under an ordering; number of
+        // lanes whose slot residue repeats
+        auto conflicts = [&](const HostStage& st, const std::vector<int>& la) {
+            std::vector<int> w(kMaxSites, 0);
+            std::vector<int> tq = la;
+            tq.insert(tq.end(), st.gates_out.begin(), st.gates_out.end());
+            tq.insert(tq.end(), waves[si].begin(), waves[si].end());
+            for (size_t q = 0; q < tq.size(); ++q) w[tq[q]] = exchange_slot(1 << q, eb);
+            for (int b = 0; b + 1 < rr; ++b) w[st.regs_out[b]] = row << b;
+            std::vector<char> seen(mod, 0);
+            int bad = 0;
+            for (int x = 0; x < (1 << n); ++x) {
+                int a = 0;
+                for (int q = 0; q < n; ++q)
+                    if (x >> q & 1) a += w[nl[q]];
+                bad += seen[a % mod];
+                seen[a % mod] = 1;
+            }
+            return bad;
+        };
+        const bool lanes_free = si > 0;
+        std::vector<int> perm(rr - 1), lp(lanes[si].size());
+        for (size_t q = 0; q < perm.size(); ++q) perm[q] = int(q);
+        HostStage best = stages[si];
+        std::vector<int> best_lanes = lanes[si];
+        int best_n = conflicts(best, best_lanes);
+        for (bool more = best_n > 0; more && best_n > 0; more = std::next_permutation(perm.begin(), perm.end()))
+            for (int sg = 0; sg < (ng == 2 ? 2 : 1) && best_n > 0; ++sg) {
+                const HostStage st = reorder_stage(stages[si], perm, sg != 0);
+                for (size_t q = 0; q < lp.size(); ++q) lp[q] = int(q);
+                // rotations of the lanes are enough beside every register order
+                for (size_t rot = 0; rot < (lanes_free ? lp.size() : 1) && best_n > 0; ++rot) {
+                    std::vector<int> la(lp.size());
+                    for (size_t q = 0; q < lp.size(); ++q) la[q] = lanes[si][(q + rot) % lp.size()];
+                    const int c = conflicts(st, la);
+                    if (c < best_n) {
+                        best_n = c;
+                        best = st;
+                        best_lanes = la;
+                    }
+                }
+            }
+        stages[si] = best;
+        lanes[si] = best_lanes;
+    }
+}
+
+}  // namespace
+
 template <typename T>
 void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, bool fixed_swizzle,
                  int engine, bool profile) {
     const int k = int(hp.sites.size());
+    std::vector<HostStage> stages = hp.stages;
     constexpr int eb = sizeof(T) * 2;
     DevPass dp{};
     dp.k = k;
@@ -1434,7 +1665,6 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
             ++nf;
         }
     dp.nfree = nf;
-    dp.obs_free_bit = local[observed] < 0 ? hp.layout[observed] : -1;
 
     // thread positions of every stage, and the LDS layout
     // Thread bit q of a stage is position tq[q].  The lanes of the last stage
@@ -1453,10 +1683,11 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
     const int nst = int(hp.stages.size());
     std::vector<uint32_t> wmask(nst, 0);
     if (!fixed_swizzle) wmask = wave_bits_plan(hp);
-    std::vector<std::vector<int>> tpos_all, lanes_all;
+    std::vector<std::vector<int>> tpos_all, lanes_all, waves_all;
     for (int si = 0; si < nst; ++si) {
         uint32_t rmask = 0;
-        for (int p : hp.stages[si].regs) rmask |= 1u << p;
+        for (int p : stages[si].regs) rmask |= 1u << p;
+        for (int p : stages[si].gates) rmask |= 1u << p;
         std::vector<int> tp, wv;
         for (int p = 0; p < k; ++p)
             if (!(rmask & (1u << p))) ((wmask[si] >> p) & 1u ? wv : tp).push_back(p);
@@ -1464,21 +1695,24 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
             std::stable_sort(tp.begin(), tp.end(),
                              [&](int a, int b) { return hp.bit_out[a] < hp.bit_out[b]; });
         lanes_all.push_back(tp);
-        tp.insert(tp.end(), wv.begin(), wv.end());
-        tpos_all.push_back(tp);
+        waves_all.push_back(wv);
     }
-    std::vector<uint32_t> img(k);
+    const bool gated = nst > 0 && !stages[0].gates.empty();
+    std::vector<uint32_t> img(k, 0u);
+    if (hp.split >= 0) {
+        // half-tile exchanges: one half of the tile in LDS at a time, the
+        // split position on the top register bit
+        for (const HostStage& st : stages)
+            if (st.regs.empty() || st.regs.back() != hp.split)
+                throw std::runtime_error("encode: split position not on the top register bit");
+        order_for_gathers(stages, lanes_all, waves_all, eb, 1 << (k - int(stages[0].regs.size())));
+    }
     if (fixed_swizzle) {
         for (int p = 0; p < k; ++p) img[p] = lds_swizzle<eb>(1u << p);
-    } else if (hp.split >= 0) {
-        // half-tile exchange: the LDS holds one half at a time, addressed by
-        // the other k - 1 positions; the split position has no image (both
-        // halves use the same slots)
-        const int h = hp.split;
-        for (const HostStage& st : hp.stages)
-            if (st.regs.empty() || st.regs.back() != h)
-                throw std::runtime_error("encode: split position not on the top register bit");
-        auto comp = [&](int p) { return p < h ? p : p - 1; };
+    } else if (hp.split >= 0 && !gated) {
+        // without register/lane exchanges a half-tile pass also has a layout
+        // shared by all its stages, over the other k - 1 positions
+        auto comp = [&](int p) { return p < hp.split ? p : p - 1; };
         std::vector<std::vector<int>> pat;
         for (const auto& lv : lanes_all) {
             std::vector<int> q;
@@ -1486,20 +1720,17 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
             pat.push_back(q);
         }
         const std::vector<uint32_t> im = search_layout(k - 1, eb, pat, uint64_t(k) * 131 + hp.ops.size());
-        for (int p = 0; p < k; ++p) img[p] = p == h ? 0u : im[comp(p)];
-        for (int si = 1; si + 1 < nst; ++si) {
-            std::vector<int> tp = lanes_all[si];
-            choose_lanes(tp, img, eb);
-            for (size_t q = 0; q < tp.size(); ++q) tpos_all[si][q] = tp[q];
-        }
-    } else {
+        for (int p = 0; p < k; ++p) img[p] = p == hp.split ? 0u : im[comp(p)];
+    } else if (hp.split < 0) {
         img = search_layout(k, eb, lanes_all, uint64_t(k) * 131 + hp.ops.size());
-        for (int si = 1; si + 1 < nst; ++si) {
-            // reorder the lane positions only; the wave positions stay last
-            std::vector<int> tp = lanes_all[si];
-            choose_lanes(tp, img, eb);
-            for (size_t q = 0; q < tp.size(); ++q) tpos_all[si][q] = tp[q];
-        }
+        // reorder the lane positions only; the wave positions stay last
+        for (int si = 1; si + 1 < nst; ++si) choose_lanes(lanes_all[si], img, eb);
+    }
+    for (int si = 0; si < nst; ++si) {
+        std::vector<int> tp = lanes_all[si];
+        tp.insert(tp.end(), stages[si].gates.begin(), stages[si].gates.end());
+        tp.insert(tp.end(), waves_all[si].begin(), waves_all[si].end());
+        tpos_all.push_back(tp);
     }
     // The exchange after stage si crosses waves (workgroup barrier) when the
     // wave positions change.  A wave's stores of a tile may overlap another
@@ -1526,38 +1757,31 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
     auto byte_off = [&](uint32_t l) { return apply_layout(img, l) * uint32_t(eb); };
 
     int nmeas = 0;
-    for (size_t si = 0; si < hp.stages.size(); ++si) {
-        const HostStage& hs = hp.stages[si];
+    std::vector<int> prev_w(k, 0);     // slot weight of every position, exchange before
+    for (size_t si = 0; si < stages.size(); ++si) {
+        const HostStage& hs = stages[si];
         DevStage ds{};
         ds.op0 = int(out.ops.size());
-        const int rr = int(hs.regs.size());
-        ds.ntb = k - rr;
+        const int rr = int(hs.regs.size()), ng = int(hs.gates.size()), ntb = k - rr;
+        const int lane0 = 6 - ng;      // lane bit of gate 0
         ds.xnext = (int(si) + 1 < nst) ? xnext[si] : 1;
-        const std::vector<int>& tq = tpos_all[si];
-        for (int q = 0; q < ds.ntb; ++q) {
+        // what the lane and register bits hold now (exchanges change it)
+        std::vector<int> tq = tpos_all[si], rq = hs.regs;
+        for (int q = 0; q < ntb; ++q) {
             ds.tmask[q] = byte_off(1u << tq[q]);
             ds.gt_in[q] = int64_t(1) << hp.bit_in[tq[q]];
-            ds.gt_out[q] = int64_t(1) << hp.bit_out[tq[q]];
         }
         for (int b = 0; b < rr; ++b) {
-            ds.rbit[b] = byte_off(1u << hs.regs[b]);
-            ds.gr_in[b] = int64_t(1) << hp.bit_in[hs.regs[b]];
-            ds.gr_out[b] = int64_t(1) << hp.bit_out[hs.regs[b]];
+            ds.rbit[b] = byte_off(1u << rq[b]);
+            ds.gr_in[b] = int64_t(1) << hp.bit_in[rq[b]];
         }
-        ds.obs_tq = -1;
-        ds.obs_mask = 0;
-        const int pobs = local[observed];
-        if (pobs >= 0) {
-            bool in_reg = false;
-            for (int b = 0; b < rr; ++b)
-                if (hs.regs[b] == pobs) { ds.obs_mask = 1 << b; in_reg = true; }
-            if (!in_reg)
-                for (int t = 0; t < ds.ntb; ++t)
-                    if (tq[t] == pobs) ds.obs_tq = t;
+        if (hp.split >= 0 && si > 0) {
+            for (int q = 0; q < ntb; ++q) ds.gw[q] = uint32_t(prev_w[tq[q]] * eb);
+            for (int b = 0; b + 1 < rr; ++b) ds.gr[b] = uint32_t(prev_w[rq[b]] * eb);
         }
         auto regbit = [&](int p) {
             for (int b = 0; b < rr; ++b)
-                if (hs.regs[b] == p) return b;
+                if (rq[b] == p) return b;
             throw std::runtime_error("encode: factor site not in registers");
         };
         if (engine == 1 && rr != 5) throw std::runtime_error("encode: matrix engine needs 5 register bits");
@@ -1571,23 +1795,30 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
             out.ops.push_back(d);
             sm.reset();
         };
-        for (int n : hs.ops) {
-            const Op& op = hp.ops[n];
+        // where an observed site's bit is now: kind and index of its aux field
+        auto site_bit = [&](int site) {
+            const int p = local[site];
+            if (p < 0) return (2 << 6) | (hp.layout[site] << 8);
+            for (int b = 0; b < rr; ++b)
+                if (rq[b] == p) return (1 << 6) | (b << 8);
+            for (int t = 0; t < ntb; ++t)
+                if (tq[t] == p) return t << 8;
+            throw std::runtime_error("encode: observed site not in the tile");
+        };
+        for (const StageItem& it : hs.prog) {
+            if (it.op < 0) {
+                if (engine == 1) throw std::runtime_error("encode: the matrix engine has no register/lane exchange");
+                std::swap(rq[it.q], tq[lane0 + it.g]);
+                DevOp<T> d{};
+                d.code = (6 + lane0 + it.g - 4) * 8 + it.q;
+                out.ops.push_back(d);
+                continue;
+            }
+            const Op& op = hp.ops[it.op];
             if (op.kind == 1 && profile) {
                 flush();
                 if (dp.pmeas >= kMaxMeasProfile) throw std::runtime_error("encode: too many observables");
                 const int site = op.i, slot = dp.pmeas++;
-                int kind = 2, index = hp.layout[site];
-                if (local[site] >= 0) {
-                    kind = 0;
-                    for (int t = 0; t < ds.ntb; ++t)
-                        if (tq[t] == local[site]) index = t;
-                    for (int b = 0; b < rr; ++b)
-                        if (hs.regs[b] == local[site]) {
-                            kind = 1;
-                            index = b;
-                        }
-                }
                 int nslot = -1;
                 if (site == observed) {
                     if (dp.pnorm >= kMaxMeas) throw std::runtime_error("encode: too many norms");
@@ -1596,7 +1827,7 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
                 }
                 DevOp<T> d{};
                 d.code = kOpMeas;
-                d.aux = slot | (kind << 6) | (index << 8) | ((nslot + 1) << 14) | (site << 17);
+                d.aux = slot | site_bit(site) | ((nslot + 1) << 14) | (site << 17);
                 dp.pmeas_step[slot] = op.step;
                 dp.pmeas_site[slot] = int8_t(site);
                 out.ops.push_back(d);
@@ -1607,7 +1838,7 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
                 if (nmeas >= kMaxMeas) throw std::runtime_error("encode: too many observables");
                 DevOp<T> d{};
                 d.code = kOpMeas;
-                d.aux = nmeas;
+                d.aux = nmeas | site_bit(op.i);
                 dp.meas_step[nmeas] = op.step;
                 ++nmeas;
                 out.ops.push_back(d);
@@ -1640,6 +1871,14 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
         }
         flush();
         ds.nop = int(out.ops.size()) - ds.op0;
+        DevOp<T> end{};
+        end.code = kOpEnd;
+        out.ops.push_back(end);
+        if (rq != hs.regs_out) throw std::runtime_error("encode: stage exit differs from its plan");
+        for (int q = 0; q < ntb; ++q) ds.gt_out[q] = int64_t(1) << hp.bit_out[tq[q]];
+        for (int b = 0; b < rr; ++b) ds.gr_out[b] = int64_t(1) << hp.bit_out[rq[b]];
+        for (int q = 0; q < ntb; ++q) prev_w[tq[q]] = exchange_slot(1 << q, eb);
+        for (int b = 0; b + 1 < rr; ++b) prev_w[rq[b]] = exchange_row_slots(1 << ntb, eb) << b;
         out.stages.push_back(ds);
     }
     dp.nmeas = nmeas;

@@ -56,9 +56,19 @@ class SeqBuilder {
     int64_t cur_step_ = -1;
 };
 
+// One op of a stage in execution order: op >= 0 is an index into
+// HostPass::ops; op = -1 exchanges register bit q with gate g of the stage.
+struct StageItem {
+    int op, q, g;
+};
+
 struct HostStage {
-    std::vector<int> regs;     // register bit q -> tile-local position
-    std::vector<int> ops;      // indices into HostPass::ops
+    std::vector<int> regs;     // entry: register bit q -> tile-local position
+    std::vector<int> gates;    // entry: tile-local positions on the top lane bits of the wave
+                               // (lane bit 6 - gates.size() + g holds gate g); may be empty
+    std::vector<int> ops;      // indices into HostPass::ops, in execution order
+    std::vector<StageItem> prog;              // ops and register/lane exchanges, in order
+    std::vector<int> regs_out, gates_out;     // as regs and gates, at exit
 };
 
 struct HostPass {
@@ -84,6 +94,11 @@ struct PassParams {
     // can move the tile through LDS in two halves (the position's two
     // values), each half through the same LDS slots.
     bool half = false;
+    // Lane bits of a stage whose positions its ops can reach by exchanging
+    // them with register bits inside the wave (0..kMaxGates, on the top lane
+    // bits; fewer when more than 4 low address bits pin the lanes).
+    int gates = 0;
+    bool rank = false;         // the plan is only compared with others (see plan_stages_coalesced)
     // Scheduling variant (plan_stream tries several and keeps the cheapest
     // by the cost model below):
     int window = 3;            // steps a pass may run ahead of the oldest pending op
@@ -126,7 +141,10 @@ void plan_stages(HostPass& pass, int r, uint32_t avoid_first = 0, uint32_t avoid
 // (output) global bit is below c.  half: also choose the pass's split
 // position (HostPass::split) and keep it on the top register bit of every
 // stage.
-void plan_stages_coalesced(HostPass& pass, int r, int c, int beam = 1, bool half = false);
+// gates: lane bits each stage can exchange with registers (PassParams::gates).
+// rank: stages only, to compare plans by; their exchanges are left out.
+void plan_stages_coalesced(HostPass& pass, int r, int c, int beam = 1, bool half = false, int gates = 0,
+                           bool rank = false);
 
 // Full streaming plan for one scheduling variant: sequence, passes, period
 // search, stages.

@@ -1,0 +1,42 @@
+"""Host checks of half-tile passes whose stages exchange register bits with
+lane bits (no GPU): tests/host_checks/gate_check.cpp emulates the encoded
+tables on one tile."""
+import os
+import subprocess
+
+import pytest
+
+import workloads
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def binary(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("gates") / "gate_check")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", os.path.join(ROOT, "tests", "host_checks", "gate_check.cpp"),
+                           os.path.join(ROOT, "paper_0710_3747_amd", "csrc", "planner.cpp"), "-o", out])
+    return out
+
+
+CASES = [
+    # name, M, couplings, prec, k, r, c, steps, observed
+    ("ladder2x9-c64-r5", 18, workloads.ladder(9), 1, 14, 5, 4, 30, 0),
+    ("ladder2x15-c64-r5-top-site", 30, workloads.ladder(15), 1, 14, 5, 4, 20, 29),
+    ("ladder2x15-c64-r6", 30, workloads.ladder(15), 1, 14, 6, 4, 20, 7),
+    ("ladder2x15-c64-one-gate", 30, workloads.ladder(15), 1, 14, 5, 5, 20, 0),
+    ("ladder2x15-c64-no-gate", 30, workloads.ladder(15), 1, 14, 5, 6, 20, 0),
+    ("ladder2x15-c128-k13-r4", 30, workloads.ladder(15), 2, 13, 4, 4, 20, 0),
+    ("ladder2x15-c128-k14", 30, workloads.ladder(15), 2, 14, 5, 4, 20, 0),
+    ("star17-c128-zz", 17, workloads.star(17, 3, a_over_b=0.5), 2, 13, 5, 4, 10, 5),
+    ("star28-blocks-c64", 28, workloads.star_m28(), 1, 14, 5, 4, 2, 0),
+    ("two-site-bond-c64", 15, [(3, 11, 0.0, 1.0)], 1, 14, 5, 4, 3, 14),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_register_lane_exchanges(case, binary):
+    _, M, J, prec, k, r, c, steps, obs = case
+    inp = f"{M} {prec} {k} {r} {c} {steps} {obs}\n" + "".join(f"{i} {j} {a!r} {b!r}\n" for i, j, a, b in J)
+    p = subprocess.run([binary], input=inp, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0 and "failures 0" in p.stdout, p.stdout
