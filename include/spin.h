@@ -130,8 +130,10 @@ typedef struct {
     int32_t schedule;     /* 0 = fused tiles (default); 1 = one full pass per factor
                              (the plain, unfused schedule, kept as a cross-check) */
     int32_t tile_bits;    /* k of the 2^k-amplitude tiles; 0 = default (14 for
-                             complex64, 13 for complex128; complex128 also takes 14,
-                             with half tiles and one workgroup per CU) */
+                             complex64, 13 for complex128, smaller for states that
+                             would leave CUs idle: 12 up to M = 20, 13 at M = 21;
+                             complex128 also takes 14, with half tiles and one
+                             workgroup per CU) */
     int32_t reg_bits;     /* amplitudes per lane = 2^reg_bits; 0 = default */
     int32_t coalesce_bits;/* low address bits every tile keeps; 0 = default (4) */
     int32_t engine;       /* 0 = VALU butterflies (default); 1 = each register stage's
@@ -145,7 +147,8 @@ typedef struct {
                              (for calls that repeat); ignored by states held by one
                              workgroup and by the unfused schedule */
     int32_t exchange;     /* tiled path, stage exchanges through LDS: 0 = default (half
-                             tiles where the shape has such a kernel, else whole tiles);
+                             tiles where the shape has such a kernel, else whole tiles,
+                             through per-lane slots where the shape is a small one);
                              1 = whole tiles (one workgroup per CU, the next tile
                              prefetched into registers); 2 = half tiles (one tile
                              position stays in registers in every stage, the tile moves

@@ -113,14 +113,14 @@ int scratch_get(hipStream_t st, size_t bytes, void** out) { return scratch_get_s
 
 // ------------------------------------------------------------- plan cache
 struct PlanKey {
-    int dev, prec, M, observed, k, r, nt, c, merge, engine, profile, half;
+    int dev, prec, M, observed, k, r, nt, c, merge, engine, profile, exchange;
     double dt;
     int64_t n_steps;
     std::vector<double> J;    // flattened couplings
     bool operator<(const PlanKey& o) const {
-        return std::tie(dev, prec, M, observed, k, r, nt, c, merge, engine, profile, half, dt, n_steps, J) <
+        return std::tie(dev, prec, M, observed, k, r, nt, c, merge, engine, profile, exchange, dt, n_steps, J) <
                std::tie(o.dev, o.prec, o.M, o.observed, o.k, o.r, o.nt, o.c, o.merge, o.engine,
-                        o.profile, o.half, o.dt, o.n_steps, o.J);
+                        o.profile, o.exchange, o.dt, o.n_steps, o.J);
     }
 };
 
@@ -171,15 +171,29 @@ static int upload_tables(const DevTables<T>& tb, DevicePlan* dp) {
 
 // Launch shape: tile bits k = r + log2(nt).  Defaults: complex64 tiles of
 // 2^14 amplitudes, complex128 tiles of 2^13 (128 KiB either way), exchanged
-// through LDS in halves where a kernel exists (two workgroups per CU).
+// through LDS in halves where a kernel exists (two workgroups per CU); states
+// too small to fill the CUs with them in smaller tiles, exchanged at once.
 Shape choose_shape(int prec, int M, const spin_options* opt) {
     Shape s;
     const bool f32 = prec == SPIN_C64;
     const int ex = opt ? opt->exchange : 0;
+    // One tile is one workgroup's work for a pass, so a state of 2^18
+    // amplitudes leaves 240 of 256 CUs idle with tiles of 2^14.  Smaller tiles
+    // hold fewer factors per pass, but a pass is shorter by more.  us per step
+    // with tiles of 2^12 / 2^13 / 2^14: ladder M = 18 11.7 / 16 / 18.2, M = 20
+    // 18 / 21 / 24, M = 22 34 / 31 / 31; star M = 17 89 / 116 / 139, M = 19 150 /
+    // 152 / 196, M = 21 308 / 267 / 279.  complex128, 2^12 / 2^13: ladder M = 18
+    // 17 / 22, M = 20 27 / 29; star M = 17 127 / 152, M = 19 208 / 214.
+    const int small = M <= 20 ? 12 : M == 21 && f32 ? 13 : 0;
+    const bool plain = ex == 0 && !(opt && (opt->engine || opt->reg_bits || opt->tile_bits));
     int k = f32 ? 14 : 13;
     // complex128 tiles: 16 amplitudes per lane with half-tile exchanges
     // (two 256-lane workgroups per CU), 8 with whole tiles
     s.r = (f32 || ex != 1) ? 5 : 4;
+    if (plain && small) {
+        k = small;
+        s.r = 4;
+    }
     // 4 low address bits in every tile: 128-byte runs of complex64 (fewer
     // passes than 256-byte runs, which outweighs the slower sweep on the
     // ladders), 256-byte runs of complex128
@@ -197,8 +211,10 @@ Shape choose_shape(int prec, int M, const spin_options* opt) {
     s.k = k;
     s.engine = opt ? opt->engine : 0;
     const bool half_ok = s.engine == 0 && pass_half_exists(f32, s.r, s.nt);
-    s.half = ex == 2 || (ex == 0 && half_ok);
-    s.valid = s.half ? half_ok : pass_shape_exists(f32, s.r, s.nt, s.engine);
+    const bool small_ok = s.engine == 0 && pass_small_exists(f32, s.r, s.nt);
+    s.exchange = ex == 2 || (ex == 0 && half_ok) ? kHalfTiles : ex == 0 && small_ok ? kSmallTiles : kWholeTiles;
+    s.valid = s.exchange == kHalfTiles ? half_ok
+                                       : s.exchange == kSmallTiles || pass_shape_exists(f32, s.r, s.nt, s.engine);
     s.res_cap = f32 ? 14 : 13;
     s.resident = M <= s.res_cap;
     return s;
@@ -212,6 +228,13 @@ static int res_shape(int prec, int M, int* r, int* nt) {
     else if (tb <= 8) *nt = 256;
     else *nt = 512;
     return SPIN_OK;
+}
+
+// Planner settings of an exchange mode.
+static void exchange_params(ExchangeMode x, PassParams* pp) {
+    pp->half = x == kHalfTiles;
+    pp->once = x == kSmallTiles;
+    pp->gates = x == kWholeTiles ? 0 : kMaxGates;
 }
 
 template <typename T>
@@ -238,14 +261,13 @@ static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, const 
             pp.r = sh.r;
             pp.c = sh.c;
             pp.profile = key.profile != 0;
-            pp.half = sh.half;
-            pp.gates = sh.half ? kMaxGates : 0;
+            exchange_params(sh.exchange, &pp);
             if (pp.profile) pp.max_meas = kMaxMeasProfile;
             dp->sp = plan_stream_best(key.M, J, key.dt, key.n_steps, key.observed, key.merge != 0, pp);
             dp->shape = PassShape{sh.r, sh.nt};
             dp->shape.engine = sh.engine;
             dp->shape.profile = pp.profile;
-            dp->shape.half = sh.half;
+            dp->shape.exchange = sh.exchange;
             dp->profile = pp.profile;
             dp->k = sh.k;
             const int64_t ntiles = int64_t(1) << (key.M - sh.k);
@@ -292,12 +314,12 @@ int get_plan(int prec, int M, const std::vector<Coupling>& J, double dt, int64_t
         std::ostringstream os;
         os << "no pass kernel for tile_bits " << sh.k << " with reg_bits " << sh.r
            << (sh.engine ? " and the matrix engine (complex64, tile_bits 14, reg_bits 5 only)" : "")
-           << (sh.half ? " and half-tile exchanges" : "");
+           << (sh.exchange == kHalfTiles ? " and half-tile exchanges" : "");
         return fail(SPIN_EUNSUPPORTED, os.str());
     }
     PlanKey key{dev, prec, M, observed, sh.k, sh.r, sh.nt, sh.c,
                 (opt && opt->no_merge) ? 0 : 1, sh.resident ? 0 : sh.engine,
-                profile ? 1 : 0, (sh.half && !sh.resident) ? 1 : 0, dt, sh.resident ? 0 : n_steps, {}};
+                profile ? 1 : 0, sh.resident ? 0 : int(sh.exchange), dt, sh.resident ? 0 : n_steps, {}};
     key.J.reserve(J.size() * 4);
     for (const Coupling& c : J) {
         key.J.push_back(c.i);
@@ -842,8 +864,7 @@ int host_plan(int32_t prec, int32_t M, const std::vector<Coupling>& Jv, double d
             pp.r = hp->sh.r;
             pp.c = hp->sh.c;
             pp.profile = profile;
-            pp.half = hp->sh.half;
-            pp.gates = hp->sh.half ? kMaxGates : 0;
+            exchange_params(hp->sh.exchange, &pp);
             if (profile) pp.max_meas = kMaxMeasProfile;
             hp->sp = plan_stream_best(M, Jv, dt, n_steps, observed, merge, pp);
         }
@@ -900,7 +921,7 @@ extern "C" int spin_describe_plan(int32_t prec, int32_t M, const spin_coupling* 
         info->lanes = hp.sh.nt;
         info->coalesce_bits = hp.sh.c;
         info->engine = hp.sh.engine;
-        info->exchange = hp.sh.half ? 2 : 1;
+        info->exchange = hp.sh.exchange == kHalfTiles ? 2 : 1;
         info->templates = int(hp.sp.passes.size());
         info->period_steps = hp.sp.period_steps;
         info->period_passes = hp.sp.period_passes;

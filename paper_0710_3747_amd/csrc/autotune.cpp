@@ -124,19 +124,32 @@ spin_options to_options(const Tuned& t) {
     return o;
 }
 
-// Candidate launch shapes; the first is the library default.  The MFMA
-// matrix engine is not among them: a dense stage matrix costs about 20x the
-// flops of the butterflies it replaces and it removes no LDS exchange, so it
-// never wins on these workloads (it stays selectable through spin_options).
-// Exchange 2 = half tiles (two workgroups per CU; one for complex128 tiles
-// of 2^14), 1 = whole tiles.
-std::vector<Tuned> candidates(int32_t prec) {
+std::vector<Tuned> large_tiles(int32_t prec) {
     if (prec == SPIN_C64)
         return {{14, 5, 4, 0, 2, 0}, {14, 5, 5, 0, 2, 0}, {14, 5, 6, 0, 2, 0}, {14, 6, 4, 0, 2, 0},
                 {14, 5, 4, 0, 1, 0}, {14, 5, 6, 0, 1, 0}, {14, 4, 4, 0, 1, 0}, {13, 5, 5, 0, 1, 0},
                 {13, 4, 4, 0, 1, 0}};
     return {{13, 4, 4, 0, 2, 0}, {13, 5, 4, 0, 2, 0}, {14, 5, 4, 0, 2, 0}, {13, 4, 4, 0, 1, 0},
             {13, 5, 4, 0, 1, 0}, {12, 4, 4, 0, 1, 0}};
+}
+
+// Candidate launch shapes; the first is the library default.  The MFMA
+// matrix engine is not among them: a dense stage matrix costs about 20x the
+// flops of the butterflies it replaces and it removes no LDS exchange, so it
+// never wins on these workloads (it stays selectable through spin_options).
+// Exchange 2 = half tiles (two workgroups per CU; one for complex128 tiles
+// of 2^14), 1 = whole tiles, 0 = the small tiles, for states that leave CUs
+// idle with large ones.
+std::vector<Tuned> candidates(int32_t prec, int32_t M) {
+    std::vector<Tuned> c;
+    if (M <= 22) {
+        c.push_back({12, 4, 4, 0, 0, 0});
+        if (prec == SPIN_C64) c.push_back({13, 4, 4, 0, 0, 0});
+    }
+    const std::vector<Tuned> large = large_tiles(prec);
+    if (choose_shape(prec, M, nullptr).exchange == kSmallTiles) c.insert(c.end(), large.begin(), large.end());
+    else c.insert(c.begin(), large.begin(), large.end());
+    return c;
 }
 
 struct DeviceBuffers {
@@ -183,7 +196,7 @@ extern "C" int spin_autotune(int32_t prec, int32_t M, const spin_coupling* J, in
         if ((rc = tune_key(prec, M, Jv, dt, observed_site, &key))) return rc;
         hipStream_t st = static_cast<hipStream_t>(stream);
 
-        std::vector<Tuned> cand = candidates(prec);
+        std::vector<Tuned> cand = candidates(prec, M);
         if (choose_shape(prec, M, nullptr).resident) cand.resize(1);   // one workgroup: nothing to tune
         DeviceBuffers b;
         const size_t elem = prec == SPIN_C64 ? 8 : 16;

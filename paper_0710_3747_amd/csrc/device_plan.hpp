@@ -19,17 +19,20 @@ constexpr int kMaxSites = 40;
 constexpr int kBatchRing = 16;      // observable slots per gang problem (steps mod 16)
 constexpr int kMaxMeasProfile = 64; // per-site observables one pass can hold (all-site profile)
 
-// Op codes.  A two-spin factor on register bits (qa < qb) of a stage has
-// code qa*8 + qb; kOpZZ is or-ed in when the factor carries an I^z I^z
-// phase.  kOpMeas accumulates the observable of the state at that point.
-// Code (6 + g)*8 + q exchanges register bit q with lane bit 4 + g (g = 0, 1):
+// Op codes.  A two-spin factor on register bits a < b of a stage is one op
+// op_xy(a, b) and, when it carries an I^z I^z phase, a second one op_zz(a, b).
+// op_gate(q, g) exchanges register bit q with lane bit 4 + g (g = 0, 1):
 // register q = 1 of the lanes with the lane bit clear trades places with
 // register q = 0 of the lanes with it set, so the site on the lane bit
-// becomes a register site and the other way round, without LDS.
-constexpr int32_t kOpZZ = 64;
-constexpr int32_t kOpMeas = 255;
-// Ends every stage's ops (not counted in DevStage::nop).
-constexpr int32_t kOpEnd = 253;
+// becomes a register site and the other way round, without LDS.  kOpMeas
+// accumulates the observable of the state at that point; kOpEnd ends every
+// stage's ops (not counted in DevStage::nop).  The codes are the slots of the
+// kernels' handlers (a phase's takes four).
+constexpr int32_t op_xy(int a, int b) { return b * (b - 1) / 2 + a; }
+constexpr int32_t op_gate(int q, int g) { return 16 + 2 * q + g; }
+constexpr int32_t op_zz(int a, int b) { return 32 + 4 * op_xy(a, b); }
+constexpr int32_t kOpEnd = 28;
+constexpr int32_t kOpMeas = 29;
 constexpr int kMaxGates = 2;        // lane bits 4 and 5
 // kOpMat (matrix engine, 32 registers per lane): multiply the lane's
 // registers by a dense 32 x 32 complex matrix, the product of consecutive
@@ -37,13 +40,14 @@ constexpr int kMaxGates = 2;        // lane bits 4 and 5
 // table: kMatFloats floats per matrix, the real 64 x 64 form
 // W = [[Re U, -Im U], [Im U, Re U]] in MFMA A-operand order
 // (W[32 b + (l % 32)][2 p + l / 32] at float (32 b + p) * 64 + l).
-constexpr int32_t kOpMat = 254;
+constexpr int32_t kOpMat = 30;
 constexpr int kMatFloats = 64 * 64;
 
 // One op of a stage.  For a factor with integrated strengths
 // (A, B) = (sum a*tau, sum b*tau) over the merged two-spin propagators:
-//   theta = B/2, t = tan(theta/2), s = sin(theta)     (three-shear rotation)
-//   (pr, pi) = exp(+i A/4)                             (anti-aligned phase)
+//   op_xy: theta = B/2, (t, s) = (tan(theta/2), sin(theta)) for the three-shear
+//          rotation, and their negatives (nt, ns)
+//   op_zz: (t, s) = (cos, sin)(A/4), the anti-aligned phase exp(+i A/4)
 // For kOpMeas, aux = slot | kind << 6 | index << 8: the observed site's bit is
 // thread bit `index` (kind 0), register bit `index` (kind 1) or global address
 // bit `index` of the tile base (kind 2) at that point of the stage; slot is
@@ -54,7 +58,7 @@ constexpr int kMatFloats = 64 * 64;
 // 32 (48) bytes, so that a record is one aligned scalar load.
 template <typename T>
 struct alignas(sizeof(T) == 4 ? 32 : 16) DevOp {
-    T t, s, pr, pi;
+    T t, s, nt, ns;
     int32_t code;
     int32_t aux;
 };
@@ -64,8 +68,8 @@ struct alignas(sizeof(T) == 4 ? 32 : 16) DevOp {
 // each), the stage's ops run on registers, and the registers are scattered
 // back.  Ops that exchange a register bit with lane bit 4 or 5 leave other
 // positions there: gw/gr and gt_in/gr_in describe the stage's entry,
-// gt_out/gr_out its exit.  tmask/rbit are the layout of whole-tile passes and
-// of the one-workgroup kernel (bits xor-ed).
+// gt_out/gr_out its exit.  tmask/rbit are the layout of passes that keep one
+// layout for all stages and of the one-workgroup kernel (bits xor-ed).
 struct DevStage {
     int32_t op0, nop;         // op range
     int32_t xnext;            // 1: the exchange after this stage moves amplitudes between
@@ -73,8 +77,8 @@ struct DevStage {
     int32_t pad_;
     uint32_t tmask[16];       // LDS byte offset of thread bit q (zero past the last)
     uint32_t rbit[8];         // LDS byte offset of register bit q
-    // Half-tile passes: LDS byte weight of thread bit q / register bit q at
-    // entry, in the exchange from the stage before (see exchange_row_slots).
+    // Exchanges through per-lane slots: LDS byte weight of thread bit q /
+    // register bit q at entry (see exchange_row_slots).
     uint32_t gw[10], gr[6];
     // Global element offsets of thread bit q / register bit q, for the first
     // stage of a pass (loaded straight from HBM, input layout, entry) and the
@@ -103,8 +107,8 @@ struct DevPass {
     int32_t pnorm_meas[kMaxMeas];          // measurement slot whose step the norm slot carries
 };
 
-// LDS slots of a half-tile exchange.  The amplitude that lane `tid` holds in
-// register j (of the half's registers) goes to slot
+// Per-lane LDS slots of an exchange.  The amplitude that lane `tid` holds in
+// register j (in a half-tile exchange: of the half's registers) goes to slot
 //     j * exchange_row_slots + tid + (tid >> P),
 // P = 5 for 8-byte and 4 for 16-byte amplitudes: an address of the lane's own
 // plus a constant per register, so the scatter needs no address arithmetic.

@@ -381,71 +381,23 @@ __device__ __forceinline__ void reg_zz(C (&v)[1 << R], T pr, T pim) {
         if ((j & (a | b)) == 0) phase_quad(v[j | a], v[j | b], v[j], v[j | a | b], pr, pim);
 }
 
-// Exchange of register bit Q with lane bit 4 (G = 0) or 5 (G = 1): one
-// v_permlane16_swap / v_permlane32_swap per register pair and component, which
-// trades the rows of the first operand that have the lane bit set for the
-// rows of the second that have it clear.
-template <int G>
-__device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {
-    const auto r = G == 0 ? __builtin_amdgcn_permlane16_swap(a, b, false, false)
-                          : __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-}
-template <int G>
-__device__ __forceinline__ void swap_rows(float& a, float& b) {
-    uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
-    swap_rows<G>(x, y);
-    a = __uint_as_float(x);
-    b = __uint_as_float(y);
-}
-template <int G>
-__device__ __forceinline__ void swap_rows(double& a, double& b) {
-    const uint64_t x = uint64_t(__double_as_longlong(a)), y = uint64_t(__double_as_longlong(b));
-    uint32_t xl = uint32_t(x), xh = uint32_t(x >> 32), yl = uint32_t(y), yh = uint32_t(y >> 32);
-    swap_rows<G>(xl, yl);
-    swap_rows<G>(xh, yh);
-    a = __longlong_as_double(int64_t((uint64_t(xh) << 32) | xl));
-    b = __longlong_as_double(int64_t((uint64_t(yh) << 32) | yl));
-}
-template <int R, int Q, int G, typename C>
-__device__ __forceinline__ void reg_gate(C (&v)[1 << R]) {
-#pragma unroll
-    for (int j = 0; j < (1 << R); ++j) {
-        if (((j >> Q) & 1) == 0) {
-            const int k = j | (1 << Q);
-            swap_rows<G>(v[j].x, v[k].x);
-            swap_rows<G>(v[j].y, v[k].y);
-        }
-    }
-}
-
-// GATES: the stage may hold register/lane exchanges.
-template <int R, bool GATES, typename C, typename T>
-__device__ __forceinline__ void reg_op(C (&v)[1 << R], int code, T t, T s, T pr, T pim) {
+// One op of a stage without register/lane exchanges.
+template <int R, typename C, typename T>
+__device__ __forceinline__ void reg_op(C (&v)[1 << R], int code, T t, T s) {
 #define SPIN_CASE(A, B)                                        \
-    case A * 8 + B:                                            \
-        if constexpr (B < R) {                                 \
-            reg_xy<R, A, B>(v, t, s);                          \
-            if (code & kOpZZ) reg_zz<R, A, B>(v, pr, pim);     \
-        }                                                      \
-        break;
-#define SPIN_GATE(Q)                                           \
-    case 48 + Q:                                               \
-        if constexpr (GATES && Q < R) reg_gate<R, Q, 0>(v);    \
+    case op_xy(A, B):                                          \
+        if constexpr (B < R) reg_xy<R, A, B>(v, t, s);         \
         break;                                                 \
-    case 56 + Q:                                               \
-        if constexpr (GATES && Q < R) reg_gate<R, Q, 1>(v);    \
+    case op_zz(A, B):                                          \
+        if constexpr (B < R) reg_zz<R, A, B>(v, t, s);         \
         break;
-    switch (code & 63) {
+    switch (code) {
         SPIN_CASE(0, 1) SPIN_CASE(0, 2) SPIN_CASE(1, 2) SPIN_CASE(0, 3) SPIN_CASE(1, 3)
         SPIN_CASE(2, 3) SPIN_CASE(0, 4) SPIN_CASE(1, 4) SPIN_CASE(2, 4) SPIN_CASE(3, 4)
         SPIN_CASE(0, 5) SPIN_CASE(1, 5) SPIN_CASE(2, 5) SPIN_CASE(3, 5) SPIN_CASE(4, 5)
-        SPIN_GATE(0) SPIN_GATE(1) SPIN_GATE(2) SPIN_GATE(3) SPIN_GATE(4) SPIN_GATE(5)
         default: break;
     }
 #undef SPIN_CASE
-#undef SPIN_GATE
 }
 
 // sum of (sign * |psi|^2, |psi|^2) over the lane's registers, FP64
@@ -469,16 +421,6 @@ __device__ __forceinline__ uint32_t stage_base(const DevStage& S, int tid) {
 #pragma unroll
     for (int q = 0; q < NTB; ++q) b ^= S.tmask[q] & (0u - ((uint32_t(tid) >> q) & 1u));
     return b;
-}
-
-// LDS byte address from which the lane gathers register 0 at the entry of
-// stage S in a half-tile exchange (weights added up, see exchange_row_slots).
-template <int NTB>
-__device__ __forceinline__ uint32_t gather_base(const DevStage& S, int tid) {
-    uint32_t a = 0;
-#pragma unroll
-    for (int q = 0; q < NTB; ++q) a += S.gw[q] & (0u - ((uint32_t(tid) >> q) & 1u));
-    return a;
 }
 
 // Barrier for LDS traffic only: global loads in flight (the next tile's
@@ -543,28 +485,24 @@ __device__ __forceinline__ void scatter(const C (&v)[1 << R], char* lds, uint32_
     }
 }
 
-// Exchange of the half of a lane's registers whose top register bit is H
-// (the split position's value).  Scatter: register i of the half goes to row
-// i, a constant offset from the lane's own slot.  Gather: Gray-code order over
-// the lower R - 1 register bits, one add or subtract per register.  Both
-// halves use the same slots, one after the other.
-template <int R, int H, int ROW, typename C>
-__device__ __forceinline__ void scatter_half(const C (&v)[1 << R], char* own) {
-    constexpr int B = 1 << (R - 1);
+// Exchange of 2^RW of a lane's registers, H * 2^RW and up (H: the half of a
+// half-tile exchange, 0 otherwise).  Scatter: register i goes to row i, a
+// constant offset from the lane's own slot.  Gather: Gray-code order over the
+// RW register bits, one add or subtract per register.
+template <int RW, int H, int ROW, typename C, int NR>
+__device__ __forceinline__ void scatter_rows(const C (&v)[NR], char* own) {
 #pragma unroll
-    for (int i = 0; i < B; ++i) *reinterpret_cast<C*>(own + i * ROW) = v[H * B + i];
+    for (int i = 0; i < (1 << RW); ++i) *reinterpret_cast<C*>(own + i * ROW) = v[(H << RW) + i];
 }
 
-template <int R, int H, typename C>
-__device__ __forceinline__ void gather_half(C (&v)[1 << R], const char* lds, uint32_t a,
-                                            const uint32_t (&w)[R - 1]) {
-    constexpr int B = 1 << (R - 1);
-    v[H * B] = *reinterpret_cast<const C*>(lds + a);
+template <int RW, int H, typename C, int NR>
+__device__ __forceinline__ void gather_rows(C (&v)[NR], const char* lds, uint32_t a, const uint32_t (&w)[RW]) {
+    v[H << RW] = *reinterpret_cast<const C*>(lds + a);
 #pragma unroll
-    for (int i = 1; i < B; ++i) {
+    for (int i = 1; i < (1 << RW); ++i) {
         const int b = __builtin_ctz(i), j = i ^ (i >> 1);
         a = (j >> b) & 1 ? a + w[b] : a - w[b];
-        v[H * B + j] = *reinterpret_cast<const C*>(lds + a);
+        v[(H << RW) + j] = *reinterpret_cast<const C*>(lds + a);
     }
 }
 
@@ -585,31 +523,348 @@ __device__ __forceinline__ ConstOp<T>* const_ops(const DevOp<T>* p) {
     return (ConstOp<T>*)(p);
 }
 
-// Runs a stage's ops from `op` up to the next observable or the end record;
-// returns that record and its code.  Each record is loaded one op ahead: the
-// scalar load's latency hides behind the current op's arithmetic, and the loop
-// itself is a pointer step, the load and a branch tree.
-template <int R, bool GATES, typename C, typename T>
+// Runs a stage's ops from `op` up to the next observable, matrix or end
+// record; returns that record and its code.  Each record is loaded one op
+// ahead: the scalar load's latency hides behind the current op's arithmetic.
+__device__ __forceinline__ bool leaves_loop(int code) { return (code & ~3) == kOpEnd; }
+
+template <int R, typename C, typename T>
 __device__ __forceinline__ ConstOp<T>* run_factors(C (&v)[1 << R], ConstOp<T>* op, int& code) {
     int c = op->code;
-    T t = op->t, s = op->s, pr = op->pr, pi = op->pi;
+    T t = op->t, s = op->s;
     // The first record and the gathered registers have arrived before the loop:
     // otherwise every op waits for them there, and so for the next record's
     // load too.
-    asm volatile("" ::"s"(t), "s"(s), "s"(pr), "s"(pi));
-    while (c < kOpEnd) {
+    asm volatile("" ::"s"(t), "s"(s));
+    while (!leaves_loop(c)) {
         ++op;
         const int cn = op->code;
-        const T tn = op->t, sn = op->s, prn = op->pr, pin = op->pi;
-        reg_op<R, GATES>(v, c, t, s, pr, pi);
+        const T tn = op->t, sn = op->s;
+        reg_op<R>(v, c, t, s);
         c = cn;
         t = tn;
         s = sn;
-        pr = prn;
-        pi = pin;
     }
     code = c;
     return op;
+}
+
+// ------------------------------------------------------- threaded op loop
+// The same loop for stages with register/lane exchanges, in assembly: every
+// handler sits at (op code << spS) behind .Lspin_ops and ends by jumping to the
+// next op's.  Compiled from C++ (a switch), an op cost a tree of compares and
+// four or five taken branches, about 310 clocks beside 24 to 48 FMAs when no
+// other wave of the SIMD could fill them (2^12-amplitude tiles, M = 18: 20.5 us
+// per pass of 50 factors and 21 exchanges); the jump costs about 80.  The
+// registers are pinned: amplitude j of complex64 is v[spV + 2j] (re) and
+// v[spV + 2j + 1] (im), complex128 takes two registers each.
+//
+// Scalars: s[72:79] the op's parameters, s[80:89] the next record (loaded when
+// the op starts, waited for before the jump), s[90:91] .Lspin_ops, s[92:93] the
+// jump's target, s[94:95] the record's address.  Handlers: op_xy does the
+// three shears of reg_xy, each over all pairs before the next (a dependent FMA
+// is 2^(R-1) instructions away); op_gate one v_permlane16/32_swap per 32-bit
+// register pair, which trades the rows of its first operand that have the lane
+// bit set for the rows of the second that have it clear; op_zz the phase of
+// reg_zz.  At least the seven scalar instructions of the jump separate two
+// handlers' vector instructions, more than the wait states a swap needs after
+// a write of its operands.  A handler longer than its slots is an assembler
+// error (.org backwards).
+#define SPIN_ASM_COMMON                                            \
+    ".set spR, %c[r]\n"                                            \
+    ".set spN, 1<<spR\n"                                           \
+    ".set spV, %c[vb]\n"                                           \
+    ".set spS, %c[sh]\n"                                           \
+    ".macro spin_slot n\n"                                         \
+    ".org .Lspin_ops_%= + ((\\n)<<spS)\n"                          \
+    ".endm\n"                                                      \
+    ".macro spin_handler_xy a b\n"                                 \
+    ".if \\b < spR\n"                                              \
+    "spin_slot (\\b*(\\b-1)/2+\\a)\n"                              \
+    "spin_head\n"                                                  \
+    "spin_shear \\a \\b 1\n"                                       \
+    "spin_shear \\a \\b 2\n"                                       \
+    "spin_shear \\a \\b 1\n"                                       \
+    "spin_next\n"                                                  \
+    ".endif\n"                                                     \
+    ".endm\n"                                                      \
+    ".macro spin_handler_gate q\n"                                 \
+    ".if \\q < spR\n"                                              \
+    "spin_slot (16+2*\\q)\n"                                       \
+    "spin_head\n"                                                  \
+    "spin_swap \\q v_permlane16_swap_b32\n"                        \
+    "spin_next\n"                                                  \
+    "spin_slot (17+2*\\q)\n"                                       \
+    "spin_head\n"                                                  \
+    "spin_swap \\q v_permlane32_swap_b32\n"                        \
+    "spin_next\n"                                                  \
+    ".endif\n"                                                     \
+    ".endm\n"                                                      \
+    ".macro spin_handler_zz a b\n"                                 \
+    ".if \\b < spR\n"                                              \
+    "spin_slot (32+4*(\\b*(\\b-1)/2+\\a))\n"                       \
+    "spin_head\n"                                                  \
+    "spin_phase \\a \\b\n"                                         \
+    "spin_next\n"                                                  \
+    ".endif\n"                                                     \
+    ".endm\n"
+#define SPIN_ASM_RUN                                               \
+    "s_mov_b64 s[94:95], %[op]\n"                                  \
+    "s_getpc_b64 s[90:91]\n"                                       \
+    ".Lspin_pc_%=:\n"                                              \
+    "s_add_u32 s90, s90, .Lspin_ops_%=-.Lspin_pc_%=\n"             \
+    "s_addc_u32 s91, s91, 0\n"                                     \
+    "spin_load\n"                                                  \
+    "spin_next\n"                                                  \
+    ".p2align 6\n"                                                 \
+    ".Lspin_ops_%=:\n"                                             \
+    "spin_handler_xy 0 1\n"                                        \
+    "spin_handler_xy 0 2\nspin_handler_xy 1 2\n"                   \
+    "spin_handler_xy 0 3\nspin_handler_xy 1 3\nspin_handler_xy 2 3\n" \
+    "spin_handler_xy 0 4\nspin_handler_xy 1 4\nspin_handler_xy 2 4\nspin_handler_xy 3 4\n" \
+    "spin_handler_xy 0 5\nspin_handler_xy 1 5\nspin_handler_xy 2 5\nspin_handler_xy 3 5\nspin_handler_xy 4 5\n" \
+    "spin_handler_gate 0\nspin_handler_gate 1\nspin_handler_gate 2\n" \
+    "spin_handler_gate 3\nspin_handler_gate 4\nspin_handler_gate 5\n" \
+    "spin_slot 28\ns_branch .Lspin_end_%=\n"                       \
+    "spin_slot 29\ns_branch .Lspin_end_%=\n"                       \
+    "spin_handler_zz 0 1\n"                                        \
+    "spin_handler_zz 0 2\nspin_handler_zz 1 2\n"                   \
+    "spin_handler_zz 0 3\nspin_handler_zz 1 3\nspin_handler_zz 2 3\n" \
+    "spin_handler_zz 0 4\nspin_handler_zz 1 4\nspin_handler_zz 2 4\nspin_handler_zz 3 4\n" \
+    "spin_handler_zz 0 5\nspin_handler_zz 1 5\nspin_handler_zz 2 5\nspin_handler_zz 3 5\nspin_handler_zz 4 5\n" \
+    ".Lspin_end_%=:\n"                                             \
+    "s_mov_b64 %[op], s[94:95]\n"                                  \
+    ".purgem spin_slot\n.purgem spin_handler_xy\n.purgem spin_handler_gate\n.purgem spin_handler_zz\n" \
+    ".purgem spin_head\n.purgem spin_load\n.purgem spin_next\n"    \
+    ".purgem spin_shear\n.purgem spin_swap\n.purgem spin_phase\n"
+#define SPIN_ASM_F32                                               \
+    SPIN_ASM_COMMON                                                \
+    ".macro spin_load\n"                                           \
+    "s_load_dwordx8 s[80:87], s[94:95], 0x0\n"                     \
+    ".endm\n"                                                      \
+    ".macro spin_head\n"                                           \
+    "s_add_u32 s94, s94, 32\n"                                     \
+    "s_addc_u32 s95, s95, 0\n"                                     \
+    "spin_load\n"                                                  \
+    ".endm\n"                                                      \
+    ".macro spin_next\n"                                           \
+    "s_waitcnt lgkmcnt(0)\n"                                       \
+    "s_lshl_b32 s92, s84, spS\n"                                   \
+    "s_mov_b64 s[72:73], s[80:81]\n"                               \
+    "s_mov_b64 s[74:75], s[82:83]\n"                               \
+    "s_add_u32 s92, s92, s90\n"                                    \
+    "s_addc_u32 s93, s91, 0\n"                                     \
+    "s_setpc_b64 s[92:93]\n"                                       \
+    ".endm\n"                                                      \
+    ".macro spin_shear a b ph\n"                                   \
+    ".set spj, 0\n"                                                \
+    ".rept spN\n"                                                  \
+    ".if (((spj>>\\a)&1)==0)&&(((spj>>\\b)&1)==1)\n"               \
+    ".set spk, spj^(1<<\\a)^(1<<\\b)\n"                            \
+    ".if \\ph == 2\n"                                              \
+    "v_fmac_f32 v[spV+2*spk+1], s75, v[spV+2*spj]\n"               \
+    "v_fmac_f32 v[spV+2*spk], s73, v[spV+2*spj+1]\n"               \
+    ".else\n"                                                      \
+    "v_fmac_f32 v[spV+2*spj], s72, v[spV+2*spk+1]\n"               \
+    "v_fmac_f32 v[spV+2*spj+1], s74, v[spV+2*spk]\n"               \
+    ".endif\n"                                                     \
+    ".endif\n"                                                     \
+    ".set spj, spj+1\n"                                            \
+    ".endr\n"                                                      \
+    ".endm\n"                                                      \
+    ".macro spin_swap q op\n"                                      \
+    ".set spj, 0\n"                                                \
+    ".rept spN\n"                                                  \
+    ".if ((spj>>\\q)&1)==0\n"                                      \
+    ".set spk, spj|(1<<\\q)\n"                                     \
+    "\\op v[spV+2*spj], v[spV+2*spk]\n"                            \
+    "\\op v[spV+2*spj+1], v[spV+2*spk+1]\n"                        \
+    ".endif\n"                                                     \
+    ".set spj, spj+1\n"                                            \
+    ".endr\n"                                                      \
+    ".endm\n"                                                      \
+    ".macro spin_phase a b\n"                                      \
+    ".set spj, 0\n"                                                \
+    ".rept spN/2\n"                                                \
+    "v_mul_f32 %[w0], s73, v[spV+2*spj+1]\n"                       \
+    "v_mul_f32 %[u0], s73, v[spV+2*spj]\n"                         \
+    "v_mul_f32 %[w1], s73, v[spV+2*spj+3]\n"                       \
+    "v_mul_f32 %[u1], s73, v[spV+2*spj+2]\n"                       \
+    ".if ((spj>>\\a)^(spj>>\\b))&1\n"                              \
+    "v_fma_f32 v[spV+2*spj], s72, v[spV+2*spj], -%[w0]\n"          \
+    "v_fma_f32 v[spV+2*spj+1], s72, v[spV+2*spj+1], %[u0]\n"       \
+    ".else\n"                                                      \
+    "v_fma_f32 v[spV+2*spj], s72, v[spV+2*spj], %[w0]\n"           \
+    "v_fma_f32 v[spV+2*spj+1], s72, v[spV+2*spj+1], -%[u0]\n"      \
+    ".endif\n"                                                     \
+    ".if (((spj+1)>>\\a)^((spj+1)>>\\b))&1\n"                      \
+    "v_fma_f32 v[spV+2*spj+2], s72, v[spV+2*spj+2], -%[w1]\n"      \
+    "v_fma_f32 v[spV+2*spj+3], s72, v[spV+2*spj+3], %[u1]\n"       \
+    ".else\n"                                                      \
+    "v_fma_f32 v[spV+2*spj+2], s72, v[spV+2*spj+2], %[w1]\n"       \
+    "v_fma_f32 v[spV+2*spj+3], s72, v[spV+2*spj+3], -%[u1]\n"      \
+    ".endif\n"                                                     \
+    ".set spj, spj+2\n"                                            \
+    ".endr\n"                                                      \
+    ".endm\n"                                                      \
+    SPIN_ASM_RUN                                                   \
+    "s_mov_b32 %[code], s84\n"
+#define SPIN_F64(n) "v[spV+4*" n ":spV+4*" n "+1]"
+#define SPIN_G64(n) "v[spV+4*" n "+2:spV+4*" n "+3]"
+#define SPIN_ASM_F64                                               \
+    SPIN_ASM_COMMON                                                \
+    ".macro spin_load\n"                                           \
+    "s_load_dwordx8 s[80:87], s[94:95], 0x0\n"                     \
+    "s_load_dword s88, s[94:95], 0x20\n"                           \
+    ".endm\n"                                                      \
+    ".macro spin_head\n"                                           \
+    "s_add_u32 s94, s94, 48\n"                                     \
+    "s_addc_u32 s95, s95, 0\n"                                     \
+    "spin_load\n"                                                  \
+    ".endm\n"                                                      \
+    ".macro spin_next\n"                                           \
+    "s_waitcnt lgkmcnt(0)\n"                                       \
+    "s_lshl_b32 s92, s88, spS\n"                                   \
+    "s_mov_b64 s[72:73], s[80:81]\n"                               \
+    "s_mov_b64 s[74:75], s[82:83]\n"                               \
+    "s_mov_b64 s[76:77], s[84:85]\n"                               \
+    "s_mov_b64 s[78:79], s[86:87]\n"                               \
+    "s_add_u32 s92, s92, s90\n"                                    \
+    "s_addc_u32 s93, s91, 0\n"                                     \
+    "s_setpc_b64 s[92:93]\n"                                       \
+    ".endm\n"                                                      \
+    ".macro spin_shear a b ph\n"                                   \
+    ".set spj, 0\n"                                                \
+    ".rept spN\n"                                                  \
+    ".if (((spj>>\\a)&1)==0)&&(((spj>>\\b)&1)==1)\n"               \
+    ".set spk, spj^(1<<\\a)^(1<<\\b)\n"                            \
+    ".if \\ph == 2\n"                                              \
+    "v_fmac_f64 " SPIN_G64("spk") ", s[78:79], " SPIN_F64("spj") "\n" \
+    "v_fmac_f64 " SPIN_F64("spk") ", s[74:75], " SPIN_G64("spj") "\n" \
+    ".else\n"                                                      \
+    "v_fmac_f64 " SPIN_F64("spj") ", s[72:73], " SPIN_G64("spk") "\n" \
+    "v_fmac_f64 " SPIN_G64("spj") ", s[76:77], " SPIN_F64("spk") "\n" \
+    ".endif\n"                                                     \
+    ".endif\n"                                                     \
+    ".set spj, spj+1\n"                                            \
+    ".endr\n"                                                      \
+    ".endm\n"                                                      \
+    ".macro spin_swap q op\n"                                      \
+    ".set spj, 0\n"                                                \
+    ".rept spN\n"                                                  \
+    ".if ((spj>>\\q)&1)==0\n"                                      \
+    ".set spk, spj|(1<<\\q)\n"                                     \
+    "\\op v[spV+4*spj], v[spV+4*spk]\n"                            \
+    "\\op v[spV+4*spj+1], v[spV+4*spk+1]\n"                        \
+    "\\op v[spV+4*spj+2], v[spV+4*spk+2]\n"                        \
+    "\\op v[spV+4*spj+3], v[spV+4*spk+3]\n"                        \
+    ".endif\n"                                                     \
+    ".set spj, spj+1\n"                                            \
+    ".endr\n"                                                      \
+    ".endm\n"                                                      \
+    ".macro spin_phase a b\n"                                      \
+    ".set spj, 0\n"                                                \
+    ".rept spN\n"                                                  \
+    "v_mul_f64 %[w0], s[74:75], " SPIN_G64("spj") "\n"             \
+    "v_mul_f64 %[u0], s[74:75], " SPIN_F64("spj") "\n"             \
+    ".if ((spj>>\\a)^(spj>>\\b))&1\n"                              \
+    "v_fma_f64 " SPIN_F64("spj") ", s[72:73], " SPIN_F64("spj") ", -%[w0]\n" \
+    "v_fma_f64 " SPIN_G64("spj") ", s[72:73], " SPIN_G64("spj") ", %[u0]\n"  \
+    ".else\n"                                                      \
+    "v_fma_f64 " SPIN_F64("spj") ", s[72:73], " SPIN_F64("spj") ", %[w0]\n"  \
+    "v_fma_f64 " SPIN_G64("spj") ", s[72:73], " SPIN_G64("spj") ", -%[u0]\n" \
+    ".endif\n"                                                     \
+    ".set spj, spj+1\n"                                            \
+    ".endr\n"                                                      \
+    ".endm\n"                                                      \
+    SPIN_ASM_RUN                                                   \
+    "s_mov_b32 %[code], s88\n"
+#define SPIN_ASM_CLOBBERS                                                                               \
+    "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85",   \
+        "s86", "s87", "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95", "scc", "memory"
+
+typedef float v8f __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v32f __attribute__((ext_vector_type(32)));
+typedef double v8d __attribute__((ext_vector_type(8)));
+typedef double v16d __attribute__((ext_vector_type(16)));
+
+// Handler slots of 2^shift bytes: the shears of 2^R registers or the swaps (4
+// bytes each) and up to 60 bytes of scalars.
+constexpr int op_slot_shift(int R) { return R <= 3 ? 7 : R == 4 ? 8 : 9; }
+
+template <int R, typename T>
+__device__ __forceinline__ ConstOp<T>* run_ops(typename CT<T>::c (&v)[1 << R], ConstOp<T>* op, int& code) {
+    constexpr int NV = 2 << R;                                   // reals
+    constexpr int W = NV * int(sizeof(T) / 4);                   // registers
+    constexpr int VB = W <= 64 ? 64 : 128;
+    constexpr int SH = op_slot_shift(R);
+    constexpr int N = W < 32 ? NV : 32 / int(sizeof(T) / 4);     // reals of one operand
+    auto get = [&](int i) { return i & 1 ? v[i / 2].y : v[i / 2].x; };
+    auto put = [&](int i, T x) { if (i & 1) v[i / 2].y = x; else v[i / 2].x = x; };
+    uint64_t p = reinterpret_cast<uint64_t>(op);
+    T w0, u0, w1, u1;
+#define SPIN_RUN(TEXT, ...)                                                                      \
+    asm volatile(TEXT : __VA_ARGS__, [op] "+s"(p), [code] "=&s"(code), [w0] "=&v"(w0),           \
+                 [u0] "=&v"(u0), [w1] "=&v"(w1), [u1] "=&v"(u1)                                  \
+                 : [r] "i"(R), [vb] "i"(VB), [sh] "i"(SH)                                        \
+                 : SPIN_ASM_CLOBBERS)
+#define SPIN_GET(X, B) _Pragma("unroll") for (int i = 0; i < N; ++i) X[i] = get((B) * N + i)
+#define SPIN_PUT(X, B) _Pragma("unroll") for (int i = 0; i < N; ++i) put((B) * N + i, X[i])
+    if constexpr (sizeof(T) == 4) {
+        if constexpr (W == 8) {
+            v8f a;
+            SPIN_GET(a, 0);
+            SPIN_RUN(SPIN_ASM_F32, "+{v[64:71]}"(a));
+            SPIN_PUT(a, 0);
+        } else if constexpr (W == 16) {
+            v16f a;
+            SPIN_GET(a, 0);
+            SPIN_RUN(SPIN_ASM_F32, "+{v[64:79]}"(a));
+            SPIN_PUT(a, 0);
+        } else if constexpr (W == 32) {
+            v32f a;
+            SPIN_GET(a, 0);
+            SPIN_RUN(SPIN_ASM_F32, "+{v[64:95]}"(a));
+            SPIN_PUT(a, 0);
+        } else if constexpr (W == 64) {
+            v32f a, b;
+            SPIN_GET(a, 0); SPIN_GET(b, 1);
+            SPIN_RUN(SPIN_ASM_F32, "+{v[64:95]}"(a), "+{v[96:127]}"(b));
+            SPIN_PUT(a, 0); SPIN_PUT(b, 1);
+        } else {
+            v32f a, b, c, d;
+            SPIN_GET(a, 0); SPIN_GET(b, 1); SPIN_GET(c, 2); SPIN_GET(d, 3);
+            SPIN_RUN(SPIN_ASM_F32, "+{v[128:159]}"(a), "+{v[160:191]}"(b), "+{v[192:223]}"(c), "+{v[224:255]}"(d));
+            SPIN_PUT(a, 0); SPIN_PUT(b, 1); SPIN_PUT(c, 2); SPIN_PUT(d, 3);
+        }
+    } else {
+        if constexpr (W == 16) {
+            v8d a;
+            SPIN_GET(a, 0);
+            SPIN_RUN(SPIN_ASM_F64, "+{v[64:79]}"(a));
+            SPIN_PUT(a, 0);
+        } else if constexpr (W == 32) {
+            v16d a;
+            SPIN_GET(a, 0);
+            SPIN_RUN(SPIN_ASM_F64, "+{v[64:95]}"(a));
+            SPIN_PUT(a, 0);
+        } else if constexpr (W == 64) {
+            v16d a, b;
+            SPIN_GET(a, 0); SPIN_GET(b, 1);
+            SPIN_RUN(SPIN_ASM_F64, "+{v[64:95]}"(a), "+{v[96:127]}"(b));
+            SPIN_PUT(a, 0); SPIN_PUT(b, 1);
+        } else {
+            v16d a, b, c, d;
+            SPIN_GET(a, 0); SPIN_GET(b, 1); SPIN_GET(c, 2); SPIN_GET(d, 3);
+            SPIN_RUN(SPIN_ASM_F64, "+{v[128:159]}"(a), "+{v[160:191]}"(b), "+{v[192:223]}"(c), "+{v[224:255]}"(d));
+            SPIN_PUT(a, 0); SPIN_PUT(b, 1); SPIN_PUT(c, 2); SPIN_PUT(d, 3);
+        }
+    }
+#undef SPIN_RUN
+#undef SPIN_GET
+#undef SPIN_PUT
+    return reinterpret_cast<ConstOp<T>*>(p);
 }
 
 // ------------------------------------------------------- matrix engine
@@ -808,34 +1063,32 @@ __device__ __forceinline__ void site_observe(const C (&v)[1 << R], int aux, int6
 }
 
 // Brings a pass's stage headers and ops into the scalar cache, several lines
-// in flight.  Read in order they miss it once per stage and once per few ops,
-// one miss after the other: on a one-tile workgroup (M <= 22) that is a
-// microsecond of every pass.
-template <typename T>
+// in flight, each wave its share.  Read in order they miss it once per stage
+// and once per few ops, one miss after the other: on a one-tile workgroup
+// (M <= 22) that is a microsecond of every pass.
+template <typename T, int NT>
 __device__ __forceinline__ void warm_tables(const DevPass& P, const DevStage* __restrict__ stages,
                                             const DevOp<T>* __restrict__ ops) {
-    constexpr int kLine = 16;     // words per 64-byte line
+    constexpr int kLine = 16, NW = NT / 64;     // words per 64-byte line; waves
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / 64);
     const DevStage* S = stages + P.stage0;
     const DevStage& L = S[P.nstage - 1];
     const int* w = reinterpret_cast<const int*>(ops + S->op0);
-    const int words = (L.op0 + L.nop + 1 - S->op0) * int(sizeof(DevOp<T>) / 4);
-    for (int si = 0; si < P.nstage; si += 2) {
+    const int last = (L.op0 + L.nop + 1 - S->op0) * int(sizeof(DevOp<T>) / 4) - 1;
+    for (int si = wave; si < P.nstage; si += NW) {
         // the first 3 lines of a stage hold what the stage loop reads
         const int* p = reinterpret_cast<const int*>(S + si);
-        const int* q = reinterpret_cast<const int*>(S + (si + 1 < P.nstage ? si + 1 : si));
-        const int a = p[0], b = p[kLine], c = p[2 * kLine], d = q[0], e = q[kLine], f = q[2 * kLine];
-        asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
+        const int a = p[0], b = p[kLine], c = p[2 * kLine];
+        asm volatile("" ::"s"(a), "s"(b), "s"(c));
     }
-    for (int i = 0; i < words; i += 6 * kLine) {
-        const int last = words - 1;
+    for (int i = wave * 4 * kLine; i <= last; i += NW * 4 * kLine) {
         auto at = [&](int n) { return w[i + n * kLine < last ? i + n * kLine : last]; };
-        const int a = at(0), b = at(1), c = at(2), d = at(3), e = at(4), f = at(5);
-        asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
+        const int a = at(0), b = at(1), c = at(2), d = at(3);
+        asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
     }
 }
 
-template <typename T, int R, int NT, bool WRITES, int ENGINE = 0, bool PROFILE = false,
-          bool HALF = false>
+template <typename T, int R, int NT, bool WRITES, int ENGINE = 0, bool PROFILE = false>
 __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, const DevPass& P,
                                            const DevStage* __restrict__ stages,
                                            const DevOp<T>* __restrict__ ops, unsigned wperm,
@@ -848,9 +1101,6 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
     const DevStage& S0 = stages[P.stage0];
     const DevStage& SL = stages[P.stage0 + P.nstage - 1];
     constexpr int NTB = __builtin_ctz(NT);
-    constexpr int EB = sizeof(C), ROW = exchange_row_slots(NT, EB) * EB;
-    char* own = ldsb + exchange_slot(tid, EB) * EB;
-    bool prev_cross = false;
     const int64_t gin_t = lane_offset<NTB>(S0.gt_in, tid);
     const int64_t gout_t = lane_offset<NTB>(SL.gt_out, tid);
 
@@ -860,40 +1110,29 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
     int64_t m_hi = P.free_mask;
     for (unsigned g = G; g > 1; g >>= 1) m_hi &= m_hi - 1;
 
-    // Full-tile exchanges: the next tile's loads are issued into `pre` at
-    // the start of a tile and always (the last tile re-reads itself), so
-    // every iteration ends with the same memory ops outstanding -- prefetch
-    // loads, then stores -- and the copy out of `pre` only waits for the
-    // loads.  Half-tile exchanges leave room for a second workgroup on the
-    // CU instead of a prefetch: a tile's loads go straight into `v` and the
-    // other workgroup's work covers their latency.
-    C pre[HALF ? 1 : (1 << R)];
+    // The next tile's loads are issued into `pre` at the start of a tile and
+    // always (the last tile re-reads itself), so every iteration ends with
+    // the same memory ops outstanding -- prefetch loads, then stores -- and
+    // the copy out of `pre` only waits for the loads.
+    C pre[1 << R];
     int64_t hi = 0;
-    if constexpr (!HALF) load_direct<R>(pre, psi, base_w + gin_t, S0.gr_in);
+    load_direct<R>(pre, psi, base_w + gin_t, S0.gr_in);
 
     auto tile_body = [&](int64_t it_tile) {
         const int64_t base = base_w | hi;
         C v[1 << R];
-        if constexpr (HALF) {
-            load_direct<R>(v, psi, base + gin_t, S0.gr_in);
-            if (it_tile + 1 < tiles_per_member) hi = next_submask(hi, m_hi);
-        } else {
 #pragma unroll
-            for (int j = 0; j < (1 << R); ++j) v[j] = pre[j];
-            if (it_tile + 1 < tiles_per_member) hi = next_submask(hi, m_hi);
-            load_direct<R>(pre, psi, (base_w | hi) + gin_t, S0.gr_in);
-        }
+        for (int j = 0; j < (1 << R); ++j) v[j] = pre[j];
+        if (it_tile + 1 < tiles_per_member) hi = next_submask(hi, m_hi);
+        load_direct<R>(pre, psi, (base_w | hi) + gin_t, S0.gr_in);
 
         for (int si = 0; si < P.nstage; ++si) {
             const DevStage& S = stages[P.stage0 + si];
-            uint32_t pb = 0;      // lane's LDS address (whole tiles)
+            const uint32_t pb = stage_base<NTB>(S, tid);
             RegBits<R> rb;
-            if constexpr (!HALF) {
-                pb = stage_base<NTB>(S, tid);
 #pragma unroll
-                for (int b = 0; b < R; ++b) rb.rbit[b] = S.rbit[b];
-                if (si > 0) gather<R>(v, ldsb, pb, rb);
-            }
+            for (int b = 0; b < R; ++b) rb.rbit[b] = S.rbit[b];
+            if (si > 0) gather<R>(v, ldsb, pb, rb);
             ConstOp<T>* op = const_ops<T>(ops + S.op0);
             while (true) {
                 int code;
@@ -905,7 +1144,7 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
                     }
                     code = op->code;
                 } else {
-                    op = run_factors<R, HALF>(v, op, code);
+                    op = run_factors<R>(v, op, code);
                 }
                 if (code == kOpEnd) break;
                 // observable of the state at this point
@@ -915,8 +1154,7 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
                     // each squared once; wave sums go to the wave's LDS
                     // row (pacc / nacc), one row per wave.
                     double tot, half[R];
-                    if constexpr (HALF) reg_half_sums_seq<R>(v, tot, half);
-                    else reg_half_sums<R>(v, tot, half);
+                    reg_half_sums<R>(v, tot, half);
                     const bool last = (tid & 63) == 63;
                     while (op->code == kOpMeas) {
                         const int aux = op->aux;
@@ -941,20 +1179,6 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
                         }
                         ++op;
                     }
-                } else if constexpr (HALF) {
-                    // wave sums into the wave's own LDS row (pacc: slot
-                    // m holds P at 2m, N at 2m + 1), no accumulator
-                    // registers
-                    const int slot = op->aux & 63;
-                    double p, n;
-                    site_observe<R>(v, op->aux, base, p, n);
-                    p = wave_sum_last(p);
-                    n = wave_sum_last(n);
-                    if ((tid & 63) == 63) {
-                        pacc[2 * slot] += p;
-                        pacc[2 * slot + 1] += n;
-                    }
-                    ++op;
                 } else {
                     const int slot = op->aux & 63;
                     double p, n;
@@ -966,52 +1190,146 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
                 }
             }
             if (si + 1 < P.nstage) {
-                // When both stages keep the same positions on the wave bits
-                // the exchange moves amplitudes only within each wave and
-                // only the wave is ordered.
-                const bool xw = S.xnext != 0;
-                auto sync = [&]() {
-                    if (xw) lds_barrier();
-                    else wave_lds_sync();
-                };
-                if constexpr (HALF) {
-                    // Half 0 through the LDS, then half 1 through the same
-                    // slots.  A lane scatters to slots of its own; after an
-                    // exchange that crossed waves (the last one of the tile
-                    // before included) other waves may still be gathering
-                    // from them.
-                    const DevStage& S2 = stages[P.stage0 + si + 1];
-                    uint32_t w[R - 1];
-#pragma unroll
-                    for (int b = 0; b + 1 < R; ++b) w[b] = S2.gr[b];
-                    const uint32_t ga = gather_base<NTB>(S2, tid);
-                    if (prev_cross) lds_barrier();
-                    prev_cross = xw;
-                    scatter_half<R, 0, ROW>(v, own);
-                    sync();
-                    gather_half<R, 0>(v, ldsb, ga, w);
-                    sync();
-                    scatter_half<R, 1, ROW>(v, own);
-                    sync();
-                    gather_half<R, 1>(v, ldsb, ga, w);
-                } else {
-                    // the lanes scatter to exactly the slots that the next
-                    // stage's lanes gather
-                    scatter<R>(v, ldsb, pb, rb);
-                    sync();
-                }
+                // A lane scatters to exactly the LDS slots the next stage's
+                // lanes gather after the barrier.  When both stages keep the
+                // same positions on the wave bits, those slots belong to the
+                // wave's own lanes and only the wave is ordered.
+                scatter<R>(v, ldsb, pb, rb);
+                if (S.xnext != 0) lds_barrier();
+                else wave_lds_sync();
             }
         }
         if constexpr (WRITES) store_direct<R>(v, psi, base + gout_t, SL.gr_out);
         // the last gathers are done before the next tile's scatters, unless
         // the last and first stages keep the same wave positions (then every
-        // wave's slots are its own across the tile boundary); half tiles have
-        // their barrier at the next scatter
-        if constexpr (!HALF)
-            if (P.tile_barrier) lds_barrier();
+        // wave's slots are its own across the tile boundary)
+        if (P.tile_barrier) lds_barrier();
     };
     tile_body(0);
     for (int64_t it_tile = 1; it_tile < tiles_per_member; ++it_tile) tile_body(it_tile);
+}
+
+// Same for passes that exchange through per-lane slots (HALF: in two halves).
+// No register prefetch: several workgroups share a CU and cover each other's
+// loads.  What bounds it, per CU: M = 30 complex64 tiles of 2^14 take 3.5 ms per
+// pass for the sweep alone, about 3.2 ms of VALU issue and 2 ms of LDS traffic,
+// of which two workgroups overlap part; one-tile launches (M <= 20) take the
+// sum of the three.
+template <typename T, int R, int NT, bool WRITES, bool PROFILE, bool HALF>
+__device__ __forceinline__ void slot_tiles(typename CT<T>::c* __restrict__ psi, const DevPass& P,
+                                           const DevStage* __restrict__ stages,
+                                           const DevOp<T>* __restrict__ ops, unsigned wperm, unsigned G,
+                                           int64_t tiles_per_member, char* ldsb, double* pacc,
+                                           double* nacc = nullptr, bool writes = true) {
+    using C = typename CT<T>::c;
+    const int tid = threadIdx.x;
+    const int nstage = P.nstage;
+    const DevStage* S0 = stages + P.stage0;
+    const DevStage& SL = S0[nstage - 1];
+    constexpr int NTB = __builtin_ctz(NT), RW = HALF ? R - 1 : R;
+    constexpr int EB = sizeof(C), ROW = exchange_row_slots(NT, EB) * EB;
+    char* own = ldsb + exchange_slot(tid, EB) * EB;
+    bool prev_cross = false;
+    const int64_t gin_t = lane_offset<NTB>(S0->gt_in, tid);
+    const int64_t gout_t = lane_offset<NTB>(SL.gt_out, tid);
+    const int64_t base_w = deposit(wperm, P.free_mask);
+    int64_t m_hi = P.free_mask, hi = 0;
+    for (unsigned g = G; g > 1; g >>= 1) m_hi &= m_hi - 1;
+
+    for (int64_t it_tile = 0; it_tile < tiles_per_member; ++it_tile) {
+        const int64_t base = base_w | hi;
+        C v[1 << R];
+        load_direct<R>(v, psi, base + gin_t, S0->gr_in);
+        hi = next_submask(hi, m_hi);
+        for (int si = 0; si < nstage; ++si) {
+            const DevStage& S = S0[si];
+            ConstOp<T>* op = const_ops<T>(ops + S.op0);
+            while (true) {
+                int code;
+                op = run_ops<R, T>(v, op, code);
+                if (code == kOpEnd) break;
+                // observable of the state at this point
+                if constexpr (PROFILE) {
+                    // Every per-site observable at this point from the
+                    // lane's total weight and its register-bit half sums,
+                    // each squared once; wave sums go to the wave's LDS
+                    // row (pacc / nacc), one row per wave.
+                    double tot, half[R];
+                    reg_half_sums_seq<R>(v, tot, half);
+                    const bool last = (tid & 63) == 63;
+                    while (op->code == kOpMeas) {
+                        const int aux = op->aux;
+                        const int slot = aux & 63, kind = (aux >> 6) & 3, idx = (aux >> 8) & 63;
+                        const int nslot = ((aux >> 14) & 7) - 1;
+                        double p;
+                        if (kind == 1) {
+                            double h = half[0];
+#pragma unroll
+                            for (int b = 1; b < R; ++b)
+                                if (b == idx) h = half[b];
+                            p = tot - 2.0 * h;
+                        } else {
+                            const int neg = kind == 0 ? ((tid >> idx) & 1) : int((base >> idx) & 1);
+                            p = neg ? -tot : tot;
+                        }
+                        p = wave_sum_last(p);
+                        if (last) pacc[slot] += p;
+                        if (nslot >= 0) {
+                            const double n = wave_sum_last(tot);
+                            if (last) nacc[nslot] += n;
+                        }
+                        ++op;
+                    }
+                } else {
+                    // wave sums into the wave's own LDS row (pacc: slot
+                    // m holds P at 2m, N at 2m + 1), no accumulator
+                    // registers
+                    const int aux = op->aux, slot = aux & 63;
+                    double p, n;
+                    site_observe<R>(v, aux, base, p, n);
+                    p = wave_sum_last(p);
+                    n = wave_sum_last(n);
+                    if ((tid & 63) == 63) {
+                        pacc[2 * slot] += p;
+                        pacc[2 * slot + 1] += n;
+                    }
+                    ++op;
+                }
+            }
+            if (si + 1 < nstage) {
+                // When both stages keep the same positions on the wave bits
+                // the exchange moves amplitudes only within each wave and
+                // only the wave is ordered.  A lane scatters to slots of its
+                // own; after an exchange that crossed waves (the last one of
+                // the tile before included) other waves may still be
+                // gathering from them.
+                const bool xw = S.xnext != 0;
+                auto sync = [&]() {
+                    if (xw) lds_barrier();
+                    else wave_lds_sync();
+                };
+                const DevStage& S2 = S0[si + 1];
+                uint32_t w[RW], ga = 0;
+#pragma unroll
+                for (int b = 0; b < RW; ++b) w[b] = S2.gr[b];
+#pragma unroll
+                for (int q = 0; q < NTB; ++q) ga += S2.gw[q] & (0u - ((uint32_t(tid) >> q) & 1u));
+                if (prev_cross) lds_barrier();
+                prev_cross = xw;
+                scatter_rows<RW, 0, ROW>(v, own);
+                sync();
+                gather_rows<RW, 0>(v, ldsb, ga, w);
+                if constexpr (HALF) {
+                    sync();
+                    scatter_rows<RW, 1, ROW>(v, own);
+                    sync();
+                    gather_rows<RW, 1>(v, ldsb, ga, w);
+                }
+            }
+        }
+        if constexpr (WRITES)
+            if (writes) store_direct<R>(v, psi, base + gout_t, SL.gr_out);
+    }
 }
 
 // Workgroup sum of measurement slot m of the accumulators (thread 0).
@@ -1030,22 +1348,24 @@ __device__ __forceinline__ void slot_sum(const double (&accP)[kMaxMeas],
 // --------------------------------------------------------------- k_pass
 // partials: [slot][nwg][2] (P, N), or with PROFILE [slot][nwg][M + 1] (P of
 // every site, then N).
-// HALF: half-tile exchanges, LDS for half a tile, no register prefetch, and
-// registers capped so that two workgroups share a CU.
-// Waves per SIMD a half-tile pass kernel is built for: two workgroups per
-// CU when their half-tile LDS buffers fit the CU's 160 KiB together (with
-// room for the small arrays), else one (complex128 tiles of 2^14).
-template <typename T, int R, int NT>
-__host__ __device__ constexpr int half_slots() {
-    return exchange_row_slots(NT, sizeof(typename CT<T>::c)) << (R - 1);
+// X: exchanges through LDS (see ExchangeMode); all but kWholeTiles have no
+// register prefetch and cap the registers so that several workgroups share a
+// CU, as many as their LDS lets in, up to 4 waves per SIMD.
+template <typename T, int R, int NT, int X>
+__host__ __device__ constexpr int exchange_slots() {
+    return X == kWholeTiles ? NT << R
+                            : exchange_row_slots(NT, sizeof(typename CT<T>::c)) << (X == kHalfTiles ? R - 1 : R);
 }
-template <typename T, int R, int NT>
-__host__ __device__ constexpr int half_waves_per_eu() {
-    return (half_slots<T, R, NT>() * sizeof(typename CT<T>::c) <= 78 * 1024 ? 2 : 1) * NT / 256;
+template <typename T, int R, int NT, int X>
+__host__ __device__ constexpr int waves_per_eu() {
+    if (X == kWholeTiles) return 1;
+    const int wg = int((160 * 1024 - 8192) / (exchange_slots<T, R, NT, X>() * sizeof(typename CT<T>::c)));
+    const int waves = (wg < 1 ? 1 : wg) * NT / 256;
+    return waves > 4 ? 4 : waves < 1 ? 1 : waves;
 }
 
-template <typename T, int R, int NT, bool WRITES, int ENGINE, bool PROFILE, bool HALF>
-__global__ __launch_bounds__(NT, (HALF ? half_waves_per_eu<T, R, NT>() : 1)) void k_pass(typename CT<T>::c* __restrict__ psi,
+template <typename T, int R, int NT, bool WRITES, int ENGINE, bool PROFILE, int X>
+__global__ __launch_bounds__(NT, (waves_per_eu<T, R, NT, X>())) void k_pass(typename CT<T>::c* __restrict__ psi,
                                              const DevPass* __restrict__ passes,
                                              const DevStage* __restrict__ stages,
                                              const DevOp<T>* __restrict__ ops, int pass_index,
@@ -1053,8 +1373,7 @@ __global__ __launch_bounds__(NT, (HALF ? half_waves_per_eu<T, R, NT>() : 1)) voi
                                              int64_t step_offset, int ch, int nwg,
                                              const float* __restrict__ mats) {
     using C = typename CT<T>::c;
-    constexpr int K = R + __builtin_ctz(NT);
-    __shared__ C lds[HALF ? half_slots<T, R, NT>() : (1 << K)];
+    __shared__ C lds[exchange_slots<T, R, NT, X>()];
     __shared__ double red[2 * (NT / 64)];
     const DevPass& P = passes[pass_index];
     double accP[kMaxMeas], accN[kMaxMeas];
@@ -1067,7 +1386,7 @@ __global__ __launch_bounds__(NT, (HALF ? half_waves_per_eu<T, R, NT>() : 1)) voi
     // line.
     const unsigned G = gridDim.x, w = blockIdx.x;
     const unsigned wperm = (G >= 8) ? (w % 8u) * (G / 8u) + w / 8u : w;
-    warm_tables<T>(P, stages, ops);
+    warm_tables<T, NT>(P, stages, ops);
     if constexpr (PROFILE) {
         // Per-wave accumulator rows; lane 63 of each wave owns its row.
         constexpr int NW = NT / 64;
@@ -1078,9 +1397,14 @@ __global__ __launch_bounds__(NT, (HALF ? half_waves_per_eu<T, R, NT>() : 1)) voi
             for (int m = 0; m < kMaxMeasProfile; ++m) pacc[wave][m] = 0.0;
             for (int m = 0; m < kMaxMeas; ++m) nacc[wave][m] = 0.0;
         }
-        pass_tiles<T, R, NT, WRITES, ENGINE, true, HALF>(psi, P, stages, ops, wperm, G, tiles_per_wg,
-                                                         reinterpret_cast<char*>(lds), accP, accN, mats,
-                                                         pacc[wave], nacc[wave]);
+        if constexpr (X != kWholeTiles)
+            slot_tiles<T, R, NT, WRITES, true, X == kHalfTiles>(psi, P, stages, ops, wperm, G, tiles_per_wg,
+                                                                reinterpret_cast<char*>(lds), pacc[wave],
+                                                                nacc[wave]);
+        else
+            pass_tiles<T, R, NT, WRITES, ENGINE, true>(psi, P, stages, ops, wperm, G, tiles_per_wg,
+                                                       reinterpret_cast<char*>(lds), accP, accN, mats,
+                                                       pacc[wave], nacc[wave]);
         __syncthreads();
         const int M = P.k + P.nfree;
         auto dst = [&](int64_t step) {
@@ -1102,16 +1426,15 @@ __global__ __launch_bounds__(NT, (HALF ? half_waves_per_eu<T, R, NT>() : 1)) voi
         }
         return;
     }
-    if constexpr (HALF) {
+    if constexpr (X != kWholeTiles) {
         // per-wave observable rows; fixed-order sum over the waves
         constexpr int NW = NT / 64;
         __shared__ double wacc[NW][2 * kMaxMeas];
         const int wave = threadIdx.x / 64;
         if ((threadIdx.x & 63) == 63)
             for (int m = 0; m < 2 * kMaxMeas; ++m) wacc[wave][m] = 0.0;
-        pass_tiles<T, R, NT, WRITES, ENGINE, false, true>(psi, P, stages, ops, wperm, G, tiles_per_wg,
-                                                          reinterpret_cast<char*>(lds), accP, accN,
-                                                          mats, wacc[wave]);
+        slot_tiles<T, R, NT, WRITES, false, X == kHalfTiles>(psi, P, stages, ops, wperm, G, tiles_per_wg,
+                                                             reinterpret_cast<char*>(lds), wacc[wave]);
         __syncthreads();
         if (threadIdx.x < P.nmeas) {
             const int m = threadIdx.x;
@@ -1127,7 +1450,7 @@ __global__ __launch_bounds__(NT, (HALF ? half_waves_per_eu<T, R, NT>() : 1)) voi
         }
         return;
     }
-    pass_tiles<T, R, NT, WRITES, ENGINE, false, false>(psi, P, stages, ops, wperm, G, tiles_per_wg,
+    pass_tiles<T, R, NT, WRITES, ENGINE, false>(psi, P, stages, ops, wperm, G, tiles_per_wg,
                                                        reinterpret_cast<char*>(lds), accP, accN, mats);
     for (int m = 0; m < P.nmeas; ++m) {
         double p, n;
@@ -1185,7 +1508,7 @@ __device__ __forceinline__ void resident_run(const ResidentJob& J, const DevStag
             ConstOp<T>* op = const_ops<T>(ops + S.op0);
             while (true) {
                 int code;
-                op = run_factors<R, false>(v, op, code);
+                op = run_factors<R>(v, op, code);
                 if (code == kOpEnd) break;
                 // observable: reduce over the workgroup now
                 const int aux = op->aux;
@@ -1287,7 +1610,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
     constexpr int K = R + __builtin_ctz(NT);
     constexpr int KL = HALF ? K - 1 : K;    // largest problem held in LDS
     constexpr int NW = NT / 64;
-    __shared__ C lds[HALF ? half_slots<T, R, NT>() : (1 << KL)];
+    __shared__ C lds[exchange_slots<T, R, NT, HALF ? kHalfTiles : kWholeTiles>()];
     __shared__ double red[2 * NW];
     __shared__ double wacc[HALF ? NW : 1][2 * kMaxMeas];
     const int tid = threadIdx.x;
@@ -1344,14 +1667,9 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                 // rows finished before the gang barrier
                 if ((tid & 63) == 63)
                     for (int m = 0; m < 2 * kMaxMeas; ++m) wacc[wave][m] = 0.0;
-                if (P.writes)
-                    pass_tiles<T, R, NT, true, 0, false, true>(psi, P, stages, ops, rank, G, tpm,
-                                                               reinterpret_cast<char*>(lds), accP, accN,
-                                                               nullptr, wacc[wave]);
-                else
-                    pass_tiles<T, R, NT, false, 0, false, true>(psi, P, stages, ops, rank, G, tpm,
-                                                                reinterpret_cast<char*>(lds), accP, accN,
-                                                                nullptr, wacc[wave]);
+                slot_tiles<T, R, NT, true, false, true>(psi, P, stages, ops, rank, G, tpm,
+                                                        reinterpret_cast<char*>(lds), wacc[wave], nullptr,
+                                                        P.writes != 0);
                 __syncthreads();
                 if (tid < P.nmeas) {
                     const int m = tid;
@@ -1425,10 +1743,10 @@ void launch_fill_int(int* p, int n, int grid, hipStream_t st);
 void launch_status_or(const int* err, int* status, hipStream_t st);
 #endif
 
-// Pass launches by kernel family (half-tile or whole-tile exchanges), each
+// Pass launches by kernel family (per-lane slots or one layout per tile), each
 // compiled in its own part.
 template <typename T>
-hipError_t launch_pass_half(const PassShape& sh, void* psi, const DevPass* passes, const DevStage* stages, const DevOp<T>* ops,
+hipError_t launch_pass_slots(const PassShape& sh, void* psi, const DevPass* passes, const DevStage* stages, const DevOp<T>* ops,
                int pass_index, int64_t tiles_per_wg, int nwg, double* partials, int64_t step_offset, int ch,
                hipStream_t st);
 template <typename T>
@@ -1513,6 +1831,12 @@ hipError_t launch_factor(void* psi, int M, int lo, int hi, double t, double s, d
     return hipGetLastError();
 }
 
+bool pass_small_exists(bool f32, int r, int nt) {
+    if (nt == 256) return r == 2 || r == 3 || r == 4;
+    if (nt == 512) return r == 3 || (f32 && r == 4);
+    return f32 && nt == 64 && r == 5;
+}
+
 bool pass_half_exists(bool f32, int r, int nt) {
     if (f32) return (r == 5 && nt == 512) || (r == 6 && nt == 256);
     return (r == 4 && nt == 512) || (r == 5 && nt == 256) || (r == 5 && nt == 512);
@@ -1558,7 +1882,7 @@ hipError_t launch_pass(const PassShape& sh, void* psi, const DevPass* passes,
                        const DevStage* stages, const DevOp<T>* ops, int pass_index,
                        int64_t tiles_per_wg, int nwg, double* partials, int64_t step_offset,
                        int ch, hipStream_t st) {
-    return (sh.half ? launch_pass_half<T> : launch_pass_whole<T>)(sh, psi, passes, stages, ops, pass_index,
+    return (sh.exchange != kWholeTiles ? launch_pass_slots<T> : launch_pass_whole<T>)(sh, psi, passes, stages, ops, pass_index,
                                                                  tiles_per_wg, nwg, partials, step_offset, ch, st);
 }
 template hipError_t launch_pass<float>(const PassShape&, void*, const DevPass*, const DevStage*,
@@ -1574,17 +1898,17 @@ int batch_blocks_per_cu(bool f32, bool half) {
 #endif
 
 #if SPIN_PART >= 2 && SPIN_PART <= 5
-template <typename T, int R, int NT, int ENGINE = 0, bool PROFILE = false, bool HALF = false>
+template <typename T, int R, int NT, int ENGINE = 0, bool PROFILE = false, int X = kWholeTiles>
 static hipError_t pass_one(bool writes, void* psi, const DevPass* passes, const DevStage* stages,
                            const DevOp<T>* ops, int pass_index, int64_t tiles_per_wg, int nwg,
                            double* partials, int64_t step_offset, int ch, const float* mats,
                            hipStream_t st) {
     if (writes)
-        hipLaunchKernelGGL((k_pass<T, R, NT, true, ENGINE, PROFILE, HALF>), dim3(nwg), dim3(NT), 0, st,
+        hipLaunchKernelGGL((k_pass<T, R, NT, true, ENGINE, PROFILE, X>), dim3(nwg), dim3(NT), 0, st,
                            reinterpret_cast<typename CT<T>::c*>(psi), passes, stages, ops,
                            pass_index, tiles_per_wg, partials, step_offset, ch, nwg, mats);
     else
-        hipLaunchKernelGGL((k_pass<T, R, NT, false, ENGINE, PROFILE, HALF>), dim3(nwg), dim3(NT), 0, st,
+        hipLaunchKernelGGL((k_pass<T, R, NT, false, ENGINE, PROFILE, X>), dim3(nwg), dim3(NT), 0, st,
                            reinterpret_cast<typename CT<T>::c*>(psi), passes, stages, ops,
                            pass_index, tiles_per_wg, partials, step_offset, ch, nwg, mats);
     return hipGetLastError();
@@ -1593,24 +1917,28 @@ static hipError_t pass_one(bool writes, void* psi, const DevPass* passes, const 
 
 #if SPIN_PART == 2 || SPIN_PART == 3
 template <typename T>
-hipError_t launch_pass_half(const PassShape& sh, void* psi, const DevPass* passes, const DevStage* stages, const DevOp<T>* ops,
+hipError_t launch_pass_slots(const PassShape& sh, void* psi, const DevPass* passes, const DevStage* stages, const DevOp<T>* ops,
                int pass_index, int64_t tiles_per_wg, int nwg, double* partials, int64_t step_offset, int ch,
                hipStream_t st) {
-#define SPIN_HALF(RR, NTT)                                                                        \
-    if (sh.r == RR && sh.nt == NTT)                                                               \
+#define SPIN_SLOTS(RR, NTT, XX)                                                                   \
+    if (sh.r == RR && sh.nt == NTT && sh.exchange == XX)                                          \
         return sh.profile                                                                         \
-                   ? pass_one<T, RR, NTT, 0, true, true>(sh.writes, psi, passes, stages, ops,     \
-                                                         pass_index, tiles_per_wg, nwg, partials, \
-                                                         step_offset, ch, nullptr, st)            \
-                   : pass_one<T, RR, NTT, 0, false, true>(sh.writes, psi, passes, stages, ops,    \
-                                                          pass_index, tiles_per_wg, nwg, partials,\
-                                                          step_offset, ch, nullptr, st);
-        if constexpr (sizeof(T) == 4) {
-            SPIN_HALF(5, 512) SPIN_HALF(6, 256)
-        } else {
-            SPIN_HALF(4, 512) SPIN_HALF(5, 256) SPIN_HALF(5, 512)
-        }
-#undef SPIN_HALF
+                   ? pass_one<T, RR, NTT, 0, true, XX>(sh.writes, psi, passes, stages, ops,       \
+                                                       pass_index, tiles_per_wg, nwg, partials,   \
+                                                       step_offset, ch, nullptr, st)              \
+                   : pass_one<T, RR, NTT, 0, false, XX>(sh.writes, psi, passes, stages, ops,      \
+                                                        pass_index, tiles_per_wg, nwg, partials,  \
+                                                        step_offset, ch, nullptr, st);
+    if constexpr (sizeof(T) == 4) {
+        SPIN_SLOTS(5, 512, kHalfTiles) SPIN_SLOTS(6, 256, kHalfTiles)
+        SPIN_SLOTS(2, 256, kSmallTiles) SPIN_SLOTS(3, 256, kSmallTiles) SPIN_SLOTS(4, 256, kSmallTiles)
+        SPIN_SLOTS(3, 512, kSmallTiles) SPIN_SLOTS(4, 512, kSmallTiles) SPIN_SLOTS(5, 64, kSmallTiles)
+    } else {
+        SPIN_SLOTS(4, 512, kHalfTiles) SPIN_SLOTS(5, 256, kHalfTiles) SPIN_SLOTS(5, 512, kHalfTiles)
+        SPIN_SLOTS(2, 256, kSmallTiles) SPIN_SLOTS(3, 256, kSmallTiles) SPIN_SLOTS(4, 256, kSmallTiles)
+        SPIN_SLOTS(3, 512, kSmallTiles)
+    }
+#undef SPIN_SLOTS
     return hipErrorInvalidValue;
 }
 #endif
@@ -1732,9 +2060,9 @@ SPIN_INST_RESIDENT(float)
 #elif SPIN_PART == 1
 SPIN_INST_RESIDENT(double)
 #elif SPIN_PART == 2
-SPIN_INST_PASS(launch_pass_half, float)
+SPIN_INST_PASS(launch_pass_slots, float)
 #elif SPIN_PART == 3
-SPIN_INST_PASS(launch_pass_half, double)
+SPIN_INST_PASS(launch_pass_slots, double)
 #elif SPIN_PART == 4
 SPIN_INST_PASS(launch_pass_whole, float)
 #elif SPIN_PART == 5

@@ -39,6 +39,14 @@ struct BatchJob {
     int32_t problem, rank;
 };
 
+// How a tiled pass moves a tile between two register stages through LDS.
+enum ExchangeMode {
+    kWholeTiles = 0,   // all amplitudes at once, one LDS layout for the pass, the next tile
+                       // prefetched into registers: one workgroup per CU
+    kHalfTiles = 1,    // per-lane slots, in two halves: two workgroups of 2^14-amplitude tiles
+    kSmallTiles = 2,   // per-lane slots, all at once: tiles of 2^13 amplitudes and fewer
+};
+
 struct PassShape {
     int r;    // register bits (amplitudes per lane = 2^r)
     int nt;   // lanes per workgroup; tile bits k = r + log2(nt)
@@ -46,12 +54,14 @@ struct PassShape {
     int engine = 0;       // 0: VALU butterflies; 1: MFMA stage matrices (complex64, r = 5, nt = 512)
     const float* mats = nullptr;   // engine 1: device matrix table
     bool profile = false;          // per-site observables: profile partials [slot][nwg][M + 1]
-    bool half = false;             // half-tile exchanges, two workgroups per CU (engine 0)
+    ExchangeMode exchange = kWholeTiles;   // engine 1: whole tiles
 };
 // Whether a pass kernel is instantiated for (precision, r, nt, engine).
 bool pass_shape_exists(bool f32, int r, int nt, int engine);
 // Whether a half-tile-exchange pass kernel is instantiated for (precision, r, nt).
 bool pass_half_exists(bool f32, int r, int nt);
+// Whether a small-tile kernel (kSmallTiles) is.
+bool pass_small_exists(bool f32, int r, int nt);
 
 template <typename T>
 hipError_t launch_init(void* psi, int M, int n, uint64_t seed, hipStream_t st);

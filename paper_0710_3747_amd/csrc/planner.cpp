@@ -611,7 +611,8 @@ static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int spli
     }
 }
 
-void plan_stages_coalesced(HostPass& pass, int r, int c, int beam, bool half, int gates, bool rank) {
+void plan_stages_coalesced(HostPass& pass, int r, int c, int beam, bool half, int gates, bool rank,
+                           bool once) {
     uint32_t af = 0, al = 0;
     const int k = int(pass.sites.size());
     for (int p = 0; p < k; ++p) {
@@ -621,6 +622,7 @@ void plan_stages_coalesced(HostPass& pass, int r, int c, int beam, bool half, in
     const int ng = usable_gates(gates, k, r, c);
     const int rx = r + ng;      // positions a stage's ops can reach
     pass.split = -1;
+    pass.slots = half || once;
     if (!half || k < 2 || r < 2) {
         plan_stages(pass, rx, af, al, beam);
         if (!rank)
@@ -895,7 +897,7 @@ static StreamPlan plan_stream_per_step(int M, const std::vector<Coupling>& J, do
         auto ap = sc.next_pass(forced, &T);
         plan.passes.push_back(make_pass(sb.ops, ap, T, M));
     }
-    for (auto& p : plan.passes) plan_stages_coalesced(p, std::min(pp.r, int(p.sites.size())), pp.c, 1, pp.half, pp.gates, pp.rank);
+    for (auto& p : plan.passes) plan_stages_coalesced(p, std::min(pp.r, int(p.sites.size())), pp.c, 1, pp.half, pp.gates, pp.rank, pp.once);
     for (int t = 0; t < nobs0; ++t) {
         plan.launch_tmpl.push_back(t);
         plan.launch_offset.push_back(0);
@@ -1053,7 +1055,7 @@ std::vector<HostPass> plan_block(int M, const std::vector<Coupling>& J, double d
 
 void finish_stages(StreamPlan& plan, const PassParams& pp) {
     for (auto& p : plan.passes)
-        plan_stages_coalesced(p, std::min(pp.r, int(p.sites.size())), pp.c, 1, pp.half, pp.gates, pp.rank);
+        plan_stages_coalesced(p, std::min(pp.r, int(p.sites.size())), pp.c, 1, pp.half, pp.gates, pp.rank, pp.once);
 }
 
 // Blocks of `W` steps repeated verbatim: the first carries the step-0
@@ -1276,7 +1278,8 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
     } else if (nv > 1) {
         for (HostPass& hp : best.passes) {
             HostPass alt = hp;
-            plan_stages_coalesced(alt, std::min(pp.r, int(alt.sites.size())), pp.c, 32, false, pp.gates);
+            plan_stages_coalesced(alt, std::min(pp.r, int(alt.sites.size())), pp.c, 32, false, pp.gates, false,
+                                  pp.once);
             if (alt.stages.size() < hp.stages.size()) hp.stages = std::move(alt.stages);
         }
     }
@@ -1580,12 +1583,13 @@ HostStage reorder_stage(const HostStage& st, const std::vector<int>& perm, bool 
 // lanes 0..15 must differ modulo the bank row.  `lanes` (positions on the
 // lane bits below the gates) of the first and last stage keep their order.
 void order_for_gathers(std::vector<HostStage>& stages, std::vector<std::vector<int>>& lanes,
-                       const std::vector<std::vector<int>>& waves, int eb, int nt) {
+                       const std::vector<std::vector<int>>& waves, int eb, int nt, bool half) {
     const int nst = int(stages.size());
     const int mod = 1 << exchange_pad_shift(eb);
     const int row = exchange_row_slots(nt, eb);
     for (int si = 0; si + 1 < nst; ++si) {
-        const int rr = int(stages[si].regs.size()), ng = int(stages[si].gates.size());
+        // register bits with a slot weight (all but the split position's)
+        const int rr = int(stages[si].regs.size()) - (half ? 1 : 0), ng = int(stages[si].gates.size());
         const std::vector<int>& nl = lanes[si + 1];
         const int n = std::min<int>(4, int(nl.size()));
         // residues of the next stage's lanes under an ordering; number of
@@ -1596,7 +1600,7 @@ void order_for_gathers(std::vector<HostStage>& stages, std::vector<std::vector<i
             tq.insert(tq.end(), st.gates_out.begin(), st.gates_out.end());
             tq.insert(tq.end(), waves[si].begin(), waves[si].end());
             for (size_t q = 0; q < tq.size(); ++q) w[tq[q]] = exchange_slot(1 << q, eb);
-            for (int b = 0; b + 1 < rr; ++b) w[st.regs_out[b]] = row << b;
+            for (int b = 0; b < rr; ++b) w[st.regs_out[b]] = row << b;
             std::vector<char> seen(mod, 0);
             int bad = 0;
             for (int x = 0; x < (1 << n); ++x) {
@@ -1609,7 +1613,7 @@ void order_for_gathers(std::vector<HostStage>& stages, std::vector<std::vector<i
             return bad;
         };
         const bool lanes_free = si > 0;
-        std::vector<int> perm(rr - 1), lp(lanes[si].size());
+        std::vector<int> perm(rr), lp(lanes[si].size());
         for (size_t q = 0; q < perm.size(); ++q) perm[q] = int(q);
         HostStage best = stages[si];
         std::vector<int> best_lanes = lanes[si];
@@ -1694,18 +1698,26 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
         if (si + 1 == nst && si > 0)
             std::stable_sort(tp.begin(), tp.end(),
                              [&](int a, int b) { return hp.bit_out[a] < hp.bit_out[b]; });
+        // a one-stage pass has no wave plan: its positions above the lanes are
+        // the wave bits, so that the gates come right above the lanes too
+        const size_t nl = 6 - stages[si].gates.size();
+        if (nst == 1 && !stages[si].gates.empty() && tp.size() > nl) {
+            wv.assign(tp.begin() + int(nl), tp.end());
+            tp.resize(nl);
+        }
         lanes_all.push_back(tp);
         waves_all.push_back(wv);
     }
     const bool gated = nst > 0 && !stages[0].gates.empty();
     std::vector<uint32_t> img(k, 0u);
-    if (hp.split >= 0) {
+    if (hp.split >= 0)
         // half-tile exchanges: one half of the tile in LDS at a time, the
         // split position on the top register bit
         for (const HostStage& st : stages)
             if (st.regs.empty() || st.regs.back() != hp.split)
                 throw std::runtime_error("encode: split position not on the top register bit");
-        order_for_gathers(stages, lanes_all, waves_all, eb, 1 << (k - int(stages[0].regs.size())));
+    if (hp.slots) {
+        order_for_gathers(stages, lanes_all, waves_all, eb, 1 << (k - int(stages[0].regs.size())), hp.split >= 0);
     }
     if (fixed_swizzle) {
         for (int p = 0; p < k; ++p) img[p] = lds_swizzle<eb>(1u << p);
@@ -1721,7 +1733,7 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
         }
         const std::vector<uint32_t> im = search_layout(k - 1, eb, pat, uint64_t(k) * 131 + hp.ops.size());
         for (int p = 0; p < k; ++p) img[p] = p == hp.split ? 0u : im[comp(p)];
-    } else if (hp.split < 0) {
+    } else if (!hp.slots) {
         img = search_layout(k, eb, lanes_all, uint64_t(k) * 131 + hp.ops.size());
         // reorder the lane positions only; the wave positions stay last
         for (int si = 1; si + 1 < nst; ++si) choose_lanes(lanes_all[si], img, eb);
@@ -1775,9 +1787,10 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
             ds.rbit[b] = byte_off(1u << rq[b]);
             ds.gr_in[b] = int64_t(1) << hp.bit_in[rq[b]];
         }
-        if (hp.split >= 0 && si > 0) {
+        const int rw = rr - (hp.split >= 0 ? 1 : 0);     // register bits with a slot weight
+        if (hp.slots && si > 0) {
             for (int q = 0; q < ntb; ++q) ds.gw[q] = uint32_t(prev_w[tq[q]] * eb);
-            for (int b = 0; b + 1 < rr; ++b) ds.gr[b] = uint32_t(prev_w[rq[b]] * eb);
+            for (int b = 0; b < rw; ++b) ds.gr[b] = uint32_t(prev_w[rq[b]] * eb);
         }
         auto regbit = [&](int p) {
             for (int b = 0; b < rr; ++b)
@@ -1810,7 +1823,7 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
                 if (engine == 1) throw std::runtime_error("encode: the matrix engine has no register/lane exchange");
                 std::swap(rq[it.q], tq[lane0 + it.g]);
                 DevOp<T> d{};
-                d.code = (6 + lane0 + it.g - 4) * 8 + it.q;
+                d.code = op_gate(it.q, lane0 + it.g - 4);
                 out.ops.push_back(d);
                 continue;
             }
@@ -1858,14 +1871,18 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
             for (int pc = 0; pc < pieces; ++pc) {
                 DevOp<T> d{};
                 const double th = theta / pieces;
-                d.code = qa * 8 + qb;
-                d.aux = 0;
+                d.code = op_xy(qa, qb);
                 d.t = T(std::tan(0.5 * th));
                 d.s = T(std::sin(th));
-                const double A = pc == 0 ? op.A : 0.0;
-                if (A != 0.0) d.code |= kOpZZ;
-                d.pr = T(std::cos(0.25 * A));
-                d.pi = T(std::sin(0.25 * A));
+                d.nt = -d.t;
+                d.ns = -d.s;
+                out.ops.push_back(d);
+            }
+            if (op.A != 0.0) {
+                DevOp<T> d{};
+                d.code = op_zz(qa, qb);
+                d.t = T(std::cos(0.25 * op.A));
+                d.s = T(std::sin(0.25 * op.A));
                 out.ops.push_back(d);
             }
         }
@@ -1878,7 +1895,7 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
         for (int q = 0; q < ntb; ++q) ds.gt_out[q] = int64_t(1) << hp.bit_out[tq[q]];
         for (int b = 0; b < rr; ++b) ds.gr_out[b] = int64_t(1) << hp.bit_out[rq[b]];
         for (int q = 0; q < ntb; ++q) prev_w[tq[q]] = exchange_slot(1 << q, eb);
-        for (int b = 0; b + 1 < rr; ++b) prev_w[rq[b]] = exchange_row_slots(1 << ntb, eb) << b;
+        for (int b = 0; b < rw; ++b) prev_w[rq[b]] = exchange_row_slots(1 << ntb, eb) << b;
         out.stages.push_back(ds);
     }
     dp.nmeas = nmeas;

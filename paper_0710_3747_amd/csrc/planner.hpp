@@ -81,6 +81,7 @@ struct HostPass {
     std::vector<Op> ops;       // execution order
     std::vector<HostStage> stages;
     bool writes = true;
+    bool slots = false;        // exchanges use per-lane slots (see exchange_row_slots)
 };
 
 struct PassParams {
@@ -94,6 +95,10 @@ struct PassParams {
     // can move the tile through LDS in two halves (the position's two
     // values), each half through the same LDS slots.
     bool half = false;
+    // Whole-tile exchanges through per-lane slots (tiles small enough that
+    // several fit a CU's LDS); neither this nor half: the tile keeps one LDS
+    // layout for all its stages.
+    bool once = false;
     // Lane bits of a stage whose positions its ops can reach by exchanging
     // them with register bits inside the wave (0..kMaxGates, on the top lane
     // bits; fewer when more than 4 low address bits pin the lanes).
@@ -143,8 +148,9 @@ void plan_stages(HostPass& pass, int r, uint32_t avoid_first = 0, uint32_t avoid
 // stage.
 // gates: lane bits each stage can exchange with registers (PassParams::gates).
 // rank: stages only, to compare plans by; their exchanges are left out.
+// once: see PassParams::once.
 void plan_stages_coalesced(HostPass& pass, int r, int c, int beam = 1, bool half = false, int gates = 0,
-                           bool rank = false);
+                           bool rank = false, bool once = false);
 
 // Full streaming plan for one scheduling variant: sequence, passes, period
 // search, stages.

@@ -1,7 +1,8 @@
-// Host check of half-tile passes with register/lane exchanges (test program;
-// links the planner).
+// Host check of passes that exchange through per-lane slots, with
+// register/lane exchanges inside their stages (test program; links the
+// planner).
 //
-// Reads "M prec k r c n_steps observed" and then K lines "i j a b" on stdin,
+// Reads "M prec k r c n_steps observed half" (half 0: whole small tiles) and then K lines "i j a b" on stdin,
 // plans the call as the library does (two gates), encodes every pass and
 // emulates the kernel on one tile, with every lane's registers holding the
 // tile-local index of their amplitude:
@@ -24,12 +25,13 @@
 using namespace spinqp;
 
 template <typename T>
-static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int64_t steps, int observed) {
+static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int64_t steps, int observed, bool half) {
     PassParams pp;
     pp.k = k;
     pp.r = r;
     pp.c = c;
-    pp.half = true;
+    pp.half = half;
+    pp.once = !half;
     pp.gates = kMaxGates;
     const StreamPlan sp = plan_stream_best(M, J, 0.05, steps, observed, true, pp);
     constexpr int EB = int(sizeof(T)) * 2;
@@ -83,14 +85,24 @@ static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int
             for (int o = S.op0; o < S.op0 + S.nop; ++o) {
                 const DevOp<T>& op = tb.ops[o];
                 if (op.code == kOpMeas) continue;
-                const int hi = (op.code & 63) >> 3, lo = op.code & 7;
-                if (hi >= 6) {
+                if (op.code >= op_gate(0, 0) && op.code < kOpEnd) {
                     ++swaps;
-                    const uint32_t lane = 1u << (hi - 6 + 4), reg = 1u << lo;
+                    const uint32_t lane = 1u << (4 + (op.code - 16) % 2), reg = 1u << ((op.code - 16) / 2);
                     for (uint32_t t = 0; t < nt; ++t)
                         if (!(t & lane))
                             for (uint32_t j = 0; j < nr; ++j)
                                 if (j & reg) std::swap(v[t][j], v[t | lane][j ^ reg]);
+                    continue;
+                }
+                int lo = -1, hi = -1;
+                for (int b = 1; b < r; ++b)
+                    for (int a = 0; a < b; ++a)
+                        if (op.code == op_xy(a, b) || op.code == op_zz(a, b)) {
+                            lo = a;
+                            hi = b;
+                        }
+                if (lo < 0) {
+                    fail("unknown op code");
                     continue;
                 }
                 ++factors;
@@ -134,23 +146,25 @@ static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int
             any_cross |= S.xnext != 0;
             const DevStage& S2 = tb.stages[P.stage0 + si + 1];
             std::vector<std::vector<uint32_t>> w(nt, std::vector<uint32_t>(nr));
-            for (uint32_t h = 0; h < 2; ++h) {
-                std::vector<int64_t> slot(size_t(row) << (r - 1), -1), owner(slot.size(), -1);
+            const int rw = half ? r - 1 : r;
+            const uint32_t nh = 1u << rw;
+            for (uint32_t h = 0; h < nr / nh; ++h) {
+                std::vector<int64_t> slot(size_t(row) << rw, -1), owner(slot.size(), -1);
                 for (uint32_t t = 0; t < nt; ++t)
-                    for (uint32_t i = 0; i < nr / 2; ++i) {
+                    for (uint32_t i = 0; i < nh; ++i) {
                         const size_t s = size_t(i) * row + size_t(exchange_slot(int(t), EB));
                         if (s >= slot.size() || slot[s] >= 0) fail("scatter slot out of range or taken");
                         else {
-                            slot[s] = v[t][h * nr / 2 + i];
+                            slot[s] = v[t][h * nh + i];
                             owner[s] = t / 64;
                         }
                     }
                 for (uint32_t t = 0; t < nt; ++t)
-                    for (uint32_t i = 0; i < nr / 2; ++i) {
+                    for (uint32_t i = 0; i < nh; ++i) {
                         uint64_t a = 0;
                         for (int q = 0; q < k - r; ++q)
                             if (t >> q & 1) a += S2.gw[q];
-                        for (int b = 0; b + 1 < r; ++b)
+                        for (int b = 0; b < rw; ++b)
                             if (i >> b & 1) a += S2.gr[b];
                         const size_t s = a / EB;
                         if (a % EB || s >= slot.size() || slot[s] < 0) {
@@ -158,7 +172,7 @@ static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int
                             continue;
                         }
                         if (!S.xnext && owner[s] != int64_t(t / 64)) fail("wave-local exchange reads another wave's slot");
-                        w[t][h * nr / 2 + i] = uint32_t(slot[s]);
+                        w[t][h * nh + i] = uint32_t(slot[s]);
                     }
             }
             v.swap(w);
@@ -192,13 +206,13 @@ static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int
 }
 
 int main() {
-    int M, prec, k, r, c, observed;
+    int M, prec, k, r, c, observed, half;
     long long steps;
-    if (std::scanf("%d %d %d %d %d %lld %d", &M, &prec, &k, &r, &c, &steps, &observed) != 7) return 2;
+    if (std::scanf("%d %d %d %d %d %lld %d %d", &M, &prec, &k, &r, &c, &steps, &observed, &half) != 8) return 2;
     std::vector<Coupling> J;
     Coupling x;
     while (std::scanf("%d %d %lf %lf", &x.i, &x.j, &x.a, &x.b) == 4) J.push_back(x);
-    const int bad = prec == 1 ? check<float>(M, J, k, r, c, steps, observed)
-                              : check<double>(M, J, k, r, c, steps, observed);
+    const int bad = prec == 1 ? check<float>(M, J, k, r, c, steps, observed, half != 0)
+                              : check<double>(M, J, k, r, c, steps, observed, half != 0);
     return bad ? 1 : 0;
 }

@@ -1,5 +1,5 @@
-"""Host checks of half-tile passes whose stages exchange register bits with
-lane bits (no GPU): tests/host_checks/gate_check.cpp emulates the encoded
+"""Host checks of passes whose stages exchange register bits with lane bits
+and go through per-lane LDS slots (no GPU): tests/host_checks/gate_check.cpp emulates the encoded
 tables on one tile."""
 import os
 import subprocess
@@ -20,23 +20,31 @@ def binary(tmp_path_factory):
 
 
 CASES = [
-    # name, M, couplings, prec, k, r, c, steps, observed
-    ("ladder2x9-c64-r5", 18, workloads.ladder(9), 1, 14, 5, 4, 30, 0),
-    ("ladder2x15-c64-r5-top-site", 30, workloads.ladder(15), 1, 14, 5, 4, 20, 29),
-    ("ladder2x15-c64-r6", 30, workloads.ladder(15), 1, 14, 6, 4, 20, 7),
-    ("ladder2x15-c64-one-gate", 30, workloads.ladder(15), 1, 14, 5, 5, 20, 0),
-    ("ladder2x15-c64-no-gate", 30, workloads.ladder(15), 1, 14, 5, 6, 20, 0),
-    ("ladder2x15-c128-k13-r4", 30, workloads.ladder(15), 2, 13, 4, 4, 20, 0),
-    ("ladder2x15-c128-k14", 30, workloads.ladder(15), 2, 14, 5, 4, 20, 0),
-    ("star17-c128-zz", 17, workloads.star(17, 3, a_over_b=0.5), 2, 13, 5, 4, 10, 5),
-    ("star28-blocks-c64", 28, workloads.star_m28(), 1, 14, 5, 4, 2, 0),
-    ("two-site-bond-c64", 15, [(3, 11, 0.0, 1.0)], 1, 14, 5, 4, 3, 14),
+    # name, M, couplings, prec, k, r, c, steps, observed, half tiles
+    ("ladder2x9-c64-r5", 18, workloads.ladder(9), 1, 14, 5, 4, 30, 0, 1),
+    ("ladder2x15-c64-r5-top-site", 30, workloads.ladder(15), 1, 14, 5, 4, 20, 29, 1),
+    ("ladder2x15-c64-r6", 30, workloads.ladder(15), 1, 14, 6, 4, 20, 7, 1),
+    ("ladder2x15-c64-one-gate", 30, workloads.ladder(15), 1, 14, 5, 5, 20, 0, 1),
+    ("ladder2x15-c64-no-gate", 30, workloads.ladder(15), 1, 14, 5, 6, 20, 0, 1),
+    ("ladder2x15-c128-k13-r4", 30, workloads.ladder(15), 2, 13, 4, 4, 20, 0, 1),
+    ("ladder2x15-c128-k14", 30, workloads.ladder(15), 2, 14, 5, 4, 20, 0, 1),
+    ("star17-c128-zz", 17, workloads.star(17, 3, a_over_b=0.5), 2, 13, 5, 4, 10, 5, 1),
+    ("star28-blocks-c64", 28, workloads.star_m28(), 1, 14, 5, 4, 2, 0, 1),
+    ("two-site-bond-c64", 15, [(3, 11, 0.0, 1.0)], 1, 14, 5, 4, 3, 14, 1),
+    ("ladder2x9-c64-k10", 18, workloads.ladder(9), 1, 10, 2, 4, 30, 0, 0),
+    ("star15-c64-k11-zz", 15, workloads.star(15, 3, a_over_b=-2.0), 1, 11, 3, 4, 10, 7, 0),
+    ("ladder2x9-c64-k12", 18, workloads.ladder(9), 1, 12, 4, 4, 30, 17, 0),
+    ("chain14-c128-k12-c2", 14, workloads.chain(14), 2, 12, 4, 2, 30, 0, 0),
+    # passes of one stage that exchanges
+    ("chain18-c64-half-c2", 18, workloads.chain(8), 1, 14, 5, 2, 3, 0, 1),
+    ("star17-c128-k12", 17, workloads.star(17, 3), 2, 12, 4, 4, 10, 0, 0),
+    ("chain13-c64-one-wave", 13, workloads.chain(13), 1, 11, 5, 4, 30, 0, 0),
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_register_lane_exchanges(case, binary):
-    _, M, J, prec, k, r, c, steps, obs = case
-    inp = f"{M} {prec} {k} {r} {c} {steps} {obs}\n" + "".join(f"{i} {j} {a!r} {b!r}\n" for i, j, a, b in J)
+    _, M, J, prec, k, r, c, steps, obs, half = case
+    inp = f"{M} {prec} {k} {r} {c} {steps} {obs} {half}\n" + "".join(f"{i} {j} {a!r} {b!r}\n" for i, j, a, b in J)
     p = subprocess.run([binary], input=inp, capture_output=True, text=True, timeout=300)
     assert p.returncode == 0 and "failures 0" in p.stdout, p.stdout
