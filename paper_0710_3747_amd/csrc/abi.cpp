@@ -136,8 +136,7 @@ struct DevicePlan {
     void* d_ops = nullptr;
     void* d_mats = nullptr;     // matrix engine
     // resident
-    int res_r = 0, res_nt = 0;
-    int pro_stage0 = 0, pro_nstage = 0, step_stage0 = 0, step_nstage = 0;
+    ResidentStages res;
     // per template: measurement steps (relative) and their sites
     std::vector<std::vector<int64_t>> meas;
     std::vector<std::vector<int>> meas_site;
@@ -215,19 +214,18 @@ Shape choose_shape(int prec, int M, const spin_options* opt) {
     s.exchange = ex == 2 || (ex == 0 && half_ok) ? kHalfTiles : ex == 0 && small_ok ? kSmallTiles : kWholeTiles;
     s.valid = s.exchange == kHalfTiles ? half_ok
                                        : s.exchange == kSmallTiles || pass_shape_exists(f32, s.r, s.nt, s.engine);
-    s.res_cap = f32 ? 14 : 13;
+    s.res_cap = resident_max(f32);
     s.resident = M <= s.res_cap;
     return s;
 }
 
-static int res_shape(int prec, int M, int* r, int* nt) {
-    const int rmax = prec == SPIN_C64 ? 5 : 4;
-    *r = std::min(rmax, M);
-    const int tb = M - *r;    // thread bits
-    if (tb <= 6) *nt = 64;
-    else if (tb <= 8) *nt = 256;
-    else *nt = 512;
-    return SPIN_OK;
+static void set_stages(const ResidentStages& rs, ResidentJob* j) {
+    j->obs_stage0 = rs.obs0;
+    j->pro_stage0 = rs.pro0;
+    j->pro_nstage = rs.npro;
+    j->step_stage0 = rs.step0;
+    j->step_nstage = rs.nstep;
+    j->last_stage0 = rs.last0;
 }
 
 // Planner settings of an exchange mode.
@@ -245,15 +243,10 @@ static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, const 
     try {
         if (sh.resident) {
             dp->resident = true;
-            res_shape(key.prec, key.M, &dp->res_r, &dp->res_nt);
-            ResidentPlan rp = plan_resident(key.M, J, key.dt, key.observed, key.merge != 0, dp->res_r,
-                                            key.profile != 0);
-            dp->pro_stage0 = 0;
-            encode_pass<T>(rp.prologue, key.M, key.observed, tb, true, 0, key.profile != 0);
-            dp->pro_nstage = int(tb.stages.size());
-            dp->step_stage0 = int(tb.stages.size());
-            encode_pass<T>(rp.step, key.M, key.observed, tb, true, 0, key.profile != 0);
-            dp->step_nstage = int(tb.stages.size()) - dp->step_stage0;
+            const int bits = resident_bits(key.M);
+            const ResidentPlan rp = plan_resident(bits, J, key.dt, key.observed, key.merge != 0, kResidentRegs,
+                                                  key.profile != 0);
+            dp->res = encode_resident<T>(rp, bits, key.observed, tb, key.profile != 0);
             dp->stages_total = tb.stages.size();
         } else {
             PassParams pp;
@@ -282,7 +275,7 @@ static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, const 
             dp->nwg = int(nwg);
             dp->tiles_per_wg = ntiles / nwg;
             for (const HostPass& hp : dp->sp.passes) {
-                encode_pass<T>(hp, key.M, key.observed, tb, false, sh.engine, key.profile != 0);
+                encode_pass<T>(hp, key.M, key.observed, tb, sh.engine, key.profile != 0);
                 std::vector<int64_t> ms;
                 std::vector<int> mst;
                 for (const Op& op : hp.ops)
@@ -481,11 +474,8 @@ static int evolve_profile(void* psi, int M, const DevicePlan& dp, int64_t n_step
         job.N = N;
         job.M = M;
         job.init = 0;
-        job.pro_stage0 = dp.pro_stage0;
-        job.pro_nstage = dp.pro_nstage;
-        job.step_stage0 = dp.step_stage0;
-        job.step_nstage = dp.step_nstage;
-        HIP_TRY((launch_resident<T>(dp.res_r, dp.res_nt, job, nullptr, 1,
+        set_stages(dp.res, &job);
+        HIP_TRY((launch_resident<T>(resident_bits(M), job, nullptr, 1,
                                     static_cast<const DevStage*>(dp.d_stages),
                                     static_cast<const DevOp<T>*>(dp.d_ops), n_steps, st)));
         return SPIN_OK;
@@ -562,11 +552,8 @@ static int evolve_fused(void* psi, int M, const std::vector<Coupling>& J, double
         job.N = N;
         job.M = M;
         job.init = 0;
-        job.pro_stage0 = dp->pro_stage0;
-        job.pro_nstage = dp->pro_nstage;
-        job.step_stage0 = dp->step_stage0;
-        job.step_nstage = dp->step_nstage;
-        HIP_TRY((launch_resident<T>(dp->res_r, dp->res_nt, job, nullptr, 1,
+        set_stages(dp->res, &job);
+        HIP_TRY((launch_resident<T>(resident_bits(M), job, nullptr, 1,
                                     static_cast<const DevStage*>(dp->d_stages),
                                     static_cast<const DevOp<T>*>(dp->d_ops), n_steps, st)));
         return SPIN_OK;
@@ -829,7 +816,6 @@ struct HostPlan {
     Shape sh;
     StreamPlan sp;
     ResidentPlan rp;
-    int res_r = 0, res_nt = 0;
     bool profile = false;
 };
 
@@ -854,9 +840,7 @@ int host_plan(int32_t prec, int32_t M, const std::vector<Coupling>& Jv, double d
             hp->path = 0;
         } else if (hp->sh.resident) {
             hp->path = 1;
-            const int rmax = prec == SPIN_C64 ? 5 : 4;
-            hp->res_r = std::min(rmax, int(M));
-            hp->rp = plan_resident(M, Jv, dt, observed, merge, hp->res_r, profile);
+            hp->rp = plan_resident(resident_bits(M), Jv, dt, observed, merge, kResidentRegs, profile);
         } else {
             hp->path = 2;
             PassParams pp;
@@ -874,11 +858,10 @@ int host_plan(int32_t prec, int32_t M, const std::vector<Coupling>& Jv, double d
             using T = decltype(tag);
             DevTables<T> tb;
             if (hp->path == 1) {
-                encode_pass<T>(hp->rp.prologue, M, observed, tb, true, 0, profile);
-                encode_pass<T>(hp->rp.step, M, observed, tb, true, 0, profile);
+                encode_resident<T>(hp->rp, resident_bits(M), observed, tb, profile);
             } else if (hp->path == 2) {
                 for (const HostPass& p : hp->sp.passes)
-                    encode_pass<T>(p, M, observed, tb, false, hp->sh.engine, profile);
+                    encode_pass<T>(p, M, observed, tb, hp->sh.engine, profile);
             }
         };
         if (prec == SPIN_C64) encode_all(float{});
@@ -908,13 +891,15 @@ extern "C" int spin_describe_plan(int32_t prec, int32_t M, const spin_coupling* 
         info->passes_per_step = 2.0 * Jv.size();
     } else if (hp.path == 1) {
         info->tile_bits = M;
-        info->reg_bits = hp.res_r;
+        info->reg_bits = kResidentRegs;
         info->launches = 1;
         info->stages_total = int(hp.rp.prologue.stages.size() + hp.rp.step.stages.size());
         info->exchanges = int64_t(hp.rp.prologue.stages.size()) + n_steps * int64_t(hp.rp.step.stages.size());
         int64_t f = 0;
         for (const Op& op : hp.rp.step.ops) f += op.kind == 0;
         info->factor_ops = f * n_steps;
+        if (n_steps > 0)
+            for (const Op& op : hp.rp.prologue.ops) info->factor_ops += op.kind == 0;
     } else {
         info->tile_bits = hp.sh.k;
         info->reg_bits = hp.sh.r;
@@ -963,6 +948,7 @@ extern "C" int spin_plan_trace(int32_t prec, int32_t M, const spin_coupling* J, 
         for (const HostStage& s : p.stages)
             for (int o : s.ops) {
                 const Op& op = p.ops[o];
+                if (op.kind == 1 && op.i >= M) continue;     // a padding site of a one-workgroup plan
                 if (op.kind == 1) put(1, double(op.step + off), op.i, 0, 0);
                 else put(0, op.i, op.j, op.A, op.B);
             }
@@ -980,8 +966,13 @@ extern "C" int spin_plan_trace(int32_t prec, int32_t M, const spin_coupling* J, 
             observe(k);
         }
     } else if (hp.path == 1) {
-        put_pass(hp.rp.prologue, 0);
-        for (int64_t k = 1; k <= n_steps; ++k) put_pass(hp.rp.step, k - 1);
+        if (n_steps == 0) {
+            for (const Op& op : hp.rp.prologue.ops)
+                if (op.kind == 1 && op.i < M) put(1, 0, op.i, 0, 0);
+        } else {
+            put_pass(hp.rp.prologue, 0);
+        }
+        for (int64_t k = 1; k <= n_steps; ++k) put_pass(k < n_steps ? hp.rp.step : hp.rp.last, k - 1);
     } else {
         for (size_t l = 0; l < hp.sp.launch_tmpl.size(); ++l)
             put_pass(hp.sp.passes[hp.sp.launch_tmpl[l]], hp.sp.launch_offset[l]);

@@ -17,142 +17,6 @@
 
 namespace spinqp {
 
-// Device tables of the grouped one-workgroup launches of one batch call,
-// kept (like the persistent launch's) until spin_release_caches so the call
-// can return without waiting for the launches.
-struct ResidentBatch {
-    struct Group {
-        int r = 0, nt = 0, njobs = 0;
-        void *d_jobs = nullptr, *d_st = nullptr, *d_ops = nullptr;
-    };
-    std::vector<Group> groups;
-    ~ResidentBatch() {
-        for (Group& g : groups)
-            for (void* p : {g.d_jobs, g.d_st, g.d_ops})
-                if (p) (void)hipFree(p);
-    }
-};
-
-static std::mutex g_rmu;
-static std::map<std::vector<double>, std::shared_ptr<ResidentBatch>> g_rcache;
-
-static std::vector<double> batch_key(const spin_problem* probs, int n,
-                                     const std::vector<std::vector<Coupling>>& Js, int prec,
-                                     double dt, int64_t n_steps, int init, int dev);
-
-template <typename T>
-static int batch_resident_build(const spin_problem* probs, int32_t n,
-                                const std::vector<std::vector<Coupling>>& Js, double dt, int init,
-                                ResidentBatch* rb) {
-    // group problems by kernel shape; each group is one launch with one
-    // workgroup per problem, largest states first
-    const int rmax = sizeof(T) == 4 ? 5 : 4;
-    std::map<std::pair<int, int>, std::vector<int>> groups;
-    for (int p = 0; p < n; ++p) {
-        const int M = probs[p].M;
-        const int r = std::min(rmax, M);
-        const int tb = M - r;
-        const int nt = tb <= 6 ? 64 : (tb <= 8 ? 256 : 512);
-        groups[{r, nt}].push_back(p);
-    }
-    for (auto& g : groups) {
-        std::vector<int>& idx = g.second;
-        std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return probs[a].M > probs[b].M; });
-        DevTables<T> tb;
-        std::vector<ResidentJob> jobs;
-        std::map<std::vector<double>, ResidentJob> shared;   // equal problems share tables
-        for (int p : idx) {
-            const spin_problem& pr = probs[p];
-            std::vector<double> skey{double(pr.M), double(pr.observed_site)};
-            for (const Coupling& c : Js[p]) {
-                skey.push_back(c.i);
-                skey.push_back(c.j);
-                skey.push_back(c.a);
-                skey.push_back(c.b);
-            }
-            ResidentJob j{};
-            auto hit = shared.find(skey);
-            if (hit != shared.end()) j = hit->second;
-            j.psi = pr.psi;
-            j.P = pr.P_dev;
-            j.N = pr.N_dev;
-            j.seed = pr.seed;
-            j.M = pr.M;
-            j.polarized = pr.polarized_site;
-            j.init = init;
-            if (hit != shared.end()) {
-                jobs.push_back(j);
-                continue;
-            }
-            ResidentPlan rp;
-            try {
-                rp = plan_resident(pr.M, Js[p], dt, pr.observed_site, true, g.first.first);
-            } catch (const std::exception& e) {
-                return fail(SPIN_EUNSUPPORTED, std::string("planning failed: ") + e.what());
-            }
-            j.pro_stage0 = int(tb.stages.size());
-            encode_pass<T>(rp.prologue, pr.M, pr.observed_site, tb, true);
-            j.pro_nstage = int(tb.stages.size()) - j.pro_stage0;
-            j.step_stage0 = int(tb.stages.size());
-            encode_pass<T>(rp.step, pr.M, pr.observed_site, tb, true);
-            j.step_nstage = int(tb.stages.size()) - j.step_stage0;
-            shared[skey] = j;
-            jobs.push_back(j);
-        }
-        ResidentBatch::Group gr;
-        gr.r = g.first.first;
-        gr.nt = g.first.second;
-        gr.njobs = int(jobs.size());
-        rb->groups.push_back(gr);
-        ResidentBatch::Group& G = rb->groups.back();
-        auto up = [&](const void* src, size_t bytes, void** dst) -> int {
-            if (bytes == 0) bytes = 16;
-            if (hipMalloc(dst, bytes) != hipSuccess) return fail(SPIN_ENOMEM, "batch table allocation failed");
-            if (src && hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice) != hipSuccess)
-                return fail(SPIN_EHIP, "batch table upload failed");
-            return SPIN_OK;
-        };
-        int rc;
-        if ((rc = up(jobs.data(), jobs.size() * sizeof(ResidentJob), &G.d_jobs))) return rc;
-        if ((rc = up(tb.stages.empty() ? nullptr : tb.stages.data(), tb.stages.size() * sizeof(DevStage),
-                     &G.d_st)))
-            return rc;
-        if ((rc = up(tb.ops.empty() ? nullptr : tb.ops.data(), tb.ops.size() * sizeof(DevOp<T>), &G.d_ops)))
-            return rc;
-    }
-    return SPIN_OK;
-}
-
-template <typename T>
-static int batch_resident(const spin_problem* probs, int32_t n, const std::vector<std::vector<Coupling>>& Js,
-                          int prec, double dt, int64_t n_steps, int init, hipStream_t st) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return fail(SPIN_EHIP, "hipGetDevice failed");
-    const std::vector<double> key = batch_key(probs, n, Js, prec, dt, n_steps, init, dev);
-    std::shared_ptr<ResidentBatch> rb;
-    {
-        std::lock_guard<std::mutex> lk(g_rmu);
-        auto it = g_rcache.find(key);
-        if (it != g_rcache.end()) rb = it->second;
-    }
-    if (!rb) {
-        rb = std::make_shared<ResidentBatch>();
-        const int rc = batch_resident_build<T>(probs, n, Js, dt, init, rb.get());
-        if (rc) return rc;
-        std::lock_guard<std::mutex> lk(g_rmu);
-        g_rcache[key] = rb;
-    }
-    ResidentJob none{};
-    for (const ResidentBatch::Group& G : rb->groups) {
-        const hipError_t e = launch_resident<T>(G.r, G.nt, none, static_cast<const ResidentJob*>(G.d_jobs),
-                                                G.njobs, static_cast<const DevStage*>(G.d_st),
-                                                static_cast<const DevOp<T>*>(G.d_ops), n_steps, st);
-        if (e != hipSuccess) return fail(SPIN_EHIP, std::string("batch launch: ") + hipGetErrorString(e));
-    }
-    return SPIN_OK;
-}
-
-
 // ------------------------------------------------------- persistent batch
 struct BatchCache {
     void *d_probs = nullptr, *d_jobs = nullptr, *d_jstart = nullptr, *d_passes = nullptr,
@@ -197,15 +61,11 @@ static int status_word(int dev, int** out) {
 }
 
 void release_batch_caches() {
-    {
-        std::lock_guard<std::mutex> lk(g_bmu);
-        g_bcache.clear();
-        for (auto& kv : g_status)
-            if (kv.second) (void)hipFree(kv.second);
-        g_status.clear();
-    }
-    std::lock_guard<std::mutex> lk(g_rmu);
-    g_rcache.clear();
+    std::lock_guard<std::mutex> lk(g_bmu);
+    g_bcache.clear();
+    for (auto& kv : g_status)
+        if (kv.second) (void)hipFree(kv.second);
+    g_status.clear();
 }
 
 // Key: everything the tables and the launch depend on.
@@ -239,7 +99,7 @@ static int batch_build(const spin_problem* probs, const std::vector<int>& sel,
                        int init, int nslots, bool half, BatchCache* bc) {
     const bool f32 = sizeof(T) == 4;
     const int K = batch_tile_bits(f32), R = batch_shape(f32, half).r;
-    const int KL = half ? K - 1 : K;    // largest problem held in LDS
+    const int KL = K - 1;               // largest one-workgroup problem
     DevTables<T> tb;
     std::vector<BatchProblem> bp;
     std::vector<int2> launches;
@@ -283,18 +143,20 @@ static int batch_build(const spin_problem* probs, const std::vector<int>& sel,
             continue;
         }
         if (pr.M <= KL) {
-            ResidentPlan rp = plan_resident(pr.M, Js[p], dt, pr.observed_site, true, R);
-            const int nthreads = 1 << (pr.M - R);
+            const int bits = batch_resident_bits(pr.M, half);
+            const int r = bits - __builtin_ctz(batch_shape(f32, half).nt);
+            const ResidentPlan rp = plan_resident(bits, Js[p], dt, pr.observed_site, true, r);
             b.gsize = 1;
-            b.pro_stage0 = int(tb.stages.size());
-            encode_pass<T>(rp.prologue, pr.M, pr.observed_site, tb, true);
-            b.pro_nstage = int(tb.stages.size()) - b.pro_stage0;
-            b.step_stage0 = int(tb.stages.size());
-            encode_pass<T>(rp.step, pr.M, pr.observed_site, tb, true);
-            b.step_nstage = int(tb.stages.size()) - b.step_stage0;
+            const ResidentStages rs = encode_resident<T>(rp, bits, pr.observed_site, tb, false);
+            b.obs_stage0 = rs.obs0;
+            b.pro_stage0 = rs.pro0;
+            b.pro_nstage = rs.npro;
+            b.step_stage0 = rs.step0;
+            b.step_nstage = rs.nstep;
+            b.last_stage0 = rs.last0;
             for (const Op& op : rp.step.ops) fops += op.kind == 0;
             // on-chip: about half the cost per amplitude of a tiled pass
-            fops = 0.5 * fops * std::ldexp(1.0, pr.M) * double(n_steps + 1);
+            fops = 0.5 * fops * std::ldexp(1.0, bits) * double(n_steps + 1);
             dur.push_back(fops);
         } else {
             PassParams pp;
@@ -523,28 +385,11 @@ extern "C" int spin_trotter_evolve_batch(const spin_problem* probs, int32_t n,
         const bool half = batch_blocks_per_cu(f32, true) >= 2;
         if (!half && batch_blocks_per_cu(f32, false) < 1)
             return fail(SPIN_EUNSUPPORTED, "batch kernel does not fit a CU");
-        // states smaller than a lane's registers: the grouped one-workgroup
-        // launches; everything else: the persistent launch
-        const int rmin = batch_shape(f32, half).r;
-        std::vector<int> small, big;
-        for (int p = 0; p < n; ++p) (probs[p].M < rmin ? small : big).push_back(p);
-        int rc = SPIN_OK;
-        if (!small.empty()) {
-            std::vector<spin_problem> sp;
-            std::vector<std::vector<Coupling>> sj;
-            for (int p : small) {
-                sp.push_back(probs[p]);
-                sj.push_back(Js[p]);
-            }
-            rc = prec == SPIN_C64 ? batch_resident<float>(sp.data(), int(sp.size()), sj, prec, dt, n_steps, init, st)
-                                  : batch_resident<double>(sp.data(), int(sp.size()), sj, prec, dt, n_steps, init, st);
-            if (rc) return rc;
-        }
-        if (!big.empty()) {
-            const bool graph = true;
-            rc = f32 ? batch_persistent<float>(probs, big, Js, prec, dt, n_steps, init, graph, half, st)
-                     : batch_persistent<double>(probs, big, Js, prec, dt, n_steps, init, graph, half, st);
-        }
+        std::vector<int> all(n);
+        for (int p = 0; p < n; ++p) all[p] = p;
+        const bool graph = true;
+        const int rc = f32 ? batch_persistent<float>(probs, all, Js, prec, dt, n_steps, init, graph, half, st)
+                           : batch_persistent<double>(probs, all, Js, prec, dt, n_steps, init, graph, half, st);
         if (rc == SPIN_OK) fail(SPIN_OK, "");
         return rc;
     } catch (const std::exception& e) {

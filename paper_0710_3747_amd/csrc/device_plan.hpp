@@ -51,7 +51,7 @@ constexpr int kMatFloats = 64 * 64;
 // For kOpMeas, aux = slot | kind << 6 | index << 8: the observed site's bit is
 // thread bit `index` (kind 0), register bit `index` (kind 1) or global address
 // bit `index` of the tile base (kind 2) at that point of the stage; slot is
-// the pass's measurement slot (one-workgroup kernels: unused).  In all-site
+// the pass's measurement slot (one-workgroup plans: unused).  In all-site
 // profile plans every site has its own kOpMeas and aux also holds
 // (norm slot + 1) << 14 | site << 17; norm slot + 1 = 0 when this observable
 // does not also carry the norm.
@@ -67,24 +67,29 @@ struct alignas(sizeof(T) == 4 ? 32 : 16) DevOp {
 // (thread bit q and register bit q of a lane hold one tile-local position
 // each), the stage's ops run on registers, and the registers are scattered
 // back.  Ops that exchange a register bit with lane bit 4 or 5 leave other
-// positions there: gw/gr and gt_in/gr_in describe the stage's entry,
-// gt_out/gr_out its exit.  tmask/rbit are the layout of passes that keep one
-// layout for all stages and of the one-workgroup kernel (bits xor-ed).
+// positions there: gt_in/gr_in describe the stage's entry, gt_out/gr_out its
+// exit.  tmask/rbit are the layout of passes that keep one layout for all
+// stages (bits xor-ed).
 struct DevStage {
     int32_t op0, nop;         // op range
     int32_t xnext;            // 1: the exchange after this stage moves amplitudes between
-                              // waves (workgroup barrier); 0: within each wave only
+                              // waves (workgroup barrier); 0: within each wave only;
+                              // kNoExchange (one-workgroup plans): there is none
     int32_t pad_;
     uint32_t tmask[16];       // LDS byte offset of thread bit q (zero past the last)
     uint32_t rbit[8];         // LDS byte offset of register bit q
-    // Exchanges through per-lane slots: LDS byte weight of thread bit q /
-    // register bit q at entry (see exchange_row_slots).
+    // Exchange through per-lane slots after this stage: LDS byte weight of
+    // thread bit q / register bit q of the next stage's entry (see
+    // exchange_row_slots).
     uint32_t gw[10], gr[6];
     // Global element offsets of thread bit q / register bit q, for the first
     // stage of a pass (loaded straight from HBM, input layout, entry) and the
-    // last (stored straight to HBM, output layout, exit).
+    // last (stored straight to HBM, output layout, exit).  One-workgroup plans:
+    // offsets in the state, where it is staged through LDS.
     int64_t gt_in[16], gr_in[8], gt_out[16], gr_out[8];
 };
+
+constexpr int32_t kNoExchange = 2;
 
 // One tiled pass over the whole state.
 struct DevPass {
@@ -125,18 +130,6 @@ SPIN_HD constexpr int exchange_slot(int tid, int elem_bytes) {
 SPIN_HD constexpr int exchange_row_slots(int nt, int elem_bytes) {
     const int n = 1 << exchange_pad_shift(elem_bytes);
     return (exchange_slot(nt - 1, elem_bytes) + n - 1) / n * n + 1;
-}
-
-// Fixed LDS swizzle of the one-workgroup kernel (tiled passes use a layout
-// searched per pass, see encode_pass): xor a band of higher local-index bits into the lowest bits
-// so that lanes striding by a power of two spread over the banks.  It is
-// linear over GF(2): swz(a ^ b) = swz(a) ^ swz(b).
-template <int ElemBytes>
-SPIN_HD inline uint32_t lds_swizzle(uint32_t l) {
-    // 8-byte elements: 32 per 256-byte bank row; 16-byte elements: 16.
-    constexpr uint32_t shift = ElemBytes == 8 ? 5 : 4;
-    constexpr uint32_t mask = ElemBytes == 8 ? 31 : 15;
-    return l ^ ((l >> shift) & mask);
 }
 
 }  // namespace spinqp

@@ -559,7 +559,7 @@ __device__ __forceinline__ ConstOp<T>* run_factors(C (&v)[1 << R], ConstOp<T>* o
 // registers are pinned: amplitude j of complex64 is v[spV + 2j] (re) and
 // v[spV + 2j + 1] (im), complex128 takes two registers each.
 //
-// Scalars: s[72:79] the op's parameters, s[80:89] the next record (loaded when
+// Scalars: s[72:79] the op's parameters, s[80:88] the next record (loaded when
 // the op starts, waited for before the jump), s[90:91] .Lspin_ops, s[92:93] the
 // jump's target, s[94:95] the record's address.  Handlers: op_xy does the
 // three shears of reg_xy, each over all pairs before the next (a dependent FMA
@@ -779,9 +779,10 @@ __device__ __forceinline__ ConstOp<T>* run_factors(C (&v)[1 << R], ConstOp<T>* o
     ".endm\n"                                                      \
     SPIN_ASM_RUN                                                   \
     "s_mov_b32 %[code], s88\n"
-#define SPIN_ASM_CLOBBERS                                                                               \
-    "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85",   \
-        "s86", "s87", "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95", "scc", "memory"
+#define SPIN_CLOBBERS_F32                                                                               \
+    "s72", "s73", "s74", "s75", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s90", "s91",   \
+        "s92", "s93", "s94", "s95", "scc", "memory"
+#define SPIN_CLOBBERS_F64 "s76", "s77", "s78", "s79", "s88", SPIN_CLOBBERS_F32
 
 typedef float v8f __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -802,62 +803,65 @@ __device__ __forceinline__ ConstOp<T>* run_ops(typename CT<T>::c (&v)[1 << R], C
     constexpr int N = W < 32 ? NV : 32 / int(sizeof(T) / 4);     // reals of one operand
     auto get = [&](int i) { return i & 1 ? v[i / 2].y : v[i / 2].x; };
     auto put = [&](int i, T x) { if (i & 1) v[i / 2].y = x; else v[i / 2].x = x; };
-    uint64_t p = reinterpret_cast<uint64_t>(op);
+    // uniform by construction; the compiler has to know it too
+    const uint64_t q = reinterpret_cast<uint64_t>(op);
+    uint64_t p = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(q >> 32))))) << 32) |
+                 uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(q))));
     T w0, u0, w1, u1;
-#define SPIN_RUN(TEXT, ...)                                                                      \
-    asm volatile(TEXT : __VA_ARGS__, [op] "+s"(p), [code] "=&s"(code), [w0] "=&v"(w0),           \
+#define SPIN_RUN(TYPE, ...)                                                                      \
+    asm volatile(SPIN_ASM_##TYPE : __VA_ARGS__, [op] "+s"(p), [code] "=&s"(code), [w0] "=&v"(w0),           \
                  [u0] "=&v"(u0), [w1] "=&v"(w1), [u1] "=&v"(u1)                                  \
                  : [r] "i"(R), [vb] "i"(VB), [sh] "i"(SH)                                        \
-                 : SPIN_ASM_CLOBBERS)
+                 : SPIN_CLOBBERS_##TYPE)
 #define SPIN_GET(X, B) _Pragma("unroll") for (int i = 0; i < N; ++i) X[i] = get((B) * N + i)
 #define SPIN_PUT(X, B) _Pragma("unroll") for (int i = 0; i < N; ++i) put((B) * N + i, X[i])
     if constexpr (sizeof(T) == 4) {
         if constexpr (W == 8) {
             v8f a;
             SPIN_GET(a, 0);
-            SPIN_RUN(SPIN_ASM_F32, "+{v[64:71]}"(a));
+            SPIN_RUN(F32, "+{v[64:71]}"(a));
             SPIN_PUT(a, 0);
         } else if constexpr (W == 16) {
             v16f a;
             SPIN_GET(a, 0);
-            SPIN_RUN(SPIN_ASM_F32, "+{v[64:79]}"(a));
+            SPIN_RUN(F32, "+{v[64:79]}"(a));
             SPIN_PUT(a, 0);
         } else if constexpr (W == 32) {
             v32f a;
             SPIN_GET(a, 0);
-            SPIN_RUN(SPIN_ASM_F32, "+{v[64:95]}"(a));
+            SPIN_RUN(F32, "+{v[64:95]}"(a));
             SPIN_PUT(a, 0);
         } else if constexpr (W == 64) {
             v32f a, b;
             SPIN_GET(a, 0); SPIN_GET(b, 1);
-            SPIN_RUN(SPIN_ASM_F32, "+{v[64:95]}"(a), "+{v[96:127]}"(b));
+            SPIN_RUN(F32, "+{v[64:95]}"(a), "+{v[96:127]}"(b));
             SPIN_PUT(a, 0); SPIN_PUT(b, 1);
         } else {
             v32f a, b, c, d;
             SPIN_GET(a, 0); SPIN_GET(b, 1); SPIN_GET(c, 2); SPIN_GET(d, 3);
-            SPIN_RUN(SPIN_ASM_F32, "+{v[128:159]}"(a), "+{v[160:191]}"(b), "+{v[192:223]}"(c), "+{v[224:255]}"(d));
+            SPIN_RUN(F32, "+{v[128:159]}"(a), "+{v[160:191]}"(b), "+{v[192:223]}"(c), "+{v[224:255]}"(d));
             SPIN_PUT(a, 0); SPIN_PUT(b, 1); SPIN_PUT(c, 2); SPIN_PUT(d, 3);
         }
     } else {
         if constexpr (W == 16) {
             v8d a;
             SPIN_GET(a, 0);
-            SPIN_RUN(SPIN_ASM_F64, "+{v[64:79]}"(a));
+            SPIN_RUN(F64, "+{v[64:79]}"(a));
             SPIN_PUT(a, 0);
         } else if constexpr (W == 32) {
             v16d a;
             SPIN_GET(a, 0);
-            SPIN_RUN(SPIN_ASM_F64, "+{v[64:95]}"(a));
+            SPIN_RUN(F64, "+{v[64:95]}"(a));
             SPIN_PUT(a, 0);
         } else if constexpr (W == 64) {
             v16d a, b;
             SPIN_GET(a, 0); SPIN_GET(b, 1);
-            SPIN_RUN(SPIN_ASM_F64, "+{v[64:95]}"(a), "+{v[96:127]}"(b));
+            SPIN_RUN(F64, "+{v[64:95]}"(a), "+{v[96:127]}"(b));
             SPIN_PUT(a, 0); SPIN_PUT(b, 1);
         } else {
             v16d a, b, c, d;
             SPIN_GET(a, 0); SPIN_GET(b, 1); SPIN_GET(c, 2); SPIN_GET(d, 3);
-            SPIN_RUN(SPIN_ASM_F64, "+{v[128:159]}"(a), "+{v[160:191]}"(b), "+{v[192:223]}"(c), "+{v[224:255]}"(d));
+            SPIN_RUN(F64, "+{v[128:159]}"(a), "+{v[160:191]}"(b), "+{v[192:223]}"(c), "+{v[224:255]}"(d));
             SPIN_PUT(a, 0); SPIN_PUT(b, 1); SPIN_PUT(c, 2); SPIN_PUT(d, 3);
         }
     }
@@ -865,6 +869,55 @@ __device__ __forceinline__ ConstOp<T>* run_ops(typename CT<T>::c (&v)[1 << R], C
 #undef SPIN_GET
 #undef SPIN_PUT
     return reinterpret_cast<ConstOp<T>*>(p);
+}
+
+// Weights of the exchange after a stage (see exchange_row_slots).
+template <int RW, int NTB>
+struct ExchangeWeights {
+    uint32_t gr[RW], gw[NTB];
+    int xnext;
+    __device__ __forceinline__ void load(const DevStage& S) {
+        xnext = S.xnext;
+#pragma unroll
+        for (int b = 0; b < RW; ++b) gr[b] = S.gr[b];
+#pragma unroll
+        for (int q = 0; q < NTB; ++q) gw[q] = S.gw[q];
+    }
+    // LDS byte address from which the lane gathers register 0.
+    __device__ __forceinline__ uint32_t base(int tid) const {
+        uint32_t a = 0;
+#pragma unroll
+        for (int q = 0; q < NTB; ++q) a += gw[q] & (0u - ((uint32_t(tid) >> q) & 1u));
+        return a;
+    }
+};
+
+// The exchange after a stage through per-lane slots (HALF: half 0 through the
+// LDS, then half 1 through the same slots).  When both stages keep the same
+// positions on the wave bits it moves amplitudes only within each wave and
+// only the wave is ordered.  A lane scatters to slots of its own; after an
+// exchange that crossed waves (prev_cross) other waves may still be gathering
+// from them.
+template <int R, int ROW, bool HALF, typename C, int RW, int NTB>
+__device__ __forceinline__ void exchange(C (&v)[1 << R], char* ldsb, char* own, const ExchangeWeights<RW, NTB>& x,
+                                         bool& prev_cross) {
+    const bool xw = x.xnext != 0;
+    auto sync = [&]() {
+        if (xw) lds_barrier();
+        else wave_lds_sync();
+    };
+    const uint32_t ga = x.base(threadIdx.x);
+    if (prev_cross) lds_barrier();
+    prev_cross = xw;
+    scatter_rows<RW, 0, ROW>(v, own);
+    sync();
+    gather_rows<RW, 0>(v, ldsb, ga, x.gr);
+    if constexpr (HALF) {
+        sync();
+        scatter_rows<RW, 1, ROW>(v, own);
+        sync();
+        gather_rows<RW, 1>(v, ldsb, ga, x.gr);
+    }
 }
 
 // ------------------------------------------------------- matrix engine
@@ -1243,6 +1296,9 @@ __device__ __forceinline__ void slot_tiles(typename CT<T>::c* __restrict__ psi, 
         hi = next_submask(hi, m_hi);
         for (int si = 0; si < nstage; ++si) {
             const DevStage& S = S0[si];
+            // read before the ops, which hide the loads' latency
+            ExchangeWeights<RW, NTB> xw;
+            xw.load(S);
             ConstOp<T>* op = const_ops<T>(ops + S.op0);
             while (true) {
                 int code;
@@ -1297,34 +1353,7 @@ __device__ __forceinline__ void slot_tiles(typename CT<T>::c* __restrict__ psi, 
                 }
             }
             if (si + 1 < nstage) {
-                // When both stages keep the same positions on the wave bits
-                // the exchange moves amplitudes only within each wave and
-                // only the wave is ordered.  A lane scatters to slots of its
-                // own; after an exchange that crossed waves (the last one of
-                // the tile before included) other waves may still be
-                // gathering from them.
-                const bool xw = S.xnext != 0;
-                auto sync = [&]() {
-                    if (xw) lds_barrier();
-                    else wave_lds_sync();
-                };
-                const DevStage& S2 = S0[si + 1];
-                uint32_t w[RW], ga = 0;
-#pragma unroll
-                for (int b = 0; b < RW; ++b) w[b] = S2.gr[b];
-#pragma unroll
-                for (int q = 0; q < NTB; ++q) ga += S2.gw[q] & (0u - ((uint32_t(tid) >> q) & 1u));
-                if (prev_cross) lds_barrier();
-                prev_cross = xw;
-                scatter_rows<RW, 0, ROW>(v, own);
-                sync();
-                gather_rows<RW, 0>(v, ldsb, ga, w);
-                if constexpr (HALF) {
-                    sync();
-                    scatter_rows<RW, 1, ROW>(v, own);
-                    sync();
-                    gather_rows<RW, 1>(v, ldsb, ga, w);
-                }
+                exchange<R, ROW, HALF>(v, ldsb, own, xw, prev_cross);
             }
         }
         if constexpr (WRITES)
@@ -1465,81 +1494,149 @@ __global__ __launch_bounds__(NT, (waves_per_eu<T, R, NT, X>())) void k_pass(type
 }
 
 // ------------------------------------------------------------ resident run
-// One workgroup owns one whole state (2^M <= NT << R amplitudes) in LDS and
-// runs the prologue stages once and the step stages n_steps times, writing
-// P[k], N[k] itself.
+// One workgroup owns one whole state in its registers (2^M <= NT << R; the
+// amplitudes past 2^M are zero and stay so) from the first step to the last
+// and exchanges it through per-lane slots between stages; LDS also stages it
+// between memory order and the registers.  A state this small is bound by the
+// serial chain of its ops, not by any rate: about 80 clocks of scalar work and
+// 2^R * 1.5 FMAs of 4 clocks per factor, 300 to 700 clocks per exchange, so 16
+// amplitudes per lane (one wave at M <= 10, one per SIMD at M = 12).
+// Observables: each wave's sums go to its row of a ring in LDS, written out
+// with a fixed-order sum over the waves every kResidentRing values (a single
+// wave writes its own).
+constexpr int kResidentRing = 8;
+
+template <int NW>
+struct ResidentRing {
+    double sum[kResidentRing][NW][2];
+    double* dstP[kResidentRing];
+    double* dstN[kResidentRing];
+};
+
+// Writes the first n entries of the ring (whole workgroup).
+template <int NW>
+__device__ __forceinline__ void flush_ring(const ResidentRing<NW>& ring, int n) {
+    __syncthreads();
+    if (int(threadIdx.x) < n) {
+        const int e = threadIdx.x;
+        double p = 0.0, q = 0.0;
+        for (int w = 0; w < NW; ++w) {
+            p += ring.sum[e][w][0];
+            q += ring.sum[e][w][1];
+        }
+        *ring.dstP[e] = p;
+        if (ring.dstN[e]) *ring.dstN[e] = q;
+    }
+    __syncthreads();
+}
+
 template <typename T, int R, int NT, bool PROFILE = false>
 __device__ __forceinline__ void resident_run(const ResidentJob& J, const DevStage* __restrict__ stages,
                                              const DevOp<T>* __restrict__ ops, int64_t n_steps,
-                                             typename CT<T>::c* lds, double* red) {
+                                             typename CT<T>::c* lds, ResidentRing<NT / 64>& ring) {
     using C = typename CT<T>::c;
-    constexpr int EB = sizeof(C);
+    constexpr int NTB = __builtin_ctz(NT), NW = NT / 64;
+    constexpr int EB = sizeof(C), ROW = exchange_row_slots(NT, EB) * EB;
     const int tid = threadIdx.x;
     const int M = J.M;
     const uint32_t dim = 1u << M;
-    const int nact = (M >= R) ? (1 << (M - R)) : 1;
     C* psi = reinterpret_cast<C*>(J.psi);
     char* ldsb = reinterpret_cast<char*>(lds);
-    if (J.init) {
-        const double scale = 1.0 / sqrt(ldexp(1.0, M - 1));
-        for (uint32_t x = tid; x < dim; x += NT) {
-            double re, im;
-            init_amp(x, M, J.init, J.polarized, J.seed, scale, &re, &im);
-            C c;
-            c.x = T(re);
-            c.y = T(im);
-            lds[lds_swizzle<EB>(x)] = c;
+    char* own = ldsb + exchange_slot(tid, EB) * EB;
+    // the state in memory order in LDS
+    const double scale = 1.0 / sqrt(ldexp(1.0, M - 1));
+    for (uint32_t x = tid; x < (uint32_t(NT) << R); x += NT) {
+        C c;
+        c.x = c.y = T(0);
+        if (x < dim) {
+            if (J.init) {
+                double re, im;
+                init_amp(x, M, J.init, J.polarized, J.seed, scale, &re, &im);
+                c.x = T(re);
+                c.y = T(im);
+            } else {
+                c = psi[x];
+            }
         }
-    } else {
-        for (uint32_t x = tid; x < dim; x += NT) lds[lds_swizzle<EB>(x)] = psi[x];
+        lds[x] = c;
     }
     __syncthreads();
-
-    auto run = [&](int st0, int nst, int64_t step) {
-        for (int si = st0; si < st0 + nst; ++si) {
-            const DevStage& S = stages[si];
-            // Lanes past the state's size shadow an active lane (same LDS
-            // slots) so that the op loop below stays free of divergence;
-            // they never scatter and contribute nothing to observables.
-            const bool act = tid < nact;
-            const uint32_t pb = stage_base<__builtin_ctz(NT)>(S, tid & (nact - 1));
-            C v[1 << R];
-            gather<R>(v, ldsb, pb, S);
+    // between memory order in LDS and an arrangement of the registers
+    C v[1 << R];
+    auto offset = [&](const int64_t* gt) { return uint32_t(lane_offset<NTB>(gt, tid)) * EB; };
+    const int first = n_steps > 0 ? J.pro_stage0 : J.obs_stage0;
+    {
+        uint32_t w[R];
+#pragma unroll
+        for (int b = 0; b < R; ++b) w[b] = uint32_t(stages[first].gr_in[b]) * EB;
+        gather_rows<R, 0>(v, ldsb, offset(stages[first].gt_in), w);
+    }
+    bool prev_cross = true;     // every wave gathers before the first scatter
+    int nring = 0;
+    int last_stage = first;
+    for (int64_t k = 0; k <= n_steps; ++k) {
+        const int st0 = k == 0 ? first : k < n_steps ? J.step_stage0 : J.last_stage0;
+        const int nst = k > 0 ? J.step_nstage : n_steps > 0 ? J.pro_nstage : 1;
+        for (int si = 0; si < nst; ++si) {
+            const DevStage& S = stages[st0 + si];
+            ExchangeWeights<R, NTB> xw;
+            xw.load(S);
             ConstOp<T>* op = const_ops<T>(ops + S.op0);
             while (true) {
                 int code;
-                op = run_factors<R>(v, op, code);
+                op = run_ops<R, T>(v, op, code);
                 if (code == kOpEnd) break;
-                // observable: reduce over the workgroup now
+                // observable of the state at this point
                 const int aux = op->aux;
                 double p, n;
                 site_observe<R>(v, aux, 0, p, n);
-                p = act ? p : 0.0;
-                n = act ? n : 0.0;
-                block_sum2<NT>(p, n, red);
-                if constexpr (PROFILE) {
-                    const int nslot = ((aux >> 14) & 7) - 1;
-                    if (tid == 0) {
-                        J.Pall[step * M + ((aux >> 17) & 63)] = p;
-                        if (nslot >= 0 && J.N) J.N[step] = n;
+                p = wave_sum_last(p);
+                n = wave_sum_last(n);
+                double* dstP = PROFILE ? J.Pall + k * M + ((aux >> 17) & 63) : J.P + k;
+                double* dstN = J.N && (!PROFILE || ((aux >> 14) & 7)) ? J.N + k : nullptr;
+                // sites past M belong to no site of the caller
+                const bool own_site = !PROFILE || ((aux >> 17) & 63) < M;
+                if constexpr (NW == 1) {
+                    if (tid == 63 && own_site) {
+                        *dstP = p;
+                        if (dstN) *dstN = n;
                     }
-                } else {
-                    if (tid == 0) {
-                        J.P[step] = p;
-                        if (J.N) J.N[step] = n;
+                } else if (own_site) {
+                    if ((tid & 63) == 63) {
+                        ring.sum[nring][tid / 64][0] = p;
+                        ring.sum[nring][tid / 64][1] = n;
+                        if (tid == 63) {
+                            ring.dstP[nring] = dstP;
+                            ring.dstN[nring] = dstN;
+                        }
+                    }
+                    if (++nring == kResidentRing) {
+                        flush_ring<NW>(ring, nring);
+                        nring = 0;
                     }
                 }
                 ++op;
             }
-            __syncthreads();    // every shadow lane has gathered
-            if (act) scatter<R>(v, ldsb, pb, S);
-            __syncthreads();
+            last_stage = st0 + si;
+            if (xw.xnext != kNoExchange && !(k == n_steps && si + 1 == nst))
+                exchange<R, ROW, false>(v, ldsb, own, xw, prev_cross);
         }
-    };
-    run(J.pro_stage0, J.pro_nstage, 0);
-    for (int64_t k = 1; k <= n_steps; ++k) run(J.step_stage0, J.step_nstage, k);
-
-    for (uint32_t x = tid; x < dim; x += NT) psi[x] = lds[lds_swizzle<EB>(x)];
+    }
+    if (NW > 1 && nring > 0) flush_ring<NW>(ring, nring);
+    __syncthreads();            // every wave has gathered
+    {
+        uint32_t a = offset(stages[last_stage].gt_out);
+        *reinterpret_cast<C*>(ldsb + a) = v[0];
+#pragma unroll
+        for (int i = 1; i < (1 << R); ++i) {
+            const int b = __builtin_ctz(i), j = i ^ (i >> 1);
+            const uint32_t w = uint32_t(stages[last_stage].gr_out[b]) * EB;
+            a = (j >> b) & 1 ? a + w : a - w;
+            *reinterpret_cast<C*>(ldsb + a) = v[j];
+        }
+    }
+    __syncthreads();
+    for (uint32_t x = tid; x < dim; x += NT) psi[x] = lds[x];
     __syncthreads();
 }
 
@@ -1550,10 +1647,13 @@ __global__ __launch_bounds__(NT) void k_resident(ResidentJob job0,
                                                  const DevOp<T>* __restrict__ ops,
                                                  int64_t n_steps) {
     using C = typename CT<T>::c;
-    __shared__ C lds[NT << R];
-    __shared__ double red[2 * ((NT + 63) / 64)];
-    const ResidentJob J = jobs ? jobs[blockIdx.x] : job0;
-    resident_run<T, R, NT, PROFILE>(J, stages, ops, n_steps, lds, red);
+    __shared__ C lds[exchange_row_slots(NT, sizeof(C)) << R];
+    __shared__ ResidentRing<NT / 64> ring;
+    ResidentJob J = jobs ? jobs[blockIdx.x] : job0;
+    for (int32_t* f : {&J.M, &J.init, &J.obs_stage0, &J.pro_stage0, &J.pro_nstage, &J.step_stage0, &J.step_nstage,
+                       &J.last_stage0})
+        *f = __builtin_amdgcn_readfirstlane(*f);
+    resident_run<T, R, NT, PROFILE>(J, stages, ops, n_steps, lds, ring);
 }
 
 // ---------------------------------------------------------------- k_batch
@@ -1608,11 +1708,12 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                                               int64_t n_steps) {
     using C = typename CT<T>::c;
     constexpr int K = R + __builtin_ctz(NT);
-    constexpr int KL = HALF ? K - 1 : K;    // largest problem held in LDS
+    constexpr int KL = K - 1;               // largest one-workgroup problem
     constexpr int NW = NT / 64;
     __shared__ C lds[exchange_slots<T, R, NT, HALF ? kHalfTiles : kWholeTiles>()];
     __shared__ double red[2 * NW];
     __shared__ double wacc[HALF ? NW : 1][2 * kMaxMeas];
+    __shared__ ResidentRing<NW> ring;
     const int tid = threadIdx.x;
     const int wave = tid / 64;
     for (int jb = job_start[blockIdx.x]; jb < job_start[blockIdx.x + 1]; ++jb) {
@@ -1628,11 +1729,19 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
             J.M = B.M;
             J.polarized = B.polarized;
             J.init = B.init;
+            J.obs_stage0 = B.obs_stage0;
             J.pro_stage0 = B.pro_stage0;
             J.pro_nstage = B.pro_nstage;
             J.step_stage0 = B.step_stage0;
             J.step_nstage = B.step_nstage;
-            resident_run<T, R, NT>(J, stages, ops, n_steps, lds, red);
+            J.last_stage0 = B.last_stage0;
+            // 16 amplitudes per lane, 32 (complex64) for the largest
+            if constexpr (NT == 256) {
+                if (B.M <= 12) resident_run<T, 4, NT>(J, stages, ops, n_steps, lds, ring);
+                else if constexpr (sizeof(T) == 4) resident_run<T, 5, NT>(J, stages, ops, n_steps, lds, ring);
+            } else {
+                resident_run<T, 4, NT>(J, stages, ops, n_steps, lds, ring);
+            }
             continue;
         }
         // gang member `rank` of `gsize`
@@ -1991,18 +2100,16 @@ static hipError_t res_one(const ResidentJob& job0, const ResidentJob* jobs, int 
 }
 
 template <typename T>
-hipError_t launch_resident(int r, int nt, const ResidentJob& job0, const ResidentJob* jobs,
+hipError_t launch_resident(int bits, const ResidentJob& job0, const ResidentJob* jobs,
                            int njobs, const DevStage* stages, const DevOp<T>* ops,
                            int64_t n_steps, hipStream_t st) {
-#define SPIN_RES(RR, NTT)                                                              \
-    if (r == RR && nt == NTT)                                                          \
-        return res_one<T, RR, NTT>(job0, jobs, njobs, stages, ops, n_steps, st);
-    SPIN_RES(1, 64) SPIN_RES(2, 64) SPIN_RES(3, 64) SPIN_RES(4, 64) SPIN_RES(5, 64)
-    SPIN_RES(4, 256) SPIN_RES(5, 256)
+#define SPIN_RES(BITS)                                                                             \
+    if (bits == BITS)                                                                              \
+        return res_one<T, kResidentRegs, 1 << (BITS - kResidentRegs)>(job0, jobs, njobs, stages,   \
+                                                                     ops, n_steps, st);
+    SPIN_RES(10) SPIN_RES(11) SPIN_RES(12) SPIN_RES(13)
     if constexpr (sizeof(T) == 4) {
-        SPIN_RES(5, 512)
-    } else {
-        SPIN_RES(4, 512)
+        SPIN_RES(14)
     }
 #undef SPIN_RES
     return hipErrorInvalidValue;
@@ -2048,7 +2155,7 @@ hipError_t launch_batch(int nslots, bool half, const BatchProblem* probs, const 
     template hipError_t NAME<T>(const PassShape&, void*, const DevPass*, const DevStage*, const DevOp<T>*, \
                                 int, int64_t, int, double*, int64_t, int, hipStream_t);
 #define SPIN_INST_RESIDENT(T)                                                                             \
-    template hipError_t launch_resident<T>(int, int, const ResidentJob&, const ResidentJob*, int,         \
+    template hipError_t launch_resident<T>(int, const ResidentJob&, const ResidentJob*, int,              \
                                            const DevStage*, const DevOp<T>*, int64_t, hipStream_t);
 #define SPIN_INST_BATCH(T)                                                                                \
     template int batch_occupancy<T>(bool);                                                                \

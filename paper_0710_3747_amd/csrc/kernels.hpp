@@ -16,7 +16,9 @@ struct ResidentJob {
     double* Pall;     // all-site profile [step][M] (profile launches only)
     uint64_t seed;
     int32_t M, polarized, init;
-    int32_t pro_stage0, pro_nstage, step_stage0, step_nstage;
+    // stage ranges: the step-0 observable alone, the prologue, the step and
+    // the last step (step_nstage stages too)
+    int32_t obs_stage0, pro_stage0, pro_nstage, step_stage0, step_nstage, last_stage0;
     int32_t pad_;
 };
 
@@ -27,8 +29,8 @@ struct BatchProblem {
     double* N;
     uint64_t seed;
     int32_t M, polarized, init, gsize;   // gsize 1 with M <= tile bits: held in LDS
-    // held in LDS: stage ranges of the prologue and of one step
-    int32_t pro_stage0, pro_nstage, step_stage0, step_nstage;
+    // one workgroup's: stage ranges as ResidentJob
+    int32_t obs_stage0, pro_stage0, pro_nstage, step_stage0, step_nstage, last_stage0;
     // gang: pass templates, launch list (template, step offset), tiles
     int32_t pass0, nlaunch;
     int64_t launch0, ntiles, part0;
@@ -108,9 +110,17 @@ BatchShape batch_shape(bool f32, bool half);
 // Workgroups of the batch kernel that fit one CU at once (0 on error).
 int batch_blocks_per_cu(bool f32, bool half);
 
+// Register and thread bits of the one-workgroup kernel for a state of M
+// sites (at least M together; 2^kResidentRegs amplitudes per lane).
+constexpr int kResidentRegs = 4;
+inline int resident_bits(int M) { return M < 10 ? 10 : M; }
+// Largest state of one workgroup.
+inline int resident_max(bool f32) { return f32 ? 14 : 13; }
 template <typename T>
-hipError_t launch_resident(int r, int nt, const ResidentJob& job0, const ResidentJob* jobs,
+hipError_t launch_resident(int bits, const ResidentJob& job0, const ResidentJob* jobs,
                            int njobs, const DevStage* stages, const DevOp<T>* ops,
                            int64_t n_steps, hipStream_t st);
-
+// Register and thread bits of a one-workgroup problem inside the batch kernel
+// (256 lanes with half tiles, else 512).
+inline int batch_resident_bits(int M, bool half) { return half && M <= 12 ? 12 : 13; }
 }  // namespace spinqp

@@ -1287,28 +1287,67 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
 }
 
 // --------------------------------------------------------------- resident
-ResidentPlan plan_resident(int M, const std::vector<Coupling>& J, double dt, int observed,
+ResidentPlan plan_resident(int k, const std::vector<Coupling>& J, double dt, int observed,
                            bool merge, int r, bool profile) {
     ResidentPlan rp;
-    rp.prologue.sites.resize(M);
-    rp.step.sites.resize(M);
-    for (int s = 0; s < M; ++s) rp.prologue.sites[s] = rp.step.sites[s] = s;
-    for (HostPass* hp : {&rp.prologue, &rp.step}) {
-        hp->bit_in = hp->bit_out = hp->sites;
-        hp->layout = hp->sites;
+    // ops of steps 1..6 of a run, by step: steps 2.. repeat when merging
+    // across the step boundary leaves every step the same ops
+    SeqBuilder sb(k, J, dt, observed, merge, profile);
+    sb.emit_observable(0);
+    constexpr int kSteps = 6;
+    for (int st = 1; st <= kSteps; ++st) sb.emit_step(st);
+    std::vector<std::vector<Op>> by(kSteps + 1);
+    for (const Op& op : sb.ops) by[op.step].push_back(op);
+    auto pair_of = [](const Op& a, const Op& b) { return a.kind == b.kind && a.i == b.i && a.j == b.j; };
+    auto same = [&](const Op& a, const Op& b) { return pair_of(a, b) && a.A == b.A && a.B == b.B; };
+    bool steady = by[kSteps].size() == by[2].size();
+    for (int st = 3; st < kSteps; ++st)
+        steady = steady && by[st].size() == by[2].size() &&
+                 std::equal(by[st].begin(), by[st].end(), by[2].begin(), same);
+    steady = steady && std::equal(by[kSteps].begin(), by[kSteps].end(), by[2].begin(), pair_of);
+    // step 1 is the repeating step plus the factors that later steps find
+    // merged already; those touch no site that an earlier op of step 1
+    // touched, so they come first
+    std::vector<Op> lead;
+    if (steady) {
+        size_t at = 0;
+        uint64_t touched = 0;
+        for (const Op& op : by[1]) {
+            if (at < by[2].size() && same(op, by[2][at])) {
+                ++at;
+                touched |= (uint64_t(1) << op.i) | (uint64_t(1) << op.j);
+            } else {
+                steady = steady && !(touched >> op.i & 1u) && !(touched >> op.j & 1u);
+                lead.push_back(op);
+            }
+        }
+        steady = steady && at == by[2].size();
     }
-    SeqBuilder sb0(M, J, dt, observed, merge, profile);
-    sb0.emit_observable(0);
-    rp.prologue.ops = sb0.ops;
-    rp.prologue.writes = false;
-    SeqBuilder sb(M, J, dt, observed, merge, profile);
-    sb.emit_step(1);
-    rp.step.ops = sb.ops;
-    rp.step.writes = true;
-    for (HostPass* hp : {&rp.prologue, &rp.step}) {
-        plan_stages(*hp, std::min(r, M));
-        for (HostStage& st : hp->stages) plan_exchanges(*hp, st, 0, -1);
+    rp.prologue.ops = by[0];
+    if (steady) {
+        rp.prologue.ops.insert(rp.prologue.ops.end(), lead.begin(), lead.end());
+        rp.bare = lead.empty();
+        rp.step.ops = by[2];
+        for (Op& op : rp.step.ops) op.step = 1;
+        rp.last.ops = by[kSteps];
+        for (Op& op : rp.last.ops) op.step = 1;
+    } else {
+        SeqBuilder one(k, J, dt, observed, merge, profile);
+        one.emit_step(1);
+        rp.step.ops = rp.last.ops = one.ops;
     }
+    for (HostPass* hp : {&rp.prologue, &rp.step}) {
+        hp->sites.resize(k);
+        for (int s = 0; s < k; ++s) hp->sites[s] = s;
+        hp->bit_in = hp->bit_out = hp->layout = hp->sites;
+        hp->slots = hp->in_registers = true;
+        const int ng = usable_gates(kMaxGates, k, r, 0);
+        plan_stages(*hp, r + ng, 0, 0, hp->ops.size() <= 128 ? 8 : 1);
+        for (HostStage& st : hp->stages) plan_exchanges(*hp, st, ng, -1);
+    }
+    const std::vector<Op> last = rp.last.ops;
+    rp.last = rp.step;
+    rp.last.ops = last;
     return rp;
 }
 
@@ -1444,7 +1483,7 @@ std::vector<uint32_t> wave_bits_plan(const HostPass& hp) {
     std::vector<uint32_t> w(nst, 0);
     if (nst == 0) return w;
     const int nw = k - int(hp.stages[0].regs.size()) - 6;
-    if (nw <= 0 || nst == 1) return w;
+    if (nw <= 0 || (nst == 1 && !hp.in_registers)) return w;
     const uint32_t all = (1u << k) - 1;
     std::vector<uint32_t> forbid(nst, 0);
     for (int si = 0; si < nst; ++si) {
@@ -1461,9 +1500,11 @@ std::vector<uint32_t> wave_bits_plan(const HostPass& hp) {
         for (int q = 0; q < nl && q < int(tp.size()); ++q) m |= 1u << tp[q];
         return m;
     };
-    const uint32_t lo_first = low_lanes(0, hp.bit_in), lo_last = low_lanes(nst - 1, hp.bit_out);
-    forbid[0] |= lo_first;
-    forbid[nst - 1] |= lo_last;
+    if (!hp.in_registers) {
+        const uint32_t lo_first = low_lanes(0, hp.bit_in), lo_last = low_lanes(nst - 1, hp.bit_out);
+        forbid[0] |= lo_first;
+        forbid[nst - 1] |= lo_last;
+    }
     // maximal runs
     std::vector<std::pair<int, int>> runs;
     std::vector<uint32_t> avail;
@@ -1581,16 +1622,19 @@ HostStage reorder_stage(const HostStage& st, const std::vector<int>& perm, bool 
 // Orders the register bits, gates and lanes of half-tile stages so that the
 // next stage's gather is free of bank conflicts: the LDS slots of the 16
 // lanes 0..15 must differ modulo the bank row.  `lanes` (positions on the
-// lane bits below the gates) of the first and last stage keep their order.
+// lane bits below the gates) of the first and last stage keep their order
+// unless free_ends.  next: the lanes the last stage exchanges into, if any.
 void order_for_gathers(std::vector<HostStage>& stages, std::vector<std::vector<int>>& lanes,
-                       const std::vector<std::vector<int>>& waves, int eb, int nt, bool half) {
+                       const std::vector<std::vector<int>>& waves, int eb, int nt, bool half, bool free_ends,
+                       const std::vector<int>* next) {
     const int nst = int(stages.size());
     const int mod = 1 << exchange_pad_shift(eb);
     const int row = exchange_row_slots(nt, eb);
-    for (int si = 0; si + 1 < nst; ++si) {
+    for (int si = 0; si < nst; ++si) {
+        if (si + 1 == nst && !next) break;
         // register bits with a slot weight (all but the split position's)
         const int rr = int(stages[si].regs.size()) - (half ? 1 : 0), ng = int(stages[si].gates.size());
-        const std::vector<int>& nl = lanes[si + 1];
+        const std::vector<int> nl = si + 1 < nst ? lanes[si + 1] : *next;
         const int n = std::min<int>(4, int(nl.size()));
         // residues of the next stage's lanes under an ordering; number of
         // lanes whose slot residue repeats
@@ -1612,7 +1656,7 @@ void order_for_gathers(std::vector<HostStage>& stages, std::vector<std::vector<i
             }
             return bad;
         };
-        const bool lanes_free = si > 0;
+        const bool lanes_free = si > 0 || free_ends;
         std::vector<int> perm(rr), lp(lanes[si].size());
         for (size_t q = 0; q < perm.size(); ++q) perm[q] = int(q);
         HostStage best = stages[si];
@@ -1642,8 +1686,8 @@ void order_for_gathers(std::vector<HostStage>& stages, std::vector<std::vector<i
 }  // namespace
 
 template <typename T>
-void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, bool fixed_swizzle,
-                 int engine, bool profile) {
+void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, int engine, bool profile,
+                 const Chain* chain) {
     const int k = int(hp.sites.size());
     std::vector<HostStage> stages = hp.stages;
     constexpr int eb = sizeof(T) * 2;
@@ -1685,8 +1729,7 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
     if (hp.stages.size() == 1 && hp.bit_in != hp.bit_out)
         throw std::runtime_error("encode: one-stage pass that moves amplitudes");
     const int nst = int(hp.stages.size());
-    std::vector<uint32_t> wmask(nst, 0);
-    if (!fixed_swizzle) wmask = wave_bits_plan(hp);
+    const std::vector<uint32_t> wmask = wave_bits_plan(hp);
     std::vector<std::vector<int>> tpos_all, lanes_all, waves_all;
     for (int si = 0; si < nst; ++si) {
         uint32_t rmask = 0;
@@ -1695,13 +1738,13 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
         std::vector<int> tp, wv;
         for (int p = 0; p < k; ++p)
             if (!(rmask & (1u << p))) ((wmask[si] >> p) & 1u ? wv : tp).push_back(p);
-        if (si + 1 == nst && si > 0)
+        if (si + 1 == nst && si > 0 && !hp.in_registers)
             std::stable_sort(tp.begin(), tp.end(),
                              [&](int a, int b) { return hp.bit_out[a] < hp.bit_out[b]; });
         // a one-stage pass has no wave plan: its positions above the lanes are
         // the wave bits, so that the gates come right above the lanes too
         const size_t nl = 6 - stages[si].gates.size();
-        if (nst == 1 && !stages[si].gates.empty() && tp.size() > nl) {
+        if (wv.empty() && !stages[si].gates.empty() && tp.size() > nl) {
             wv.assign(tp.begin() + int(nl), tp.end());
             tp.resize(nl);
         }
@@ -1716,12 +1759,15 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
         for (const HostStage& st : stages)
             if (st.regs.empty() || st.regs.back() != hp.split)
                 throw std::runtime_error("encode: split position not on the top register bit");
+    const int lanes_below = 6 - int(stages[0].gates.size());
     if (hp.slots) {
-        order_for_gathers(stages, lanes_all, waves_all, eb, 1 << (k - int(stages[0].regs.size())), hp.split >= 0);
+        std::vector<int> nl;
+        if (chain && chain->cyclic) nl = lanes_all[0];
+        else if (chain && chain->next) nl.assign(chain->next->tq.begin(), chain->next->tq.begin() + lanes_below);
+        order_for_gathers(stages, lanes_all, waves_all, eb, 1 << (k - int(stages[0].regs.size())), hp.split >= 0,
+                          hp.in_registers, nl.empty() ? nullptr : &nl);
     }
-    if (fixed_swizzle) {
-        for (int p = 0; p < k; ++p) img[p] = lds_swizzle<eb>(1u << p);
-    } else if (hp.split >= 0 && !gated) {
+    if (hp.split >= 0 && !gated) {
         // without register/lane exchanges a half-tile pass also has a layout
         // shared by all its stages, over the other k - 1 positions
         auto comp = [&](int p) { return p < hp.split ? p : p - 1; };
@@ -1744,6 +1790,14 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
         tp.insert(tp.end(), waves_all[si].begin(), waves_all[si].end());
         tpos_all.push_back(tp);
     }
+    if (chain && chain->fixed) {
+        if (nst != 1 || !stages[0].gates_out.empty() != !stages[0].gates.empty() || stages[0].regs != stages[0].regs_out)
+            throw std::runtime_error("encode: fixed arrangement of a pass that moves amplitudes");
+        tpos_all[0] = chain->fixed->tq;
+        waves_all[0] = chain->fixed->waves;
+        stages[0].regs = stages[0].regs_out = chain->fixed->rq;
+    }
+    if (chain && chain->entry) *chain->entry = StageEntry{tpos_all[0], stages[0].regs, waves_all[0]};
     // The exchange after stage si crosses waves (workgroup barrier) when the
     // wave positions change.  A wave's stores of a tile may overlap another
     // wave's loads of it unless both keep the same wave positions on the
@@ -1756,27 +1810,37 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
     std::vector<int> xnext(std::max(nst - 1, 0), 0);
     bool any_cross = false;
     for (int si = 0; si + 1 < nst; ++si) {
-        xnext[si] = (fixed_swizzle || wmask[si] != wmask[si + 1]) ? 1 : 0;
+        xnext[si] = wmask[si] != wmask[si + 1] ? 1 : 0;
         any_cross |= xnext[si] != 0;
     }
-    if (nst > 1) {
+    if (nst > 1 && !hp.in_registers) {
         bool keep_bits = true;
         for (int p = 0; p < k; ++p)
             if ((wmask[0] >> p) & 1u) keep_bits &= hp.bit_in[p] == hp.bit_out[p];
         if (!any_cross && !(wmask[0] == wmask[nst - 1] && keep_bits)) xnext[0] = 1;
-        dp.tile_barrier = (fixed_swizzle || wmask[0] != wmask[nst - 1]) ? 1 : 0;
+        dp.tile_barrier = wmask[0] != wmask[nst - 1] ? 1 : 0;
     }
     auto byte_off = [&](uint32_t l) { return apply_layout(img, l) * uint32_t(eb); };
 
     int nmeas = 0;
-    std::vector<int> prev_w(k, 0);     // slot weight of every position, exchange before
     for (size_t si = 0; si < stages.size(); ++si) {
         const HostStage& hs = stages[si];
         DevStage ds{};
         ds.op0 = int(out.ops.size());
         const int rr = int(hs.regs.size()), ng = int(hs.gates.size()), ntb = k - rr;
         const int lane0 = 6 - ng;      // lane bit of gate 0
-        ds.xnext = (int(si) + 1 < nst) ? xnext[si] : 1;
+        // what the stage exchanges into, if anything
+        const bool inner = int(si) + 1 < nst;
+        const bool onward = inner || (chain && (chain->cyclic || chain->next) && !chain->fixed);
+        const StageEntry into = inner ? StageEntry{tpos_all[si + 1], stages[si + 1].regs, waves_all[si + 1]}
+                                : chain && chain->cyclic ? StageEntry{tpos_all[0], stages[0].regs, waves_all[0]}
+                                : chain && chain->next   ? *chain->next
+                                                         : StageEntry{};
+        ds.xnext = inner ? xnext[si] : onward ? (into.waves != waves_all[si] ? 1 : 0) : 1;
+        // nothing moves into a pass that starts as this stage ends
+        if (!inner && chain && (chain->fixed || (chain->cyclic && nst == 1 && stages[si].regs == stages[si].regs_out &&
+                                                 stages[si].gates == stages[si].gates_out)))
+            ds.xnext = kNoExchange;
         // what the lane and register bits hold now (exchanges change it)
         std::vector<int> tq = tpos_all[si], rq = hs.regs;
         for (int q = 0; q < ntb; ++q) {
@@ -1786,11 +1850,6 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
         for (int b = 0; b < rr; ++b) {
             ds.rbit[b] = byte_off(1u << rq[b]);
             ds.gr_in[b] = int64_t(1) << hp.bit_in[rq[b]];
-        }
-        const int rw = rr - (hp.split >= 0 ? 1 : 0);     // register bits with a slot weight
-        if (hp.slots && si > 0) {
-            for (int q = 0; q < ntb; ++q) ds.gw[q] = uint32_t(prev_w[tq[q]] * eb);
-            for (int b = 0; b < rw; ++b) ds.gr[b] = uint32_t(prev_w[rq[b]] * eb);
         }
         auto regbit = [&](int p) {
             for (int b = 0; b < rr; ++b)
@@ -1894,16 +1953,65 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, boo
         if (rq != hs.regs_out) throw std::runtime_error("encode: stage exit differs from its plan");
         for (int q = 0; q < ntb; ++q) ds.gt_out[q] = int64_t(1) << hp.bit_out[tq[q]];
         for (int b = 0; b < rr; ++b) ds.gr_out[b] = int64_t(1) << hp.bit_out[rq[b]];
-        for (int q = 0; q < ntb; ++q) prev_w[tq[q]] = exchange_slot(1 << q, eb);
-        for (int b = 0; b < rw; ++b) prev_w[rq[b]] = exchange_row_slots(1 << ntb, eb) << b;
+        if (hp.slots && onward) {
+            std::vector<int> w(k, 0);     // slot weight of every position at exit
+            const int rw = rr - (hp.split >= 0 ? 1 : 0);
+            for (int q = 0; q < ntb; ++q) w[tq[q]] = exchange_slot(1 << q, eb);
+            for (int b = 0; b < rw; ++b) w[rq[b]] = exchange_row_slots(1 << ntb, eb) << b;
+            for (int q = 0; q < ntb; ++q) ds.gw[q] = uint32_t(w[into.tq[q]] * eb);
+            for (int b = 0; b < rw; ++b) ds.gr[b] = uint32_t(w[into.rq[b]] * eb);
+        }
         out.stages.push_back(ds);
     }
     dp.nmeas = nmeas;
     out.passes.push_back(dp);
 }
 
-template void encode_pass<float>(const HostPass&, int, int, DevTables<float>&, bool, int, bool);
-template void encode_pass<double>(const HostPass&, int, int, DevTables<double>&, bool, int, bool);
+template <typename T>
+ResidentStages encode_resident(const ResidentPlan& rp, int k, int observed, DevTables<T>& out, bool profile) {
+    ResidentStages rs;
+    auto encode = [&](const HostPass& hp, const Chain& chain, int* first, int* count) {
+        *first = int(out.stages.size());
+        encode_pass<T>(hp, k, observed, out, 0, profile, &chain);
+        *count = int(out.stages.size()) - *first;
+    };
+    int n = 0;
+    StageEntry step;
+    Chain cyc;
+    cyc.cyclic = true;
+    cyc.entry = &step;
+    encode(rp.step, cyc, &rs.step0, &rs.nstep);
+    encode(rp.last, cyc, &rs.last0, &n);
+    // the step-0 observable alone, in the step's entry arrangement
+    HostPass obs = rp.prologue;
+    obs.ops.clear();
+    for (const Op& op : rp.prologue.ops)
+        if (op.kind == 1) obs.ops.push_back(op);
+    HostStage st;
+    st.regs = st.regs_out = step.rq;
+    for (size_t i = 0; i < obs.ops.size(); ++i) {
+        st.ops.push_back(int(i));
+        st.prog.push_back(StageItem{int(i), 0, 0});
+    }
+    obs.stages = {st};
+    Chain keep;
+    keep.fixed = &step;
+    encode(obs, keep, &rs.obs0, &n);
+    if (rp.bare) {
+        rs.pro0 = rs.obs0;
+        rs.npro = 1;
+    } else {
+        Chain to_step;
+        to_step.next = &step;
+        encode(rp.prologue, to_step, &rs.pro0, &rs.npro);
+    }
+    return rs;
+}
+
+template void encode_pass<float>(const HostPass&, int, int, DevTables<float>&, int, bool, const Chain*);
+template void encode_pass<double>(const HostPass&, int, int, DevTables<double>&, int, bool, const Chain*);
+template ResidentStages encode_resident<float>(const ResidentPlan&, int, int, DevTables<float>&, bool);
+template ResidentStages encode_resident<double>(const ResidentPlan&, int, int, DevTables<double>&, bool);
 
 std::string describe_plan(const StreamPlan& plan) {
     std::ostringstream os;

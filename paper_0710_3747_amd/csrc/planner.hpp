@@ -82,6 +82,7 @@ struct HostPass {
     std::vector<HostStage> stages;
     bool writes = true;
     bool slots = false;        // exchanges use per-lane slots (see exchange_row_slots)
+    bool in_registers = false; // neither loaded from nor stored to HBM by its stages
 };
 
 struct PassParams {
@@ -166,15 +167,18 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
                             int observed, bool merge, const PassParams& pp,
                             const PlanCostModel& cm = PlanCostModel());
 
-// Plan for a state that fits one workgroup: stages over all M sites for the
-// prologue (observable of step 0) and for one periodic step (factors, then
-// the observable).  No merging across step boundaries, so every step is
-// identical.
+// Plan for a state that fits one workgroup (k register and thread bits in
+// all, sites M..k-1 are uncoupled and never up): the prologue (the observable
+// of step 0 and the factors that every later step finds merged into the step
+// before), the step, and the last step, whose stages are the step's with the
+// strengths of ops that no further step follows.
 struct ResidentPlan {
     HostPass prologue;
     HostPass step;
+    HostPass last;
+    bool bare = true;          // the prologue holds observables only
 };
-ResidentPlan plan_resident(int M, const std::vector<Coupling>& J, double dt, int observed,
+ResidentPlan plan_resident(int k, const std::vector<Coupling>& J, double dt, int observed,
                            bool merge, int r, bool profile = false);
 
 // Encoded device tables.
@@ -186,14 +190,36 @@ struct DevTables {
     std::vector<float> mats;           // matrix engine: kMatFloats per kOpMat
 };
 
-// Encodes one pass (or the stages of a one-workgroup plan) into the device
-// tables.  fixed_swizzle: use the one-workgroup kernel's fixed LDS swizzle
-// instead of a layout searched for this pass.  engine 1: the factors of each
+// Entry arrangement of a stage: thread bit -> position, register bit ->
+// position, positions on the wave bits.
+struct StageEntry {
+    std::vector<int> tq, rq, waves;
+};
+// Passes that follow each other with the state kept in registers: what the
+// last stage exchanges into (`next`, or the pass itself when cyclic), the
+// arrangement a one-stage pass must use (`fixed`; it then keeps it and
+// exchanges nothing), and the pass's own entry on return.
+struct Chain {
+    bool cyclic = false;
+    const StageEntry* next = nullptr;
+    const StageEntry* fixed = nullptr;
+    StageEntry* entry = nullptr;
+};
+
+// Encodes one pass into the device tables.  engine 1: the factors of each
 // stage (between observables) become one kOpMat (needs 5 register bits).
 // profile: observables of every site, each with its own slot (see kOpMeas).
 template <typename T>
-void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out,
-                 bool fixed_swizzle = false, int engine = 0, bool profile = false);
+void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, int engine = 0,
+                 bool profile = false, const Chain* chain = nullptr);
+
+// Encodes a one-workgroup plan; stage ranges in the tables.
+struct ResidentStages {
+    int obs0 = 0;                       // the step-0 observable alone (no steps)
+    int pro0 = 0, npro = 0, step0 = 0, nstep = 0, last0 = 0;
+};
+template <typename T>
+ResidentStages encode_resident(const ResidentPlan& rp, int k, int observed, DevTables<T>& out, bool profile);
 
 std::string describe_plan(const StreamPlan& plan);
 

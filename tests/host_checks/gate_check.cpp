@@ -2,7 +2,8 @@
 // register/lane exchanges inside their stages (test program; links the
 // planner).
 //
-// Reads "M prec k r c n_steps observed half" (half 0: whole small tiles) and then K lines "i j a b" on stdin,
+// Reads "M prec k r c n_steps observed half" (half 0: whole small tiles, half 2:
+// the one-workgroup plan on k bits, run for n_steps steps) and then K lines "i j a b" on stdin,
 // plans the call as the library does (two gates), encodes every pass and
 // emulates the kernel on one tile, with every lane's registers holding the
 // tile-local index of their amplitude:
@@ -144,7 +145,6 @@ static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int
             ++exchanges;
             cross += S.xnext != 0;
             any_cross |= S.xnext != 0;
-            const DevStage& S2 = tb.stages[P.stage0 + si + 1];
             std::vector<std::vector<uint32_t>> w(nt, std::vector<uint32_t>(nr));
             const int rw = half ? r - 1 : r;
             const uint32_t nh = 1u << rw;
@@ -163,9 +163,9 @@ static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int
                     for (uint32_t i = 0; i < nh; ++i) {
                         uint64_t a = 0;
                         for (int q = 0; q < k - r; ++q)
-                            if (t >> q & 1) a += S2.gw[q];
+                            if (t >> q & 1) a += S.gw[q];
                         for (int b = 0; b < rw; ++b)
-                            if (i >> b & 1) a += S2.gr[b];
+                            if (i >> b & 1) a += S.gr[b];
                         const size_t s = a / EB;
                         if (a % EB || s >= slot.size() || slot[s] < 0) {
                             fail("gather slot out of range or empty");
@@ -181,7 +181,7 @@ static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int
             for (uint32_t t = 0; t < 16; ++t) {
                 uint64_t a = 0;
                 for (int q = 0; q < 4; ++q)
-                    if (t >> q & 1) a += S2.gw[q];
+                    if (t >> q & 1) a += S.gw[q];
                 res.insert(uint32_t(a / EB % mod));
             }
             conflicts += 16.0 - double(res.size());
@@ -205,6 +205,112 @@ static int check(int M, const std::vector<Coupling>& J, int k, int r, int c, int
     return bad;
 }
 
+// One-workgroup plan: the stages run one after the other on one state held in
+// registers, with an exchange after each (between steps too).
+template <typename T>
+static int check_resident(const std::vector<Coupling>& J, int k, int r, int64_t steps, int observed) {
+    const ResidentPlan rp = plan_resident(k, J, 0.05, observed, true, r);
+    DevTables<T> tb;
+    const ResidentStages rs = encode_resident<T>(rp, k, observed, tb, false);
+    constexpr int EB = int(sizeof(T)) * 2;
+    const uint32_t nt = 1u << (k - r), nr = 1u << r;
+    const uint32_t row = uint32_t(exchange_row_slots(int(nt), EB));
+    int bad = 0;
+    long exchanges = 0, factors = 0, measured = 0;
+    auto fail = [&](const char* what) {
+        if (bad < 10) std::printf("%s\n", what);
+        ++bad;
+    };
+    auto index = [&](const int64_t* gt, const int64_t* gr, uint32_t t, uint32_t j) {
+        int64_t o = 0;
+        for (int q = 0; q < k - r; ++q)
+            if (t >> q & 1) o += gt[q];
+        for (int b = 0; b < r; ++b)
+            if (j >> b & 1) o += gr[b];
+        return uint32_t(o);
+    };
+    std::vector<std::vector<uint32_t>> v(nt, std::vector<uint32_t>(nr));
+    const int first = steps > 0 ? rs.pro0 : rs.obs0;
+    for (uint32_t t = 0; t < nt; ++t)
+        for (uint32_t j = 0; j < nr; ++j) v[t][j] = index(tb.stages[first].gt_in, tb.stages[first].gr_in, t, j);
+    const DevStage* lastS = nullptr;
+    for (int64_t step = 0; step <= steps; ++step) {
+        const int st0 = step == 0 ? first : step < steps ? rs.step0 : rs.last0;
+        const int nst = step > 0 ? rs.nstep : steps > 0 ? rs.npro : 1;
+        for (int si = 0; si < nst; ++si) {
+            const DevStage& S = tb.stages[st0 + si];
+            lastS = &S;
+            for (int o = S.op0; o < S.op0 + S.nop; ++o) {
+                const DevOp<T>& op = tb.ops[o];
+                if (op.code == kOpMeas) {
+                    ++measured;
+                    const int kind = (op.aux >> 6) & 3, idx = (op.aux >> 8) & 63;
+                    for (uint32_t t = 0; t < nt; ++t)
+                        if ((v[t][1] >> observed & 1) != (kind == 0 ? t >> idx & 1 : idx == 0)) {
+                            fail("observed site's bit");
+                            break;
+                        }
+                } else if (op.code >= op_gate(0, 0) && op.code < kOpEnd) {
+                    const uint32_t lane = 1u << (4 + (op.code - 16) % 2), reg = 1u << ((op.code - 16) / 2);
+                    for (uint32_t t = 0; t < nt; ++t)
+                        if (!(t & lane))
+                            for (uint32_t j = 0; j < nr; ++j)
+                                if (j & reg) std::swap(v[t][j], v[t | lane][j ^ reg]);
+                } else {
+                    ++factors;
+                }
+            }
+            if (step == steps && si + 1 == nst) break;
+            if (S.xnext == kNoExchange) continue;
+            ++exchanges;
+            std::vector<std::vector<uint32_t>> w(nt, std::vector<uint32_t>(nr));
+            std::vector<int64_t> slot(size_t(row) << r, -1), owner(slot.size(), -1);
+            for (uint32_t t = 0; t < nt; ++t)
+                for (uint32_t j = 0; j < nr; ++j) {
+                    const size_t s = size_t(j) * row + size_t(exchange_slot(int(t), EB));
+                    slot[s] = v[t][j];
+                    owner[s] = t / 64;
+                }
+            for (uint32_t t = 0; t < nt; ++t)
+                for (uint32_t j = 0; j < nr; ++j) {
+                    uint64_t a = 0;
+                    for (int q = 0; q < k - r; ++q)
+                        if (t >> q & 1) a += S.gw[q];
+                    for (int b = 0; b < r; ++b)
+                        if (j >> b & 1) a += S.gr[b];
+                    const size_t s = a / EB;
+                    if (a % EB || s >= slot.size() || slot[s] < 0) {
+                        fail("gather slot out of range or empty");
+                        continue;
+                    }
+                    if (!S.xnext && owner[s] != int64_t(t / 64)) fail("wave-local exchange reads another wave's slot");
+                    w[t][j] = uint32_t(slot[s]);
+                }
+            v.swap(w);
+            // the next stage's entry is where the exchange put everything
+            const int nx = si + 1 < nst ? st0 + si + 1 : step + 1 < steps ? rs.step0 : rs.last0;
+            const DevStage& N = tb.stages[nx];
+            for (uint32_t t = 0; t < nt; ++t)
+                for (uint32_t j = 0; j < nr; ++j)
+                    if (v[t][j] != index(N.gt_in, N.gr_in, t, j)) {
+                        fail("exchange does not give the next stage's entry");
+                        t = nt - 1;
+                        break;
+                    }
+        }
+    }
+    for (uint32_t t = 0; t < nt; ++t)
+        for (uint32_t j = 0; j < nr; ++j)
+            if (v[t][j] != index(lastS->gt_out, lastS->gr_out, t, j)) {
+                fail("an amplitude is stored at another index");
+                t = nt - 1;
+                break;
+            }
+    if (measured != steps + 1) fail("not one observable per step");
+    std::printf("resident exchanges %ld factors %ld failures %d\n", exchanges, factors, bad);
+    return bad;
+}
+
 int main() {
     int M, prec, k, r, c, observed, half;
     long long steps;
@@ -212,6 +318,9 @@ int main() {
     std::vector<Coupling> J;
     Coupling x;
     while (std::scanf("%d %d %lf %lf", &x.i, &x.j, &x.a, &x.b) == 4) J.push_back(x);
+    if (half == 2)
+        return (prec == 1 ? check_resident<float>(J, k, r, steps, observed)
+                          : check_resident<double>(J, k, r, steps, observed)) ? 1 : 0;
     const int bad = prec == 1 ? check<float>(M, J, k, r, c, steps, observed, half != 0)
                               : check<double>(M, J, k, r, c, steps, observed, half != 0);
     return bad ? 1 : 0;
