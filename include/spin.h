@@ -131,9 +131,12 @@ typedef struct {
                              (the plain, unfused schedule, kept as a cross-check) */
     int32_t tile_bits;    /* k of the 2^k-amplitude tiles; 0 = default (14 for
                              complex64, 13 for complex128, smaller for states that
-                             would leave CUs idle: 12 up to M = 20, 13 at M = 21;
-                             complex128 also takes 14, with half tiles and one
-                             workgroup per CU) */
+                             would leave CUs idle: 10 to 12 up to M = 20, 13 at
+                             M = 21; complex128 also takes 14, with half tiles and
+                             one workgroup per CU).  By default one workgroup holds
+                             states up to M = 13 (complex128 12, with I^z I^z parts
+                             11); with options, allocation-free calls and under
+                             stream capture up to M = 14 (complex128 13) */
     int32_t reg_bits;     /* amplitudes per lane = 2^reg_bits; 0 = default */
     int32_t coalesce_bits;/* low address bits every tile keeps; 0 = default (4) */
     int32_t engine;       /* 0 = VALU butterflies (default); 1 = each register stage's

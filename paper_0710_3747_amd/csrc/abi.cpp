@@ -168,11 +168,21 @@ static int upload_tables(const DevTables<T>& tb, DevicePlan* dp) {
     return SPIN_OK;
 }
 
+bool any_phase(const std::vector<Coupling>& J) {
+    for (const Coupling& c : J)
+        if (c.a != 0.0) return true;
+    return false;
+}
+
 // Launch shape: tile bits k = r + log2(nt).  Defaults: complex64 tiles of
 // 2^14 amplitudes, complex128 tiles of 2^13 (128 KiB either way), exchanged
 // through LDS in halves where a kernel exists (two workgroups per CU); states
-// too small to fill the CUs with them in smaller tiles, exchanged at once.
-Shape choose_shape(int prec, int M, const spin_options* opt) {
+// too small to fill the CUs with them in smaller tiles, exchanged at once, or
+// in one workgroup.  phases: some coupling has an I^z I^z part; one_launch:
+// the caller can take neither scratch memory nor a plan per number of steps
+// (allocation-free calls, a stream being captured), so every state that fits
+// one workgroup stays in it.
+Shape choose_shape(int prec, int M, const spin_options* opt, bool phases, bool one_launch) {
     Shape s;
     const bool f32 = prec == SPIN_C64;
     const int ex = opt ? opt->exchange : 0;
@@ -181,17 +191,26 @@ Shape choose_shape(int prec, int M, const spin_options* opt) {
     // hold fewer factors per pass, but a pass is shorter by more.  us per step
     // with tiles of 2^12 / 2^13 / 2^14: ladder M = 18 11.7 / 16 / 18.2, M = 20
     // 18 / 21 / 24, M = 22 34 / 31 / 31; star M = 17 89 / 116 / 139, M = 19 150 /
-    // 152 / 196, M = 21 308 / 267 / 279.  complex128, 2^12 / 2^13: ladder M = 18
-    // 17 / 22, M = 20 27 / 29; star M = 17 127 / 152, M = 19 208 / 214.
-    const int small = M <= 20 ? 12 : M == 21 && f32 ? 13 : 0;
-    const bool plain = ex == 0 && !(opt && (opt->engine || opt->reg_bits || opt->tile_bits));
+    // 152 / 196, M = 21 308 / 267 / 279; complex128, 2^12 / 2^13: ladder M = 18
+    // 17 / 22, M = 20 27 / 29; star M = 17 127 / 152, M = 19 208 / 214.  2^11 /
+    // 2^12: star M = 16 69 / 70, M = 17 98 / 89, chain M = 16 5.4 / 6.0.  Against
+    // one workgroup in registers: star M = 13 43 / 43, M = 14 50 / 74, complex128
+    // M = 12 44 / 37, M = 13 49 / 63.  I^z I^z phases take 2.7 times the
+    // arithmetic of a rotation, which moves the lines to smaller tiles: dipolar
+    // star 2^10 / 2^11 / 2^12, M = 12 45 / 53 / 50 (one workgroup), M = 14 62 /
+    // 70 / 85, M = 16 92 / 96 / 112.
+    const bool plain = ex == 0 && !one_launch && !(opt && (opt->engine || opt->reg_bits || opt->tile_bits ||
+                                                opt->coalesce_bits > 4));
+    const int one = (phases ? 11 : f32 ? 13 : 12);     // largest state of one workgroup
+    const int small = M <= one ? 0 : M <= 16 ? (phases ? 10 : 11) : M <= 18 && phases ? 11
+                    : M <= 20 ? 12 : M == 21 && f32 ? 13 : 0;
     int k = f32 ? 14 : 13;
     // complex128 tiles: 16 amplitudes per lane with half-tile exchanges
     // (two 256-lane workgroups per CU), 8 with whole tiles
     s.r = (f32 || ex != 1) ? 5 : 4;
     if (plain && small) {
         k = small;
-        s.r = 4;
+        s.r = std::min(4, k - 8);
     }
     // 4 low address bits in every tile: 128-byte runs of complex64 (fewer
     // passes than 256-byte runs, which outweighs the slower sweep on the
@@ -210,12 +229,14 @@ Shape choose_shape(int prec, int M, const spin_options* opt) {
     s.k = k;
     s.engine = opt ? opt->engine : 0;
     const bool half_ok = s.engine == 0 && pass_half_exists(f32, s.r, s.nt);
-    const bool small_ok = s.engine == 0 && pass_small_exists(f32, s.r, s.nt);
+    // tiles below 2^12 are the library's own choice, not a caller's
+    const bool small_ok = s.engine == 0 && pass_small_exists(f32, s.r, s.nt) &&
+                          (plain || pass_shape_exists(f32, s.r, s.nt, 0));
     s.exchange = ex == 2 || (ex == 0 && half_ok) ? kHalfTiles : ex == 0 && small_ok ? kSmallTiles : kWholeTiles;
     s.valid = s.exchange == kHalfTiles ? half_ok
                                        : s.exchange == kSmallTiles || pass_shape_exists(f32, s.r, s.nt, s.engine);
     s.res_cap = resident_max(f32);
-    s.resident = M <= s.res_cap;
+    s.resident = M <= (plain ? one : s.res_cap);
     return s;
 }
 
@@ -299,10 +320,10 @@ static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, const 
 
 int get_plan(int prec, int M, const std::vector<Coupling>& J, double dt, int64_t n_steps,
              int observed, const spin_options* opt, bool profile,
-             std::shared_ptr<DevicePlan>* out, Shape* shape_out, bool lookup_only = false) {
+             std::shared_ptr<DevicePlan>* out, Shape* shape_out, bool one_launch, bool lookup_only = false) {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
-    Shape sh = choose_shape(prec, M, opt);
+    Shape sh = choose_shape(prec, M, opt, any_phase(J), one_launch);
     if (!sh.resident && !sh.valid) {
         std::ostringstream os;
         os << "no pass kernel for tile_bits " << sh.k << " with reg_bits " << sh.r
@@ -335,9 +356,16 @@ int get_plan(int prec, int M, const std::vector<Coupling>& J, double dt, int64_t
     std::shared_ptr<DevicePlan> dp;
     int rc = prec == SPIN_C64 ? build_plan<float>(key, J, sh, &dp) : build_plan<double>(key, J, sh, &dp);
     if (rc) return rc;
-    std::lock_guard<std::mutex> lk(g_mu);
-    g_plans[key] = dp;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        g_plans[key] = dp;
+    }
     *out = dp;
+    // the plan that the same call takes where it can have neither scratch
+    // memory nor a new plan
+    std::shared_ptr<DevicePlan> single;
+    if (!sh.resident && M <= sh.res_cap)
+        return get_plan(prec, M, J, dt, n_steps, observed, opt, profile, &single, nullptr, true);
     return SPIN_OK;
 }
 
@@ -541,8 +569,11 @@ static int evolve_fused(void* psi, int M, const std::vector<Coupling>& J, double
     if (ws && (graph || profile))
         return fail(SPIN_EUNSUPPORTED, "the allocation-free call supports neither graph capture nor the "
                                        "all-site profile");
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(st, &cs));
+    const bool capturing = cs != hipStreamCaptureStatusNone;
     int rc = get_plan(sizeof(T) == 4 ? SPIN_C64 : SPIN_C128, M, J, dt, n_steps, observed, opt,
-                      profile, &dp, &sh, ws != nullptr);
+                      profile, &dp, &sh, ws != nullptr || capturing, ws != nullptr);
     if (rc) return rc;
     if (profile) return evolve_profile<T>(psi, M, *dp, n_steps, P, N, graph, st);
     if (dp->resident) {
@@ -768,7 +799,7 @@ int spin_prepare_plan(int32_t prec, int32_t M, const spin_coupling* J, int32_t K
             return SPIN_OK;     // the unfused schedule has no plan
         }
         std::shared_ptr<DevicePlan> dp;
-        rc = get_plan(prec, M, Jv, dt, n_steps, observed_site, opt, profile, &dp, nullptr);
+        rc = get_plan(prec, M, Jv, dt, n_steps, observed_site, opt, profile, &dp, nullptr, false);
         if (rc == SPIN_OK) g_err.clear();
         return rc;
     } catch (const std::exception& e) {
@@ -831,7 +862,7 @@ int host_plan(int32_t prec, int32_t M, const std::vector<Coupling>& Jv, double d
     if (profile && opt && opt->engine != 0)
         return fail(SPIN_EUNSUPPORTED, "the all-site profile runs on the butterfly engine only");
     hp->profile = profile;
-    hp->sh = choose_shape(prec, M, opt);
+    hp->sh = choose_shape(prec, M, opt, any_phase(Jv), false);
     if (!(opt && opt->schedule == 1) && !hp->sh.resident && !hp->sh.valid)
         return fail(SPIN_EUNSUPPORTED, "no pass kernel for the requested tile shape");
     const bool merge = !(opt && opt->no_merge);

@@ -28,7 +28,9 @@ struct Shape {
     bool resident = false;
     bool valid = true;  // a pass kernel exists for (r, nt, engine)
 };
-Shape choose_shape(int prec, int M, const spin_options* opt);
+Shape choose_shape(int prec, int M, const spin_options* opt, bool phases, bool one_launch);
+// Whether any coupling has an I^z I^z part.
+bool any_phase(const std::vector<Coupling>& J);
 
 // Caller-provided device workspace for the per-workgroup partial sums (the
 // allocation-free entry point); with one, plans must already be cached.

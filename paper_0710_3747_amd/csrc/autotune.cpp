@@ -138,17 +138,15 @@ std::vector<Tuned> large_tiles(int32_t prec) {
 // flops of the butterflies it replaces and it removes no LDS exchange, so it
 // never wins on these workloads (it stays selectable through spin_options).
 // Exchange 2 = half tiles (two workgroups per CU; one for complex128 tiles
-// of 2^14), 1 = whole tiles, 0 = the small tiles, for states that leave CUs
-// idle with large ones.
-std::vector<Tuned> candidates(int32_t prec, int32_t M) {
-    std::vector<Tuned> c;
-    if (M <= 22) {
-        c.push_back({12, 4, 4, 0, 0, 0});
-        if (prec == SPIN_C64) c.push_back({13, 4, 4, 0, 0, 0});
+// of 2^14), 1 = whole tiles, 0 = the small tiles, for the states whose default
+// they are.
+std::vector<Tuned> candidates(int32_t prec, const Shape& def) {
+    std::vector<Tuned> c = large_tiles(prec);
+    if (def.exchange == kSmallTiles) {
+        if (prec == SPIN_C64 && def.k != 13) c.insert(c.begin(), Tuned{13, 4, 4, 0, 0, 0});
+        if (def.k != 12) c.insert(c.begin(), Tuned{12, 4, 4, 0, 0, 0});
+        c.insert(c.begin(), Tuned{});
     }
-    const std::vector<Tuned> large = large_tiles(prec);
-    if (choose_shape(prec, M, nullptr).exchange == kSmallTiles) c.insert(c.end(), large.begin(), large.end());
-    else c.insert(c.begin(), large.begin(), large.end());
     return c;
 }
 
@@ -196,8 +194,11 @@ extern "C" int spin_autotune(int32_t prec, int32_t M, const spin_coupling* J, in
         if ((rc = tune_key(prec, M, Jv, dt, observed_site, &key))) return rc;
         hipStream_t st = static_cast<hipStream_t>(stream);
 
-        std::vector<Tuned> cand = candidates(prec, M);
-        if (choose_shape(prec, M, nullptr).resident) cand.resize(1);   // one workgroup: nothing to tune
+        // the default of one workgroup, or the shape that the options of such
+        // a state would be ignored for: nothing to tune
+        const Shape def = choose_shape(prec, M, nullptr, any_phase(Jv), false);
+        std::vector<Tuned> cand = candidates(prec, def);
+        if (M <= resident_max(prec == SPIN_C64)) cand.assign(1, Tuned{});
         DeviceBuffers b;
         const size_t elem = prec == SPIN_C64 ? 8 : 16;
         if (hipMalloc(&b.psi, elem << M) != hipSuccess) return fail(SPIN_ENOMEM, "autotune state allocation failed");

@@ -1941,9 +1941,7 @@ hipError_t launch_factor(void* psi, int M, int lo, int hi, double t, double s, d
 }
 
 bool pass_small_exists(bool f32, int r, int nt) {
-    if (nt == 256) return r == 2 || r == 3 || r == 4;
-    if (nt == 512) return r == 3 || (f32 && r == 4);
-    return f32 && nt == 64 && r == 5;
+    return (nt == 256 && r >= 2 && r <= 4) || (f32 && nt == 512 && r == 4);
 }
 
 bool pass_half_exists(bool f32, int r, int nt) {
@@ -2041,11 +2039,10 @@ hipError_t launch_pass_slots(const PassShape& sh, void* psi, const DevPass* pass
     if constexpr (sizeof(T) == 4) {
         SPIN_SLOTS(5, 512, kHalfTiles) SPIN_SLOTS(6, 256, kHalfTiles)
         SPIN_SLOTS(2, 256, kSmallTiles) SPIN_SLOTS(3, 256, kSmallTiles) SPIN_SLOTS(4, 256, kSmallTiles)
-        SPIN_SLOTS(3, 512, kSmallTiles) SPIN_SLOTS(4, 512, kSmallTiles) SPIN_SLOTS(5, 64, kSmallTiles)
+        SPIN_SLOTS(4, 512, kSmallTiles)
     } else {
         SPIN_SLOTS(4, 512, kHalfTiles) SPIN_SLOTS(5, 256, kHalfTiles) SPIN_SLOTS(5, 512, kHalfTiles)
         SPIN_SLOTS(2, 256, kSmallTiles) SPIN_SLOTS(3, 256, kSmallTiles) SPIN_SLOTS(4, 256, kSmallTiles)
-        SPIN_SLOTS(3, 512, kSmallTiles)
     }
 #undef SPIN_SLOTS
     return hipErrorInvalidValue;

@@ -1,0 +1,66 @@
+"""The states around the limits of one workgroup and of the small tiles: the
+default choice against the oracle's Trotter loop, and the one-launch plan that
+calls under stream capture and allocation-free calls take instead."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from oracle import cref
+import paper_0710_3747_amd as spq
+from gpu_helpers import TOL_P, assert_state_close, gpu_evolve, note, torch_dtype
+from test_zz_no_alloc import _run
+
+pytestmark = pytest.mark.gpu
+C64, C128 = spq.SPIN_C64, spq.SPIN_C128
+
+
+@pytest.mark.parametrize("prec", [C128, C64])
+@pytest.mark.parametrize("phases", [False, True])
+@pytest.mark.parametrize("M", [11, 12, 13, 14, 15, 16, 17, 18, 19])
+def test_default_shapes_match_the_oracle(prec, phases, M):
+    note("dispatch", M, prec, phases)
+    J = workloads.star(M, 7, a_over_b=-2.0 if phases else 0.0)
+    dt, steps = 0.03, 3
+    ref = np.ascontiguousarray(oracle.random_phase_state(M, M - 1, 5))
+    P0, N0 = cref.trotter_run(ref, M, J, dt, steps, M - 1)
+    P, N, psi, _ = gpu_evolve(prec, M, J, dt, steps, M - 1, polarized=M - 1, seed=5)
+    assert np.abs(P - P0).max() < TOL_P[prec]
+    assert np.abs(N / N0 - 1).max() < TOL_P[prec]
+    assert_state_close(psi, ref, prec)
+
+
+@pytest.mark.parametrize("prec,M", [(C64, 12), (C64, 14), (C128, 13)])
+def test_one_launch_plan_serves_captured_and_allocation_free_calls(prec, M):
+    """Prepared with one number of steps, called with another; replayed three
+    times with eager calls between."""
+    import torch
+    note("one launch", M, prec)
+    lib = spq.load_library()
+    J = workloads.star(M, 7, a_over_b=-2.0)
+    dt, steps = 0.03, 4
+    spq.spin_prepare_plan(prec, M, J, dt, steps + 3, 0, None)
+    psi = torch.empty(2 ** M, dtype=torch_dtype(prec), device="cuda")
+    P = torch.zeros(steps + 1, dtype=torch.float64, device="cuda")
+    N = torch.zeros_like(P)
+    spq.spin_init_random_phase(psi, M, 0, 2)
+    start = psi.clone()
+    assert _run(lib, "spin_trotter_evolve_noalloc", psi, prec, M, J, dt, steps, 0, P, N, None, torch) == 0
+    torch.cuda.synchronize()
+    want, wantP = psi.clone(), P.clone()
+    want_np = want.cpu().numpy().astype(np.complex128)
+    Pe, _, psie, _ = gpu_evolve(prec, M, J, dt, steps, 0, polarized=0, seed=2)
+    assert np.abs(Pe - wantP.cpu().numpy()).max() < TOL_P[prec]
+    assert_state_close(psie, want_np, prec)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        spq.spin_trotter_evolve_ex(psi, M, J, dt, steps, 0, P, N, None)
+    for _ in range(3):
+        psi.copy_(start)
+        P.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(torch.view_as_real(psi), torch.view_as_real(want)) and torch.equal(P, wantP)
+        gpu_evolve(prec, M, J, dt, steps, 0, seed=9)
