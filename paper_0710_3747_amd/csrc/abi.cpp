@@ -199,9 +199,10 @@ Shape choose_shape(int prec, int M, const spin_options* opt, bool phases, bool o
     // arithmetic of a rotation, which moves the lines to smaller tiles: dipolar
     // star 2^10 / 2^11 / 2^12, M = 12 45 / 53 / 50 (one workgroup), M = 14 62 /
     // 70 / 85, M = 16 92 / 96 / 112.
-    const bool plain = ex == 0 && !one_launch && !(opt && (opt->engine || opt->reg_bits || opt->tile_bits ||
+    const bool plain = ex == 0 && !(opt && (opt->engine || opt->reg_bits || opt->tile_bits ||
                                                 opt->coalesce_bits > 4));
-    const int one = (phases ? 11 : f32 ? 13 : 12);     // largest state of one workgroup
+    // largest state of one workgroup
+    const int one = one_launch ? resident_max(f32) : phases ? 11 : f32 ? 13 : 12;
     const int small = M <= one ? 0 : M <= 16 ? (phases ? 10 : 11) : M <= 18 && phases ? 11
                     : M <= 20 ? 12 : M == 21 && f32 ? 13 : 0;
     int k = f32 ? 14 : 13;
@@ -211,6 +212,12 @@ Shape choose_shape(int prec, int M, const spin_options* opt, bool phases, bool o
     if (plain && small) {
         k = small;
         s.r = std::min(4, k - 8);
+    } else if (plain && f32 && M >= 24) {
+        // 64 amplitudes per lane, four wavefronts per workgroup: a third
+        // fewer exchanges; against 32, us per step: ladder M = 22 27 / 26,
+        // M = 24 70 / 72, M = 26 328 / 355, M = 28 1379 / 1444, M = 30 5950 /
+        // 6191; star M = 22 310 / 302, M = 24 886 / 918, M = 28 23195 / 23387
+        s.r = 6;
     }
     // 4 low address bits in every tile: 128-byte runs of complex64 (fewer
     // passes than 256-byte runs, which outweighs the slower sweep on the
@@ -235,6 +242,7 @@ Shape choose_shape(int prec, int M, const spin_options* opt, bool phases, bool o
     s.exchange = ex == 2 || (ex == 0 && half_ok) ? kHalfTiles : ex == 0 && small_ok ? kSmallTiles : kWholeTiles;
     s.valid = s.exchange == kHalfTiles ? half_ok
                                        : s.exchange == kSmallTiles || pass_shape_exists(f32, s.r, s.nt, s.engine);
+    s.try_large = plain && !f32 && M >= 27;
     s.res_cap = resident_max(f32);
     s.resident = M <= (plain ? one : s.res_cap);
     return s;
@@ -256,8 +264,42 @@ static void exchange_params(ExchangeMode x, PassParams* pp) {
     pp->gates = x == kWholeTiles ? 0 : kMaxGates;
 }
 
+// The passes of a tiled call.  complex128 states from M = 27 on by default
+// also try tiles of 2^14 (one workgroup per CU): a pass with more factors takes
+// longer, so they are taken where they save enough launches (ladder M = 30, 10
+// steps: 21 passes of 7.54 ms against 13 of 10.1 ms; M = 28, 21 steps: 36 of
+// 1.96 against 27 of 2.50, 8 steps: 15 of 1.94 against 12 of 2.40, 5 steps: 11
+// of 1.88 against 9 of 2.37; star M = 28 40 of 2.18 against 35 of 2.73; below
+// M = 27, where the state stays in the last-level cache for longer, star M = 26
+// 35 of 0.567 against 25 of 0.797, ladder M = 26 28 of 0.50 against 21 of 0.69).
+static StreamPlan plan_tiled(int M, const std::vector<Coupling>& J, double dt, int64_t n_steps, int observed,
+                             bool merge, bool profile, Shape* sh) {
+    auto plan = [&](const Shape& s) {
+        PassParams pp;
+        pp.k = s.k;
+        pp.r = s.r;
+        pp.c = s.c;
+        pp.profile = profile;
+        exchange_params(s.exchange, &pp);
+        if (profile) pp.max_meas = kMaxMeasProfile;
+        return plan_stream_best(M, J, dt, n_steps, observed, merge, pp);
+    };
+    StreamPlan sp = plan(*sh);
+    if (sh->try_large) {
+        Shape large = *sh;
+        large.k = 14;
+        large.nt = 512;
+        StreamPlan lp = plan(large);
+        if (4 * sp.launch_tmpl.size() > 5 * lp.launch_tmpl.size()) {
+            *sh = large;
+            return lp;
+        }
+    }
+    return sp;
+}
+
 template <typename T>
-static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, const Shape& sh,
+static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, Shape sh,
                       std::shared_ptr<DevicePlan>* out) {
     auto dp = std::make_shared<DevicePlan>();
     DevTables<T> tb;
@@ -270,19 +312,13 @@ static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, const 
             dp->res = encode_resident<T>(rp, bits, key.observed, tb, key.profile != 0);
             dp->stages_total = tb.stages.size();
         } else {
-            PassParams pp;
-            pp.k = sh.k;
-            pp.r = sh.r;
-            pp.c = sh.c;
-            pp.profile = key.profile != 0;
-            exchange_params(sh.exchange, &pp);
-            if (pp.profile) pp.max_meas = kMaxMeasProfile;
-            dp->sp = plan_stream_best(key.M, J, key.dt, key.n_steps, key.observed, key.merge != 0, pp);
+            dp->sp = plan_tiled(key.M, J, key.dt, key.n_steps, key.observed, key.merge != 0,
+                                key.profile != 0, &sh);
             dp->shape = PassShape{sh.r, sh.nt};
             dp->shape.engine = sh.engine;
-            dp->shape.profile = pp.profile;
+            dp->shape.profile = key.profile != 0;
             dp->shape.exchange = sh.exchange;
-            dp->profile = pp.profile;
+            dp->profile = key.profile != 0;
             dp->k = sh.k;
             const int64_t ntiles = int64_t(1) << (key.M - sh.k);
             int dev_cu = 256;
@@ -874,14 +910,7 @@ int host_plan(int32_t prec, int32_t M, const std::vector<Coupling>& Jv, double d
             hp->rp = plan_resident(resident_bits(M), Jv, dt, observed, merge, kResidentRegs, profile);
         } else {
             hp->path = 2;
-            PassParams pp;
-            pp.k = hp->sh.k;
-            pp.r = hp->sh.r;
-            pp.c = hp->sh.c;
-            pp.profile = profile;
-            exchange_params(hp->sh.exchange, &pp);
-            if (profile) pp.max_meas = kMaxMeasProfile;
-            hp->sp = plan_stream_best(M, Jv, dt, n_steps, observed, merge, pp);
+            hp->sp = plan_tiled(M, Jv, dt, n_steps, observed, merge, profile, &hp->sh);
         }
         // encode the tables as the evolve call would (nothing is uploaded),
         // so that the host-only calls report the errors that call would

@@ -26,6 +26,7 @@ struct Shape {
     int engine = 0;     // 0: VALU butterflies, 1: MFMA stage matrices
     ExchangeMode exchange = kWholeTiles;
     bool resident = false;
+    bool try_large = false;  // complex128: tiles of 2^14 may take fewer, longer passes
     bool valid = true;  // a pass kernel exists for (r, nt, engine)
 };
 Shape choose_shape(int prec, int M, const spin_options* opt, bool phases, bool one_launch);

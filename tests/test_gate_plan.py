@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+import paper_0710_3747_amd as spq
 import workloads
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -58,3 +59,12 @@ def test_register_lane_exchanges(case, binary):
     inp = f"{M} {prec} {k} {r} {c} {steps} {obs} {half}\n" + "".join(f"{i} {j} {a!r} {b!r}\n" for i, j, a, b in J)
     p = subprocess.run([binary], input=inp, capture_output=True, text=True, timeout=300)
     assert p.returncode == 0 and " failures 0" in p.stdout, p.stdout
+
+
+@pytest.mark.parametrize("M,steps,tile", [(26, 20, 13), (28, 2, 13), (28, 21, 14), (30, 10, 14)])
+def test_double_precision_tiles_follow_the_launches_they_save(M, steps, tile):
+    args = (spq.SPIN_C128, M, workloads.ladder(M // 2), 0.05, steps, 0)
+    got = spq.spin_describe_plan(*args, spq.Options())
+    n = {k: spq.spin_describe_plan(*args, spq.Options(tile_bits=k))["launches"] for k in (13, 14)}
+    assert got["tile_bits"] == tile and got["launches"] == n[tile]
+    assert (4 * n[13] > 5 * n[14]) == (tile == 14) or M < 27
