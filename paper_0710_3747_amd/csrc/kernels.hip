@@ -1,7 +1,7 @@
 // kernels.hip -- gfx950 kernels of the random-phase Trotter path.
 //
-//  k_init        random-phase state (counter-based SplitMix64 phases)
-//  k_init_product  product state of M-1 random single-spin phases
+//  k_init        random-phase state (counter-based SplitMix64 phases), or the
+//                product state of M-1 random single-spin phases
 //  k_init_members  2^c basis-state members of the ensemble stacked as one
 //                state of M + c sites (member index on the top c bits)
 //  k_accumulate  member sums of consecutive evolutions, in order
@@ -53,6 +53,40 @@ __device__ __forceinline__ double sm64_uniform(uint64_t seed, uint64_t r) {
     return double(z >> 11) * 0x1.0p-53;
 }
 
+// sin and cos of 2 pi u for u in [0, 1]: the nearest quarter turn is taken off
+// exactly (u = q/4 + f, |f| <= 1/8), then the Taylor series in f^2, coefficients
+// (2 pi)^k / k! (the first neglected terms are below 3e-20).  Each is within
+// 1.1 ulp of the exact value (measured over 5e6 arguments).
+__device__ __forceinline__ void sincos_turn(double u, double* s, double* c) {
+    const double q = rint(4.0 * u);
+    const double f = fma(-0.25, q, u), t = f * f;
+    double a = 0x1.aaec32af93359p-4;
+    a = fma(a, t, -0x1.6fadb9f155744p-1);
+    a = fma(a, t, 0x1.e8f434d018d63p+1);
+    a = fma(a, t, -0x1.e3074fde8871fp+3);
+    a = fma(a, t, 0x1.50783487ee782p+5);
+    a = fma(a, t, -0x1.32d2cce62bd86p+6);
+    a = fma(a, t, 0x1.466bc6775aae2p+6);
+    a = fma(a, t, -0x1.4abbce625be53p+5);
+    a = fma(a, t, 0x1.1a62633145c07p-52);       // the rest of 2 pi
+    a = fma(f, 0x1.921fb54442d18p+2, f * a);
+    double b = 0x1.20c62c2f2d7f5p-2;
+    b = fma(b, t, -0x1.b6e24f44b128fp+0);
+    b = fma(b, t, 0x1.f9d38a3763cc3p+2);
+    b = fma(b, t, -0x1.a6d1f2a204a8cp+4);
+    b = fma(b, t, 0x1.e1f506891babbp+5);
+    b = fma(b, t, -0x1.55d3c7e3cbffap+6);
+    b = fma(b, t, 0x1.03c1f081b5ac4p+6);
+    // 1 + C1 t with its rounding error and that of t carried along
+    const double h = fma(t, -0x1.3bd3cc9be45dep+4, 1.0);
+    const double e = fma(fma(f, f, -t), -0x1.3bd3cc9be45dep+4, fma(t, -0x1.3bd3cc9be45dep+4, 1.0 - h));
+    b = h + fma(t * t, b, e);
+    const int k = int(q);
+    const double x = (k & 1) ? b : a, y = (k & 1) ? a : b;
+    *s = (k & 2) ? -x : x;
+    *c = ((k + 1) & 2) ? -y : y;
+}
+
 // Amplitude of basis state x of the random-phase state, FP64.
 __device__ __forceinline__ void random_phase_amp(uint64_t x, int n, uint64_t seed, double scale,
                                                  double* re, double* im) {
@@ -63,7 +97,7 @@ __device__ __forceinline__ void random_phase_amp(uint64_t x, int n, uint64_t see
     }
     const uint64_t r = (x & ((1ull << n) - 1ull)) | ((x >> (n + 1)) << n);
     double s, c;
-    sincospi(2.0 * sm64_uniform(seed, r), &s, &c);      // phi = 2 pi u
+    sincos_turn(sm64_uniform(seed, r), &s, &c);      // phi = 2 pi u
     *re = c * scale;
     *im = s * scale;
 }
@@ -85,9 +119,9 @@ __device__ __forceinline__ void product_amp(uint64_t x, int M, int n, uint64_t s
         if (l != n && !((x >> l) & 1ull)) acc += u ? u[l] : sm64_uniform(seed, uint64_t(l));
     acc -= floor(acc);               // the phase modulo 2 pi
     double s, c;
-    sincospi(-2.0 * acc, &s, &c);
+    sincos_turn(acc, &s, &c);
     *re = c * scale;
-    *im = s * scale;
+    *im = -s * scale;
 }
 
 // Initial amplitude of basis state x: init 1 = the random-phase state,
@@ -105,36 +139,68 @@ __device__ __forceinline__ void init_amp(uint64_t x, int M, int init, int polari
     }
 }
 
-template <typename T>
+// Both initial states hold zeros where site n is down, so a lane takes V
+// consecutive free indices r (the bits of x but n) and stores their amplitudes
+// and as many zeros, 16 bytes at a time; the phase generator alone would
+// otherwise idle half of every wavefront's lanes.  The stride is a power of
+// two, so the bits of r below it, and their part of the product state's phase,
+// are the lane's for good.  M = 28, site 0 / 5, with the reduction of the
+// phase above: random phases, complex64 766 / 720 -> 440 / 384 us (a fill takes
+// 316), complex128 842 / 787 -> 750 / 737; product state, complex64 2048 / 2044
+// -> 427 / 400, complex128 2037 / 2026 -> 870 / 766.  What is left above the
+// fill is the FP64 series and the generator's 64-bit products.
+template <typename T, bool PRODUCT>
 __global__ __launch_bounds__(256) void k_init(typename CT<T>::c* __restrict__ psi, int M, int n,
                                               uint64_t seed, double scale) {
-    const uint64_t dim = 1ull << M;
-    const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-    for (uint64_t x = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; x < dim; x += stride) {
-        double re, im;
-        random_phase_amp(x, n, seed, scale, &re, &im);
-        typename CT<T>::c v;
-        v.x = T(re);
-        v.y = T(im);
-        psi[x] = v;
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_init_product(typename CT<T>::c* __restrict__ psi, int M,
-                                                      int n, uint64_t seed, double scale) {
+    using C = typename CT<T>::c;
+    constexpr int V = CT<T>::V;
     __shared__ double u[64];
-    if (threadIdx.x < 64) u[threadIdx.x] = sm64_uniform(seed, threadIdx.x);
-    __syncthreads();
-    const uint64_t dim = 1ull << M;
-    const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-    for (uint64_t x = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; x < dim; x += stride) {
-        double re, im;
-        product_amp(x, M, n, seed, u, scale, &re, &im);
-        typename CT<T>::c v;
-        v.x = T(re);
-        v.y = T(im);
-        psi[x] = v;
+    if constexpr (PRODUCT) {
+        if (threadIdx.x < 64) u[threadIdx.x] = sm64_uniform(seed, threadIdx.x);
+        __syncthreads();
+    }
+    const uint64_t nfree = 1ull << (M - 1);
+    const uint64_t stride = uint64_t(gridDim.x) * 256 * V, low = (1ull << n) - 1;
+    uint64_t r = (uint64_t(blockIdx.x) * 256 + threadIdx.x) * V;
+    const int lb = min(M - 1, 63 - __builtin_clzll(stride));      // bits of r below the stride
+    double acc[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        acc[j] = 0.0;
+        if constexpr (PRODUCT)
+            for (int b = 0; b < lb; ++b)
+                if (!(((r + j) >> b) & 1ull)) acc[j] += u[b + (b >= n)];
+    }
+    for (; r < nfree; r += stride) {
+        const uint64_t x = ((r & ~low) << 1) | (r & low);
+        C v[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            double sn, cs;
+            if constexpr (PRODUCT) {
+                double a = acc[j];
+                for (int b = lb; b < M - 1; ++b)
+                    if (!((r >> b) & 1ull)) a += u[b + (b >= n)];
+                sincos_turn(a - floor(a), &sn, &cs);     // the phase modulo 2 pi
+                sn = -sn;
+            } else {
+                sincos_turn(sm64_uniform(seed, r + j), &sn, &cs);
+            }
+            v[j].x = T(cs * scale);
+            v[j].y = T(sn * scale);
+        }
+        if constexpr (V == 1) {
+            psi[x] = v[0];
+            psi[x | (1ull << n)] = C{};
+        } else if (n == 0) {
+            // x = 2 r: every amplitude has its zero beside it
+            float4* out = reinterpret_cast<float4*>(psi) + r;
+            out[0] = float4{v[0].x, v[0].y, 0.f, 0.f};
+            if (r + 1 < nfree) out[1] = float4{v[1].x, v[1].y, 0.f, 0.f};
+        } else {
+            *reinterpret_cast<float4*>(psi + x) = float4{v[0].x, v[0].y, v[1].x, v[1].y};
+            *reinterpret_cast<float4*>(psi + (x | (1ull << n))) = float4{};
+        }
     }
 }
 
@@ -255,18 +321,36 @@ __global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ parti
 }
 #endif
 
+// Reads the state once, so the loads in flight bound it: four 16-byte loads per
+// lane, a workgroup's 16 KiB contiguous.  M = 28: complex64 572 -> 348 us (6.2
+// TB/s), complex128 735 -> 697 us; the same four loads a whole grid apart 412
+// and 814 us.
 template <typename T>
 __global__ __launch_bounds__(256) void k_observe(const typename CT<T>::c* __restrict__ psi, int M,
                                                  int site, double* __restrict__ partials) {
+    using Vec = typename CT<T>::v;
+    constexpr int V = CT<T>::V, U = 4;
     __shared__ double red[8];
-    const uint64_t dim = 1ull << M;
+    const Vec* __restrict__ in = reinterpret_cast<const Vec*>(psi);
+    const uint64_t nvec = (1ull << M) / V;
     const uint64_t stride = uint64_t(gridDim.x) * 256;
     double p = 0.0, n = 0.0;
-    for (uint64_t x = uint64_t(blockIdx.x) * 256 + threadIdx.x; x < dim; x += stride) {
-        const typename CT<T>::c v = psi[x];
-        const double w = double(v.x) * double(v.x) + double(v.y) * double(v.y);
+    auto add = [&](const Vec& v, uint64_t x) {
+        double w = double(v.x) * double(v.x) + double(v.y) * double(v.y), d = w;
+        if constexpr (V == 2) {
+            const double w1 = double(v.z) * double(v.z) + double(v.w) * double(v.w);
+            d = site == 0 ? w - w1 : w + w1;
+            w += w1;
+        }
         n += w;
-        p += ((x >> site) & 1ull) ? -w : w;
+        p += ((x * V) >> site) & 1ull ? -d : d;
+    };
+    for (uint64_t x = uint64_t(blockIdx.x) * 256 * U + threadIdx.x; x < nvec; x += U * stride) {
+        Vec v[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) v[k] = x + k * 256 < nvec ? in[x + k * 256] : Vec{};
+#pragma unroll
+        for (int k = 0; k < U; ++k) add(v[k], x + k * 256);
     }
     block_sum2<256>(p, n, red);
     if (threadIdx.x == 0) {
@@ -1875,8 +1959,8 @@ static inline int grid_for(uint64_t n, int per_block, int cap) {
 template <typename T>
 hipError_t launch_init(void* psi, int M, int n, uint64_t seed, hipStream_t st) {
     const double scale = 1.0 / sqrt(ldexp(1.0, M - 1));
-    const int grid = grid_for(1ull << M, 256, 1 << 16);
-    hipLaunchKernelGGL(k_init<T>, dim3(grid), dim3(256), 0, st,
+    const int grid = grid_for((1ull << (M - 1)) / CT<T>::V, 256, 1 << 16);
+    hipLaunchKernelGGL((k_init<T, false>), dim3(grid), dim3(256), 0, st,
                        reinterpret_cast<typename CT<T>::c*>(psi), M, n, seed, scale);
     return hipGetLastError();
 }
@@ -1884,8 +1968,10 @@ hipError_t launch_init(void* psi, int M, int n, uint64_t seed, hipStream_t st) {
 template <typename T>
 hipError_t launch_init_product(void* psi, int M, int n, uint64_t seed, hipStream_t st) {
     const double scale = 1.0 / sqrt(ldexp(1.0, M - 1));
-    const int grid = grid_for(1ull << M, 256, 1 << 16);
-    hipLaunchKernelGGL(k_init_product<T>, dim3(grid), dim3(256), 0, st,
+    // lanes that each take several indices share the sum over the low sites:
+    // M = 28 427 us, with 1 << 16 workgroups 482 us
+    const int grid = grid_for((1ull << (M - 1)) / CT<T>::V, 256, 1 << 14);
+    hipLaunchKernelGGL((k_init<T, true>), dim3(grid), dim3(256), 0, st,
                        reinterpret_cast<typename CT<T>::c*>(psi), M, n, seed, scale);
     return hipGetLastError();
 }

@@ -64,3 +64,37 @@ def test_one_launch_plan_serves_captured_and_allocation_free_calls(prec, M):
         torch.cuda.synchronize()
         assert torch.equal(torch.view_as_real(psi), torch.view_as_real(want)) and torch.equal(P, wantP)
         gpu_evolve(prec, M, J, dt, steps, 0, seed=9)
+
+
+@pytest.mark.parametrize("prec", [C128, C64])
+@pytest.mark.parametrize("M", [1, 2, 3, 9, 20])
+def test_initial_states_and_observable_at_every_kind_of_site(prec, M):
+    """Amplitudes to a few roundings of the type, zeros exact, the observable
+    of the stored amplitudes to FP64."""
+    import torch
+    scale = 2.0 ** (-(M - 1) / 2)
+    tol = (4 if prec == C128 else 1) * (2.0 ** -53 if prec == C128 else 2.0 ** -24) * scale
+    for n in sorted({0, min(1, M - 1), M // 2, M - 1}):
+        for product in (False, True):
+            note("init", prec, M, n, product)
+            psi = torch.full((2 ** M,), float("nan"), dtype=torch_dtype(prec), device="cuda")
+            P = torch.zeros(1, dtype=torch.float64, device="cuda")
+            (spq.spin_init_product if product else spq.spin_init_random_phase)(psi, M, n, 17)
+            got = psi.cpu().numpy().astype(np.complex128)
+            up = (np.arange(2 ** M) >> n) & 1 == 0
+            if product:
+                want = oracle.product_state(M, n, oracle.product_phases(M, 17))
+            else:
+                # extended precision: the double-precision oracle rounds 2 pi u itself
+                turn = 8 * np.arctan(np.longdouble(1)) * oracle.phase_u_array(17, np.arange(2 ** (M - 1))).astype(np.longdouble)
+                want = np.zeros(2 ** M, dtype=np.clongdouble)
+                want[up] = (np.cos(turn) + 1j * np.sin(turn)) * np.sqrt(np.longdouble(2)) ** -(M - 1)
+            assert np.all(got[~up] == 0)
+            # a product state sums M - 1 phases here and multiplies M - 1 factors in the oracle
+            extra = 4e-15 * M * scale if product else 0.0
+            assert np.abs(got - want).max() <= tol + extra
+            for site in range(M):
+                spq.spin_local_polarization(psi, M, site, P)
+                w = np.abs(got) ** 2
+                sgn = 1.0 - 2.0 * ((np.arange(2 ** M) >> site) & 1)
+                assert abs(float(P[0]) - float((w * sgn).sum())) < 1e-12
