@@ -100,6 +100,19 @@ static int batch_build(const spin_problem* probs, const std::vector<int>& sel,
     const bool f32 = sizeof(T) == 4;
     const int K = batch_tile_bits(f32), R = batch_shape(f32, half).r;
     const int KL = K - 1;               // largest one-workgroup problem
+    // Workgroups per gang, at most: as many as leave every gang a slot of its
+    // own, or nearly (half of the gangs may wait for another).  Stars of M = 14
+    // to 20, 10 steps, ms with gangs of 8 / 16 / 32 / 64: 32 problems 16.5 / 10.2
+    // / 9.5 / 11.3, 4 of M = 20 14.2 / 7.7 / 4.9 / 3.6; 4 steps of 128 problems
+    // 14.2 / 14.2 / 16.0 / 18.1; 2 steps of 256 18.7 / 19.5.
+    auto demand = [&](int64_t g) {
+        int64_t n = 0;
+        for (int p : sel) n += probs[p].M <= KL ? 1 : std::min(int64_t(1) << (probs[p].M - K), g);
+        return n;
+    };
+    int64_t gang = 8;
+    while (2 * gang <= nslots && 2 * demand(2 * gang) <= 3 * int64_t(nslots)) gang *= 2;
+    gang = std::min<int64_t>(gang, nslots);
     DevTables<T> tb;
     std::vector<BatchProblem> bp;
     std::vector<int2> launches;
@@ -175,11 +188,7 @@ static int batch_build(const spin_problem* probs, const std::vector<int>& sel,
             for (size_t l = 0; l < sp.launch_tmpl.size(); ++l)
                 launches.push_back(make_int2(sp.launch_tmpl[l], int(sp.launch_offset[l])));
             b.ntiles = int64_t(1) << (pr.M - K);
-            // Gangs of at most 8 workgroups with half tiles (two per CU):
-            // more problems run at once and fewer wait at each barrier; on
-            // 256 stars of M 14..20 the batch took 1.85 s with 8, 1.94 s
-            // with 16, 2.25 s with 32 and 2.61 s with 4.
-            b.gsize = int(std::min<int64_t>(b.ntiles, half ? 8 : 32));
+            b.gsize = int(std::min<int64_t>(b.ntiles, gang));
             b.part0 = part;
             part += int64_t(kBatchRing) * b.gsize * 2;
             b.counter = ncounter++;
@@ -192,36 +201,23 @@ static int batch_build(const spin_problem* probs, const std::vector<int>& sel,
         shared[skey] = {b, fops};
         bp.push_back(b);
     }
-    // Gang schedule: slots w with the same w % 8 form an XCD group; longest
-    // jobs first, each onto the group where its gang can start earliest.
-    const int ngroup = nslots >= 8 ? 8 : 1;
+    // Gang schedule: longest jobs first, each on the slots that are free first.
     std::vector<double> avail(nslots, 0.0);
     std::vector<std::vector<BatchJob>> lists(nslots);
-    std::vector<int> order(bp.size());
+    std::vector<int> order(bp.size()), slots(nslots);
     for (size_t i = 0; i < order.size(); ++i) order[i] = int(i);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return dur[a] > dur[b]; });
     for (int q : order) {
         const int g = bp[q].gsize;
-        double best_start = 1e300;
-        std::vector<int> best;
-        for (int x = 0; x < ngroup; ++x) {
-            std::vector<int> slots;
-            for (int w = x; w < nslots; w += ngroup) slots.push_back(w);
-            if (int(slots.size()) < g) continue;
-            std::stable_sort(slots.begin(), slots.end(), [&](int a, int b) { return avail[a] < avail[b]; });
-            slots.resize(g);
-            double start = 0;
-            for (int w : slots) start = std::max(start, avail[w]);
-            if (start < best_start) {
-                best_start = start;
-                best = slots;
-            }
-        }
-        if (best.empty()) throw std::runtime_error("batch: gang larger than an XCD group");
-        std::sort(best.begin(), best.end());
+        for (int w = 0; w < nslots; ++w) slots[w] = w;
+        std::partial_sort(slots.begin(), slots.begin() + g, slots.end(), [&](int a, int b) {
+            return avail[a] < avail[b] || (avail[a] == avail[b] && a < b);
+        });
+        const double start = avail[slots[g - 1]];
+        std::sort(slots.begin(), slots.begin() + g);
         for (int r = 0; r < g; ++r) {
-            lists[best[r]].push_back(BatchJob{q, r});
-            avail[best[r]] = best_start + dur[q];
+            lists[slots[r]].push_back(BatchJob{q, r});
+            avail[slots[r]] = start + dur[q];
         }
     }
     std::vector<BatchJob> jobs;

@@ -1895,17 +1895,21 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                 }
             }
             ok = gang_barrier(ctr, ++epoch * int(G), err);
-            if (rank == 0 && tid == 0 && ok) {
+            if (rank == 0 && tid < 64 && ok) {
                 for (int m = 0; m < P.nmeas; ++m) {
                     const int64_t s = int64_t(la.y) + P.meas_step[m];
                     const double* src = partials + B.part0 + (s % kBatchRing) * G * 2;
                     double p = 0.0, n = 0.0;
-                    for (unsigned r = 0; r < G; ++r) {
+                    for (unsigned r = tid; r < G; r += 64) {
                         p += src[2 * r];
                         n += src[2 * r + 1];
                     }
-                    B.P[s] = p;
-                    if (B.N) B.N[s] = n;
+                    p = wave_sum_last(p);
+                    n = wave_sum_last(n);
+                    if (tid == 63) {
+                        B.P[s] = p;
+                        if (B.N) B.N[s] = n;
+                    }
                 }
             }
         }
