@@ -3,11 +3,15 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <exception>
+#include <list>
 #include <map>
 #include <memory>
 #include <mutex>
 #include <sstream>
+#include <thread>
 #include <vector>
 
 #include "../../include/spin.h"
@@ -18,11 +22,25 @@
 namespace spinqp {
 
 // ------------------------------------------------------- persistent batch
+// What the couplings decide: plans, tables and the schedule.  Read-only once
+// built, and shared by the calls that differ in states, seeds and outputs only.
+struct BatchTables {
+    void *d_jobs = nullptr, *d_jstart = nullptr, *d_passes = nullptr, *d_stages = nullptr, *d_ops = nullptr,
+         *d_launch = nullptr;
+    std::vector<BatchProblem> probs;    // without pointers, seeds and polarised sites
+    int64_t part = 0;
+    int ncounters = 0;
+    ~BatchTables() {
+        for (void* p : {d_jobs, d_jstart, d_passes, d_stages, d_ops, d_launch})
+            if (p) (void)hipFree(p);
+    }
+};
+
+// One call's problems and the memory its gangs write.
 struct BatchCache {
-    void *d_probs = nullptr, *d_jobs = nullptr, *d_jstart = nullptr, *d_passes = nullptr,
-         *d_stages = nullptr, *d_ops = nullptr, *d_launch = nullptr, *d_part = nullptr,
-         *d_ctr = nullptr, *d_err = nullptr;
-    int nslots = 0, ncounters = 0;
+    std::shared_ptr<const BatchTables> tables;
+    void *d_probs = nullptr, *d_part = nullptr, *d_ctr = nullptr, *d_err = nullptr;
+    int nslots = 0;
     bool half = false;
     hipStream_t side = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -31,17 +49,24 @@ struct BatchCache {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
         if (side) (void)hipStreamDestroy(side);
-        for (void* p : {d_probs, d_jobs, d_jstart, d_passes, d_stages, d_ops, d_launch, d_part,
-                        d_ctr, d_err})
+        for (void* p : {d_probs, d_part, d_ctr, d_err})
             if (p) (void)hipFree(p);
     }
 };
 
 static std::mutex g_bmu;
 static std::map<std::vector<double>, std::shared_ptr<BatchCache>> g_bcache;
+// The tables of the latest sets of couplings, latest first.
+constexpr size_t kBatchTablesKept = 8;
+static std::list<std::pair<std::vector<double>, std::shared_ptr<const BatchTables>>> g_btables;
 // Per device: sticky status word of the persistent launches (non-zero once a
 // gang barrier has timed out), read and cleared by spin_batch_status.
 static std::map<int, int*> g_status;
+// Per device: the end of the latest persistent launch.  A gang waits for its
+// members, so the launch's workgroups must all find a slot: launches on
+// several streams run one after the other.
+static std::mutex g_launch_mu;
+static std::map<int, hipEvent_t> g_last_launch;
 
 static int status_word(int dev, int** out) {
     std::lock_guard<std::mutex> lk(g_bmu);
@@ -63,6 +88,13 @@ static int status_word(int dev, int** out) {
 void release_batch_caches() {
     std::lock_guard<std::mutex> lk(g_bmu);
     g_bcache.clear();
+    g_btables.clear();
+    {
+        std::lock_guard<std::mutex> ll(g_launch_mu);
+        for (auto& kv : g_last_launch)
+            if (kv.second) (void)hipEventDestroy(kv.second);
+        g_last_launch.clear();
+    }
     for (auto& kv : g_status)
         if (kv.second) (void)hipFree(kv.second);
     g_status.clear();
@@ -93,12 +125,93 @@ static std::vector<double> batch_key(const spin_problem* probs, int n,
     return k;
 }
 
+// Key of the tables: what a problem's plan and the schedule depend on.
+static std::vector<double> tables_key(const spin_problem* probs, int n, const std::vector<std::vector<Coupling>>& Js,
+                                      int prec, double dt, int64_t n_steps, int dev, bool half) {
+    std::vector<double> k{double(prec), dt, double(n_steps), double(dev), double(half), double(n)};
+    for (int p = 0; p < n; ++p) {
+        k.push_back(probs[p].M);
+        k.push_back(probs[p].observed_site);
+        k.push_back(double(Js[p].size()));
+        for (const Coupling& c : Js[p]) {
+            k.push_back(c.i);
+            k.push_back(c.j);
+            k.push_back(c.a);
+            k.push_back(c.b);
+        }
+    }
+    return k;
+}
+
+static int upload(const void* src, size_t n, void** dst) {
+    if (n == 0) n = 16;
+    if (hipMalloc(dst, n) != hipSuccess) return fail(SPIN_ENOMEM, "batch table allocation failed");
+    if (src && hipMemcpy(*dst, src, n, hipMemcpyHostToDevice) != hipSuccess)
+        return fail(SPIN_EHIP, "batch table upload failed");
+    return SPIN_OK;
+}
+
+// The plan of one problem: its own tables, indices from 0.
 template <typename T>
-static int batch_build(const spin_problem* probs, const std::vector<int>& sel,
-                       const std::vector<std::vector<Coupling>>& Js, double dt, int64_t n_steps,
-                       int init, int nslots, bool half, BatchCache* bc) {
+struct ProblemPlan {
+    const spin_problem* pr = nullptr;
+    const std::vector<Coupling>* J = nullptr;
+    BatchProblem b{};
+    DevTables<T> tb;
+    std::vector<int2> launches;
+    double dur = 0;
+};
+
+template <typename T>
+static void plan_problem(double dt, int64_t n_steps, int64_t gang, bool half, ProblemPlan<T>* out) {
     const bool f32 = sizeof(T) == 4;
-    const int K = batch_tile_bits(f32), R = batch_shape(f32, half).r;
+    const int K = batch_tile_bits(f32), KL = K - 1;
+    const spin_problem& pr = *out->pr;
+    BatchProblem& b = out->b;
+    double fops = 0;
+    if (pr.M <= KL) {
+        const int bits = batch_resident_bits(pr.M, half);
+        const int r = bits - __builtin_ctz(batch_shape(f32, half).nt);
+        const ResidentPlan rp = plan_resident(bits, *out->J, dt, pr.observed_site, true, r);
+        b.gsize = 1;
+        const ResidentStages rs = encode_resident<T>(rp, bits, pr.observed_site, out->tb, false);
+        b.obs_stage0 = rs.obs0;
+        b.pro_stage0 = rs.pro0;
+        b.pro_nstage = rs.npro;
+        b.step_stage0 = rs.step0;
+        b.step_nstage = rs.nstep;
+        b.last_stage0 = rs.last0;
+        for (const Op& op : rp.step.ops) fops += op.kind == 0;
+        // on-chip: about half the cost per amplitude of a tiled pass
+        out->dur = 0.5 * fops * std::ldexp(1.0, bits) * double(n_steps + 1);
+        return;
+    }
+    PassParams pp;
+    pp.k = K;
+    pp.r = batch_shape(f32, half).r;
+    // the library's default launch shape; a gang plans one scheduling
+    // variant (plan_stream), not the single path's variant search
+    pp.c = 4;
+    pp.half = half;
+    pp.gates = half ? kMaxGates : 0;
+    const StreamPlan sp = plan_stream(pr.M, *out->J, dt, n_steps, pr.observed_site, true, pp);
+    for (const HostPass& hp : sp.passes) encode_pass<T>(hp, pr.M, pr.observed_site, out->tb);
+    b.nlaunch = int(sp.launch_tmpl.size());
+    for (size_t l = 0; l < sp.launch_tmpl.size(); ++l)
+        out->launches.push_back(make_int2(sp.launch_tmpl[l], int(sp.launch_offset[l])));
+    b.ntiles = int64_t(1) << (pr.M - K);
+    b.gsize = int(std::min<int64_t>(b.ntiles, gang));
+    for (int t : sp.launch_tmpl)
+        for (const Op& op : sp.passes[t].ops) fops += op.kind == 0;
+    // factor work plus one sweep per launch, shared by the gang
+    out->dur = (fops + 6.0 * sp.launch_tmpl.size()) * std::ldexp(1.0, pr.M) / b.gsize;
+}
+
+template <typename T>
+static int build_tables(const std::vector<spin_problem>& probs, const std::vector<std::vector<Coupling>>& Js,
+                        double dt, int64_t n_steps, int nslots, bool half, BatchTables* bt) {
+    const bool f32 = sizeof(T) == 4;
+    const int K = batch_tile_bits(f32);
     const int KL = K - 1;               // largest one-workgroup problem
     // Workgroups per gang, at most: as many as leave every gang a slot of its
     // own, or nearly (half of the gangs may wait for another).  Stars of M = 14
@@ -107,108 +220,95 @@ static int batch_build(const spin_problem* probs, const std::vector<int>& sel,
     // 14.2 / 14.2 / 16.0 / 18.1; 2 steps of 256 18.7 / 19.5.
     auto demand = [&](int64_t g) {
         int64_t n = 0;
-        for (int p : sel) n += probs[p].M <= KL ? 1 : std::min(int64_t(1) << (probs[p].M - K), g);
+        for (const spin_problem& pr : probs)
+            n += pr.M <= KL ? 1 : std::min(int64_t(1) << (pr.M - K), g);
         return n;
     };
     int64_t gang = 8;
     while (2 * gang <= nslots && 2 * demand(2 * gang) <= 3 * int64_t(nslots)) gang *= 2;
     gang = std::min<int64_t>(gang, nslots);
-    DevTables<T> tb;
-    std::vector<BatchProblem> bp;
-    std::vector<int2> launches;
-    std::vector<double> dur;
-    int64_t part = 0;
-    int ncounter = 0;
-    // problems with equal (M, observed site, couplings) share their tables
+    // problems with equal (M, observed site, couplings) share their plan
     // (e.g. the basis-state members of one ensemble)
-    std::map<std::vector<double>, std::pair<BatchProblem, double>> shared;
-    for (int p : sel) {
-        const spin_problem& pr = probs[p];
-        std::vector<double> skey{double(pr.M), double(pr.observed_site)};
+    std::map<std::vector<double>, int> seen;
+    std::vector<ProblemPlan<T>> plans;
+    std::vector<int> plan_of(probs.size());
+    for (size_t p = 0; p < probs.size(); ++p) {
+        std::vector<double> skey{double(probs[p].M), double(probs[p].observed_site)};
         for (const Coupling& c : Js[p]) {
             skey.push_back(c.i);
             skey.push_back(c.j);
             skey.push_back(c.a);
             skey.push_back(c.b);
         }
-        BatchProblem b{};
-        double fops = 0;
-        auto hit = shared.find(skey);
-        if (hit != shared.end()) {
-            b = hit->second.first;
-            fops = hit->second.second;
-            if (b.gsize > 1 || b.M > KL) {   // gang: own partial sums and counter
-                b.part0 = part;
-                part += int64_t(kBatchRing) * b.gsize * 2;
-                b.counter = ncounter++;
+        const auto at = seen.emplace(skey, int(plans.size()));
+        if (at.second) {
+            plans.emplace_back();
+            plans.back().pr = &probs[p];
+            plans.back().J = &Js[p];
+        }
+        plan_of[p] = at.first->second;
+    }
+    // The plans do not depend on each other; a few threads make them (32
+    // stars of M = 14 to 20, 25 steps: the first call 1.37 s with one, 0.20 with 8).
+    std::atomic<size_t> next{0};
+    std::vector<std::exception_ptr> errors(plans.size());
+    auto work = [&] {
+        for (size_t i; (i = next.fetch_add(1)) < plans.size();) {
+            try {
+                plan_problem<T>(dt, n_steps, gang, half, &plans[i]);
+            } catch (...) {
+                errors[i] = std::current_exception();
             }
         }
-        b.psi = pr.psi;
-        b.P = pr.P_dev;
-        b.N = pr.N_dev;
-        b.seed = pr.seed;
-        b.M = pr.M;
-        b.polarized = pr.polarized_site;
-        b.init = init;
-        if (hit != shared.end()) {
-            dur.push_back(fops);
-            bp.push_back(b);
-            continue;
+    };
+    std::vector<std::thread> pool;
+    const size_t nthreads = std::min<size_t>({plans.size(), std::max(1u, std::thread::hardware_concurrency()), 8});
+    try {
+        while (pool.size() + 1 < nthreads) pool.emplace_back(work);
+    } catch (const std::system_error&) {
+        // no more threads to be had: those there are do the work
+    }
+    work();
+    for (std::thread& t : pool) t.join();
+    for (const std::exception_ptr& e : errors)
+        if (e) std::rethrow_exception(e);
+
+    DevTables<T> tb;
+    std::vector<int2> launches;
+    for (ProblemPlan<T>& pl : plans) {
+        const int pass0 = int(tb.passes.size()), stage0 = int(tb.stages.size()), op0 = int(tb.ops.size());
+        for (DevStage& s : pl.tb.stages) s.op0 += op0;
+        for (DevPass& s : pl.tb.passes) s.stage0 += stage0;
+        for (int32_t* f : {&pl.b.obs_stage0, &pl.b.pro_stage0, &pl.b.step_stage0, &pl.b.last_stage0}) *f += stage0;
+        pl.b.pass0 = pass0;
+        pl.b.launch0 = int64_t(launches.size());
+        tb.passes.insert(tb.passes.end(), pl.tb.passes.begin(), pl.tb.passes.end());
+        tb.stages.insert(tb.stages.end(), pl.tb.stages.begin(), pl.tb.stages.end());
+        tb.ops.insert(tb.ops.end(), pl.tb.ops.begin(), pl.tb.ops.end());
+        launches.insert(launches.end(), pl.launches.begin(), pl.launches.end());
+        pl.tb = DevTables<T>();
+    }
+    std::vector<double> dur;
+    for (size_t p = 0; p < probs.size(); ++p) {
+        const ProblemPlan<T>& pl = plans[plan_of[p]];
+        BatchProblem b = pl.b;
+        b.M = probs[p].M;
+        if (b.M > KL) {     // a gang: partial sums and a counter of its own
+            b.part0 = bt->part;
+            bt->part += int64_t(kBatchRing) * b.gsize * 2;
+            b.counter = bt->ncounters++;
         }
-        if (pr.M <= KL) {
-            const int bits = batch_resident_bits(pr.M, half);
-            const int r = bits - __builtin_ctz(batch_shape(f32, half).nt);
-            const ResidentPlan rp = plan_resident(bits, Js[p], dt, pr.observed_site, true, r);
-            b.gsize = 1;
-            const ResidentStages rs = encode_resident<T>(rp, bits, pr.observed_site, tb, false);
-            b.obs_stage0 = rs.obs0;
-            b.pro_stage0 = rs.pro0;
-            b.pro_nstage = rs.npro;
-            b.step_stage0 = rs.step0;
-            b.step_nstage = rs.nstep;
-            b.last_stage0 = rs.last0;
-            for (const Op& op : rp.step.ops) fops += op.kind == 0;
-            // on-chip: about half the cost per amplitude of a tiled pass
-            fops = 0.5 * fops * std::ldexp(1.0, bits) * double(n_steps + 1);
-            dur.push_back(fops);
-        } else {
-            PassParams pp;
-            pp.k = K;
-            pp.r = R;
-            // the library's default launch shape; a gang plans one scheduling
-            // variant (plan_stream), not the single path's variant search
-            pp.c = 4;
-            pp.half = half;
-            pp.gates = half ? kMaxGates : 0;
-            StreamPlan sp = plan_stream(pr.M, Js[p], dt, n_steps, pr.observed_site, true, pp);
-            b.pass0 = int(tb.passes.size());
-            for (const HostPass& hp : sp.passes) encode_pass<T>(hp, pr.M, pr.observed_site, tb);
-            b.launch0 = int64_t(launches.size());
-            b.nlaunch = int(sp.launch_tmpl.size());
-            for (size_t l = 0; l < sp.launch_tmpl.size(); ++l)
-                launches.push_back(make_int2(sp.launch_tmpl[l], int(sp.launch_offset[l])));
-            b.ntiles = int64_t(1) << (pr.M - K);
-            b.gsize = int(std::min<int64_t>(b.ntiles, gang));
-            b.part0 = part;
-            part += int64_t(kBatchRing) * b.gsize * 2;
-            b.counter = ncounter++;
-            for (int t : sp.launch_tmpl)
-                for (const Op& op : sp.passes[t].ops) fops += op.kind == 0;
-            // factor work plus one sweep per launch, shared by the gang
-            fops = (fops + 6.0 * sp.launch_tmpl.size()) * std::ldexp(1.0, pr.M) / b.gsize;
-            dur.push_back(fops);
-        }
-        shared[skey] = {b, fops};
-        bp.push_back(b);
+        dur.push_back(pl.dur);
+        bt->probs.push_back(b);
     }
     // Gang schedule: longest jobs first, each on the slots that are free first.
     std::vector<double> avail(nslots, 0.0);
     std::vector<std::vector<BatchJob>> lists(nslots);
-    std::vector<int> order(bp.size()), slots(nslots);
+    std::vector<int> order(bt->probs.size()), slots(nslots);
     for (size_t i = 0; i < order.size(); ++i) order[i] = int(i);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return dur[a] > dur[b]; });
     for (int q : order) {
-        const int g = bp[q].gsize;
+        const int g = bt->probs[q].gsize;
         for (int w = 0; w < nslots; ++w) slots[w] = w;
         std::partial_sort(slots.begin(), slots.begin() + g, slots.end(), [&](int a, int b) {
             return avail[a] < avail[b] || (avail[a] == avail[b] && a < b);
@@ -228,27 +328,32 @@ static int batch_build(const spin_problem* probs, const std::vector<int>& sel,
     }
     jstart[nslots] = int(jobs.size());
 
-    auto up = [&](const void* src, size_t n, void** dst) -> int {
-        if (n == 0) n = 16;
-        if (hipMalloc(dst, n) != hipSuccess) return fail(SPIN_ENOMEM, "batch table allocation failed");
-        if (src && hipMemcpy(*dst, src, n, hipMemcpyHostToDevice) != hipSuccess)
-            return fail(SPIN_EHIP, "batch table upload failed");
-        return SPIN_OK;
-    };
     int rc;
-    if ((rc = up(bp.data(), bp.size() * sizeof(BatchProblem), &bc->d_probs))) return rc;
-    if ((rc = up(jobs.data(), jobs.size() * sizeof(BatchJob), &bc->d_jobs))) return rc;
-    if ((rc = up(jstart.data(), jstart.size() * sizeof(int), &bc->d_jstart))) return rc;
-    if ((rc = up(tb.passes.data(), tb.passes.size() * sizeof(DevPass), &bc->d_passes))) return rc;
-    if ((rc = up(tb.stages.data(), tb.stages.size() * sizeof(DevStage), &bc->d_stages))) return rc;
-    if ((rc = up(tb.ops.data(), tb.ops.size() * sizeof(DevOp<T>), &bc->d_ops))) return rc;
-    if ((rc = up(launches.data(), launches.size() * sizeof(int2), &bc->d_launch))) return rc;
-    if ((rc = up(nullptr, std::max<int64_t>(part, 2) * sizeof(double), &bc->d_part))) return rc;
-    if ((rc = up(nullptr, std::max(ncounter, 1) * sizeof(int), &bc->d_ctr))) return rc;
-    if ((rc = up(nullptr, sizeof(int), &bc->d_err))) return rc;
+    if ((rc = upload(jobs.data(), jobs.size() * sizeof(BatchJob), &bt->d_jobs))) return rc;
+    if ((rc = upload(jstart.data(), jstart.size() * sizeof(int), &bt->d_jstart))) return rc;
+    if ((rc = upload(tb.passes.data(), tb.passes.size() * sizeof(DevPass), &bt->d_passes))) return rc;
+    if ((rc = upload(tb.stages.data(), tb.stages.size() * sizeof(DevStage), &bt->d_stages))) return rc;
+    if ((rc = upload(tb.ops.data(), tb.ops.size() * sizeof(DevOp<T>), &bt->d_ops))) return rc;
+    return upload(launches.data(), launches.size() * sizeof(int2), &bt->d_launch);
+}
+
+static int build_call(const std::vector<spin_problem>& probs, int init, int nslots, bool half, BatchCache* bc) {
+    std::vector<BatchProblem> bp = bc->tables->probs;
+    for (size_t p = 0; p < bp.size(); ++p) {
+        bp[p].psi = probs[p].psi;
+        bp[p].P = probs[p].P_dev;
+        bp[p].N = probs[p].N_dev;
+        bp[p].seed = probs[p].seed;
+        bp[p].polarized = probs[p].polarized_site;
+        bp[p].init = init;
+    }
+    int rc;
+    if ((rc = upload(bp.data(), bp.size() * sizeof(BatchProblem), &bc->d_probs))) return rc;
+    if ((rc = upload(nullptr, std::max<int64_t>(bc->tables->part, 2) * sizeof(double), &bc->d_part))) return rc;
+    if ((rc = upload(nullptr, std::max(bc->tables->ncounters, 1) * sizeof(int), &bc->d_ctr))) return rc;
+    if ((rc = upload(nullptr, sizeof(int), &bc->d_err))) return rc;
     bc->nslots = nslots;
     bc->half = half;
-    bc->ncounters = std::max(ncounter, 1);
     return SPIN_OK;
 }
 
@@ -280,13 +385,31 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
     }
     if (!bc) {
         bc = std::make_shared<BatchCache>();
-        int rc;
-        try {
-            rc = batch_build<T>(probs, sel, Js, dt, n_steps, init, nslots, half, bc.get());
-        } catch (const std::exception& e) {
-            return fail(SPIN_EUNSUPPORTED, std::string("batch planning failed: ") + e.what());
+        const std::vector<double> tkey = tables_key(ps.data(), int(ps.size()), js, prec, dt, n_steps, dev, half);
+        {
+            std::lock_guard<std::mutex> lk(g_bmu);
+            for (auto it = g_btables.begin(); it != g_btables.end(); ++it)
+                if (it->first == tkey) {
+                    bc->tables = it->second;
+                    g_btables.splice(g_btables.begin(), g_btables, it);
+                    break;
+                }
         }
-        if (rc) return rc;
+        int rc;
+        if (!bc->tables) {
+            auto bt = std::make_shared<BatchTables>();
+            try {
+                rc = build_tables<T>(ps, js, dt, n_steps, nslots, half, bt.get());
+            } catch (const std::exception& e) {
+                return fail(SPIN_EUNSUPPORTED, std::string("batch planning failed: ") + e.what());
+            }
+            if (rc) return rc;
+            bc->tables = bt;
+            std::lock_guard<std::mutex> lk(g_bmu);
+            g_btables.emplace_front(tkey, bt);
+            if (g_btables.size() > kBatchTablesKept) g_btables.pop_back();
+        }
+        if ((rc = build_call(ps, init, nslots, half, bc.get()))) return rc;
         std::lock_guard<std::mutex> lk(g_bmu);
         g_bcache[key] = bc;
     }
@@ -294,15 +417,20 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
     if (int rc = status_word(dev, &status)) return rc;
     auto enqueue = [&](hipStream_t s) {
         return launch_batch<T>(bc->nslots, bc->half, static_cast<const BatchProblem*>(bc->d_probs),
-                               static_cast<const BatchJob*>(bc->d_jobs),
-                               static_cast<const int*>(bc->d_jstart),
-                               static_cast<const DevPass*>(bc->d_passes),
-                               static_cast<const DevStage*>(bc->d_stages),
-                               static_cast<const DevOp<T>*>(bc->d_ops),
-                               static_cast<const int2*>(bc->d_launch),
+                               static_cast<const BatchJob*>(bc->tables->d_jobs),
+                               static_cast<const int*>(bc->tables->d_jstart),
+                               static_cast<const DevPass*>(bc->tables->d_passes),
+                               static_cast<const DevStage*>(bc->tables->d_stages),
+                               static_cast<const DevOp<T>*>(bc->tables->d_ops),
+                               static_cast<const int2*>(bc->tables->d_launch),
                                static_cast<double*>(bc->d_part), static_cast<int*>(bc->d_ctr),
-                               bc->ncounters, static_cast<int*>(bc->d_err), status, n_steps, s);
+                               std::max(bc->tables->ncounters, 1), static_cast<int*>(bc->d_err), status, n_steps, s);
     };
+    std::lock_guard<std::mutex> launch_lock(g_launch_mu);
+    hipEvent_t& last = g_last_launch[dev];
+    const bool first = last == nullptr;
+    if (first && hipEventCreateWithFlags(&last, hipEventDisableTiming) != hipSuccess)
+        return fail(SPIN_EHIP, "event create failed");
     hipError_t e = hipSuccess;
     if (use_graph) {
         // capture on a library stream ordered after the caller's stream
@@ -323,12 +451,16 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
             return fail(SPIN_EHIP, "event create failed");
         e = hipEventRecord(ev, st);
         if (e == hipSuccess) e = hipStreamWaitEvent(bc->side, ev, 0);
+        if (e == hipSuccess && !first) e = hipStreamWaitEvent(bc->side, last, 0);
         if (e == hipSuccess) e = hipGraphLaunch(bc->exec, bc->side);
+        if (e == hipSuccess) e = hipEventRecord(last, bc->side);
         if (e == hipSuccess) e = hipEventRecord(ev, bc->side);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, ev, 0);
         (void)hipEventDestroy(ev);
     } else {
-        e = enqueue(st);
+        if (!first) e = hipStreamWaitEvent(st, last, 0);
+        if (e == hipSuccess) e = enqueue(st);
+        if (e == hipSuccess) e = hipEventRecord(last, st);
     }
     if (e != hipSuccess) return fail(SPIN_EHIP, std::string("batch launch: ") + hipGetErrorString(e));
     return SPIN_OK;

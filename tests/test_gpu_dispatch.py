@@ -98,3 +98,40 @@ def test_initial_states_and_observable_at_every_kind_of_site(prec, M):
                 w = np.abs(got) ** 2
                 sgn = 1.0 - 2.0 * ((np.arange(2 ** M) >> site) & 1)
                 assert abs(float(P[0]) - float((w * sgn).sum())) < 1e-12
+
+
+@pytest.mark.parametrize("prec", [C128, C64])
+def test_batches_of_equal_couplings_share_tables_not_states(prec):
+    """Equal couplings with other states, seeds, polarised sites and initial
+    kinds, two of them in flight on two streams, against single runs."""
+    import torch
+    note("batch tables", prec)
+    dt, steps = 0.03, 4
+    nets = [(9, workloads.ladder(4) + [(0, 8, 0.2, 0.3)]), (15, workloads.star(15, 3)), (17, workloads.star(17, 4)),
+            (15, workloads.star(15, 3))]
+    spq.spin_release_caches()
+
+    def problems(first):
+        return [{"psi": torch.zeros(2 ** M, dtype=torch_dtype(prec), device="cuda"), "M": M, "couplings": J,
+                 "observed_site": 1, "polarized_site": (first + q) % M, "seed": first + q,
+                 "P": torch.zeros(steps + 1, dtype=torch.float64, device="cuda"),
+                 "N": torch.zeros(steps + 1, dtype=torch.float64, device="cuda")} for q, (M, J) in enumerate(nets)]
+
+    calls = [(problems(3), spq.SPIN_INIT_RANDOM_PHASE), (problems(40), spq.SPIN_INIT_RANDOM_PHASE),
+             (problems(5), spq.SPIN_INIT_PRODUCT)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for k, (ps, init) in enumerate(calls):
+        spq.spin_trotter_evolve_batch(ps, prec, dt, steps, init=init, stream=streams[k % 2].cuda_stream)
+    torch.cuda.synchronize()
+    assert spq.spin_batch_status() == 0
+    for ps, init in calls:
+        for p in ps:
+            psi = torch.empty_like(p["psi"])
+            P, N = torch.zeros_like(p["P"]), torch.zeros_like(p["P"])
+            make = spq.spin_init_product if init == spq.SPIN_INIT_PRODUCT else spq.spin_init_random_phase
+            make(psi, p["M"], p["polarized_site"], p["seed"])
+            spq.spin_trotter_evolve_ex(psi, p["M"], p["couplings"], dt, steps, 1, P, N)
+            torch.cuda.synchronize()
+            assert float((P - p["P"]).abs().max()) < TOL_P[prec]
+            assert_state_close(p["psi"].cpu().numpy().astype(np.complex128), psi.cpu().numpy().astype(np.complex128), prec)
