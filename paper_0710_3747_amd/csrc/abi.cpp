@@ -257,6 +257,10 @@ static void set_stages(const ResidentStages& rs, ResidentJob* j) {
     j->last_stage0 = rs.last0;
 }
 
+// Workgroups per pass, at most; each leaves its partial sums of every step, the
+// profile's for every site.
+constexpr int64_t kMaxWg = 1 << 14, kMaxWgProfile = 1 << 12;
+
 // Planner settings of an exchange mode.
 static void exchange_params(ExchangeMode x, PassParams* pp) {
     pp->half = x == kHalfTiles;
@@ -267,11 +271,11 @@ static void exchange_params(ExchangeMode x, PassParams* pp) {
 // The passes of a tiled call.  complex128 states from M = 27 on by default
 // also try tiles of 2^14 (one workgroup per CU): a pass with more factors takes
 // longer, so they are taken where they save enough launches (ladder M = 30, 10
-// steps: 21 passes of 7.54 ms against 13 of 10.1 ms; M = 28, 21 steps: 36 of
-// 1.96 against 27 of 2.50, 8 steps: 15 of 1.94 against 12 of 2.40, 5 steps: 11
-// of 1.88 against 9 of 2.37; star M = 28 40 of 2.18 against 35 of 2.73; below
+// steps: 21 passes of 7.2 ms against 13 of 10.1 ms; M = 28, 21 steps: 36 of
+// 1.85 against 27 of 2.50, 8 steps: 15 of 1.85 against 12 of 2.40, 5 steps: 11
+// of 1.80 against 9 of 2.37; star M = 28 40 of 2.1 against 35 of 2.73; below
 // M = 27, where the state stays in the last-level cache for longer, star M = 26
-// 35 of 0.567 against 25 of 0.797, ladder M = 26 28 of 0.50 against 21 of 0.69).
+// 35 of 0.53 against 25 of 0.797, ladder M = 26 28 of 0.48 against 21 of 0.69).
 static StreamPlan plan_tiled(int M, const std::vector<Coupling>& J, double dt, int64_t n_steps, int observed,
                              bool merge, bool profile, Shape* sh) {
     auto plan = [&](const Shape& s) {
@@ -290,7 +294,7 @@ static StreamPlan plan_tiled(int M, const std::vector<Coupling>& J, double dt, i
         large.k = 14;
         large.nt = 512;
         StreamPlan lp = plan(large);
-        if (4 * sp.launch_tmpl.size() > 5 * lp.launch_tmpl.size()) {
+        if (10 * sp.launch_tmpl.size() > 13 * lp.launch_tmpl.size()) {
             *sh = large;
             return lp;
         }
@@ -326,9 +330,21 @@ static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, Shape 
                 hipDeviceProp_t prop;
                 if (hipGetDeviceProperties(&prop, key.dev) == hipSuccess) dev_cu = prop.multiProcessorCount;
             }
-            // persistent grid: a power of two <= tiles, ~4 workgroups per CU
+            // Where one workgroup fills a CU (whole tiles, which prefetch the
+            // next one; complex128 tiles of 2^14), a persistent grid, ~4
+            // workgroups per CU.  Else a workgroup per tile, up to kMaxWg: a
+            // CU draws the next one when it is done, where a persistent grid
+            // left a seventh of the wavefront slots empty at its end.  us per
+            // pass with 4 / 16 / 64 workgroups per CU and one per tile,
+            // complex64: ladder M = 30 5189 / 4785 / 4693 / 4719, M = 28 1284 /
+            // 1201 / 1163, M = 26 337 / 301; star M = 28 1348 / 1250 / 1206;
+            // complex128 ladder M = 30 7626 / 7271 / 7174 / 7226, star M = 26
+            // 573 / 552 / 530, but with tiles of 2^14 ladder M = 30 10119 /
+            // - / 10570.
+            const bool alone = sh.exchange == kWholeTiles || (sizeof(T) == 8 && sh.k == 14);
+            const int64_t most = alone ? int64_t(dev_cu) * 4 : dp->profile ? kMaxWgProfile : kMaxWg;
             int64_t nwg = 1;
-            while (nwg * 2 <= ntiles && nwg * 2 <= int64_t(dev_cu) * 4) nwg *= 2;
+            while (nwg * 2 <= ntiles && nwg * 2 <= most) nwg *= 2;
             dp->nwg = int(nwg);
             dp->tiles_per_wg = ntiles / nwg;
             for (const HostPass& hp : dp->sp.passes) {
@@ -626,24 +642,28 @@ static int evolve_fused(void* psi, int M, const std::vector<Coupling>& J, double
         return SPIN_OK;
     }
     const int64_t total = n_steps + 1;
-    int ch = int(std::min<int64_t>(total, 1024));
+    // A launch measures at most kMaxMeas consecutive steps and the slots are
+    // reduced once half of them are in use, so 2 * kMaxMeas slots suffice; as
+    // many as 16 MiB hold, or the workspace.
+    int nwg = dp->nwg;
+    int ch = int(std::min<int64_t>(total, std::max(2 * kMaxMeas, (1 << 20) / nwg)));
+    ch = std::min(ch, 1024);
     void* scratch = nullptr;
     if (ws) {
-        // as many step slots as the workspace holds; a launch measures at
-        // most kMaxMeas consecutive steps and the slots are reduced once half
-        // of them are in use, so 2 * kMaxMeas slots suffice
-        const int64_t fit = int64_t(ws->doubles / (size_t(2) * size_t(dp->nwg)));
-        ch = int(std::min<int64_t>(ch, fit));
+        auto fit = [&] { return int64_t(ws->doubles / (size_t(2) * size_t(nwg))); };
+        while (nwg > 1 && fit() < std::min<int64_t>(total, 2 * kMaxMeas)) nwg /= 2;
+        ch = int(std::min<int64_t>(std::min<int64_t>(total, 1024), fit()));
         if (ch < std::min<int64_t>(total, 2 * kMaxMeas)) {
             std::ostringstream os;
-            os << "workspace too small: " << dp->nwg << " workgroups need " << 2 * kMaxMeas * 2 * dp->nwg
+            os << "workspace too small: " << nwg << " workgroups need " << 2 * kMaxMeas * 2 * nwg
                << " doubles, the allocation-free workspace holds " << ws->doubles;
             return fail(SPIN_EUNSUPPORTED, os.str());
         }
         scratch = ws->ptr;
-    } else if ((rc = scratch_get(st, size_t(ch) * dp->nwg * 2 * sizeof(double), &scratch))) {
+    } else if ((rc = scratch_get(st, size_t(ch) * nwg * 2 * sizeof(double), &scratch))) {
         return rc;
     }
+    const int64_t tiles_per_wg = dp->tiles_per_wg * (dp->nwg / nwg);
     double* part = static_cast<double*>(scratch);
     auto enqueue = [&](hipStream_t st) -> int {
         int64_t measured = 0, reduced = 0;
@@ -656,11 +676,11 @@ static int evolve_fused(void* psi, int M, const std::vector<Coupling>& J, double
             shp.writes = dp->sp.passes[t].writes;
             HIP_TRY((launch_pass<T>(shp, psi, static_cast<const DevPass*>(dp->d_passes),
                                     static_cast<const DevStage*>(dp->d_stages),
-                                    static_cast<const DevOp<T>*>(dp->d_ops), t, dp->tiles_per_wg,
-                                    dp->nwg, part, off, ch, st)));
+                                    static_cast<const DevOp<T>*>(dp->d_ops), t, tiles_per_wg,
+                                    nwg, part, off, ch, st)));
             for (int64_t s : dp->meas[t]) measured = std::max(measured, s + off + 1);
             if (measured - reduced >= ch / 2 || (l + 1 == nl && measured > reduced)) {
-                HIP_TRY(launch_reduce(part, dp->nwg, ch, reduced, measured - reduced, P, N, st));
+                HIP_TRY(launch_reduce(part, nwg, ch, reduced, measured - reduced, P, N, st));
                 reduced = measured;
             }
         }

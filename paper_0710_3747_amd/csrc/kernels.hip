@@ -302,18 +302,19 @@ __global__ __launch_bounds__(256) void k_reduce_profile(const double* __restrict
 }
 
 // partials: [slot][nwg][2]; P/N for steps s0..s1-1, slot = s % ch.
-__global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ partials, int nwg, int ch,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_reduce(const double* __restrict__ partials, int nwg, int ch,
                                                 int64_t s0, double* __restrict__ P,
                                                 double* __restrict__ N) {
-    __shared__ double red[8];
+    __shared__ double red[2 * (NT / 64)];
     const int64_t s = s0 + blockIdx.x;
     const double* base = partials + (size_t)(s % ch) * nwg * 2;
     double p = 0.0, n = 0.0;
-    for (int w = threadIdx.x; w < nwg; w += 256) {
+    for (int w = threadIdx.x; w < nwg; w += NT) {
         p += base[2 * w];
         n += base[2 * w + 1];
     }
-    block_sum2<256>(p, n, red);
+    block_sum2<NT>(p, n, red);
     if (threadIdx.x == 0) {
         P[s] = p;
         if (N) N[s] = n;
@@ -2015,8 +2016,11 @@ hipError_t launch_reduce_profile(const double* partials, int nwg, int ch, int M,
 hipError_t launch_reduce(const double* partials, int nwg, int ch, int64_t s0, int64_t count,
                          double* P, double* N, hipStream_t st) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce, dim3(unsigned(count)), dim3(256), 0, st, partials, nwg, ch, s0,
-                       P, N);
+    // one workgroup per step: a large one where it has many partial sums to read
+    if (nwg > 4096)
+        hipLaunchKernelGGL(k_reduce<1024>, dim3(unsigned(count)), dim3(1024), 0, st, partials, nwg, ch, s0, P, N);
+    else
+        hipLaunchKernelGGL(k_reduce<256>, dim3(unsigned(count)), dim3(256), 0, st, partials, nwg, ch, s0, P, N);
     return hipGetLastError();
 }
 
