@@ -1754,12 +1754,17 @@ __global__ __launch_bounds__(NT) void k_resident(ResidentJob job0,
 constexpr uint64_t kGangWaitTicks = 20ull * 100000000ull;   // 20 s
 
 __device__ __forceinline__ bool gang_barrier(int* counter, int target, int* err) {
-    // release: this workgroup's global stores, visible device-wide
-    __threadfence();
+    // Every wave waits until its stores are in the XCD's L2; after the barrier
+    // one lane writes that back for all (release) and, when the gang has met,
+    // invalidates what the CU and the L2 hold (acquire).  A release by every
+    // wave wrote the L2 back four times: 32 stars of M = 14 to 20, 25 steps,
+    // 20.5 -> 16.9 ms.
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
     __shared__ int ok_s;
     if (threadIdx.x == 0) {
         int ok = 1;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         atomicAdd(counter, 1);
         const uint64_t t0 = wall_clock64();
         while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
@@ -1771,7 +1776,7 @@ __device__ __forceinline__ bool gang_barrier(int* counter, int target, int* err)
                 break;
             }
         }
-        __threadfence();    // acquire
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         ok_s = ok;
     }
     __syncthreads();
