@@ -214,10 +214,11 @@ static int build_tables(const std::vector<spin_problem>& probs, const std::vecto
     const int K = batch_tile_bits(f32);
     const int KL = K - 1;               // largest one-workgroup problem
     // Workgroups per gang, at most: as many as leave every gang a slot of its
-    // own, or nearly (half of the gangs may wait for another).  Stars of M = 14
-    // to 20, 10 steps, ms with gangs of 8 / 16 / 32 / 64: 32 problems 16.5 / 10.2
-    // / 9.5 / 11.3, 4 of M = 20 14.2 / 7.7 / 4.9 / 3.6; 4 steps of 128 problems
-    // 14.2 / 14.2 / 16.0 / 18.1; 2 steps of 256 18.7 / 19.5.
+    // own, or nearly (a third of them may wait for another).  Stars of M = 14 to
+    // 20, ms where the batch may ask for 1 / 1.5 / 2 / 3 times the slots: 32
+    // problems, 25 steps 21.0 / 16.9 / 18.4 / 18.2; 64
+    // problems, 5 steps 11.1 / 7.5 / 7.9 / 8.5; 128, 4 steps 13.2 / 13.1 / 13.1 /
+    // 12.8; complex128, 32 problems, 5 steps 10.8 / 8.5 / 8.5 / 9.5.
     auto demand = [&](int64_t g) {
         int64_t n = 0;
         for (const spin_problem& pr : probs)

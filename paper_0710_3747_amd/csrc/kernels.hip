@@ -5,11 +5,13 @@
 //  k_init_members  2^c basis-state members of the ensemble stacked as one
 //                state of M + c sites (member index on the top c bits)
 //  k_accumulate  member sums of consecutive evolutions, in order
-//  k_pass        one tiled sweep: a 2^k-amplitude tile per workgroup is
-//                staged through LDS; register stages apply the two-spin
-//                factors as three-shear rotations; observables are
-//                accumulated in FP64 and reduced per workgroup
-//  k_resident    whole state in one workgroup's LDS for every step
+//  k_pass        one tiled sweep: a 2^k-amplitude tile per workgroup is held
+//                in registers, whose stages apply the two-spin factors as
+//                three-shear rotations and exchange through LDS; observables
+//                are accumulated in FP64 and reduced per workgroup
+//  k_resident    whole state in one workgroup's registers for every step
+//  k_batch       many problems in one launch: whole ones in a workgroup, larger
+//                ones by gangs of workgroups that meet after every pass
 //  k_factor      one factor over the whole state (the unfused schedule)
 //  k_observe     observable of a state as it is
 //  k_reduce      fixed-order reduction of per-workgroup partial sums
@@ -1349,10 +1351,12 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
 
 // Same for passes that exchange through per-lane slots (HALF: in two halves).
 // No register prefetch: several workgroups share a CU and cover each other's
-// loads.  What bounds it, per CU: M = 30 complex64 tiles of 2^14 take 3.5 ms per
-// pass for the sweep alone, about 3.2 ms of VALU issue and 2 ms of LDS traffic,
-// of which two workgroups overlap part; one-tile launches (M <= 20) take the
-// sum of the three.
+// loads (half of the next tile prefetched into the registers that are left
+// gained 2 % with several tiles per workgroup and nothing with one).  What
+// bounds it, per CU: M = 30 complex64 tiles of 2^14 take 3.5 ms per pass for the
+// sweep alone, about 3 ms of VALU issue and 1.4 ms of LDS traffic, of which two
+// workgroups overlap a part: 4.7 ms (star M = 28: VALU busy 69 % of the time);
+// small tiles (M <= 20) take the sum of the three.
 template <typename T, int R, int NT, bool WRITES, bool PROFILE, bool HALF>
 __device__ __forceinline__ void slot_tiles(typename CT<T>::c* __restrict__ psi, const DevPass& P,
                                            const DevStage* __restrict__ stages,
@@ -1438,7 +1442,11 @@ __device__ __forceinline__ void slot_tiles(typename CT<T>::c* __restrict__ psi, 
                 }
             }
             if (si + 1 < nstage) {
+                // few instructions between two waits: they go before the other
+                // workgroup's arithmetic (star M = 28 64.8 -> 64.0 ms)
+                if constexpr (HALF) __builtin_amdgcn_s_setprio(2);
                 exchange<R, ROW, HALF>(v, ldsb, own, xw, prev_cross);
+                if constexpr (HALF) __builtin_amdgcn_s_setprio(0);
             }
         }
         if constexpr (WRITES)
