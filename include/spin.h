@@ -133,11 +133,13 @@ typedef struct {
                              complex64, 13 for complex128, smaller for states that
                              would leave CUs idle: 10 to 12 up to M = 20, 13 at
                              M = 21; complex128 also takes 14, with half tiles and
-                             one workgroup per CU).  By default one workgroup holds
+                             one workgroup per CU, by default from M = 27 on where
+                             that saves enough passes).  By default one workgroup holds
                              states up to M = 13 (complex128 12, with I^z I^z parts
                              11); with options, allocation-free calls and under
                              stream capture up to M = 14 (complex128 13) */
-    int32_t reg_bits;     /* amplitudes per lane = 2^reg_bits; 0 = default */
+    int32_t reg_bits;     /* amplitudes per lane = 2^reg_bits; 0 = default (6 for
+                             complex64 from M = 24 on, 5 or less below) */
     int32_t coalesce_bits;/* low address bits every tile keeps; 0 = default (4) */
     int32_t engine;       /* 0 = VALU butterflies (default); 1 = each register stage's
                              factors as one dense 32 x 32 complex matrix on FP32 MFMA
@@ -272,8 +274,10 @@ enum {
  * The states must not overlap.  The work is enqueued on `stream` and the
  * call returns without synchronising (the first call with a new problem set
  * plans and uploads its tables synchronously; later equal calls reuse them
- * until spin_release_caches).  Problems larger than one workgroup's tile run
- * as gangs of workgroups that meet at bounded device-wide barriers; if a
+ * until spin_release_caches, and calls with other states, seeds or outputs
+ * reuse the tables of their couplings).  Problems larger than one workgroup's
+ * tile run as gangs of workgroups that meet at bounded device-wide barriers,
+ * so batched launches on one device run one after the other; if a
  * barrier times out, the problem's P is set to NaN and spin_batch_status
  * reports it.  Errors as spin_trotter_evolve (plus SPIN_EINVAL for a bad
  * init or a basis index >= 2^M), reported for the first offending problem.
