@@ -3,15 +3,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
-#include <exception>
 #include <list>
 #include <map>
 #include <memory>
 #include <mutex>
 #include <sstream>
-#include <thread>
 #include <vector>
 
 #include "../../include/spin.h"
@@ -251,28 +248,7 @@ static int build_tables(const std::vector<spin_problem>& probs, const std::vecto
     }
     // The plans do not depend on each other; a few threads make them (32
     // stars of M = 14 to 20, 25 steps: the first call 1.37 s with one, 0.20 with 8).
-    std::atomic<size_t> next{0};
-    std::vector<std::exception_ptr> errors(plans.size());
-    auto work = [&] {
-        for (size_t i; (i = next.fetch_add(1)) < plans.size();) {
-            try {
-                plan_problem<T>(dt, n_steps, gang, half, &plans[i]);
-            } catch (...) {
-                errors[i] = std::current_exception();
-            }
-        }
-    };
-    std::vector<std::thread> pool;
-    const size_t nthreads = std::min<size_t>({plans.size(), std::max(1u, std::thread::hardware_concurrency()), 8});
-    try {
-        while (pool.size() + 1 < nthreads) pool.emplace_back(work);
-    } catch (const std::system_error&) {
-        // no more threads to be had: those there are do the work
-    }
-    work();
-    for (std::thread& t : pool) t.join();
-    for (const std::exception_ptr& e : errors)
-        if (e) std::rethrow_exception(e);
+    run_on_threads(plans.size(), [&](size_t i) { plan_problem<T>(dt, n_steps, gang, half, &plans[i]); });
 
     DevTables<T> tb;
     std::vector<int2> launches;

@@ -3,13 +3,16 @@
 #include "planner.hpp"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <complex>
 #include <cstdio>
+#include <exception>
 #include <functional>
 #include <map>
 #include <sstream>
 #include <stdexcept>
+#include <thread>
 
 namespace spinqp {
 
@@ -1199,6 +1202,19 @@ StreamPlan plan_stream(int M, const std::vector<Coupling>& J, double dt, int64_t
                        int observed, bool merge, const PassParams& pp) {
     if (M > 63) throw std::runtime_error("planner: M too large");
     const int64_t kGen = 48;     // steps scheduled when searching for a period
+    // Small tiles (states up to M = 21) run in a fraction of a millisecond per
+    // step, so the planning of a call with new couplings shows beside it: a
+    // repeating schedule, found after a few steps, is taken as it is, without
+    // the blocks of kGen steps (or of the whole run) to compare it with.  Stars,
+    // ladders, chains and random graphs of M = 12 to 20, 17 to 250 steps: the
+    // same launches, planned in 8 instead of 88 ms (dipolar star M = 14, 40
+    // steps), 20 instead of 150 ms (star M = 17, 100 steps).
+    if (pp.once && n_steps > 16) {
+        try {
+            return plan_stream_periodic(M, J, dt, n_steps, observed, merge, pp, kGen);
+        } catch (const std::runtime_error&) {
+        }
+    }
     if (n_steps <= 2 * kGen)
         return plan_stream_blocks(M, J, dt, n_steps, observed, merge, pp, std::max<int64_t>(n_steps, 1));
     StreamPlan best;
@@ -1231,6 +1247,32 @@ double plan_cost(const StreamPlan& plan, const PlanCostModel& cm) {
     return c;
 }
 
+void run_on_threads(size_t n, const std::function<void(size_t)>& job) {
+    std::atomic<size_t> next{0};
+    std::vector<std::exception_ptr> errors(n);
+    auto work = [&] {
+        for (size_t i; (i = next.fetch_add(1)) < n;) {
+            try {
+                job(i);
+            } catch (...) {
+                errors[i] = std::current_exception();
+            }
+        }
+    };
+    const size_t most = std::min<size_t>({n, std::max(1u, std::thread::hardware_concurrency()), 8});
+    std::vector<std::thread> pool;
+    pool.reserve(most);
+    try {
+        while (pool.size() + 1 < most) pool.emplace_back(work);
+    } catch (...) {
+        // no more threads to be had: those there are do the work
+    }
+    work();
+    for (std::thread& t : pool) t.join();
+    for (const std::exception_ptr& e : errors)
+        if (e) std::rethrow_exception(e);
+}
+
 StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, int64_t n_steps,
                             int observed, bool merge, const PassParams& pp,
                             const PlanCostModel& cm) {
@@ -1250,7 +1292,7 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
                 if (window == 5 && policy != 2) continue;
                 PassParams v = pp;
                 v.half = false;
-                v.rank = pp.half;
+                v.rank = true;
                 v.window = window;
                 v.low_policy = policy;
                 v.rotate = rotate % std::max(M, 1);
@@ -1258,16 +1300,21 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
             }
     const double work = std::ldexp(double(std::max<int64_t>(n_steps, 1)), M);
     const size_t nv = work < std::ldexp(1.0, 28) ? 1 : work < std::ldexp(1.0, 33) ? 4 : vs.size();
-    StreamPlan best;
+    // The variants do not depend on each other; a few threads plan them and the
+    // first of the cheapest is kept, whatever the order they end in (ladder
+    // M = 30 complex128, 20 steps, two shapes: 950 ms with one, 205 with 8).
+    std::vector<StreamPlan> plans(nv);
+    run_on_threads(nv, [&](size_t i) { plans[i] = plan_stream(M, J, dt, n_steps, observed, merge, vs[i]); });
+    size_t at = 0;
     double best_cost = 0;
     for (size_t i = 0; i < nv; ++i) {
-        StreamPlan sp = plan_stream(M, J, dt, n_steps, observed, merge, vs[i]);
-        const double c = plan_cost(sp, cm);
+        const double c = plan_cost(plans[i], cm);
         if (i == 0 || c < best_cost) {
-            best = std::move(sp);
+            at = i;
             best_cost = c;
         }
     }
+    StreamPlan best = std::move(plans[at]);
     // The chosen plan's register stages again, with a beam search (too slow
     // for every variant); a pass keeps whichever staging is shorter.  For
     // half-tile exchanges every pass is staged again around its split
@@ -1275,12 +1322,16 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
     if (pp.half) {
         for (HostPass& hp : best.passes)
             plan_stages_coalesced(hp, std::min(pp.r, int(hp.sites.size())), pp.c, nv > 1 ? 32 : 1, true, pp.gates);
-    } else if (nv > 1) {
+    } else {
         for (HostPass& hp : best.passes) {
-            HostPass alt = hp;
-            plan_stages_coalesced(alt, std::min(pp.r, int(alt.sites.size())), pp.c, 32, false, pp.gates, false,
-                                  pp.once);
-            if (alt.stages.size() < hp.stages.size()) hp.stages = std::move(alt.stages);
+            const int r = std::min(pp.r, int(hp.sites.size()));
+            if (nv > 1) {
+                HostPass alt = hp;
+                plan_stages_coalesced(alt, r, pp.c, 32, false, pp.gates, true, pp.once);
+                if (alt.stages.size() < hp.stages.size()) hp.stages = std::move(alt.stages);
+            }
+            const int ng = usable_gates(pp.gates, int(hp.sites.size()), r, pp.c);
+            for (HostStage& st : hp.stages) plan_exchanges(hp, st, ng, -1);
         }
     }
     return best;

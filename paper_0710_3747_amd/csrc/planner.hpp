@@ -12,6 +12,7 @@
 #pragma once
 
 #include <cstdint>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -152,6 +153,10 @@ void plan_stages(HostPass& pass, int r, uint32_t avoid_first = 0, uint32_t avoid
 // once: see PassParams::once.
 void plan_stages_coalesced(HostPass& pass, int r, int c, int beam = 1, bool half = false, int gates = 0,
                            bool rank = false, bool once = false);
+
+// Calls job(0) .. job(n - 1) on up to 8 threads, this one among them, and
+// returns when all have ended; the first exception in index order is thrown on.
+void run_on_threads(size_t n, const std::function<void(size_t)>& job);
 
 // Full streaming plan for one scheduling variant: sequence, passes, period
 // search, stages.

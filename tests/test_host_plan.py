@@ -382,3 +382,15 @@ def test_describe_counts_stage_exchanges():
     assert t["path"] == 2
     assert 0 < t["exchanges"] < t["launches"] * 64
     assert t["exchanges"] >= t["stages_total"] - t["templates"]
+
+
+@pytest.mark.parametrize("prec,M,J,steps", [(spq.SPIN_C64, 14, workloads.star(14, 77, 1.0, 1.0, a_over_b=-2.0), 40),
+                                            (spq.SPIN_C128, 17, workloads.star(17, 3), 40),
+                                            (spq.SPIN_C64, 20, workloads.star(20, 3), 30),
+                                            (spq.SPIN_C64, 18, workloads.ladder(9), 90)])
+def test_small_tiles_repeat_a_short_block(prec, M, J, steps):
+    """A call on a small state plans a few steps and repeats them, instead of
+    every pass of the run: planning stays short beside the run."""
+    info = spq.spin_describe_plan(prec, M, J, 0.02, steps, 0)
+    assert info["path"] == 2 and 1 <= info["period_steps"] <= 16
+    assert 2 * info["templates"] < info["launches"]
