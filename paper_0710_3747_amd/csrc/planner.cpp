@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <exception>
 #include <functional>
+#include <limits>
 #include <map>
 #include <sstream>
 #include <stdexcept>
@@ -1077,6 +1078,7 @@ StreamPlan plan_stream_blocks(int M, const std::vector<Coupling>& J, double dt, 
         auto mid = plan_block(M, J, dt, observed, merge, pp, W, false);
         const int nm = int(mid.size());
         const int t0 = add_templates(plan, std::move(mid));
+        plan.passes[t0].block_start = true;
         for (int64_t r = 1; r < reps; ++r) add_launches(plan, t0, nm, r * W);
         plan.period_steps = int(W);
         plan.period_passes = nm;
@@ -1154,6 +1156,7 @@ StreamPlan plan_stream_periodic(int M, const std::vector<Coupling>& J, double dt
             plan.launch_tmpl.push_back(p);
             plan.launch_offset.push_back(r * delta);
         }
+    plan.passes[p1].block_start = true;
     plan.period_steps = int(delta);
     plan.period_passes = p2 - p1;
 
@@ -1736,11 +1739,59 @@ void order_for_gathers(std::vector<HostStage>& stages, std::vector<std::vector<i
 
 }  // namespace
 
+namespace {
+
+// Coefficients t = tan(theta/2), s = sin(theta) of a three-shear rotation in
+// the kernels' type.  The shears' product has the off-diagonal elements
+// t (2 - t s) and -s: rounded one by one, t and s make it a little off
+// orthogonal and off its angle, by as much in every application, and since the
+// polarisation flows one way the norm and the curve drift with it (ladder
+// 2x15, 1000 steps, complex64: norm -4.7e-8, max |dP| 4.8e-8 against
+// complex128).  So each application takes, among the neighbours of the rounded
+// values, those that bring back what the pair's earlier ones have added up to
+// (`first`: the pair's lower site is on the lower register bit, which fixes the
+// sign of the off-diagonal difference): the sums stay within a few units of the
+// last place for any number of steps: norm 1.4e-9, max |dP| 3.0e-9.
+void round_rotation(double theta, bool first, RoundingCarry& c, float* t, float* s) {
+    const float t0 = float(std::tan(0.5 * theta)), s0 = float(std::sin(theta));
+    *t = t0;
+    *s = s0;
+    if (theta == 0.0) return;
+    const float inf = std::numeric_limits<float>::infinity();
+    RoundingCarry best;
+    double least = -1.0;
+    for (const float tc : {t0, std::nextafter(t0, -inf), std::nextafter(t0, inf)})
+        for (const float sc : {s0, std::nextafter(s0, -inf), std::nextafter(s0, inf)}) {
+            const double diag = 1.0 - double(tc) * sc, b = tc * (1.0 + diag);
+            const double across = (first ? 1.0 : -1.0) * (b - sc);
+            const double angle = std::atan2(0.5 * (b + sc), diag) - theta;
+            const RoundingCarry sum{c.across + across, c.angle + angle};
+            // the sums first; among pairs that serve them alike the nearest one
+            const double cost = sum.across * sum.across + sum.angle * sum.angle +
+                                1e-3 * (across * across + angle * angle);
+            if (least < 0.0 || cost < least) {
+                least = cost;
+                best = sum;
+                *t = tc;
+                *s = sc;
+            }
+        }
+    c = best;
+}
+void round_rotation(double theta, bool, RoundingCarry&, double* t, double* s) {
+    *t = std::tan(0.5 * theta);
+    *s = std::sin(theta);
+}
+
+}  // namespace
+
 template <typename T>
 void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, int engine, bool profile,
                  const Chain* chain) {
     const int k = int(hp.sites.size());
     std::vector<HostStage> stages = hp.stages;
+    // a block that repeats brings its own sums back to zero
+    if (hp.block_start) out.carry.clear();
     constexpr int eb = sizeof(T) * 2;
     DevPass dp{};
     dp.k = k;
@@ -1968,7 +2019,8 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, int
                 continue;
             }
             int qa = regbit(local[op.i]), qb = regbit(local[op.j]);
-            if (qa > qb) std::swap(qa, qb);
+            const bool first = qa < qb;
+            if (!first) std::swap(qa, qb);
             if (engine == 1) {
                 sm.apply(qa, qb, op.A, op.B);
                 continue;
@@ -1982,8 +2034,7 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, int
                 DevOp<T> d{};
                 const double th = theta / pieces;
                 d.code = op_xy(qa, qb);
-                d.t = T(std::tan(0.5 * th));
-                d.s = T(std::sin(th));
+                round_rotation(th, first, out.carry[{op.i, op.j}], &d.t, &d.s);
                 d.nt = -d.t;
                 d.ns = -d.s;
                 out.ops.push_back(d);

@@ -13,7 +13,9 @@
 
 #include <cstdint>
 #include <functional>
+#include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "device_plan.hpp"
@@ -84,6 +86,7 @@ struct HostPass {
     bool writes = true;
     bool slots = false;        // exchanges use per-lane slots (see exchange_row_slots)
     bool in_registers = false; // neither loaded from nor stored to HBM by its stages
+    bool block_start = false;  // first pass of a block that the run repeats
 };
 
 struct PassParams {
@@ -186,6 +189,13 @@ struct ResidentPlan {
 ResidentPlan plan_resident(int k, const std::vector<Coupling>& J, double dt, int observed,
                            bool merge, int r, bool profile = false);
 
+// What the rounded coefficients of a pair's rotations have added up to so far:
+// `across`, by which the two off-diagonal elements differ (in the direction of
+// the pair's lower site), and the angle.
+struct RoundingCarry {
+    double across = 0, angle = 0;
+};
+
 // Encoded device tables.
 template <typename T>
 struct DevTables {
@@ -193,6 +203,8 @@ struct DevTables {
     std::vector<DevStage> stages;
     std::vector<DevOp<T>> ops;
     std::vector<float> mats;           // matrix engine: kMatFloats per kOpMat
+    // per pair of sites, over the passes encoded so far (see round_rotation)
+    std::map<std::pair<int, int>, RoundingCarry> carry;
 };
 
 // Entry arrangement of a stage: thread bit -> position, register bit ->
