@@ -524,8 +524,16 @@ static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int spli
         int in = 0, out = 0;      // position `in` from a gate with position `out`
     };
     // Runs everything that can run; observables after the factors before
-    // them, so that they form groups.
+    // them, so that they form groups, but those of step 0 before any factor:
+    // they are the state's as it was passed in (a factor on other sites leaves
+    // them alone only to its rounding).
     auto close = [&](State& s, std::vector<StageItem>* prog) {
+        for (int i = 0; i < n; ++i)
+            if (meas[i] && pass.ops[st.ops[i]].step == 0 && !s.done.get(i)) {
+                s.done.set(i);
+                ++s.ndone;
+                if (prog) prog->push_back(StageItem{st.ops[i], 0, 0});
+            }
         for (bool any = true; any;) {
             any = false;
             for (int kind = 0; kind < 2; ++kind) {

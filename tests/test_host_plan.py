@@ -394,3 +394,18 @@ def test_small_tiles_repeat_a_short_block(prec, M, J, steps):
     info = spq.spin_describe_plan(prec, M, J, 0.02, steps, 0)
     assert info["path"] == 2 and 1 <= info["period_steps"] <= 16
     assert 2 * info["templates"] < info["launches"]
+
+
+@pytest.mark.parametrize("M,J,observed", [(10, workloads.ladder(5), 0), (18, workloads.ladder(9), 0),
+                                          (18, workloads.ladder(9), 17), (30, workloads.ladder(15), 0),
+                                          (27, workloads.ladder(7), 13), (30, workloads.chain(30), 29),
+                                          (13, workloads.star(13, 3), 4), (30, workloads.ladder(15), spq.SPIN_ALL_SITES)])
+@pytest.mark.parametrize("prec", [spq.SPIN_C64, spq.SPIN_C128])
+def test_observables_of_step_0_come_before_any_factor(prec, M, J, observed):
+    """P[0] and N[0] are those of the state as it was passed in, not of one
+    that factors on other sites have rounded."""
+    for steps in (1, 20):
+        t = spq.spin_plan_trace(prec, M, J, 0.05, steps, observed, spq.Options())
+        first = int((t[:, 0] == 0).argmax())
+        zeros = [n for n, rec in enumerate(t) if rec[0] == 1 and rec[1] == 0]
+        assert len(zeros) == (M if observed == spq.SPIN_ALL_SITES else 1) and max(zeros) < first
