@@ -114,13 +114,15 @@ int scratch_get(hipStream_t st, size_t bytes, void** out) { return scratch_get_s
 // ------------------------------------------------------------- plan cache
 struct PlanKey {
     int dev, prec, M, observed, k, r, nt, c, merge, engine, profile, exchange;
+    int try_large;            // the tile size of the plan may be a larger one than k
     double dt;
     int64_t n_steps;
     std::vector<double> J;    // flattened couplings
     bool operator<(const PlanKey& o) const {
-        return std::tie(dev, prec, M, observed, k, r, nt, c, merge, engine, profile, exchange, dt, n_steps, J) <
+        return std::tie(dev, prec, M, observed, k, r, nt, c, merge, engine, profile, exchange, try_large, dt,
+                        n_steps, J) <
                std::tie(o.dev, o.prec, o.M, o.observed, o.k, o.r, o.nt, o.c, o.merge, o.engine,
-                        o.profile, o.exchange, o.dt, o.n_steps, o.J);
+                        o.profile, o.exchange, o.try_large, o.dt, o.n_steps, o.J);
     }
 };
 
@@ -385,7 +387,8 @@ int get_plan(int prec, int M, const std::vector<Coupling>& J, double dt, int64_t
     }
     PlanKey key{dev, prec, M, observed, sh.k, sh.r, sh.nt, sh.c,
                 (opt && opt->no_merge) ? 0 : 1, sh.resident ? 0 : sh.engine,
-                profile ? 1 : 0, sh.resident ? 0 : int(sh.exchange), dt, sh.resident ? 0 : n_steps, {}};
+                profile ? 1 : 0, sh.resident ? 0 : int(sh.exchange), !sh.resident && sh.try_large, dt,
+                sh.resident ? 0 : n_steps, {}};
     key.J.reserve(J.size() * 4);
     for (const Coupling& c : J) {
         key.J.push_back(c.i);

@@ -135,3 +135,30 @@ def test_batches_of_equal_couplings_share_tables_not_states(prec):
             torch.cuda.synchronize()
             assert float((P - p["P"]).abs().max()) < TOL_P[prec]
             assert_state_close(p["psi"].cpu().numpy().astype(np.complex128), psi.cpu().numpy().astype(np.complex128), prec)
+
+
+def test_default_and_explicit_double_precision_tiles_keep_their_plans():
+    """At M = 28, 21 steps, the default takes tiles of 2^14: asking for 2^13
+    before or after it changes neither call's bits."""
+    import torch
+    M, J, dt, steps = 28, workloads.ladder(14), 0.05, 21
+    args = (C128, M, J, dt, steps, 0)
+    assert [spq.spin_describe_plan(*args, o)["tile_bits"] for o in (spq.Options(), spq.Options(tile_bits=13))] == [14, 13]
+
+    def run(opts):
+        note("plans", opts)
+        P, N, _, psi = gpu_evolve(C128, M, J, dt, steps, 0, seed=4, opts=opts, keep_state=False)
+        return P, N, psi
+
+    def same(a, b):
+        return np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and torch.equal(a[2], b[2])
+
+    spq.spin_release_caches()
+    default = run({})
+    spq.spin_release_caches()
+    explicit = run({"tile_bits": 13})
+    assert not np.array_equal(default[0], explicit[0])
+    assert same(run({}), default)                   # after the explicit call
+    spq.spin_release_caches()
+    run({})
+    assert same(run({"tile_bits": 13}), explicit)   # after the default call
