@@ -132,4 +132,28 @@ SPIN_HD constexpr int exchange_row_slots(int nt, int elem_bytes) {
     return (exchange_slot(nt - 1, elem_bytes) + n - 1) / n * n + 1;
 }
 
+// LDS slots of a workgroup that holds a whole state, 2^r amplitudes on each of
+// nt lanes: it is exchanged in padded rows and staged in memory order.
+SPIN_HD constexpr int resident_slots(int r, int nt, int elem_bytes) {
+    const int rows = exchange_row_slots(nt, elem_bytes) << r, order = nt << r;
+    return rows > order ? rows : order;
+}
+
+// Register bits and lanes of the batch kernel's tiles (see batch_shape).
+SPIN_HD constexpr int batch_regs(bool f32, bool half) { return (f32 ? 5 : 4) + (half ? 1 : 0); }
+SPIN_HD constexpr int batch_lanes(bool half) { return half ? 256 : 512; }
+// Amplitudes per lane, as a power of two, of its one-workgroup problems: 16, and
+// 32 for M = 13 on 256 lanes.
+SPIN_HD constexpr int batch_resident_regs(int M, bool half) { return half && M > 12 ? 5 : 4; }
+// LDS slots of the batch kernel: the tiles of its gangs (whole ones in one
+// layout, or half of them in padded rows) and its one-workgroup problems, up to
+// half a tile.
+SPIN_HD constexpr int batch_lds_slots(bool f32, bool half) {
+    const int eb = f32 ? 8 : 16, r = batch_regs(f32, half), nt = batch_lanes(half);
+    const int tile = half ? exchange_row_slots(nt, eb) << (r - 1) : nt << r;
+    const int most = f32 ? 13 : 12;
+    const int whole = resident_slots(batch_resident_regs(most, half), nt, eb);
+    return tile > whole ? tile : whole;
+}
+
 }  // namespace spinqp

@@ -1630,11 +1630,12 @@ __device__ __forceinline__ void flush_ring(const ResidentRing<NW>& ring, int n) 
     __syncthreads();
 }
 
-template <typename T, int R, int NT, bool PROFILE = false>
+template <typename T, int R, int NT, bool PROFILE = false, int SLOTS>
 __device__ __forceinline__ void resident_run(const ResidentJob& J, const DevStage* __restrict__ stages,
                                              const DevOp<T>* __restrict__ ops, int64_t n_steps,
-                                             typename CT<T>::c* lds, ResidentRing<NT / 64>& ring) {
+                                             typename CT<T>::c (&lds)[SLOTS], ResidentRing<NT / 64>& ring) {
     using C = typename CT<T>::c;
+    static_assert(SLOTS >= resident_slots(R, NT, int(sizeof(C))), "the state's rows do not fit the LDS buffer");
     constexpr int NTB = __builtin_ctz(NT), NW = NT / 64;
     constexpr int EB = sizeof(C), ROW = exchange_row_slots(NT, EB) * EB;
     const int tid = threadIdx.x;
@@ -1747,7 +1748,7 @@ __global__ __launch_bounds__(NT) void k_resident(ResidentJob job0,
                                                  const DevOp<T>* __restrict__ ops,
                                                  int64_t n_steps) {
     using C = typename CT<T>::c;
-    __shared__ C lds[exchange_row_slots(NT, sizeof(C)) << R];
+    __shared__ C lds[resident_slots(R, NT, sizeof(C))];
     __shared__ ResidentRing<NT / 64> ring;
     ResidentJob J = jobs ? jobs[blockIdx.x] : job0;
     for (int32_t* f : {&J.M, &J.init, &J.obs_stage0, &J.pro_stage0, &J.pro_nstage, &J.step_stage0, &J.step_nstage,
@@ -1815,7 +1816,8 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
     constexpr int K = R + __builtin_ctz(NT);
     constexpr int KL = K - 1;               // largest one-workgroup problem
     constexpr int NW = NT / 64;
-    __shared__ C lds[exchange_slots<T, R, NT, HALF ? kHalfTiles : kWholeTiles>()];
+    static_assert(R == batch_regs(sizeof(T) == 4, HALF) && NT == batch_lanes(HALF), "not the batch kernel's shape");
+    __shared__ C lds[batch_lds_slots(sizeof(T) == 4, HALF)];
     __shared__ double red[2 * NW];
     __shared__ double wacc[HALF ? NW : 1][2 * kMaxMeas];
     __shared__ ResidentRing<NW> ring;
@@ -2081,8 +2083,7 @@ int batch_tile_bits(bool f32) { return f32 ? 14 : 13; }
 // workgroup per CU); half tiles 2^(R+1) x 256 lanes (two per CU), whose
 // larger register stages take fewer LDS exchanges on dense coupling graphs.
 BatchShape batch_shape(bool f32, bool half) {
-    if (half) return BatchShape{true, f32 ? 6 : 5, 256};
-    return BatchShape{false, f32 ? 5 : 4, 512};
+    return BatchShape{half, batch_regs(f32, half), batch_lanes(half)};
 }
 
 template hipError_t launch_init<float>(void*, int, int, uint64_t, hipStream_t);

@@ -122,5 +122,5 @@ hipError_t launch_resident(int bits, const ResidentJob& job0, const ResidentJob*
                            int64_t n_steps, hipStream_t st);
 // Register and thread bits of a one-workgroup problem inside the batch kernel
 // (256 lanes with half tiles, else 512).
-inline int batch_resident_bits(int M, bool half) { return half && M <= 12 ? 12 : 13; }
+inline int batch_resident_bits(int M, bool half) { return batch_resident_regs(M, half) + (half ? 8 : 9); }
 }  // namespace spinqp

@@ -68,3 +68,13 @@ def test_double_precision_tiles_follow_the_launches_they_save(M, steps, tile):
     n = {k: spq.spin_describe_plan(*args, spq.Options(tile_bits=k))["launches"] for k in (13, 14)}
     assert got["tile_bits"] == tile and got["launches"] == n[tile]
     assert (10 * n[13] > 13 * n[14]) == (tile == 14) or M < 27
+
+
+def test_batch_kernel_buffer_holds_what_its_problems_touch(tmp_path):
+    """One-workgroup problems of the batch kernel exchange in padded rows; the
+    kernel's LDS buffer holds them for both precisions and tile modes."""
+    out = str(tmp_path / "batch_lds_check")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", os.path.join(ROOT, "tests", "host_checks", "batch_lds_check.cpp"),
+                           "-o", out])
+    p = subprocess.run([out], capture_output=True, text=True, timeout=60)
+    assert p.returncode == 0, p.stdout
