@@ -111,6 +111,15 @@ int scratch_get_slot(hipStream_t st, int slot, size_t bytes, void** out) {
 
 int scratch_get(hipStream_t st, size_t bytes, void** out) { return scratch_get_slot(st, 0, bytes, out); }
 
+// Bytes of the stream's scratch memory of slot 0 as it is.
+static size_t scratch_held(hipStream_t st) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    std::lock_guard<std::mutex> lk(g_mu);
+    const auto it = g_scratch.find(std::make_tuple(dev, st, 0));
+    return it == g_scratch.end() ? 0 : it->second.bytes;
+}
+
 // ------------------------------------------------------------- plan cache
 struct PlanKey {
     int dev, prec, M, observed, k, r, nt, c, merge, engine, profile, exchange;
@@ -262,6 +271,9 @@ static void set_stages(const ResidentStages& rs, ResidentJob* j) {
 // Workgroups per pass, at most; each leaves its partial sums of every step, the
 // profile's for every site.
 constexpr int64_t kMaxWg = 1 << 14, kMaxWgProfile = 1 << 12;
+// The allocation-free call has the same workgroups, so the same sums.
+static_assert(kMaxWg * kMaxMeas * 2 * sizeof(double) <= SPIN_NOALLOC_SCRATCH_BYTES,
+              "the fixed workspace holds one launch's observables of every plan");
 
 // Planner settings of an exchange mode.
 static void exchange_params(ExchangeMode x, PassParams* pp) {
@@ -549,7 +561,7 @@ static int evolve_naive(void* psi, int M, const std::vector<Coupling>& J, double
 // complete steps are reduced in chunks out of a ring of `ch` step slots.
 template <typename T>
 static int evolve_profile(void* psi, int M, const DevicePlan& dp, int64_t n_steps, double* P,
-                          double* N, bool graph, hipStream_t st) {
+                          double* N, bool graph, bool capturing, hipStream_t st) {
     if (dp.resident) {
         ResidentJob job{};
         job.psi = psi;
@@ -564,19 +576,46 @@ static int evolve_profile(void* psi, int M, const DevicePlan& dp, int64_t n_step
         return SPIN_OK;
     }
     const int64_t total = n_steps + 1;
-    const int ch = int(std::min<int64_t>(total, 64));
+    // Ring of step slots, which must hold the steps between the last complete one
+    // and the furthest that a launch measures; while `st` is captured, no more of
+    // them than its scratch memory holds already, if it holds those.
+    int64_t ch = std::min<int64_t>(total, 64);
+    const size_t slot_bytes = size_t(dp.nwg) * (M + 1) * sizeof(double);
+    if (capturing) {
+        std::vector<int64_t> next(M, 0);
+        int64_t least = 1, high = 0;
+        for (size_t l = 0; l < dp.sp.launch_tmpl.size(); ++l) {
+            const int t = dp.sp.launch_tmpl[l];
+            const int64_t off = dp.sp.launch_offset[l];
+            for (int64_t s : dp.meas[t]) high = std::max(high, s + off + 1);
+            least = std::max(least, high - *std::min_element(next.begin(), next.end()));
+            for (size_t m = 0; m < dp.meas[t].size(); ++m) {
+                int64_t& nx = next[dp.meas_site[t][m]];
+                nx = std::max(nx, dp.meas[t][m] + off + 1);
+            }
+        }
+        const int64_t fit = int64_t(scratch_held(st) / slot_bytes);
+        if (fit >= least) ch = std::min(ch, fit);
+    }
     void* scratch = nullptr;
-    int rc = scratch_get(st, size_t(ch) * dp.nwg * (M + 1) * sizeof(double), &scratch);
+    int rc = scratch_get(st, size_t(ch) * slot_bytes, &scratch);
     if (rc) return rc;
     double* part = static_cast<double*>(scratch);
     auto enqueue = [&](hipStream_t st) -> int {
         std::vector<int64_t> next(M, 0);    // per site: steps measured so far
         int64_t complete = 0, reduced = 0, highest = 0;
+        auto reduce = [&]() -> int {
+            HIP_TRY(launch_reduce_profile(part, dp.nwg, int(ch), M, reduced, complete - reduced, P, N, st));
+            reduced = complete;
+            return SPIN_OK;
+        };
         const size_t nl = dp.sp.launch_tmpl.size();
         for (size_t l = 0; l < nl; ++l) {
             const int t = dp.sp.launch_tmpl[l];
             const int64_t off = dp.sp.launch_offset[l];
             for (int64_t s : dp.meas[t]) highest = std::max(highest, s + off + 1);
+            int rc = SPIN_OK;
+            if (highest - reduced > ch && complete > reduced && (rc = reduce())) return rc;
             if (highest - reduced > ch) {
                 std::ostringstream os;
                 os << "internal: profile measurements run " << highest - reduced
@@ -588,16 +627,13 @@ static int evolve_profile(void* psi, int M, const DevicePlan& dp, int64_t n_step
             HIP_TRY((launch_pass<T>(shp, psi, static_cast<const DevPass*>(dp.d_passes),
                                     static_cast<const DevStage*>(dp.d_stages),
                                     static_cast<const DevOp<T>*>(dp.d_ops), t, dp.tiles_per_wg,
-                                    dp.nwg, part, off, ch, st)));
+                                    dp.nwg, part, off, int(ch), st)));
             for (size_t m = 0; m < dp.meas[t].size(); ++m) {
                 int64_t& nx = next[dp.meas_site[t][m]];
                 nx = std::max(nx, dp.meas[t][m] + off + 1);
             }
             complete = *std::min_element(next.begin(), next.end());
-            if (complete - reduced >= ch / 2 || (l + 1 == nl && complete > reduced)) {
-                HIP_TRY(launch_reduce_profile(part, dp.nwg, ch, M, reduced, complete - reduced, P, N, st));
-                reduced = complete;
-            }
+            if ((complete - reduced >= ch / 2 || l + 1 == nl) && complete > reduced && (rc = reduce())) return rc;
         }
         if (reduced != total) {
             std::ostringstream os;
@@ -630,7 +666,7 @@ static int evolve_fused(void* psi, int M, const std::vector<Coupling>& J, double
     int rc = get_plan(sizeof(T) == 4 ? SPIN_C64 : SPIN_C128, M, J, dt, n_steps, observed, opt,
                       profile, &dp, &sh, ws != nullptr || capturing, ws != nullptr);
     if (rc) return rc;
-    if (profile) return evolve_profile<T>(psi, M, *dp, n_steps, P, N, graph, st);
+    if (profile) return evolve_profile<T>(psi, M, *dp, n_steps, P, N, graph, capturing, st);
     if (dp->resident) {
         ResidentJob job{};
         job.psi = psi;
@@ -645,28 +681,31 @@ static int evolve_fused(void* psi, int M, const std::vector<Coupling>& J, double
         return SPIN_OK;
     }
     const int64_t total = n_steps + 1;
-    // A launch measures at most kMaxMeas consecutive steps and the slots are
-    // reduced once half of them are in use, so 2 * kMaxMeas slots suffice; as
-    // many as 16 MiB hold, or the workspace.
-    int nwg = dp->nwg;
-    int ch = int(std::min<int64_t>(total, std::max(2 * kMaxMeas, (1 << 20) / nwg)));
-    ch = std::min(ch, 1024);
+    // Ring of step slots for the partial sums: as many as 16 MiB hold, or the
+    // workspace; while `st` is captured, as many as the stream's scratch memory
+    // holds already (a capture cannot allocate).  How many does not show in the
+    // results.
+    const int nwg = dp->nwg;
+    const size_t slot_bytes = size_t(nwg) * 2 * sizeof(double);
+    const int64_t least = std::min<int64_t>(total, kMaxMeas);
+    int64_t ch = std::min<int64_t>(std::min<int64_t>(total, 1024), std::max(2 * kMaxMeas, (1 << 20) / nwg));
     void* scratch = nullptr;
     if (ws) {
-        auto fit = [&] { return int64_t(ws->doubles / (size_t(2) * size_t(nwg))); };
-        while (nwg > 1 && fit() < std::min<int64_t>(total, 2 * kMaxMeas)) nwg /= 2;
-        ch = int(std::min<int64_t>(std::min<int64_t>(total, 1024), fit()));
-        if (ch < std::min<int64_t>(total, 2 * kMaxMeas)) {
+        ch = std::min<int64_t>(std::min<int64_t>(total, 1024), int64_t(ws->doubles * sizeof(double) / slot_bytes));
+        if (ch < least) {
             std::ostringstream os;
-            os << "workspace too small: " << nwg << " workgroups need " << 2 * kMaxMeas * 2 * nwg
+            os << "workspace too small: " << nwg << " workgroups need " << kMaxMeas * 2 * nwg
                << " doubles, the allocation-free workspace holds " << ws->doubles;
             return fail(SPIN_EUNSUPPORTED, os.str());
         }
         scratch = ws->ptr;
-    } else if ((rc = scratch_get(st, size_t(ch) * nwg * 2 * sizeof(double), &scratch))) {
-        return rc;
+    } else {
+        if (capturing) {
+            const int64_t fit = int64_t(scratch_held(st) / slot_bytes);
+            if (fit >= least) ch = std::min(ch, fit);
+        }
+        if ((rc = scratch_get(st, size_t(ch) * slot_bytes, &scratch))) return rc;
     }
-    const int64_t tiles_per_wg = dp->tiles_per_wg * (dp->nwg / nwg);
     double* part = static_cast<double*>(scratch);
     auto enqueue = [&](hipStream_t st) -> int {
         int64_t measured = 0, reduced = 0;
@@ -674,16 +713,24 @@ static int evolve_fused(void* psi, int M, const std::vector<Coupling>& J, double
         for (size_t l = 0; l < nl; ++l) {
             const int t = dp->sp.launch_tmpl[l];
             const int64_t off = dp->sp.launch_offset[l];
+            // a launch measures at most kMaxMeas consecutive steps: room for them
+            int64_t after = measured;
+            for (int64_t s : dp->meas[t]) after = std::max(after, s + off + 1);
+            if (after - reduced > ch && measured > reduced) {
+                HIP_TRY(launch_reduce(part, nwg, int(ch), reduced, measured - reduced, P, N, st));
+                reduced = measured;
+            }
+            if (after - reduced > ch) return fail(SPIN_EUNSUPPORTED, "internal: more steps in a launch than slots");
             PassShape shp = dp->shape;
             shp.mats = static_cast<const float*>(dp->d_mats);
             shp.writes = dp->sp.passes[t].writes;
             HIP_TRY((launch_pass<T>(shp, psi, static_cast<const DevPass*>(dp->d_passes),
                                     static_cast<const DevStage*>(dp->d_stages),
-                                    static_cast<const DevOp<T>*>(dp->d_ops), t, tiles_per_wg,
-                                    nwg, part, off, ch, st)));
-            for (int64_t s : dp->meas[t]) measured = std::max(measured, s + off + 1);
+                                    static_cast<const DevOp<T>*>(dp->d_ops), t, dp->tiles_per_wg,
+                                    nwg, part, off, int(ch), st)));
+            measured = after;
             if (measured - reduced >= ch / 2 || (l + 1 == nl && measured > reduced)) {
-                HIP_TRY(launch_reduce(part, nwg, ch, reduced, measured - reduced, P, N, st));
+                HIP_TRY(launch_reduce(part, nwg, int(ch), reduced, measured - reduced, P, N, st));
                 reduced = measured;
             }
         }

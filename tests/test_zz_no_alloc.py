@@ -104,3 +104,73 @@ def test_noalloc_refuses_what_it_cannot_serve_without_allocating():
                 torch) == spq.SPIN_EUNSUPPORTED
     torch.cuda.synchronize()
     assert torch.equal(psi, before)
+
+
+@pytest.mark.parametrize("prec,M,steps", [(spq.SPIN_C64, 28, 2), (spq.SPIN_C64, 28, 9), (spq.SPIN_C128, 27, 9)])
+def test_noalloc_is_bit_for_bit_the_same_with_the_most_workgroups(prec, M, steps):
+    """One workgroup per tile, 2^14 of them: the fixed array holds four step
+    slots, and the sums are still those of spin_trotter_evolve_ex."""
+    import torch
+    lib = spq.load_library()
+    _set_up(lib, torch)
+    J, dt = workloads.chain(M), 0.05
+    note("noalloc", M, prec, steps)
+    psi = torch.empty(2 ** M, dtype=torch_dtype(prec), device="cuda")
+    P, Pr, N, Nr = (torch.full((steps + 1,), float("nan"), dtype=torch.float64, device="cuda") for _ in range(4))
+    spq.spin_prepare_plan(prec, M, J, dt, steps, 0, None)
+    out = []
+    for fn, p, n in (("spin_trotter_evolve_ex", Pr, Nr), ("spin_trotter_evolve_noalloc", P, N)):
+        spq.spin_init_random_phase(psi, M, 0, 11)
+        assert _run(lib, fn, psi, prec, M, J, dt, steps, 0, p, n, None, torch) == 0, spq.spin_last_error()
+        out.append(psi.clone())
+    torch.cuda.synchronize()
+    assert torch.equal(P, Pr) and torch.equal(N, Nr) and torch.equal(*out)
+
+
+@pytest.mark.parametrize("kind,M,steps", [("evolve", 26, 40), ("profile", 20, 60)])
+def test_captured_calls_use_the_scratch_memory_the_stream_has(kind, M, steps):
+    """A prepared call can be captured after any call that took scratch memory
+    on the stream (1 MiB), however many step slots it would take otherwise;
+    replayed three times with eager calls between."""
+    import torch
+    note("captured", kind, M)
+    J, dt = workloads.ladder(M // 2), 0.05
+    rows = steps + 1
+    shape = rows * (M if kind == "profile" else 1)
+    spq.spin_release_caches()
+    P, Pr = (torch.zeros(shape, dtype=torch.float64, device="cuda") for _ in range(2))
+    N, Nr = (torch.zeros(rows, dtype=torch.float64, device="cuda") for _ in range(2))
+    psi = torch.empty(2 ** M, dtype=torch.complex64, device="cuda")
+    spq.spin_init_random_phase(psi, M, 0, 3)
+    start = psi.clone()
+    spq.spin_prepare_plan(spq.SPIN_C64, M, J, dt, steps, spq.SPIN_ALL_SITES if kind == "profile" else 0, None)
+
+    def call(p, n):
+        if kind == "profile":
+            spq.spin_trotter_evolve_profile(psi, M, J, dt, steps, p, n)
+        else:
+            spq.spin_trotter_evolve_ex(psi, M, J, dt, steps, 0, p, n, None)
+
+    side = torch.cuda.Stream()
+    one = torch.zeros(1, dtype=torch.float64, device="cuda")
+    with torch.cuda.stream(side):
+        spq.spin_local_polarization(psi, M, 0, one)        # the least scratch memory there is
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        call(P, N)
+    psi.copy_(start)
+    call(Pr, Nr)
+    torch.cuda.synchronize()
+    want = psi.clone()
+    for _ in range(3):
+        psi.copy_(start)
+        P.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(psi, want) and torch.equal(P, Pr) and torch.equal(N, Nr)
+        psi.copy_(start)
+        call(Pr, Nr)
+    torch.cuda.synchronize()
+    del g
