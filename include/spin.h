@@ -277,7 +277,8 @@ enum {
  * until spin_release_caches, and calls with other states, seeds or outputs
  * reuse the tables of their couplings).  Problems larger than one workgroup's
  * tile run as gangs of workgroups that meet at bounded device-wide barriers,
- * so batched launches on one device run one after the other; if a
+ * so batched launches with such problems run one after the other on a device
+ * (others overlap as their streams allow); if a
  * barrier times out, the problem's P is set to NaN and spin_batch_status
  * reports it.  Errors as spin_trotter_evolve (plus SPIN_EINVAL for a bad
  * init or a basis index >= 2^M), reported for the first offending problem.

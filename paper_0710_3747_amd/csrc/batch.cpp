@@ -51,7 +51,21 @@ struct BatchCache {
     }
 };
 
+// Problems of fewer sites than a lane of the persistent launch has register
+// bits: a wave each, in a launch of their own straight on the caller's stream.
+// They wait for nothing, so they need no chaining, and the launch can be
+// captured once its tables are there.
+struct SmallBatch {
+    void *d_jobs = nullptr, *d_stages = nullptr, *d_ops = nullptr;
+    int njobs = 0, bits = 0;
+    ~SmallBatch() {
+        for (void* p : {d_jobs, d_stages, d_ops})
+            if (p) (void)hipFree(p);
+    }
+};
+
 static std::mutex g_bmu;
+static std::map<std::vector<double>, std::shared_ptr<SmallBatch>> g_small;
 static std::map<std::vector<double>, std::shared_ptr<BatchCache>> g_bcache;
 // The tables of the latest sets of couplings, latest first.
 constexpr size_t kBatchTablesKept = 8;
@@ -59,9 +73,10 @@ static std::list<std::pair<std::vector<double>, std::shared_ptr<const BatchTable
 // Per device: sticky status word of the persistent launches (non-zero once a
 // gang barrier has timed out), read and cleared by spin_batch_status.
 static std::map<int, int*> g_status;
-// Per device: the end of the latest persistent launch.  A gang waits for its
-// members, so the launch's workgroups must all find a slot: launches on
-// several streams run one after the other.
+// Per device: the end of the latest persistent launch with gangs.  A gang waits
+// for its members, so the launch's workgroups must all find a slot: such launches
+// on several streams run one after the other.  Launches without gangs end by
+// themselves and are not chained.
 static std::mutex g_launch_mu;
 static std::map<int, hipEvent_t> g_last_launch;
 
@@ -86,6 +101,7 @@ void release_batch_caches() {
     std::lock_guard<std::mutex> lk(g_bmu);
     g_bcache.clear();
     g_btables.clear();
+    g_small.clear();
     {
         std::lock_guard<std::mutex> ll(g_launch_mu);
         for (auto& kv : g_last_launch)
@@ -334,6 +350,89 @@ static int build_call(const std::vector<spin_problem>& probs, int init, int nslo
     return SPIN_OK;
 }
 
+// ------------------------------------------------- small problems
+template <typename T>
+static int build_small(const std::vector<spin_problem>& probs, const std::vector<std::vector<Coupling>>& Js,
+                       double dt, int init, SmallBatch* sb) {
+    sb->bits = resident_bits(1);
+    sb->njobs = int(probs.size());
+    DevTables<T> tb;
+    std::vector<ResidentJob> jobs;
+    std::map<std::vector<double>, ResidentStages> seen;
+    for (size_t p = 0; p < probs.size(); ++p) {
+        const spin_problem& pr = probs[p];
+        std::vector<double> skey{double(pr.M), double(pr.observed_site)};
+        for (const Coupling& c : Js[p]) {
+            skey.push_back(c.i);
+            skey.push_back(c.j);
+            skey.push_back(c.a);
+            skey.push_back(c.b);
+        }
+        auto at = seen.find(skey);
+        if (at == seen.end()) {
+            tb.carry.clear();
+            const ResidentPlan rp = plan_resident(sb->bits, Js[p], dt, pr.observed_site, true, kResidentRegs);
+            at = seen.emplace(skey, encode_resident<T>(rp, sb->bits, pr.observed_site, tb, false)).first;
+        }
+        const ResidentStages& rs = at->second;
+        ResidentJob j{};
+        j.psi = pr.psi;
+        j.P = pr.P_dev;
+        j.N = pr.N_dev;
+        j.seed = pr.seed;
+        j.M = pr.M;
+        j.polarized = pr.polarized_site;
+        j.init = init;
+        j.obs_stage0 = rs.obs0;
+        j.pro_stage0 = rs.pro0;
+        j.pro_nstage = rs.npro;
+        j.step_stage0 = rs.step0;
+        j.step_nstage = rs.nstep;
+        j.last_stage0 = rs.last0;
+        jobs.push_back(j);
+    }
+    int rc;
+    if ((rc = upload(jobs.data(), jobs.size() * sizeof(ResidentJob), &sb->d_jobs))) return rc;
+    if ((rc = upload(tb.stages.data(), tb.stages.size() * sizeof(DevStage), &sb->d_stages))) return rc;
+    return upload(tb.ops.data(), tb.ops.size() * sizeof(DevOp<T>), &sb->d_ops);
+}
+
+template <typename T>
+static int batch_small(const spin_problem* probs, const std::vector<int>& sel,
+                       const std::vector<std::vector<Coupling>>& Js, int prec, double dt, int64_t n_steps,
+                       int init, hipStream_t st) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return fail(SPIN_EHIP, "hipGetDevice failed");
+    std::vector<spin_problem> ps;
+    std::vector<std::vector<Coupling>> js;
+    for (int p : sel) {
+        ps.push_back(probs[p]);
+        js.push_back(Js[p]);
+    }
+    const std::vector<double> key = batch_key(ps.data(), int(ps.size()), js, prec, dt, n_steps, init, dev);
+    std::shared_ptr<SmallBatch> sb;
+    {
+        std::lock_guard<std::mutex> lk(g_bmu);
+        auto it = g_small.find(key);
+        if (it != g_small.end()) sb = it->second;
+    }
+    if (!sb) {
+        sb = std::make_shared<SmallBatch>();
+        try {
+            if (int rc = build_small<T>(ps, js, dt, init, sb.get())) return rc;
+        } catch (const std::exception& e) {
+            return fail(SPIN_EUNSUPPORTED, std::string("batch planning failed: ") + e.what());
+        }
+        std::lock_guard<std::mutex> lk(g_bmu);
+        g_small[key] = sb;
+    }
+    const hipError_t e = launch_resident<T>(sb->bits, ResidentJob{}, static_cast<const ResidentJob*>(sb->d_jobs), sb->njobs,
+                                            static_cast<const DevStage*>(sb->d_stages),
+                                            static_cast<const DevOp<T>*>(sb->d_ops), n_steps, st);
+    if (e != hipSuccess) return fail(SPIN_EHIP, std::string("batch launch: ") + hipGetErrorString(e));
+    return SPIN_OK;
+}
+
 template <typename T>
 static int batch_persistent(const spin_problem* probs, const std::vector<int>& sel,
                             const std::vector<std::vector<Coupling>>& Js, int prec, double dt,
@@ -404,9 +503,11 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
                                std::max(bc->tables->ncounters, 1), static_cast<int*>(bc->d_err), status, n_steps, s);
     };
     std::lock_guard<std::mutex> launch_lock(g_launch_mu);
-    hipEvent_t& last = g_last_launch[dev];
+    hipEvent_t unchained = nullptr;
+    const bool gangs = bc->tables->ncounters > 0;
+    hipEvent_t& last = gangs ? g_last_launch[dev] : unchained;
     const bool first = last == nullptr;
-    if (first && hipEventCreateWithFlags(&last, hipEventDisableTiming) != hipSuccess)
+    if (gangs && first && hipEventCreateWithFlags(&last, hipEventDisableTiming) != hipSuccess)
         return fail(SPIN_EHIP, "event create failed");
     hipError_t e = hipSuccess;
     if (use_graph) {
@@ -430,14 +531,14 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
         if (e == hipSuccess) e = hipStreamWaitEvent(bc->side, ev, 0);
         if (e == hipSuccess && !first) e = hipStreamWaitEvent(bc->side, last, 0);
         if (e == hipSuccess) e = hipGraphLaunch(bc->exec, bc->side);
-        if (e == hipSuccess) e = hipEventRecord(last, bc->side);
+        if (e == hipSuccess && gangs) e = hipEventRecord(last, bc->side);
         if (e == hipSuccess) e = hipEventRecord(ev, bc->side);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, ev, 0);
         (void)hipEventDestroy(ev);
     } else {
         if (!first) e = hipStreamWaitEvent(st, last, 0);
         if (e == hipSuccess) e = enqueue(st);
-        if (e == hipSuccess) e = hipEventRecord(last, st);
+        if (e == hipSuccess && gangs) e = hipEventRecord(last, st);
     }
     if (e != hipSuccess) return fail(SPIN_EHIP, std::string("batch launch: ") + hipGetErrorString(e));
     return SPIN_OK;
@@ -490,11 +591,16 @@ extern "C" int spin_trotter_evolve_batch(const spin_problem* probs, int32_t n,
         const bool half = batch_blocks_per_cu(f32, true) >= 2;
         if (!half && batch_blocks_per_cu(f32, false) < 1)
             return fail(SPIN_EUNSUPPORTED, "batch kernel does not fit a CU");
-        std::vector<int> all(n);
-        for (int p = 0; p < n; ++p) all[p] = p;
+        std::vector<int> small, large;
+        for (int p = 0; p < n; ++p) (probs[p].M < batch_shape(f32, half).r ? small : large).push_back(p);
         const bool graph = true;
-        const int rc = f32 ? batch_persistent<float>(probs, all, Js, prec, dt, n_steps, init, graph, half, st)
-                           : batch_persistent<double>(probs, all, Js, prec, dt, n_steps, init, graph, half, st);
+        int rc = SPIN_OK;
+        if (!small.empty())
+            rc = f32 ? batch_small<float>(probs, small, Js, prec, dt, n_steps, init, st)
+                     : batch_small<double>(probs, small, Js, prec, dt, n_steps, init, st);
+        if (rc == SPIN_OK && !large.empty())
+            rc = f32 ? batch_persistent<float>(probs, large, Js, prec, dt, n_steps, init, graph, half, st)
+                     : batch_persistent<double>(probs, large, Js, prec, dt, n_steps, init, graph, half, st);
         if (rc == SPIN_OK) fail(SPIN_OK, "");
         return rc;
     } catch (const std::exception& e) {
