@@ -195,8 +195,10 @@ static void plan_problem(double dt, int64_t n_steps, int64_t gang, bool half, Pr
         b.step_nstage = rs.nstep;
         b.last_stage0 = rs.last0;
         for (const Op& op : rp.step.ops) fops += op.kind == 0;
-        // on-chip: about half the cost per amplitude of a tiled pass
-        out->dur = 0.5 * fops * std::ldexp(1.0, bits) * double(n_steps + 1);
+        // on-chip: about half the cost per amplitude of a tiled pass; the
+        // observable counts as a factor (a problem without couplings takes time
+        // too: 1024 of them had all been given to one slot)
+        out->dur = 0.5 * (fops + 1.0) * std::ldexp(1.0, bits) * double(n_steps + 1);
         return;
     }
     PassParams pp;

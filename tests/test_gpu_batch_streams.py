@@ -1,5 +1,7 @@
-"""Batched launches that need no gang: they run beside other work of the device
-and small ones can be captured."""
+"""Batched launches that need no gang: they run beside other work of the device,
+small ones can be captured, and problems without couplings share the slots."""
+import time
+
 import pytest
 
 import workloads
@@ -90,3 +92,21 @@ def test_batches_without_gangs_overlap(M):
     torch.cuda.synchronize()
     assert running
 
+
+def test_problems_without_couplings_share_the_slots():
+    """512 problems of 11 sites without couplings take less time than with a chain."""
+    import torch
+    note("uncoupled")
+    steps, n, M = 50, 512, 11
+    took = []
+    for J in ([], workloads.chain(M)):
+        ps = problems(C64, [M] * n, steps, couplings=J)
+        best = 1e9
+        for _ in range(3):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            spq.spin_trotter_evolve_batch(ps, C64, 0.05, steps)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t0)
+        took.append(best)
+    assert took[0] <= took[1], took
