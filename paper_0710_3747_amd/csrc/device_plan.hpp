@@ -132,6 +132,12 @@ SPIN_HD constexpr int exchange_row_slots(int nt, int elem_bytes) {
     return (exchange_slot(nt - 1, elem_bytes) + n - 1) / n * n + 1;
 }
 
+// Whether a gang's member still waits: its counter of arrivals has not reached
+// `target`, the arrivals up to this meeting.  Both wrap after 2^32 arrivals (a
+// gang of 512 makes that many in 8.4 million meetings); at most a gang's
+// arrivals apart, their difference does not.
+SPIN_HD constexpr bool gang_waits(uint32_t arrived, uint32_t target) { return int32_t(arrived - target) < 0; }
+
 // LDS slots of a workgroup that holds a whole state, 2^r amplitudes on each of
 // nt lanes: it is exchanged in padded rows and staged in memory order.
 SPIN_HD constexpr int resident_slots(int r, int nt, int elem_bytes) {

@@ -1769,7 +1769,7 @@ __global__ __launch_bounds__(NT) void k_resident(ResidentJob job0,
 // up at once when any workgroup has flagged an error.
 constexpr uint64_t kGangWaitTicks = 20ull * 100000000ull;   // 20 s
 
-__device__ __forceinline__ bool gang_barrier(int* counter, int target, int* err) {
+__device__ __forceinline__ bool gang_barrier(int* counter, uint32_t target, int* err) {
     // Every wave waits until its stores are in the XCD's L2; after the barrier
     // one lane writes that back for all (release) and, when the gang has met,
     // invalidates what the CU and the L2 hold (acquire).  A release by every
@@ -1783,7 +1783,7 @@ __device__ __forceinline__ bool gang_barrier(int* counter, int target, int* err)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         atomicAdd(counter, 1);
         const uint64_t t0 = wall_clock64();
-        while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+        while (gang_waits(uint32_t(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)), target)) {
             __builtin_amdgcn_s_sleep(4);
             if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
                 wall_clock64() - t0 > kGangWaitTicks) {
@@ -1855,7 +1855,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
         C* psi = reinterpret_cast<C*>(B.psi);
         const unsigned G = unsigned(B.gsize), rank = unsigned(job.rank);
         int* ctr = counters + B.counter;
-        int epoch = 0;
+        uint32_t epoch = 0;
         bool ok = true;
         if (B.init) {
             const uint64_t dim = 1ull << B.M;
@@ -1868,7 +1868,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                 c.y = T(im);
                 psi[x] = c;
             }
-            ok = gang_barrier(ctr, ++epoch * int(G), err);
+            ok = gang_barrier(ctr, ++epoch * G, err);
         }
         const int64_t tpm = B.ntiles / G;
         for (int l = 0; l < B.nlaunch && ok; ++l) {
@@ -1917,7 +1917,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                     }
                 }
             }
-            ok = gang_barrier(ctr, ++epoch * int(G), err);
+            ok = gang_barrier(ctr, ++epoch * G, err);
             if (rank == 0 && tid < 64 && ok) {
                 for (int m = 0; m < P.nmeas; ++m) {
                     const int64_t s = int64_t(la.y) + P.meas_step[m];
