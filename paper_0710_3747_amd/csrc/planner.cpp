@@ -1766,13 +1766,14 @@ void round_rotation(double theta, bool first, RoundingCarry& c, float* t, float*
     *s = s0;
     if (theta == 0.0) return;
     const float inf = std::numeric_limits<float>::infinity();
+    const double cs = std::cos(theta), sn = std::sin(theta);
     RoundingCarry best;
     double least = -1.0;
     for (const float tc : {t0, std::nextafter(t0, -inf), std::nextafter(t0, inf)})
         for (const float sc : {s0, std::nextafter(s0, -inf), std::nextafter(s0, inf)}) {
             const double diag = 1.0 - double(tc) * sc, b = tc * (1.0 + diag);
             const double across = (first ? 1.0 : -1.0) * (b - sc);
-            const double angle = std::atan2(0.5 * (b + sc), diag) - theta;
+            const double angle = 0.5 * (b + sc) * cs - diag * sn;     // its sine
             const RoundingCarry sum{c.across + across, c.angle + angle};
             // the sums first; among pairs that serve them alike the nearest one
             const double cost = sum.across * sum.across + sum.angle * sum.angle +
