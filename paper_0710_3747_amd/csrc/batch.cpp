@@ -345,7 +345,7 @@ static int build_call(const std::vector<spin_problem>& probs, int init, int nslo
     int rc;
     if ((rc = upload(bp.data(), bp.size() * sizeof(BatchProblem), &bc->d_probs))) return rc;
     if ((rc = upload(nullptr, std::max<int64_t>(bc->tables->part, 2) * sizeof(double), &bc->d_part))) return rc;
-    if ((rc = upload(nullptr, std::max(bc->tables->ncounters, 1) * sizeof(int), &bc->d_ctr))) return rc;
+    if ((rc = upload(nullptr, (bc->tables->ncounters + 1) * sizeof(int), &bc->d_ctr))) return rc;
     if ((rc = upload(nullptr, sizeof(int), &bc->d_err))) return rc;
     bc->nslots = nslots;
     bc->half = half;
@@ -502,7 +502,7 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
                                static_cast<const DevOp<T>*>(bc->tables->d_ops),
                                static_cast<const int2*>(bc->tables->d_launch),
                                static_cast<double*>(bc->d_part), static_cast<int*>(bc->d_ctr),
-                               std::max(bc->tables->ncounters, 1), static_cast<int*>(bc->d_err), status, n_steps, s);
+                               bc->tables->ncounters + 1, static_cast<int*>(bc->d_err), status, n_steps, s);
     };
     std::lock_guard<std::mutex> launch_lock(g_launch_mu);
     hipEvent_t unchained = nullptr;

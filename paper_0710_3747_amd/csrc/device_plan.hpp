@@ -138,6 +138,24 @@ SPIN_HD constexpr int exchange_row_slots(int nt, int elem_bytes) {
 // arrivals apart, their difference does not.
 SPIN_HD constexpr bool gang_waits(uint32_t arrived, uint32_t target) { return int32_t(arrived - target) < 0; }
 
+// Bound of a member's wait.  Before a gang's first meeting a member may wait for
+// others that are still busy with earlier problems, as long as those take, so the
+// time counts from the last progress anywhere in the launch (meetings passed,
+// one-workgroup problems ended and steps of theirs).
+constexpr uint64_t kGangWaitTicks = 20ull * 100000000ull;   // 20 s of the 100 MHz real-time counter
+struct GangClock {
+    uint64_t since;
+    uint32_t seen = 0;
+    SPIN_HD constexpr bool due(uint64_t now) const { return now - since > kGangWaitTicks; }
+    // To be asked with the launch's progress when due: whether it stands still.
+    SPIN_HD constexpr bool stalled(uint64_t now, uint32_t progress) {
+        if (progress == seen) return true;
+        seen = progress;
+        since = now;
+        return false;
+    }
+};
+
 // LDS slots of a workgroup that holds a whole state, 2^r amplitudes on each of
 // nt lanes: it is exchanged in padded rows and staged in memory order.
 SPIN_HD constexpr int resident_slots(int r, int nt, int elem_bytes) {

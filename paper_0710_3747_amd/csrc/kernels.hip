@@ -1633,7 +1633,8 @@ __device__ __forceinline__ void flush_ring(const ResidentRing<NW>& ring, int n) 
 template <typename T, int R, int NT, bool PROFILE = false, int SLOTS>
 __device__ __forceinline__ void resident_run(const ResidentJob& J, const DevStage* __restrict__ stages,
                                              const DevOp<T>* __restrict__ ops, int64_t n_steps,
-                                             typename CT<T>::c (&lds)[SLOTS], ResidentRing<NT / 64>& ring) {
+                                             typename CT<T>::c (&lds)[SLOTS], ResidentRing<NT / 64>& ring,
+                                             int* progress = nullptr) {
     using C = typename CT<T>::c;
     static_assert(SLOTS >= resident_slots(R, NT, int(sizeof(C))), "the state's rows do not fit the LDS buffer");
     constexpr int NTB = __builtin_ctz(NT), NW = NT / 64;
@@ -1677,6 +1678,8 @@ __device__ __forceinline__ void resident_run(const ResidentJob& J, const DevStag
     int last_stage = first;
     for (int64_t k = 0; k <= n_steps; ++k) {
         const int st0 = k == 0 ? first : k < n_steps ? J.step_stage0 : J.last_stage0;
+        // gangs that wait for this workgroup see that it moves (every 0.1 to 10 s)
+        if (progress && (k & 0xffff) == 0 && tid == 0) atomicAdd(progress, 1);
         const int nst = k > 0 ? J.step_nstage : n_steps > 0 ? J.pro_nstage : 1;
         for (int si = 0; si < nst; ++si) {
             const DevStage& S = stages[st0 + si];
@@ -1765,11 +1768,18 @@ __global__ __launch_bounds__(NT) void k_resident(ResidentJob job0,
 // job lists consistently (a global order of gang start times), so every
 // wait is on members busy with earlier jobs: no cycle, no deadlock.  Each
 // wait is bounded; on time-out the problem is flagged and its P set to NaN.
-// Waits at most kGangWaitTicks of the 100 MHz real-time counter, and gives
-// up at once when any workgroup has flagged an error.
-constexpr uint64_t kGangWaitTicks = 20ull * 100000000ull;   // 20 s
+// A wait gives up when nothing in the launch has moved for kGangWaitTicks (the sum
+// of its counters: every gang's arrivals, and the last one, of the one-workgroup
+// problems), and at once when any workgroup has flagged an error.
+__device__ __forceinline__ uint32_t launch_progress(const int* counters, int n) {
+    uint32_t sum = 0;
+    for (int i = 0; i < n; ++i)
+        sum += uint32_t(__hip_atomic_load(counters + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return sum;
+}
 
-__device__ __forceinline__ bool gang_barrier(int* counter, uint32_t target, int* err) {
+__device__ __forceinline__ bool gang_barrier(int* counter, uint32_t target, int* err, const int* counters,
+                                             int ncounters) {
     // Every wave waits until its stores are in the XCD's L2; after the barrier
     // one lane writes that back for all (release) and, when the gang has met,
     // invalidates what the CU and the L2 hold (acquire).  A release by every
@@ -1782,11 +1792,12 @@ __device__ __forceinline__ bool gang_barrier(int* counter, uint32_t target, int*
         int ok = 1;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         atomicAdd(counter, 1);
-        const uint64_t t0 = wall_clock64();
+        GangClock clock{uint64_t(wall_clock64())};
         while (gang_waits(uint32_t(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)), target)) {
             __builtin_amdgcn_s_sleep(4);
+            const uint64_t now = uint64_t(wall_clock64());
             if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-                wall_clock64() - t0 > kGangWaitTicks) {
+                (clock.due(now) && clock.stalled(now, launch_progress(counters, ncounters)))) {
                 atomicOr(err, 1);
                 ok = 0;
                 break;
@@ -1810,8 +1821,8 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                                               const DevOp<T>* __restrict__ ops,
                                               const int2* __restrict__ launches,
                                               double* __restrict__ partials,
-                                              int* __restrict__ counters, int* __restrict__ err,
-                                              int64_t n_steps) {
+                                              int* __restrict__ counters, int ncounters,
+                                              int* __restrict__ err, int64_t n_steps) {
     using C = typename CT<T>::c;
     constexpr int K = R + __builtin_ctz(NT);
     constexpr int KL = K - 1;               // largest one-workgroup problem
@@ -1842,12 +1853,13 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
             J.step_stage0 = B.step_stage0;
             J.step_nstage = B.step_nstage;
             J.last_stage0 = B.last_stage0;
+            int* progress = counters + ncounters - 1;
             // 16 amplitudes per lane, 32 (complex64) for the largest
             if constexpr (NT == 256) {
-                if (B.M <= 12) resident_run<T, 4, NT>(J, stages, ops, n_steps, lds, ring);
-                else if constexpr (sizeof(T) == 4) resident_run<T, 5, NT>(J, stages, ops, n_steps, lds, ring);
+                if (B.M <= 12) resident_run<T, 4, NT>(J, stages, ops, n_steps, lds, ring, progress);
+                else if constexpr (sizeof(T) == 4) resident_run<T, 5, NT>(J, stages, ops, n_steps, lds, ring, progress);
             } else {
-                resident_run<T, 4, NT>(J, stages, ops, n_steps, lds, ring);
+                resident_run<T, 4, NT>(J, stages, ops, n_steps, lds, ring, progress);
             }
             continue;
         }
@@ -1868,7 +1880,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                 c.y = T(im);
                 psi[x] = c;
             }
-            ok = gang_barrier(ctr, ++epoch * G, err);
+            ok = gang_barrier(ctr, ++epoch * G, err, counters, ncounters);
         }
         const int64_t tpm = B.ntiles / G;
         for (int l = 0; l < B.nlaunch && ok; ++l) {
@@ -1917,7 +1929,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                     }
                 }
             }
-            ok = gang_barrier(ctr, ++epoch * G, err);
+            ok = gang_barrier(ctr, ++epoch * G, err, counters, ncounters);
             if (rank == 0 && tid < 64 && ok) {
                 for (int m = 0; m < P.nmeas; ++m) {
                     const int64_t s = int64_t(la.y) + P.meas_step[m];
@@ -2251,12 +2263,12 @@ hipError_t launch_batch(int nslots, bool half, const BatchProblem* probs, const 
     constexpr bool F = sizeof(T) == 4;
     if (half)
         hipLaunchKernelGGL((k_batch<T, F ? 6 : 5, 256, true>), dim3(nslots), dim3(256), 0, st, probs,
-                           jobs, job_start, passes, stages, ops, launches, partials, counters, err,
-                           n_steps);
+                           jobs, job_start, passes, stages, ops, launches, partials, counters,
+                           ncounters, err, n_steps);
     else
         hipLaunchKernelGGL((k_batch<T, F ? 5 : 4, 512, false>), dim3(nslots), dim3(512), 0, st, probs,
-                           jobs, job_start, passes, stages, ops, launches, partials, counters, err,
-                           n_steps);
+                           jobs, job_start, passes, stages, ops, launches, partials, counters,
+                           ncounters, err, n_steps);
     launch_status_or(err, status, st);
     return hipGetLastError();
 }

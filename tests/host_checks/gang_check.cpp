@@ -27,6 +27,18 @@ int main() {
                     if (gang_waits(counter + ahead, target)) ++bad;
             }
         }
+    const uint64_t second = kGangWaitTicks / 20;
+    for (const uint64_t every : {1 * second, 15 * second, 19 * second})
+        for (const uint64_t ends : {uint64_t(0), 30 * second, 5000 * second}) {
+            const uint64_t t0 = 1234567;
+            GangClock clock{t0};
+            uint64_t gave_up = 0;
+            for (uint64_t t = 0; t < 6000 * second && !gave_up; t += second / 4) {
+                const uint32_t progress = uint32_t((t < ends ? t : ends) / every);
+                if (clock.due(t0 + t) && clock.stalled(t0 + t, progress)) gave_up = t;
+            }
+            if (gave_up <= ends / every * every || gave_up > ends + 2 * kGangWaitTicks + second) ++bad;
+        }
     std::printf("failures %d\n", bad);
     return bad ? 1 : 0;
 }

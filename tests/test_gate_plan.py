@@ -82,7 +82,7 @@ def test_batch_kernel_buffer_holds_what_its_problems_touch(tmp_path):
 
 def test_gang_meetings_across_the_wrap_of_their_counter(tmp_path):
     """A gang's counter of arrivals wraps in a long run: no meeting is passed
-    early and none waits for ever."""
+    early and none waits for ever; a wait ends by time only when nothing moves."""
     out = str(tmp_path / "gang_check")
     subprocess.check_call(["g++", "-O2", "-std=c++17", os.path.join(ROOT, "tests", "host_checks", "gang_check.cpp"),
                            "-o", out])
