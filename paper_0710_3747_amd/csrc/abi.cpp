@@ -111,6 +111,29 @@ int scratch_get_slot(hipStream_t st, int slot, size_t bytes, void** out) {
 
 int scratch_get(hipStream_t st, size_t bytes, void** out) { return scratch_get_slot(st, 0, bytes, out); }
 
+// One call's turn on a stream: its launches use the stream's scratch memory one
+// after the other, so calls of several threads on one stream enqueue theirs as
+// a whole, one call at a time.
+class StreamTurn {
+  public:
+    explicit StreamTurn(hipStream_t st) {
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        std::lock_guard<std::mutex> lk(g_mu);
+        std::shared_ptr<std::mutex>& m = g_turns[{dev, st}];
+        if (!m) m = std::make_shared<std::mutex>();
+        mu_ = m;
+        held_ = std::unique_lock<std::mutex>(*mu_, std::defer_lock);
+    }
+    void take() { held_.lock(); }
+
+  private:
+    static std::map<std::pair<int, hipStream_t>, std::shared_ptr<std::mutex>> g_turns;
+    std::shared_ptr<std::mutex> mu_;
+    std::unique_lock<std::mutex> held_;
+};
+std::map<std::pair<int, hipStream_t>, std::shared_ptr<std::mutex>> StreamTurn::g_turns;
+
 // Bytes of the stream's scratch memory of slot 0 as it is.
 static size_t scratch_held(hipStream_t st) {
     int dev = 0;
@@ -514,6 +537,8 @@ static int evolve_naive(void* psi, int M, const std::vector<Coupling>& J, double
     const int nblk = 1024;
     void* scratch = nullptr;
     int rc;
+    StreamTurn turn(st);
+    if (!ws) turn.take();
     if (ws) {
         if (ws->doubles < size_t(nblk) * 2) return fail(SPIN_EUNSUPPORTED, "workspace too small");
         scratch = ws->ptr;
@@ -598,6 +623,8 @@ static int evolve_profile(void* psi, int M, const DevicePlan& dp, int64_t n_step
         if (fit >= least) ch = std::min(ch, fit);
     }
     void* scratch = nullptr;
+    StreamTurn turn(st);
+    turn.take();
     int rc = scratch_get(st, size_t(ch) * slot_bytes, &scratch);
     if (rc) return rc;
     double* part = static_cast<double*>(scratch);
@@ -690,6 +717,8 @@ static int evolve_fused(void* psi, int M, const std::vector<Coupling>& J, double
     const int64_t least = std::min<int64_t>(total, kMaxMeas);
     int64_t ch = std::min<int64_t>(std::min<int64_t>(total, 1024), std::max(2 * kMaxMeas, (1 << 20) / nwg));
     void* scratch = nullptr;
+    StreamTurn turn(st);
+    if (!ws) turn.take();
     if (ws) {
         ch = std::min<int64_t>(std::min<int64_t>(total, 1024), int64_t(ws->doubles * sizeof(double) / slot_bytes));
         if (ch < least) {
@@ -794,6 +823,8 @@ int spin_local_polarization_ex(const void* psi, int32_t prec, int32_t M, int32_t
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int nblk = 1024;
     void* scratch = nullptr;
+    StreamTurn turn(st);
+    turn.take();
     if ((rc = scratch_get(st, size_t(nblk) * 2 * sizeof(double), &scratch))) return rc;
     double* part = static_cast<double*>(scratch);
     hipError_t e = prec == SPIN_C64 ? launch_observe<float>(psi, M, site, part, nblk, st)

@@ -162,3 +162,46 @@ def test_default_and_explicit_double_precision_tiles_keep_their_plans():
     spq.spin_release_caches()
     run({})
     assert same(run({"tile_bits": 13}), explicit)   # after the default call
+
+
+@pytest.mark.parametrize("prec,M", [(C64, 13), (C128, 13)])
+def test_threads_on_one_stream_do_not_share_partial_sums(prec, M):
+    """Dipolar states of 12 to 14 sites run as tiled passes whose partial sums
+    lie in the stream's scratch memory: calls of several threads on one stream
+    give the bits of calls made one by one."""
+    import threading
+    import torch
+    note("threads", prec, M)
+    J = workloads.star(M, 7, a_over_b=-2.0)
+    dt, steps, n, calls = 0.03, 6, 4, 12
+    spq.spin_prepare_plan(prec, M, J, dt, steps, 0, None)
+    psi = [torch.empty(2 ** M, dtype=torch_dtype(prec), device="cuda") for _ in range(n)]
+    out = torch.zeros(2, n, calls, steps + 1, dtype=torch.float64, device="cuda")
+    norm = torch.zeros_like(out)
+    Pall = torch.zeros(2, n, calls, (steps + 1) * M, dtype=torch.float64, device="cuda")
+    one = torch.zeros(2, n, calls, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(q, row):
+        try:
+            for c in range(calls):
+                spq.spin_init_random_phase(psi[q], M, 0, 100 * q + c)
+                spq.spin_trotter_evolve_ex(psi[q], M, J, dt, steps, 0, out[row, q, c], norm[row, q, c])
+                spq.spin_local_polarization(psi[q], M, 0, one[row, q, c:c + 1])
+                spq.spin_trotter_evolve_profile(psi[q], M, J, dt, steps, Pall[row, q, c])
+        except Exception as e:      # noqa: BLE001 - reported below
+            failed.append(e)
+
+    for q in range(n):
+        work(q, 0)
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(q, 1)) for q in range(n)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for a in (out, norm, Pall, one):
+        assert torch.equal(a[0], a[1])
