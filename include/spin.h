@@ -274,8 +274,9 @@ enum {
  * The states must not overlap.  The work is enqueued on `stream` and the
  * call returns without synchronising (the first call with a new problem set
  * plans and uploads its tables synchronously; later equal calls reuse them
- * until spin_release_caches, and calls with other states, seeds or outputs
- * reuse the tables of their couplings).  Problems larger than one workgroup's
+ * until spin_release_caches, or until 1024 others or 1 GiB of them have been
+ * used since, and calls with other states, seeds or outputs reuse the tables
+ * of their couplings).  Problems larger than one workgroup's
  * tile run as gangs of workgroups that meet at bounded device-wide barriers,
  * so batched launches with such problems run one after the other on a device
  * (others overlap as their streams allow); if a

@@ -13,6 +13,7 @@
 
 #include "../../include/spin.h"
 #include "abi_internal.hpp"
+#include "kept.hpp"
 #include "kernels.hpp"
 #include "planner.hpp"
 
@@ -27,6 +28,7 @@ struct BatchTables {
     std::vector<BatchProblem> probs;    // without pointers, seeds and polarised sites
     int64_t part = 0;
     int ncounters = 0;
+    size_t bytes = 0;
     ~BatchTables() {
         for (void* p : {d_jobs, d_jstart, d_passes, d_stages, d_ops, d_launch})
             if (p) (void)hipFree(p);
@@ -42,7 +44,10 @@ struct BatchCache {
     hipStream_t side = nullptr;
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
+    size_t bytes = 0;
     ~BatchCache() {
+        // its latest launch may still run
+        if (side) (void)hipStreamSynchronize(side);
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
         if (side) (void)hipStreamDestroy(side);
@@ -58,15 +63,20 @@ struct BatchCache {
 struct SmallBatch {
     void *d_jobs = nullptr, *d_stages = nullptr, *d_ops = nullptr;
     int njobs = 0, bits = 0;
+    size_t bytes = 0;
     ~SmallBatch() {
         for (void* p : {d_jobs, d_stages, d_ops})
             if (p) (void)hipFree(p);
     }
 };
 
+// Kept of past calls, by everything that their launches hold.  A program that
+// draws new states or seeds for every call would otherwise leave an entry of
+// device memory, a stream and a graph behind with each.
+constexpr size_t kCallsKept = 1024, kCallBytesKept = size_t(1) << 30;
 static std::mutex g_bmu;
-static std::map<std::vector<double>, std::shared_ptr<SmallBatch>> g_small;
-static std::map<std::vector<double>, std::shared_ptr<BatchCache>> g_bcache;
+static Kept<SmallBatch> g_small(kCallsKept, kCallBytesKept);
+static Kept<BatchCache> g_bcache(kCallsKept, kCallBytesKept);
 // The tables of the latest sets of couplings, latest first.
 constexpr size_t kBatchTablesKept = 8;
 static std::list<std::pair<std::vector<double>, std::shared_ptr<const BatchTables>>> g_btables;
@@ -156,8 +166,9 @@ static std::vector<double> tables_key(const spin_problem* probs, int n, const st
     return k;
 }
 
-static int upload(const void* src, size_t n, void** dst) {
+static int upload(const void* src, size_t n, void** dst, size_t* total) {
     if (n == 0) n = 16;
+    *total += n;
     if (hipMalloc(dst, n) != hipSuccess) return fail(SPIN_ENOMEM, "batch table allocation failed");
     if (src && hipMemcpy(*dst, src, n, hipMemcpyHostToDevice) != hipSuccess)
         return fail(SPIN_EHIP, "batch table upload failed");
@@ -324,12 +335,12 @@ static int build_tables(const std::vector<spin_problem>& probs, const std::vecto
     jstart[nslots] = int(jobs.size());
 
     int rc;
-    if ((rc = upload(jobs.data(), jobs.size() * sizeof(BatchJob), &bt->d_jobs))) return rc;
-    if ((rc = upload(jstart.data(), jstart.size() * sizeof(int), &bt->d_jstart))) return rc;
-    if ((rc = upload(tb.passes.data(), tb.passes.size() * sizeof(DevPass), &bt->d_passes))) return rc;
-    if ((rc = upload(tb.stages.data(), tb.stages.size() * sizeof(DevStage), &bt->d_stages))) return rc;
-    if ((rc = upload(tb.ops.data(), tb.ops.size() * sizeof(DevOp<T>), &bt->d_ops))) return rc;
-    return upload(launches.data(), launches.size() * sizeof(int2), &bt->d_launch);
+    if ((rc = upload(jobs.data(), jobs.size() * sizeof(BatchJob), &bt->d_jobs, &bt->bytes))) return rc;
+    if ((rc = upload(jstart.data(), jstart.size() * sizeof(int), &bt->d_jstart, &bt->bytes))) return rc;
+    if ((rc = upload(tb.passes.data(), tb.passes.size() * sizeof(DevPass), &bt->d_passes, &bt->bytes))) return rc;
+    if ((rc = upload(tb.stages.data(), tb.stages.size() * sizeof(DevStage), &bt->d_stages, &bt->bytes))) return rc;
+    if ((rc = upload(tb.ops.data(), tb.ops.size() * sizeof(DevOp<T>), &bt->d_ops, &bt->bytes))) return rc;
+    return upload(launches.data(), launches.size() * sizeof(int2), &bt->d_launch, &bt->bytes);
 }
 
 static int build_call(const std::vector<spin_problem>& probs, int init, int nslots, bool half, BatchCache* bc) {
@@ -343,10 +354,10 @@ static int build_call(const std::vector<spin_problem>& probs, int init, int nslo
         bp[p].init = init;
     }
     int rc;
-    if ((rc = upload(bp.data(), bp.size() * sizeof(BatchProblem), &bc->d_probs))) return rc;
-    if ((rc = upload(nullptr, std::max<int64_t>(bc->tables->part, 2) * sizeof(double), &bc->d_part))) return rc;
-    if ((rc = upload(nullptr, (bc->tables->ncounters + 1) * sizeof(int), &bc->d_ctr))) return rc;
-    if ((rc = upload(nullptr, sizeof(int), &bc->d_err))) return rc;
+    if ((rc = upload(bp.data(), bp.size() * sizeof(BatchProblem), &bc->d_probs, &bc->bytes))) return rc;
+    if ((rc = upload(nullptr, std::max<int64_t>(bc->tables->part, 2) * sizeof(double), &bc->d_part, &bc->bytes))) return rc;
+    if ((rc = upload(nullptr, (bc->tables->ncounters + 1) * sizeof(int), &bc->d_ctr, &bc->bytes))) return rc;
+    if ((rc = upload(nullptr, sizeof(int), &bc->d_err, &bc->bytes))) return rc;
     bc->nslots = nslots;
     bc->half = half;
     return SPIN_OK;
@@ -394,9 +405,9 @@ static int build_small(const std::vector<spin_problem>& probs, const std::vector
         jobs.push_back(j);
     }
     int rc;
-    if ((rc = upload(jobs.data(), jobs.size() * sizeof(ResidentJob), &sb->d_jobs))) return rc;
-    if ((rc = upload(tb.stages.data(), tb.stages.size() * sizeof(DevStage), &sb->d_stages))) return rc;
-    return upload(tb.ops.data(), tb.ops.size() * sizeof(DevOp<T>), &sb->d_ops);
+    if ((rc = upload(jobs.data(), jobs.size() * sizeof(ResidentJob), &sb->d_jobs, &sb->bytes))) return rc;
+    if ((rc = upload(tb.stages.data(), tb.stages.size() * sizeof(DevStage), &sb->d_stages, &sb->bytes))) return rc;
+    return upload(tb.ops.data(), tb.ops.size() * sizeof(DevOp<T>), &sb->d_ops, &sb->bytes);
 }
 
 template <typename T>
@@ -412,11 +423,14 @@ static int batch_small(const spin_problem* probs, const std::vector<int>& sel,
         js.push_back(Js[p]);
     }
     const std::vector<double> key = batch_key(ps.data(), int(ps.size()), js, prec, dt, n_steps, init, dev);
+    // a captured launch keeps its tables' addresses
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) return fail(SPIN_EHIP, "stream query failed");
+    const bool pin = cs != hipStreamCaptureStatusNone;
     std::shared_ptr<SmallBatch> sb;
     {
         std::lock_guard<std::mutex> lk(g_bmu);
-        auto it = g_small.find(key);
-        if (it != g_small.end()) sb = it->second;
+        sb = g_small.find(key, pin);
     }
     if (!sb) {
         sb = std::make_shared<SmallBatch>();
@@ -425,8 +439,9 @@ static int batch_small(const spin_problem* probs, const std::vector<int>& sel,
         } catch (const std::exception& e) {
             return fail(SPIN_EUNSUPPORTED, std::string("batch planning failed: ") + e.what());
         }
+        std::vector<std::shared_ptr<SmallBatch>> gone;
         std::lock_guard<std::mutex> lk(g_bmu);
-        g_small[key] = sb;
+        gone = g_small.insert(key, sb, sb->bytes, pin);
     }
     const hipError_t e = launch_resident<T>(sb->bits, ResidentJob{}, static_cast<const ResidentJob*>(sb->d_jobs), sb->njobs,
                                             static_cast<const DevStage*>(sb->d_stages),
@@ -458,8 +473,7 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
     std::shared_ptr<BatchCache> bc;
     {
         std::lock_guard<std::mutex> lk(g_bmu);
-        auto it = g_bcache.find(key);
-        if (it != g_bcache.end()) bc = it->second;
+        bc = g_bcache.find(key);
     }
     if (!bc) {
         bc = std::make_shared<BatchCache>();
@@ -488,8 +502,9 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
             if (g_btables.size() > kBatchTablesKept) g_btables.pop_back();
         }
         if ((rc = build_call(ps, init, nslots, half, bc.get()))) return rc;
+        std::vector<std::shared_ptr<BatchCache>> gone;      // let go of after the lock
         std::lock_guard<std::mutex> lk(g_bmu);
-        g_bcache[key] = bc;
+        gone = g_bcache.insert(key, bc, bc->bytes + bc->tables->bytes);
     }
     int* status = nullptr;
     if (int rc = status_word(dev, &status)) return rc;

@@ -88,3 +88,12 @@ def test_gang_meetings_across_the_wrap_of_their_counter(tmp_path):
                            "-o", out])
     p = subprocess.run([out], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout
+
+
+def test_calls_kept_are_bounded(tmp_path):
+    """What is kept of past batched calls is bounded in number and bytes."""
+    out = str(tmp_path / "kept_check")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", os.path.join(ROOT, "tests", "host_checks", "kept_check.cpp"),
+                           "-o", out])
+    p = subprocess.run([out], capture_output=True, text=True, timeout=60)
+    assert p.returncode == 0, p.stdout

@@ -110,3 +110,25 @@ def test_problems_without_couplings_share_the_slots():
             best = min(best, time.perf_counter() - t0)
         took.append(best)
     assert took[0] <= took[1], took
+
+
+def test_calls_with_new_seeds_do_not_pile_up():
+    """More calls with new seeds than are kept, on two streams: the states stay
+    right and the device's free memory stops falling."""
+    import torch
+    note("new seeds")
+    dt, steps, M = 0.05, 2, 14
+    ps = problems(C64, [M], steps, couplings=workloads.chain(M))
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    spq.spin_release_caches()
+    free = []
+    for turn in range(3):
+        for q in range(1100):
+            ps[0]["seed"] = 1100 * turn + q
+            spq.spin_trotter_evolve_batch(ps, C64, dt, steps, stream=streams[q % 2].cuda_stream)
+            if q % 100 == 99:
+                torch.cuda.synchronize()
+        check_against_single_runs(C64, ps, dt, steps)
+        free.append(torch.cuda.mem_get_info()[0])
+    assert free[2] == free[1]
+    assert spq.spin_batch_status() == 0
