@@ -421,15 +421,19 @@ typedef struct {
     int32_t period_steps, period_passes;  /* repeating block of the plan (path 2) */
     int32_t stages_total;   /* register stages over all templates */
     int32_t engine;         /* stage arithmetic of path 2: 0 VALU butterflies, 1 MFMA matrices */
-    int32_t exchange;       /* stage exchanges of path 2: 1 whole tiles, 2 half tiles */
+    int32_t exchange;       /* stage exchanges of path 2: 1 whole tiles in one layout, 2 half
+                               tiles, 0 small tiles, whole through per-lane slots (as
+                               spin_options.exchange with tile_bits 12 or 13; those of
+                               2^10 and 2^11 are taken by default only) */
     int32_t reserved_;
     int64_t launches;       /* pass-kernel launches for the whole call */
     int64_t factor_ops;     /* two-spin factor applications after merging, whole call */
     double passes_per_step; /* launches / n_steps (path 2) */
     int64_t exchanges;      /* stage exchanges through LDS over the whole call: each
                                writes and reads every amplitude once (path 2: register
-                               stages after the first of each launch; path 1: every
-                               stage, the state lives in LDS) */
+                               stages after the first of each launch; path 1: the state
+                               is held in registers and exchanged between its stages and
+                               steps, counted as one per stage) */
 } spin_plan_info;
 
 int spin_describe_plan(int32_t prec, int32_t M, const spin_coupling *J, int32_t K, double dt,

@@ -1067,7 +1067,7 @@ extern "C" int spin_describe_plan(int32_t prec, int32_t M, const spin_coupling* 
         info->lanes = hp.sh.nt;
         info->coalesce_bits = hp.sh.c;
         info->engine = hp.sh.engine;
-        info->exchange = hp.sh.exchange == kHalfTiles ? 2 : 1;
+        info->exchange = hp.sh.exchange == kHalfTiles ? 2 : hp.sh.exchange == kWholeTiles ? 1 : 0;
         info->templates = int(hp.sp.passes.size());
         info->period_steps = hp.sp.period_steps;
         info->period_passes = hp.sp.period_passes;

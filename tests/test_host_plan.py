@@ -409,3 +409,19 @@ def test_observables_of_step_0_come_before_any_factor(prec, M, J, observed):
         first = int((t[:, 0] == 0).argmax())
         zeros = [n for n, rec in enumerate(t) if rec[0] == 1 and rec[1] == 0]
         assert len(zeros) == (M if observed == spq.SPIN_ALL_SITES else 1) and max(zeros) < first
+
+
+@pytest.mark.parametrize("prec,M,opts,exchange", [
+    (spq.SPIN_C64, 18, {}, 0), (spq.SPIN_C64, 21, {}, 0), (spq.SPIN_C128, 16, {}, 0), (spq.SPIN_C64, 24, {}, 2),
+    (spq.SPIN_C64, 18, {"tile_bits": 14}, 2), (spq.SPIN_C64, 18, {"exchange": 1}, 1),
+    (spq.SPIN_C64, 18, {"tile_bits": 12, "reg_bits": 4, "exchange": 1}, 1)])
+def test_plan_info_names_the_exchange_of_small_tiles(prec, M, opts, exchange):
+    """0 is the small tiles' own exchange; a plan on tiles of 2^12 or 2^13 can be
+    asked for again by the fields of its description."""
+    args = (prec, M, workloads.ladder(M // 2), 0.05, 20, 0)
+    info = spq.spin_describe_plan(*args, spq.Options(**opts))
+    assert info["path"] == 2 and info["exchange"] == exchange
+    if info["tile_bits"] >= 12:
+        again = spq.spin_describe_plan(*args, spq.Options(**{k: info[k] for k in (
+            "tile_bits", "reg_bits", "coalesce_bits", "exchange")}))
+        assert again == info
