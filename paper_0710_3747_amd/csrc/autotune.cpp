@@ -133,7 +133,9 @@ std::vector<Tuned> large_tiles(int32_t prec) {
             {13, 5, 4, 0, 1, 0}, {12, 4, 4, 0, 1, 0}};
 }
 
-// Candidate launch shapes; the first is the library default.  The MFMA
+// Candidate launch shapes; the first is the library default as a caller gets it
+// without options (which no explicit shape need equal), and an explicit shape
+// that is the same one is left out.  The MFMA
 // matrix engine is not among them: a dense stage matrix costs about 20x the
 // flops of the butterflies it replaces and it removes no LDS exchange, so it
 // never wins on these workloads (it stays selectable through spin_options).
@@ -141,12 +143,20 @@ std::vector<Tuned> large_tiles(int32_t prec) {
 // of 2^14), 1 = whole tiles, 0 = the small tiles, for the states whose default
 // they are.
 std::vector<Tuned> candidates(int32_t prec, const Shape& def) {
-    std::vector<Tuned> c = large_tiles(prec);
+    std::vector<Tuned> c;
     if (def.exchange == kSmallTiles) {
-        if (prec == SPIN_C64 && def.k != 13) c.insert(c.begin(), Tuned{13, 4, 4, 0, 0, 0});
-        if (def.k != 12) c.insert(c.begin(), Tuned{12, 4, 4, 0, 0, 0});
-        c.insert(c.begin(), Tuned{});
+        c.push_back(Tuned{12, 4, 4, 0, 0, 0});
+        if (prec == SPIN_C64) c.push_back(Tuned{13, 4, 4, 0, 0, 0});
     }
+    for (const Tuned& t : large_tiles(prec)) c.push_back(t);
+    const int exchange = def.exchange == kHalfTiles ? 2 : def.exchange == kWholeTiles ? 1 : 0;
+    c.erase(std::remove_if(c.begin(), c.end(),
+                           [&](const Tuned& t) {
+                               return !def.try_large && t.tile_bits == def.k && t.reg_bits == def.r &&
+                                      t.coalesce_bits == def.c && t.exchange == exchange;
+                           }),
+            c.end());
+    c.insert(c.begin(), Tuned{});
     return c;
 }
 

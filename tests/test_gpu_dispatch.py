@@ -205,3 +205,17 @@ def test_threads_on_one_stream_do_not_share_partial_sums(prec, M):
     assert not failed, failed
     for a in (out, norm, Pall, one):
         assert torch.equal(a[0], a[1])
+
+
+@pytest.mark.parametrize("prec,M", [(C64, 18), (C64, 24), (C128, 20), (C64, 13)])
+def test_autotuner_tries_the_default_first_and_once(prec, M):
+    import torch
+    torch.zeros(1, device="cuda")
+    note("autotune", prec, M)
+    J, dt = workloads.ladder(M // 2), 0.05
+    spq.spin_release_caches()
+    res = spq.spin_autotune(prec, M, J, dt, 0, trial_steps=4)["results"]
+    names = ("tile_bits", "reg_bits", "coalesce_bits", "exchange")
+    assert all(r["status"] == 0 for r in res) and [res[0][k] for k in names] == [0] * 4
+    shapes = [spq.spin_describe_plan(prec, M, J, dt, 4, 0, spq.Options(**{k: r[k] for k in names})) for r in res]
+    assert all([s[k] for k in names] != [shapes[0][k] for k in names] for s in shapes[1:])
