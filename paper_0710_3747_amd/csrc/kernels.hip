@@ -324,15 +324,18 @@ __global__ __launch_bounds__(NT) void k_reduce(const double* __restrict__ partia
 }
 #endif
 
-// Reads the state once, so the loads in flight bound it: four 16-byte loads per
+// Reads the state once, so the loads in flight bound it: U = 4 16-byte loads per
 // lane, a workgroup's 16 KiB contiguous.  M = 28: complex64 572 -> 348 us (6.2
-// TB/s), complex128 735 -> 697 us; the same four loads a whole grid apart 412
-// and 814 us.
-template <typename T>
+// TB/s), complex128 738 -> 692 us; the same four loads a whole grid apart 412
+// and 814 us.  complex128 states that stay in the last-level cache (256 MiB, M =
+// 24) are read one load at a time: 40.9 us against 42.5, M = 23 23.1 against
+// 23.6, M = 25 89.0 against 90.0, M = 26 176 against 175 (complex64 is faster
+// with four at every size).
+template <typename T, int U>
 __global__ __launch_bounds__(256) void k_observe(const typename CT<T>::c* __restrict__ psi, int M,
                                                  int site, double* __restrict__ partials) {
     using Vec = typename CT<T>::v;
-    constexpr int V = CT<T>::V, U = 4;
+    constexpr int V = CT<T>::V;
     __shared__ double red[8];
     const Vec* __restrict__ in = reinterpret_cast<const Vec*>(psi);
     const uint64_t nvec = (1ull << M) / V;
@@ -2034,8 +2037,11 @@ hipError_t launch_accumulate(double* acc, const double* add, int64_t n, double s
 template <typename T>
 hipError_t launch_observe(const void* psi, int M, int site, double* partials, int nblk,
                           hipStream_t st) {
-    hipLaunchKernelGGL(k_observe<T>, dim3(nblk), dim3(256), 0, st,
-                       reinterpret_cast<const typename CT<T>::c*>(psi), M, site, partials);
+    const auto* in = reinterpret_cast<const typename CT<T>::c*>(psi);
+    if (sizeof(T) == 8 && M <= 25)
+        hipLaunchKernelGGL((k_observe<T, 1>), dim3(nblk), dim3(256), 0, st, in, M, site, partials);
+    else
+        hipLaunchKernelGGL((k_observe<T, 4>), dim3(nblk), dim3(256), 0, st, in, M, site, partials);
     return hipGetLastError();
 }
 

@@ -219,3 +219,19 @@ def test_autotuner_tries_the_default_first_and_once(prec, M):
     assert all(r["status"] == 0 for r in res) and [res[0][k] for k in names] == [0] * 4
     shapes = [spq.spin_describe_plan(prec, M, J, dt, 4, 0, spq.Options(**{k: r[k] for k in names})) for r in res]
     assert all([s[k] for k in names] != [shapes[0][k] for k in names] for s in shapes[1:])
+
+
+@pytest.mark.parametrize("prec,M", [(C128, 25), (C128, 26), (C64, 25)])
+def test_observable_of_states_around_the_last_level_cache(prec, M):
+    """Either way of reading a state against torch's FP64 sums."""
+    import torch
+    note("observable", prec, M)
+    psi = torch.empty(2 ** M, dtype=torch_dtype(prec), device="cuda")
+    spq.spin_init_random_phase(psi, M, 3, 8)
+    P, N = torch.zeros(1, dtype=torch.float64, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+    w = torch.view_as_real(psi).double().square().sum(-1)
+    for site in (0, 1, 3, M - 1):
+        spq.spin_local_polarization_ex(psi, M, site, P, N)
+        v = w.view(-1, 2, 2 ** site)
+        want = float(v[:, 0].sum() - v[:, 1].sum())
+        assert abs(float(P) - want) < 1e-12 and abs(float(N) - float(w.sum())) < 1e-12
