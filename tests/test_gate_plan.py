@@ -50,6 +50,22 @@ CASES = [
     ("resident-star13-r5", 13, workloads.star(13, 7), 1, 13, 5, 0, 2, 0, 2),
     ("resident-duplicates", 6, workloads.chain(6) + [(0, 1, 0.0, 1.0), (1, 0, 0.0, 0.5)], 2, 10, 4, 0, 4, 1, 2),
     ("chain13-c64-one-wave", 13, workloads.chain(13), 1, 11, 5, 4, 30, 0, 0),
+    # 512 lanes of 16 amplitudes, the default at M = 21
+    ("star21-c64-k13", 21, workloads.star(21, 3), 1, 13, 4, 4, 3, 20, 0),
+    ("ladder2x10-dangling-c64-k13-zz", 21, workloads.ladder(10, a_over_b=0.5) + [(0, 20, 0.0, 0.3)], 1, 13, 4, 4, 30, 0, 0),
+    ("chain22-c64-r5", 22, workloads.chain(22), 1, 14, 5, 4, 30, 11, 1),
+    ("star23-c64-r5", 23, workloads.star(23, 3), 1, 14, 5, 4, 3, 0, 1),
+    ("chain21-c128-k13", 21, workloads.chain(21, a_over_b=-2.0), 2, 13, 5, 4, 30, 0, 1),
+    # what half tiles of every shape exchange through in a run (test_host_plan
+    # checks the one layout that they could share)
+    ("ladder2x15-c64-k14r5c4-1000", 30, workloads.ladder(15), 1, 14, 5, 4, 1000, 0, 1),
+    ("ladder2x15-c64-k14r5c5-3steps", 30, workloads.ladder(15), 1, 14, 5, 5, 3, 0, 1),
+    ("ladder2x15-c64-k14r6c4-100", 30, workloads.ladder(15), 1, 14, 6, 4, 100, 0, 1),
+    ("ladder2x15-c128-k13r4c4-100", 30, workloads.ladder(15), 2, 13, 4, 4, 100, 0, 1),
+    ("ladder2x15-c128-k13r5c4-100", 30, workloads.ladder(15), 2, 13, 5, 4, 100, 0, 1),
+    ("ladder2x15-c128-k14r5c4-100", 30, workloads.ladder(15), 2, 14, 5, 4, 100, 0, 1),
+    ("star28-c64-k14r5c6", 28, workloads.star(28, 33), 1, 14, 5, 6, 12, 0, 1),
+    ("star28-blocks-c64-k14r6c4", 28, workloads.star_m28(), 1, 14, 6, 4, 12, 0, 1),
 ]
 
 

@@ -10,7 +10,7 @@ import oracle
 import workloads
 from oracle import cref
 import paper_0710_3747_amd as spq
-from gpu_helpers import TOL_P, assert_state_close, gpu_evolve, note, torch_dtype
+from gpu_helpers import TOL_P, assert_state_close, gpu_evolve, gpu_profile, note, torch_dtype
 from test_zz_no_alloc import _run
 
 pytestmark = pytest.mark.gpu
@@ -235,3 +235,33 @@ def test_observable_of_states_around_the_last_level_cache(prec, M):
         v = w.view(-1, 2, 2 ** site)
         want = float(v[:, 0].sum() - v[:, 1].sum())
         assert abs(float(P) - want) < 1e-12 and abs(float(N) - float(w.sum())) < 1e-12
+
+
+@pytest.mark.parametrize("prec,M,J,steps", [
+    (C64, 20, workloads.star(20, 7), 2), (C64, 21, workloads.star(21, 7), 2),
+    (C64, 21, workloads.chain(21, a_over_b=-2.0), 4), (C64, 22, workloads.ladder(11), 4),
+    (C64, 23, workloads.chain(23, a_over_b=0.5), 3), (C64, 24, workloads.ladder(12), 3),
+    (C128, 20, workloads.ladder(10), 6), (C128, 21, workloads.chain(21), 4), (C128, 22, workloads.ladder(11, a_over_b=0.5), 3),
+], ids=lambda v: str(v) if isinstance(v, int) else "")
+def test_default_shapes_past_the_smallest_tiles_match_the_oracle(prec, M, J, steps):
+    """Tiles of 2^12, 2^13 on 512 lanes (M = 21), and 2^14 with 32 and 64
+    amplitudes per lane, where the default goes from one to the next."""
+    note("dispatch", M, prec)
+    site = M - 1
+    ref = np.ascontiguousarray(oracle.random_phase_state(M, site, 5))
+    P0, N0 = cref.trotter_run(ref, M, J, 0.03, steps, site)
+    P, N, psi, _ = gpu_evolve(prec, M, J, 0.03, steps, site, polarized=site, seed=5)
+    assert np.abs(P - P0).max() < TOL_P[prec]
+    assert np.abs(N / N0 - 1).max() < TOL_P[prec]
+    assert_state_close(psi, ref, prec)
+
+
+@pytest.mark.parametrize("M", [21, 23])
+def test_default_profiles_past_the_smallest_tiles_match_the_single_site_curves(M):
+    note("dispatch profile", M)
+    J, steps = workloads.chain(M), 5
+    Pall, N, _ = gpu_profile(C64, M, J, 0.05, steps, seed=3, keep_state=False)
+    for site in (0, M // 2, M - 1):
+        P, N1, _, _ = gpu_evolve(C128, M, J, 0.05, steps, site, seed=3, keep_state=False)
+        assert np.abs(Pall[:, site] - P).max() < TOL_P[C64]
+    assert np.abs(N - N1).max() < TOL_P[C64]
