@@ -635,6 +635,7 @@ void plan_stages_coalesced(HostPass& pass, int r, int c, int beam, bool half, in
     const int rx = r + ng;      // positions a stage's ops can reach
     pass.split = -1;
     pass.slots = half || once;
+    pass.one_layout = half && gates == 0;
     if (!half || k < 2 || r < 2) {
         plan_stages(pass, rx, af, al, beam);
         if (!rank)
@@ -1862,7 +1863,6 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, int
         lanes_all.push_back(tp);
         waves_all.push_back(wv);
     }
-    const bool gated = nst > 0 && !stages[0].gates.empty();
     std::vector<uint32_t> img(k, 0u);
     if (hp.split >= 0)
         // half-tile exchanges: one half of the tile in LDS at a time, the
@@ -1878,9 +1878,10 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, int
         order_for_gathers(stages, lanes_all, waves_all, eb, 1 << (k - int(stages[0].regs.size())), hp.split >= 0,
                           hp.in_registers, nl.empty() ? nullptr : &nl);
     }
-    if (hp.split >= 0 && !gated) {
-        // without register/lane exchanges a half-tile pass also has a layout
-        // shared by all its stages, over the other k - 1 positions
+    if (hp.split >= 0 && hp.one_layout) {
+        // a half-tile pass planned without gates also has a layout shared by all
+        // its stages, over the other k - 1 positions (no kernel reads it: half
+        // tiles go through per-lane slots; the host checks' reference for them)
         auto comp = [&](int p) { return p < hp.split ? p : p - 1; };
         std::vector<std::vector<int>> pat;
         for (const auto& lv : lanes_all) {

@@ -86,6 +86,7 @@ struct HostPass {
     bool writes = true;
     bool slots = false;        // exchanges use per-lane slots (see exchange_row_slots)
     bool in_registers = false; // neither loaded from nor stored to HBM by its stages
+    bool one_layout = false;   // staged without gates: also lay the tile out in LDS as a whole
     bool block_start = false;  // first pass of a block that the run repeats
 };
 
