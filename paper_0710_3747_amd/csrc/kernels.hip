@@ -206,8 +206,34 @@ __global__ __launch_bounds__(256) void k_init(typename CT<T>::c* __restrict__ ps
     }
 }
 
+// Amplitude of ensemble member r where it is up: 1, and in single precision a
+// point of the unit circle at a phase of the member's own, which no observable
+// sees.  With 1 in all of them the first factors round every member alike, and
+// the mean keeps that rounding (ladder 2x7, 100 steps: norm 6.3e-8 off from the
+// first steps on, with phases 1.2e-8).  Of 32 neighbouring points whose
+// components are rounded to single precision the one closest to the circle is
+// taken (|x^2 + y^2 - 1| about 1e-9, 1e-8 at most).
+__device__ __forceinline__ double2 member_amp(uint64_t r, double) { return double2{1.0, 0.0}; }
+__device__ __forceinline__ float2 member_amp(uint64_t r, float) {
+    double sn, cs;
+    sincos_turn(0.125 * sm64_uniform(0, r) + 0.0625, &sn, &cs);     // 22.5 to 67.5 degrees
+    const int first = __float_as_int(float(cs));
+    float2 best{1.f, 0.f};
+    double least = 1.0;
+    for (int k = 0; k < 32; ++k) {
+        const float x = __int_as_float(first + k);
+        const float y = float(sqrt(1.0 - double(x) * double(x)));
+        const double off = fabs(fma(double(x), double(x), double(y) * double(y)) - 1.0);
+        if (off < least) {
+            least = off;
+            best = float2{x, y};
+        }
+    }
+    return best;
+}
+
 // Ensemble members stacked as one state of M + cbits sites: amplitude
-// x = (m << M) | y is 1 when m < count and y is the basis state of member
+// x = (m << M) | y is member_amp when m < count and y is the basis state of member
 // first + m (its bits spread over the sites other than `polarized`, whose
 // bit is 0: spin up), and 0 otherwise.
 template <typename T>
@@ -223,8 +249,8 @@ __global__ __launch_bounds__(256) void k_init_members(typename CT<T>::c* __restr
         const uint64_t r = first + m;
         const uint64_t basis = ((r & ~low) << 1) | (r & low);
         typename CT<T>::c v;
-        v.x = T((m < count && (x & ymask) == basis) ? 1 : 0);
-        v.y = T(0);
+        v.x = v.y = T(0);
+        if (m < count && (x & ymask) == basis) v = member_amp(r, T(0));
         psi[x] = v;
     }
 }

@@ -248,3 +248,29 @@ def test_ensemble_options_reach_the_evolutions(prec, opts):
     want = oracle_ensemble(name, M, steps, pol, obs)
     assert np.abs(P - want).max() < TOL_P[prec], np.abs(P - want).max()
     assert np.abs(N - 1).max() < TOL_P[prec]
+
+
+def test_rounding_does_not_add_up_over_the_members():
+    """Single precision rounds members independently: over the 8192 members of
+    the 2x7 ladder the mean norm, and P against complex128, stay within half the
+    spacing of single-precision numbers below 1, where one member alone, or
+    members that all round alike, may be off by several times that."""
+    import torch
+    M, J, dt, steps = 14, workloads.ladder(7), 0.05, 50
+    out = {}
+    for prec, dtype in ((C64, torch.complex64), (C128, torch.complex128)):
+        note("members", prec)
+        work = torch.empty(2 ** (2 * M - 1), dtype=dtype, device="cuda")
+        P = torch.empty(steps + 1, dtype=torch.float64, device="cuda")
+        N = torch.empty_like(P)
+        spq.spin_ensemble_evolve(work, M, J, dt, steps, 0, 0, P, N, first_member=0, n_members=2 ** (M - 1))
+        torch.cuda.synchronize()
+        out[prec] = (P, N)
+        del work
+    assert float((out[C64][1] - 1).abs().max()) < 2.0 ** -25
+    assert float((out[C64][0] - out[C128][0]).abs().max()) < 2.0 ** -25
+    # a member alone starts on the unit circle to the closest of 32 points
+    work = torch.empty(2 ** M, dtype=torch.complex64, device="cuda")
+    for r in (0, 1, 2, 77, 4095, 8191):
+        spq.spin_ensemble_evolve(work, M, J, dt, 0, 0, 0, P[:1], N[:1], first_member=r, n_members=1)
+        assert abs(float(N[0]) - 1) < 2e-8 and abs(float(P[0]) - 1) < 2e-8
