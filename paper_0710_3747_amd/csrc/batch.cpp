@@ -27,7 +27,7 @@ struct BatchTables {
          *d_launch = nullptr;
     std::vector<BatchProblem> probs;    // without pointers, seeds and polarised sites
     int64_t part = 0;
-    int ncounters = 0;
+    int ngangs = 0;
     size_t bytes = 0;
     ~BatchTables() {
         for (void* p : {d_jobs, d_jstart, d_passes, d_stages, d_ops, d_launch})
@@ -38,7 +38,7 @@ struct BatchTables {
 // One call's problems and the memory its gangs write.
 struct BatchCache {
     std::shared_ptr<const BatchTables> tables;
-    void *d_probs = nullptr, *d_part = nullptr, *d_ctr = nullptr, *d_err = nullptr;
+    void *d_probs = nullptr, *d_part = nullptr, *d_sync = nullptr;
     int nslots = 0;
     bool half = false;
     hipStream_t side = nullptr;
@@ -51,7 +51,7 @@ struct BatchCache {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
         if (side) (void)hipStreamDestroy(side);
-        for (void* p : {d_probs, d_part, d_ctr, d_err})
+        for (void* p : {d_probs, d_part, d_sync})
             if (p) (void)hipFree(p);
     }
 };
@@ -302,7 +302,7 @@ static int build_tables(const std::vector<spin_problem>& probs, const std::vecto
         if (b.M > KL) {     // a gang: partial sums and a counter of its own
             b.part0 = bt->part;
             bt->part += int64_t(kBatchRing) * b.gsize * 2;
-            b.counter = bt->ncounters++;
+            b.counter = bt->ngangs++;
         }
         dur.push_back(pl.dur);
         bt->probs.push_back(b);
@@ -356,8 +356,7 @@ static int build_call(const std::vector<spin_problem>& probs, int init, int nslo
     int rc;
     if ((rc = upload(bp.data(), bp.size() * sizeof(BatchProblem), &bc->d_probs, &bc->bytes))) return rc;
     if ((rc = upload(nullptr, std::max<int64_t>(bc->tables->part, 2) * sizeof(double), &bc->d_part, &bc->bytes))) return rc;
-    if ((rc = upload(nullptr, (bc->tables->ncounters + 1) * sizeof(int), &bc->d_ctr, &bc->bytes))) return rc;
-    if ((rc = upload(nullptr, sizeof(int), &bc->d_err, &bc->bytes))) return rc;
+    if ((rc = upload(nullptr, (kSyncGangs + bc->tables->ngangs) * sizeof(int), &bc->d_sync, &bc->bytes))) return rc;
     bc->nslots = nslots;
     bc->half = half;
     return SPIN_OK;
@@ -516,12 +515,12 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
                                static_cast<const DevStage*>(bc->tables->d_stages),
                                static_cast<const DevOp<T>*>(bc->tables->d_ops),
                                static_cast<const int2*>(bc->tables->d_launch),
-                               static_cast<double*>(bc->d_part), static_cast<int*>(bc->d_ctr),
-                               bc->tables->ncounters + 1, static_cast<int*>(bc->d_err), status, n_steps, s);
+                               static_cast<double*>(bc->d_part), static_cast<int*>(bc->d_sync),
+                               bc->tables->ngangs, status, n_steps, s);
     };
     std::lock_guard<std::mutex> launch_lock(g_launch_mu);
     hipEvent_t unchained = nullptr;
-    const bool gangs = bc->tables->ncounters > 0;
+    const bool gangs = bc->tables->ngangs > 0;
     hipEvent_t& last = gangs ? g_last_launch[dev] : unchained;
     const bool first = last == nullptr;
     if (gangs && first && hipEventCreateWithFlags(&last, hipEventDisableTiming) != hipSuccess)

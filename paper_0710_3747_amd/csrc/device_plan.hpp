@@ -156,6 +156,11 @@ struct GangClock {
     }
 };
 
+// The integers that a batch launch's workgroups share: the error flag, their
+// number, the movements of one-workgroup problems, and a counter of arrivals per
+// gang.  One array, so that the kernel keeps one pointer.
+constexpr int kSyncError = 0, kSyncCount = 1, kSyncProgress = 2, kSyncGangs = 3;
+
 // LDS slots of a workgroup that holds a whole state, 2^r amplitudes on each of
 // nt lanes: it is exchanged in padded rows and staged in memory order.
 SPIN_HD constexpr int resident_slots(int r, int nt, int elem_bytes) {

@@ -1798,17 +1798,16 @@ __global__ __launch_bounds__(NT) void k_resident(ResidentJob job0,
 // wait is on members busy with earlier jobs: no cycle, no deadlock.  Each
 // wait is bounded; on time-out the problem is flagged and its P set to NaN.
 // A wait gives up when nothing in the launch has moved for kGangWaitTicks (the sum
-// of its counters: every gang's arrivals, and the last one, of the one-workgroup
-// problems), and at once when any workgroup has flagged an error.
-__device__ __forceinline__ uint32_t launch_progress(const int* counters, int n) {
+// of its counters stands still), and at once when any workgroup has flagged an
+// error.
+__device__ __forceinline__ uint32_t launch_progress(const int* sync) {
     uint32_t sum = 0;
-    for (int i = 0; i < n; ++i)
-        sum += uint32_t(__hip_atomic_load(counters + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    for (int i = sync[kSyncCount]; --i >= kSyncProgress;)
+        sum += uint32_t(__hip_atomic_load(sync + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     return sum;
 }
 
-__device__ __forceinline__ bool gang_barrier(int* counter, uint32_t target, int* err, const int* counters,
-                                             int ncounters) {
+__device__ __forceinline__ bool gang_barrier(int* counter, uint32_t target, int* sync) {
     // Every wave waits until its stores are in the XCD's L2; after the barrier
     // one lane writes that back for all (release) and, when the gang has met,
     // invalidates what the CU and the L2 hold (acquire).  A release by every
@@ -1822,12 +1821,17 @@ __device__ __forceinline__ bool gang_barrier(int* counter, uint32_t target, int*
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         atomicAdd(counter, 1);
         GangClock clock{uint64_t(wall_clock64())};
-        while (gang_waits(uint32_t(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)), target)) {
+        for (int polls = 1;
+             gang_waits(uint32_t(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)), target);
+             ++polls) {
             __builtin_amdgcn_s_sleep(4);
+            // the flag and the clock take as long to read as the counter: not
+            // every time
+            if (polls & 15) continue;
             const uint64_t now = uint64_t(wall_clock64());
-            if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-                (clock.due(now) && clock.stalled(now, launch_progress(counters, ncounters)))) {
-                atomicOr(err, 1);
+            if (__hip_atomic_load(sync + kSyncError, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
+                (clock.due(now) && clock.stalled(now, launch_progress(sync)))) {
+                atomicOr(sync + kSyncError, 1);
                 ok = 0;
                 break;
             }
@@ -1850,8 +1854,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                                               const DevOp<T>* __restrict__ ops,
                                               const int2* __restrict__ launches,
                                               double* __restrict__ partials,
-                                              int* __restrict__ counters, int ncounters,
-                                              int* __restrict__ err, int64_t n_steps) {
+                                              int* __restrict__ sync, int64_t n_steps) {
     using C = typename CT<T>::c;
     constexpr int K = R + __builtin_ctz(NT);
     constexpr int KL = K - 1;               // largest one-workgroup problem
@@ -1865,7 +1868,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
     const int wave = tid / 64;
     for (int jb = job_start[blockIdx.x]; jb < job_start[blockIdx.x + 1]; ++jb) {
         const BatchJob job = jobs[jb];
-        if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
+        if (__hip_atomic_load(sync + kSyncError, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
         const BatchProblem& B = probs[job.problem];
         if (B.gsize == 1 && B.M <= KL) {
             ResidentJob J{};
@@ -1882,7 +1885,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
             J.step_stage0 = B.step_stage0;
             J.step_nstage = B.step_nstage;
             J.last_stage0 = B.last_stage0;
-            int* progress = counters + ncounters - 1;
+            int* progress = sync + kSyncProgress;
             // 16 amplitudes per lane, 32 (complex64) for the largest
             if constexpr (NT == 256) {
                 if (B.M <= 12) resident_run<T, 4, NT>(J, stages, ops, n_steps, lds, ring, progress);
@@ -1895,7 +1898,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
         // gang member `rank` of `gsize`
         C* psi = reinterpret_cast<C*>(B.psi);
         const unsigned G = unsigned(B.gsize), rank = unsigned(job.rank);
-        int* ctr = counters + B.counter;
+        int* ctr = sync + kSyncGangs + B.counter;
         uint32_t epoch = 0;
         bool ok = true;
         if (B.init) {
@@ -1909,7 +1912,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                 c.y = T(im);
                 psi[x] = c;
             }
-            ok = gang_barrier(ctr, ++epoch * G, err, counters, ncounters);
+            ok = gang_barrier(ctr, ++epoch * G, sync);
         }
         const int64_t tpm = B.ntiles / G;
         for (int l = 0; l < B.nlaunch && ok; ++l) {
@@ -1958,7 +1961,7 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
                     }
                 }
             }
-            ok = gang_barrier(ctr, ++epoch * G, err, counters, ncounters);
+            ok = gang_barrier(ctr, ++epoch * G, sync);
             if (rank == 0 && tid < 64 && ok) {
                 for (int m = 0; m < P.nmeas; ++m) {
                     const int64_t s = int64_t(la.y) + P.meas_step[m];
@@ -1983,8 +1986,10 @@ __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const Bat
 }
 
 #if SPIN_PART == 0
-__global__ void k_fill_int(int* p, int n, int v) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = v;
+// Sync integers of a batch launch at its start (see kSyncError).
+__global__ void k_sync_start(int* sync, int n) {
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+        sync[i] = i == kSyncCount ? n : 0;
 }
 
 // Folds a launch's error flag into the device's sticky batch status word.
@@ -1992,15 +1997,15 @@ __global__ void k_status_or(const int* err, int* status) {
     if (threadIdx.x == 0 && *err != 0) atomicOr(status, *err);
 }
 
-void launch_fill_int(int* p, int n, int grid, hipStream_t st) {
-    hipLaunchKernelGGL(k_fill_int, dim3(grid), dim3(256), 0, st, p, n, 0);
+void launch_sync_start(int* sync, int n, hipStream_t st) {
+    hipLaunchKernelGGL(k_sync_start, dim3((n + 255) / 256), dim3(256), 0, st, sync, n);
 }
 
 void launch_status_or(const int* err, int* status, hipStream_t st) {
     hipLaunchKernelGGL(k_status_or, dim3(1), dim3(64), 0, st, err, status);
 }
 #else
-void launch_fill_int(int* p, int n, int grid, hipStream_t st);
+void launch_sync_start(int* sync, int n, hipStream_t st);
 void launch_status_or(const int* err, int* status, hipStream_t st);
 #endif
 
@@ -2286,22 +2291,18 @@ int batch_occupancy(bool half) {
 template <typename T>
 hipError_t launch_batch(int nslots, bool half, const BatchProblem* probs, const BatchJob* jobs,
                         const int* job_start, const DevPass* passes, const DevStage* stages,
-                        const DevOp<T>* ops, const int2* launches, double* partials, int* counters,
-                        int ncounters, int* err, int* status, int64_t n_steps, hipStream_t st) {
-    // counters and the error flag start at zero (a fill kernel, not a
-    // memset node, so the pair can sit in a captured graph)
-    launch_fill_int(counters, ncounters, 64, st);
-    launch_fill_int(err, 1, 1, st);
+                        const DevOp<T>* ops, const int2* launches, double* partials, int* sync,
+                        int ngangs, int* status, int64_t n_steps, hipStream_t st) {
+    // a fill kernel, not a memset node, so the pair can sit in a captured graph
+    launch_sync_start(sync, kSyncGangs + ngangs, st);
     constexpr bool F = sizeof(T) == 4;
     if (half)
         hipLaunchKernelGGL((k_batch<T, F ? 6 : 5, 256, true>), dim3(nslots), dim3(256), 0, st, probs,
-                           jobs, job_start, passes, stages, ops, launches, partials, counters,
-                           ncounters, err, n_steps);
+                           jobs, job_start, passes, stages, ops, launches, partials, sync, n_steps);
     else
         hipLaunchKernelGGL((k_batch<T, F ? 5 : 4, 512, false>), dim3(nslots), dim3(512), 0, st, probs,
-                           jobs, job_start, passes, stages, ops, launches, partials, counters,
-                           ncounters, err, n_steps);
-    launch_status_or(err, status, st);
+                           jobs, job_start, passes, stages, ops, launches, partials, sync, n_steps);
+    launch_status_or(sync + kSyncError, status, st);
     return hipGetLastError();
 }
 #endif
@@ -2317,7 +2318,7 @@ hipError_t launch_batch(int nslots, bool half, const BatchProblem* probs, const 
     template int batch_occupancy<T>(bool);                                                                \
     template hipError_t launch_batch<T>(int, bool, const BatchProblem*, const BatchJob*, const int*,      \
                                         const DevPass*, const DevStage*, const DevOp<T>*, const int2*,    \
-                                        double*, int*, int, int*, int*, int64_t, hipStream_t);
+                                        double*, int*, int, int*, int64_t, hipStream_t);
 #if SPIN_PART == 0
 SPIN_INST_RESIDENT(float)
 #elif SPIN_PART == 1
