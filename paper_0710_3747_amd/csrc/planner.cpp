@@ -7,9 +7,9 @@
 #include <cmath>
 #include <complex>
 #include <cstdio>
+#include <cstring>
 #include <exception>
 #include <functional>
-#include <limits>
 #include <map>
 #include <sstream>
 #include <stdexcept>
@@ -503,9 +503,11 @@ static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int spli
     const uint32_t kOutside = 1u << 31;
     std::vector<uint32_t> need(n);
     std::vector<char> meas(n);
+    std::vector<int> entry;      // observables of step 0
     for (int i = 0; i < n; ++i) {
         const Op& op = pass.ops[st.ops[i]];
         meas[i] = op.kind == 1;
+        if (meas[i] && op.step == 0) entry.push_back(i);
         if (meas[i]) need[i] = local[op.i] >= 0 ? 1u << local[op.i] : kOutside;
         else need[i] = (1u << local[op.i]) | (1u << local[op.j]);
     }
@@ -528,8 +530,8 @@ static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int spli
     // they are the state's as it was passed in (a factor on other sites leaves
     // them alone only to its rounding).
     auto close = [&](State& s, std::vector<StageItem>* prog) {
-        for (int i = 0; i < n; ++i)
-            if (meas[i] && pass.ops[st.ops[i]].step == 0 && !s.done.get(i)) {
+        for (int i : entry)
+            if (!s.done.get(i)) {
                 s.done.set(i);
                 ++s.ndone;
                 if (prog) prog->push_back(StageItem{st.ops[i], 0, 0});
@@ -1762,16 +1764,24 @@ namespace {
 // sign of the off-diagonal difference): the sums stay within a few units of the
 // last place for any number of steps: norm 1.4e-9, max |dP| 3.0e-9.
 void round_rotation(double theta, bool first, RoundingCarry& c, float* t, float* s) {
-    const float t0 = float(std::tan(0.5 * theta)), s0 = float(std::sin(theta));
+    const double half = std::tan(0.5 * theta), unit = 1.0 / (1.0 + half * half);
+    const double cs = (1.0 - half * half) * unit, sn = 2.0 * half * unit;
+    const float t0 = float(half), s0 = float(sn);
     *t = t0;
     *s = s0;
-    if (theta == 0.0) return;
-    const float inf = std::numeric_limits<float>::infinity();
-    const double cs = std::cos(theta), sn = std::sin(theta);
+    if (t0 == 0.0f || s0 == 0.0f) return;
+    // the numbers next to a finite one other than zero
+    auto next = [](float v, int by) {
+        int32_t bits;
+        std::memcpy(&bits, &v, sizeof bits);
+        bits += by;
+        std::memcpy(&v, &bits, sizeof bits);
+        return v;
+    };
     RoundingCarry best;
     double least = -1.0;
-    for (const float tc : {t0, std::nextafter(t0, -inf), std::nextafter(t0, inf)})
-        for (const float sc : {s0, std::nextafter(s0, -inf), std::nextafter(s0, inf)}) {
+    for (const float tc : {t0, next(t0, -1), next(t0, 1)})
+        for (const float sc : {s0, next(s0, -1), next(s0, 1)}) {
             const double diag = 1.0 - double(tc) * sc, b = tc * (1.0 + diag);
             const double across = (first ? 1.0 : -1.0) * (b - sc);
             const double angle = 0.5 * (b + sc) * cs - diag * sn;     // its sine
@@ -2044,7 +2054,7 @@ void encode_pass(const HostPass& hp, int M, int observed, DevTables<T>& out, int
                 DevOp<T> d{};
                 const double th = theta / pieces;
                 d.code = op_xy(qa, qb);
-                round_rotation(th, first, out.carry[{op.i, op.j}], &d.t, &d.s);
+                round_rotation(th, first, out.carry.of(op.i, op.j), &d.t, &d.s);
                 d.nt = -d.t;
                 d.ns = -d.s;
                 out.ops.push_back(d);

@@ -13,9 +13,7 @@
 
 #include <cstdint>
 #include <functional>
-#include <map>
 #include <string>
-#include <utility>
 #include <vector>
 
 #include "device_plan.hpp"
@@ -196,6 +194,17 @@ ResidentPlan plan_resident(int k, const std::vector<Coupling>& J, double dt, int
 struct RoundingCarry {
     double across = 0, angle = 0;
 };
+class RoundingCarries {
+  public:
+    RoundingCarry& of(int i, int j) {
+        if (c_.empty()) c_.resize(kMaxSites * kMaxSites);
+        return c_[i * kMaxSites + j];
+    }
+    void clear() { c_.clear(); }
+
+  private:
+    std::vector<RoundingCarry> c_;
+};
 
 // Encoded device tables.
 template <typename T>
@@ -205,7 +214,7 @@ struct DevTables {
     std::vector<DevOp<T>> ops;
     std::vector<float> mats;           // matrix engine: kMatFloats per kOpMat
     // per pair of sites, over the passes encoded so far (see round_rotation)
-    std::map<std::pair<int, int>, RoundingCarry> carry;
+    RoundingCarries carry;
 };
 
 // Entry arrangement of a stage: thread bit -> position, register bit ->
