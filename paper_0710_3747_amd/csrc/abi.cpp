@@ -339,71 +339,80 @@ static StreamPlan plan_tiled(int M, const std::vector<Coupling>& J, double dt, i
     return sp;
 }
 
+// A plan and its encoded tables (host work only).
 template <typename T>
-static int build_plan(const PlanKey& key, const std::vector<Coupling>& J, Shape sh,
-                      std::shared_ptr<DevicePlan>* out) {
-    auto dp = std::make_shared<DevicePlan>();
-    DevTables<T> tb;
-    try {
-        if (sh.resident) {
-            dp->resident = true;
-            const int bits = resident_bits(key.M);
-            const ResidentPlan rp = plan_resident(bits, J, key.dt, key.observed, key.merge != 0, kResidentRegs,
-                                                  key.profile != 0);
-            dp->res = encode_resident<T>(rp, bits, key.observed, tb, key.profile != 0);
-            dp->stages_total = tb.stages.size();
-        } else {
-            dp->sp = plan_tiled(key.M, J, key.dt, key.n_steps, key.observed, key.merge != 0,
-                                key.profile != 0, &sh);
-            dp->shape = PassShape{sh.r, sh.nt};
-            dp->shape.engine = sh.engine;
-            dp->shape.profile = key.profile != 0;
-            dp->shape.exchange = sh.exchange;
-            dp->profile = key.profile != 0;
-            dp->k = sh.k;
-            const int64_t ntiles = int64_t(1) << (key.M - sh.k);
-            int dev_cu = 256;
-            {
-                hipDeviceProp_t prop;
-                if (hipGetDeviceProperties(&prop, key.dev) == hipSuccess) dev_cu = prop.multiProcessorCount;
-            }
-            // Where one workgroup fills a CU (whole tiles, which prefetch the
-            // next one; complex128 tiles of 2^14), a persistent grid, ~4
-            // workgroups per CU.  Else a workgroup per tile, up to kMaxWg: a
-            // CU draws the next one when it is done, where a persistent grid
-            // left a seventh of the wavefront slots empty at its end.  us per
-            // pass with 4 / 16 / 64 workgroups per CU and one per tile,
-            // complex64: ladder M = 30 5189 / 4785 / 4693 / 4719, M = 28 1284 /
-            // 1201 / 1163, M = 26 337 / 301; star M = 28 1348 / 1250 / 1206;
-            // complex128 ladder M = 30 7626 / 7271 / 7174 / 7226, star M = 26
-            // 573 / 552 / 530, but with tiles of 2^14 ladder M = 30 10119 /
-            // - / 10570.
-            const bool alone = sh.exchange == kWholeTiles || (sizeof(T) == 8 && sh.k == 14);
-            const int64_t most = alone ? int64_t(dev_cu) * 4 : dp->profile ? kMaxWgProfile : kMaxWg;
-            int64_t nwg = 1;
-            while (nwg * 2 <= ntiles && nwg * 2 <= most) nwg *= 2;
-            dp->nwg = int(nwg);
-            dp->tiles_per_wg = ntiles / nwg;
-            for (const HostPass& hp : dp->sp.passes) {
-                encode_pass<T>(hp, key.M, key.observed, tb, sh.engine, key.profile != 0);
-                std::vector<int64_t> ms;
-                std::vector<int> mst;
-                for (const Op& op : hp.ops)
-                    if (op.kind == 1) {
-                        ms.push_back(op.step);
-                        mst.push_back(op.i);
-                    }
-                dp->meas.push_back(ms);
-                dp->meas_site.push_back(mst);
-            }
-            dp->stages_total = tb.stages.size();
+static void plan_tables(const PlanKey& key, const std::vector<Coupling>& J, Shape sh, DevicePlan* dp,
+                        DevTables<T>* tables) {
+    DevTables<T>& tb = *tables;
+    if (sh.resident) {
+        dp->resident = true;
+        const int bits = resident_bits(key.M);
+        const ResidentPlan rp = plan_resident(bits, J, key.dt, key.observed, key.merge != 0, kResidentRegs,
+                                              key.profile != 0);
+        dp->res = encode_resident<T>(rp, bits, key.observed, tb, key.profile != 0);
+        dp->stages_total = tb.stages.size();
+    } else {
+        dp->sp = plan_tiled(key.M, J, key.dt, key.n_steps, key.observed, key.merge != 0,
+                            key.profile != 0, &sh);
+        dp->shape = PassShape{sh.r, sh.nt};
+        dp->shape.engine = sh.engine;
+        dp->shape.profile = key.profile != 0;
+        dp->shape.exchange = sh.exchange;
+        dp->profile = key.profile != 0;
+        dp->k = sh.k;
+        const int64_t ntiles = int64_t(1) << (key.M - sh.k);
+        int dev_cu = 256;
+        {
+            hipDeviceProp_t prop;
+            if (hipGetDeviceProperties(&prop, key.dev) == hipSuccess) dev_cu = prop.multiProcessorCount;
         }
+        // Where one workgroup fills a CU (whole tiles, which prefetch the
+        // next one; complex128 tiles of 2^14), a persistent grid, ~4
+        // workgroups per CU.  Else a workgroup per tile, up to kMaxWg: a
+        // CU draws the next one when it is done, where a persistent grid
+        // left a seventh of the wavefront slots empty at its end.  us per
+        // pass with 4 / 16 / 64 workgroups per CU and one per tile,
+        // complex64: ladder M = 30 5189 / 4785 / 4693 / 4719, M = 28 1284 /
+        // 1201 / 1163, M = 26 337 / 301; star M = 28 1348 / 1250 / 1206;
+        // complex128 ladder M = 30 7626 / 7271 / 7174 / 7226, star M = 26
+        // 573 / 552 / 530, but with tiles of 2^14 ladder M = 30 10119 /
+        // - / 10570.
+        const bool alone = sh.exchange == kWholeTiles || (sizeof(T) == 8 && sh.k == 14);
+        const int64_t most = alone ? int64_t(dev_cu) * 4 : dp->profile ? kMaxWgProfile : kMaxWg;
+        int64_t nwg = 1;
+        while (nwg * 2 <= ntiles && nwg * 2 <= most) nwg *= 2;
+        dp->nwg = int(nwg);
+        dp->tiles_per_wg = ntiles / nwg;
+        for (const HostPass& hp : dp->sp.passes) {
+            encode_pass<T>(hp, key.M, key.observed, tb, sh.engine, key.profile != 0);
+            std::vector<int64_t> ms;
+            std::vector<int> mst;
+            for (const Op& op : hp.ops)
+                if (op.kind == 1) {
+                    ms.push_back(op.step);
+                    mst.push_back(op.i);
+                }
+            dp->meas.push_back(ms);
+            dp->meas_site.push_back(mst);
+        }
+        dp->stages_total = tb.stages.size();
+    }
+}
+
+// Builds the plans of `keys`, side by side on the host, and uploads their tables.
+template <typename T>
+static int build_plans(const std::vector<std::pair<PlanKey, Shape>>& keys, const std::vector<Coupling>& J,
+                       std::vector<std::shared_ptr<DevicePlan>>* out) {
+    std::vector<DevTables<T>> tb(keys.size());
+    for (size_t n = 0; n < keys.size(); ++n) out->push_back(std::make_shared<DevicePlan>());
+    try {
+        run_on_threads(keys.size(),
+                       [&](size_t n) { plan_tables<T>(keys[n].first, J, keys[n].second, (*out)[n].get(), &tb[n]); });
     } catch (const std::exception& e) {
         return fail(SPIN_EUNSUPPORTED, std::string("planning failed: ") + e.what());
     }
-    int rc = upload_tables<T>(tb, dp.get());
-    if (rc) return rc;
-    *out = dp;
+    for (size_t n = 0; n < keys.size(); ++n)
+        if (const int rc = upload_tables<T>(tb[n], (*out)[n].get())) return rc;
     return SPIN_OK;
 }
 
@@ -420,42 +429,39 @@ int get_plan(int prec, int M, const std::vector<Coupling>& J, double dt, int64_t
            << (sh.exchange == kHalfTiles ? " and half-tile exchanges" : "");
         return fail(SPIN_EUNSUPPORTED, os.str());
     }
-    PlanKey key{dev, prec, M, observed, sh.k, sh.r, sh.nt, sh.c,
-                (opt && opt->no_merge) ? 0 : 1, sh.resident ? 0 : sh.engine,
-                profile ? 1 : 0, sh.resident ? 0 : int(sh.exchange), !sh.resident && sh.try_large, dt,
-                sh.resident ? 0 : n_steps, {}};
-    key.J.reserve(J.size() * 4);
-    for (const Coupling& c : J) {
-        key.J.push_back(c.i);
-        key.J.push_back(c.j);
-        key.J.push_back(c.a);
-        key.J.push_back(c.b);
-    }
+    std::vector<double> flat;
+    flat.reserve(J.size() * 4);
+    for (const Coupling& c : J) flat.insert(flat.end(), {double(c.i), double(c.j), c.a, c.b});
+    auto key_of = [&](const Shape& s) {
+        return PlanKey{dev, prec, M, observed, s.k, s.r, s.nt, s.c, (opt && opt->no_merge) ? 0 : 1,
+                       s.resident ? 0 : s.engine, profile ? 1 : 0, s.resident ? 0 : int(s.exchange),
+                       !s.resident && s.try_large, dt, s.resident ? 0 : n_steps, flat};
+    };
+    std::vector<std::pair<PlanKey, Shape>> missing{{key_of(sh), sh}};
     if (shape_out) *shape_out = sh;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        auto it = g_plans.find(key);
+        auto it = g_plans.find(missing[0].first);
         if (it != g_plans.end()) {
             *out = it->second;
             return SPIN_OK;
+        }
+        // the plan that the same call takes where it can have neither scratch
+        // memory nor a new plan
+        if (!sh.resident && M <= sh.res_cap) {
+            const Shape one = choose_shape(prec, M, opt, any_phase(J), true);
+            if (!g_plans.count(key_of(one))) missing.emplace_back(key_of(one), one);
         }
     }
     if (lookup_only)
         return fail(SPIN_EUNSUPPORTED, "no prepared plan for these arguments: call spin_prepare_plan with "
                                        "the same arguments first (this entry point allocates nothing)");
-    std::shared_ptr<DevicePlan> dp;
-    int rc = prec == SPIN_C64 ? build_plan<float>(key, J, sh, &dp) : build_plan<double>(key, J, sh, &dp);
+    std::vector<std::shared_ptr<DevicePlan>> built;
+    const int rc = prec == SPIN_C64 ? build_plans<float>(missing, J, &built) : build_plans<double>(missing, J, &built);
     if (rc) return rc;
-    {
-        std::lock_guard<std::mutex> lk(g_mu);
-        g_plans[key] = dp;
-    }
-    *out = dp;
-    // the plan that the same call takes where it can have neither scratch
-    // memory nor a new plan
-    std::shared_ptr<DevicePlan> single;
-    if (!sh.resident && M <= sh.res_cap)
-        return get_plan(prec, M, J, dt, n_steps, observed, opt, profile, &single, nullptr, true);
+    std::lock_guard<std::mutex> lk(g_mu);
+    for (size_t n = 0; n < missing.size(); ++n) g_plans[missing[n].first] = built[n];
+    *out = built[0];
     return SPIN_OK;
 }
 

@@ -3,6 +3,7 @@
 #include "planner.hpp"
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <complex>
@@ -504,18 +505,25 @@ static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int spli
     std::vector<uint32_t> need(n);
     std::vector<char> meas(n);
     std::vector<int> entry;      // observables of step 0
+    bool observes = false;
+    uint32_t every = 0;
     for (int i = 0; i < n; ++i) {
         const Op& op = pass.ops[st.ops[i]];
         meas[i] = op.kind == 1;
+        observes |= meas[i] != 0;
         if (meas[i] && op.step == 0) entry.push_back(i);
         if (meas[i]) need[i] = local[op.i] >= 0 ? 1u << local[op.i] : kOutside;
         else need[i] = (1u << local[op.i]) | (1u << local[op.j]);
+        every |= need[i];
     }
-    struct Done {        // ops run; the first 64 inline
-        uint64_t w = 0;
+    constexpr int kInline = 4;
+    const int nwords = (n + 63) / 64;
+    struct Done {        // ops run; the first 256 inline
+        std::array<uint64_t, kInline> w{};
         std::vector<uint64_t> more;
-        bool get(int i) const { return (i < 64 ? w >> i : more[i / 64 - 1] >> (i % 64)) & 1u; }
-        void set(int i) { (i < 64 ? w : more[i / 64 - 1]) |= uint64_t(1) << (i % 64); }
+        uint64_t& word(int q) { return q < kInline ? w[q] : more[q - kInline]; }
+        bool get(int i) { return word(i / 64) >> (i % 64) & 1u; }
+        void set(int i) { word(i / 64) |= uint64_t(1) << (i % 64); }
         bool operator==(const Done& o) const { return w == o.w && more == o.more; }
     };
     struct State {
@@ -536,13 +544,17 @@ static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int spli
                 ++s.ndone;
                 if (prog) prog->push_back(StageItem{st.ops[i], 0, 0});
             }
-        for (bool any = true; any;) {
-            any = false;
-            for (int kind = 0; kind < 2; ++kind) {
-                uint32_t blocked = 0;
-                for (int i = 0; i < n; ++i) {
-                    if (s.done.get(i)) continue;
-                    if ((need[i] & blocked) || meas[i] != kind || (!meas[i] && (need[i] & s.gates))) {
+        // Every op of one kind that can run, in order: one scan finds them all,
+        // and ends once every position waits for an earlier op.
+        auto scan = [&](bool observables) {
+            bool any = false;
+            uint32_t blocked = 0;
+            for (int q = 0; q < nwords && blocked != every; ++q) {
+                uint64_t left = ~s.done.word(q);
+                if (n - 64 * q < 64) left &= (uint64_t(1) << (n - 64 * q)) - 1;
+                for (; left; left &= left - 1) {
+                    const int i = 64 * q + __builtin_ctzll(left);
+                    if ((need[i] & blocked) || (meas[i] != 0) != observables || (!meas[i] && (need[i] & s.gates))) {
                         blocked |= need[i];
                         continue;
                     }
@@ -552,7 +564,10 @@ static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int spli
                     any = true;
                 }
             }
-        }
+            return any;
+        };
+        do scan(false);
+        while (observes && scan(true));
     };
     uint32_t movable = 0;
     for (int p : st.regs)
@@ -562,7 +577,7 @@ static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int spli
         if (__builtin_popcount(g) == ng) {
             State s;
             s.gates = g;
-            s.done.more.assign(n > 64 ? (n - 1) / 64 : 0, 0);
+            s.done.more.assign(std::max(nwords - kInline, 0), 0);
             close(s, nullptr);
             levels[0].push_back(std::move(s));
         }
@@ -598,7 +613,7 @@ static void plan_exchanges(const HostPass& pass, HostStage& st, int ng, int spli
         path.push_back(&levels[d][f]);
     State s;
     s.gates = path.back()->gates;
-    s.done.more.assign(n > 64 ? (n - 1) / 64 : 0, 0);
+    s.done.more.assign(std::max(nwords - kInline, 0), 0);
     std::vector<int> regs, gates;
     for (int p : st.regs)
         if (p != split) (s.gates >> p & 1u ? gates : regs).push_back(p);
@@ -1223,7 +1238,7 @@ StreamPlan plan_stream(int M, const std::vector<Coupling>& J, double dt, int64_t
     // ladders, chains and random graphs of M = 12 to 20, 17 to 250 steps: the
     // same launches, planned in 8 instead of 88 ms (dipolar star M = 14, 40
     // steps), 20 instead of 150 ms (star M = 17, 100 steps).
-    if (pp.once && n_steps > 16) {
+    if (pp.once && n_steps > 8) {
         try {
             return plan_stream_periodic(M, J, dt, n_steps, observed, merge, pp, kGen);
         } catch (const std::runtime_error&) {
@@ -1333,12 +1348,16 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
     // for every variant); a pass keeps whichever staging is shorter.  For
     // half-tile exchanges every pass is staged again around its split
     // position.
-    if (pp.half) {
-        for (HostPass& hp : best.passes)
-            plan_stages_coalesced(hp, std::min(pp.r, int(hp.sites.size())), pp.c, nv > 1 ? 32 : 1, true, pp.gates);
-    } else {
-        for (HostPass& hp : best.passes) {
+    // Pass by pass, a share of them per job.
+    const size_t npass = best.passes.size(), per = npass < 16 ? npass : (npass + 31) / 32;
+    run_on_threads(npass == 0 ? 0 : (npass + per - 1) / per, [&](size_t job) {
+        for (size_t q = job * per; q < std::min(npass, (job + 1) * per); ++q) {
+            HostPass& hp = best.passes[q];
             const int r = std::min(pp.r, int(hp.sites.size()));
+            if (pp.half) {
+                plan_stages_coalesced(hp, r, pp.c, nv > 1 ? 32 : 1, true, pp.gates);
+                continue;
+            }
             if (nv > 1) {
                 HostPass alt = hp;
                 plan_stages_coalesced(alt, r, pp.c, 32, false, pp.gates, true, pp.once);
@@ -1347,7 +1366,7 @@ StreamPlan plan_stream_best(int M, const std::vector<Coupling>& J, double dt, in
             const int ng = usable_gates(pp.gates, int(hp.sites.size()), r, pp.c);
             for (HostStage& st : hp.stages) plan_exchanges(hp, st, ng, -1);
         }
-    }
+    });
     return best;
 }
 
