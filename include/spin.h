@@ -320,9 +320,9 @@ int spin_batch_status(void *stream);
  *             rounded up to a power of two, and keeps M + c within
  *             SPIN_MAX_M_*; a buffer of 2^M amplitudes evolves one member at
  *             a time.  Unused member slots of the last evolution hold zeros.
- *             In complex64 a member's state carries a phase of its own, which
- *             no observable sees (equal amplitudes would round alike in every
- *             member, and the mean would keep that rounding).
+ *             In complex64 and from 64 members on, a member's state carries a
+ *             phase of its own, which no observable sees (equal amplitudes would
+ *             round alike in every member, and the mean would keep that).
  *   P_dev   : n_steps + 1 doubles (device), (1/n_members) sum_r P_r[k].
  *   N_dev   : n_steps + 1 doubles (device), the mean norm, or NULL.
  *   opt     : launch options of the (M + c)-site evolutions, as

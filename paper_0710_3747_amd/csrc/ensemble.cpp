@@ -47,6 +47,9 @@ int ensemble_args(int32_t prec, int32_t M, const spin_coupling* J, int32_t K, do
     return validate_couplings(M, J, K, &Jv);
 }
 
+// Members from which each starts with a phase of its own (see member_amp).
+constexpr int64_t kPhasedMembers = 64;
+
 // log2 of the members per evolution (see spin_ensemble_evolve).
 int member_bits(int32_t prec, int32_t M, int64_t n_members, int64_t work_amplitudes) {
     const int maxM = prec == SPIN_C64 ? SPIN_MAX_M_C64 : SPIN_MAX_M_C128;
@@ -85,9 +88,9 @@ extern "C" int spin_ensemble_evolve(int32_t prec, int32_t M, const spin_coupling
             const int64_t count = std::min(per, n_members - q * per);
             hipError_t e = prec == SPIN_C64
                                ? launch_init_members<float>(work, M, c, polarized_site, uint64_t(first),
-                                                            uint64_t(count), st)
+                                                            uint64_t(count), n_members >= kPhasedMembers, st)
                                : launch_init_members<double>(work, M, c, polarized_site, uint64_t(first),
-                                                             uint64_t(count), st);
+                                                             uint64_t(count), n_members >= kPhasedMembers, st);
             if (e != hipSuccess) return fail(SPIN_EHIP, std::string("member init: ") + hipGetErrorString(e));
             double* Pq = q == 0 ? P_dev : tmp;
             double* Nq = N_dev ? (q == 0 ? N_dev : tmp + len) : nullptr;

@@ -206,24 +206,25 @@ __global__ __launch_bounds__(256) void k_init(typename CT<T>::c* __restrict__ ps
     }
 }
 
-// Amplitude of ensemble member r where it is up: 1, and in single precision a
+// Amplitude of ensemble member r's basis state: 1, or in single precision a
 // point of the unit circle at a phase of the member's own, which no observable
 // sees.  With 1 in all of them the first factors round every member alike, and
 // the mean keeps that rounding (ladder 2x7, 100 steps: norm 6.3e-8 off from the
-// first steps on, with phases 1.2e-8).  Of 32 neighbouring points whose
-// components are rounded to single precision the one closest to the circle is
-// taken (|x^2 + y^2 - 1| about 1e-9, 1e-8 at most).
+// first steps on, with phases 1.2e-8).  Of 8 neighbouring points in single
+// precision the one closest to the circle is taken (|x^2 + y^2 - 1| 3e-9, seldom
+// 4e-8), at 0.5 us per call.  A mean over fewer than 64 members gains nothing from
+// independent roundings (1.5e-7 of the norm each): they all start with 1.
 __device__ __forceinline__ double2 member_amp(uint64_t r, double) { return double2{1.0, 0.0}; }
 __device__ __forceinline__ float2 member_amp(uint64_t r, float) {
-    double sn, cs;
-    sincos_turn(0.125 * sm64_uniform(0, r) + 0.0625, &sn, &cs);     // 22.5 to 67.5 degrees
-    const int first = __float_as_int(float(cs));
+    const int first = __float_as_int(float(fma(0.5, sm64_uniform(0, r), 0.4)));
     float2 best{1.f, 0.f};
     double least = 1.0;
-    for (int k = 0; k < 32; ++k) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
         const float x = __int_as_float(first + k);
-        const float y = float(sqrt(1.0 - double(x) * double(x)));
-        const double off = fabs(fma(double(x), double(x), double(y) * double(y)) - 1.0);
+        const double y2 = 1.0 - double(x) * double(x);
+        const float y = sqrtf(float(y2));        // or a neighbour of the nearest
+        const double off = fabs(double(y) * double(y) - y2);
         if (off < least) {
             least = off;
             best = float2{x, y};
@@ -239,7 +240,7 @@ __device__ __forceinline__ float2 member_amp(uint64_t r, float) {
 template <typename T>
 __global__ __launch_bounds__(256) void k_init_members(typename CT<T>::c* __restrict__ psi, int M,
                                                       int cbits, int polarized, uint64_t first,
-                                                      uint64_t count) {
+                                                      uint64_t count, bool phases) {
     const uint64_t dim = 1ull << (M + cbits);
     const uint64_t ymask = (1ull << M) - 1;
     const uint64_t low = (1ull << polarized) - 1;
@@ -250,7 +251,10 @@ __global__ __launch_bounds__(256) void k_init_members(typename CT<T>::c* __restr
         const uint64_t basis = ((r & ~low) << 1) | (r & low);
         typename CT<T>::c v;
         v.x = v.y = T(0);
-        if (m < count && (x & ymask) == basis) v = member_amp(r, T(0));
+        if (m < count && (x & ymask) == basis) {
+            if (phases) v = member_amp(r, T(0));
+            else v.x = T(1);
+        }
         psi[x] = v;
     }
 }
@@ -2051,10 +2055,10 @@ hipError_t launch_init_product(void* psi, int M, int n, uint64_t seed, hipStream
 
 template <typename T>
 hipError_t launch_init_members(void* psi, int M, int cbits, int polarized, uint64_t first,
-                               uint64_t count, hipStream_t st) {
+                               uint64_t count, bool phases, hipStream_t st) {
     const int grid = grid_for(1ull << (M + cbits), 256, 1 << 16);
     hipLaunchKernelGGL(k_init_members<T>, dim3(grid), dim3(256), 0, st,
-                       reinterpret_cast<typename CT<T>::c*>(psi), M, cbits, polarized, first, count);
+                       reinterpret_cast<typename CT<T>::c*>(psi), M, cbits, polarized, first, count, phases);
     return hipGetLastError();
 }
 
@@ -2139,8 +2143,8 @@ template hipError_t launch_init<float>(void*, int, int, uint64_t, hipStream_t);
 template hipError_t launch_init<double>(void*, int, int, uint64_t, hipStream_t);
 template hipError_t launch_init_product<float>(void*, int, int, uint64_t, hipStream_t);
 template hipError_t launch_init_product<double>(void*, int, int, uint64_t, hipStream_t);
-template hipError_t launch_init_members<float>(void*, int, int, int, uint64_t, uint64_t, hipStream_t);
-template hipError_t launch_init_members<double>(void*, int, int, int, uint64_t, uint64_t, hipStream_t);
+template hipError_t launch_init_members<float>(void*, int, int, int, uint64_t, uint64_t, bool, hipStream_t);
+template hipError_t launch_init_members<double>(void*, int, int, int, uint64_t, uint64_t, bool, hipStream_t);
 template hipError_t launch_observe<float>(const void*, int, int, double*, int, hipStream_t);
 template hipError_t launch_observe<double>(const void*, int, int, double*, int, hipStream_t);
 template hipError_t launch_factor<float>(void*, int, int, int, double, double, double, double, int,

@@ -73,7 +73,7 @@ hipError_t launch_init_product(void* psi, int M, int n, uint64_t seed, hipStream
 // M + cbits sites (member index on the top cbits bits, zeros beyond count).
 template <typename T>
 hipError_t launch_init_members(void* psi, int M, int cbits, int polarized, uint64_t first,
-                               uint64_t count, hipStream_t st);
+                               uint64_t count, bool phases, hipStream_t st);
 // acc[i] = (acc[i] + add[i]) * scale for i < n (add may be null).
 hipError_t launch_accumulate(double* acc, const double* add, int64_t n, double scale,
                              hipStream_t st);

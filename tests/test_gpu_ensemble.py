@@ -269,8 +269,13 @@ def test_rounding_does_not_add_up_over_the_members():
         del work
     assert float((out[C64][1] - 1).abs().max()) < 2.0 ** -25
     assert float((out[C64][0] - out[C128][0]).abs().max()) < 2.0 ** -25
-    # a member alone starts on the unit circle to the closest of 32 points
-    work = torch.empty(2 ** M, dtype=torch.complex64, device="cuda")
-    for r in (0, 1, 2, 77, 4095, 8191):
-        spq.spin_ensemble_evolve(work, M, J, dt, 0, 0, 0, P[:1], N[:1], first_member=r, n_members=1)
-        assert abs(float(N[0]) - 1) < 2e-8 and abs(float(P[0]) - 1) < 2e-8
+    # few members start as they are: basis states of amplitude 1
+    work = torch.empty(2 ** (M + 6), dtype=torch.complex64, device="cuda")
+    for first, n in ((0, 1), (4095, 1), (8191, 1), (77, 63)):
+        spq.spin_ensemble_evolve(work, M, J, dt, 0, 0, 0, P[:1], N[:1], first_member=first, n_members=n)
+        assert float(N[0]) == 1 and float(P[0]) == 1
+    # many by a phase each, all on the unit circle
+    spq.spin_ensemble_evolve(work, M, J, dt, 0, 0, 0, P[:1], N[:1], first_member=5, n_members=64)
+    amp = torch.view_as_real(work).double().square().sum(-1)
+    assert int((amp > 0).sum()) == 64 and float((amp[amp > 0] - 1).abs().max()) < 1.2e-7
+    assert len(set(torch.view_as_real(work[amp > 0])[:, 0].tolist())) == 64
