@@ -1197,7 +1197,7 @@ __device__ __forceinline__ void reg_half_sums(const C (&v)[1 << R], double& tot,
 // the register bits is walked depth first, so that one partial sum per level is
 // live, and every right branch is added to its level's half sum: two adds per
 // amplitude (one accumulator per sum took 1 + R / 2): ladder
-// 2x13, 26 sites, 24.2 -> 22.9 ms per 40 steps.
+// 2x13, 26 sites, 24.2 -> 22.9 ms per 50 steps.
 template <int R, int LEVEL, int J, typename C>
 __device__ __forceinline__ double half_sum_tree(const C (&v)[1 << R], double (&half)[R]) {
     if constexpr (LEVEL == 0) {
@@ -1395,7 +1395,7 @@ __device__ __forceinline__ void pass_tiles(typename CT<T>::c* __restrict__ psi, 
 // gained 2 % with several tiles per workgroup and nothing with one).  What
 // bounds it, per CU: M = 30 complex64 tiles of 2^14 take 3.5 ms per pass for the
 // sweep alone, about 3 ms of VALU issue and 1.4 ms of LDS traffic, of which two
-// workgroups overlap a part: 4.7 ms (star M = 28: VALU busy 69 % of the time);
+// workgroups overlap a part: 4.7 ms (star M = 28: VALU busy 70 % of the time);
 // small tiles (M <= 20) take the sum of the three.
 template <typename T, int R, int NT, bool WRITES, bool PROFILE, bool HALF>
 __device__ __forceinline__ void slot_tiles(typename CT<T>::c* __restrict__ psi, const DevPass& P,
@@ -1795,7 +1795,7 @@ __global__ __launch_bounds__(NT) void k_resident(ResidentJob job0,
 
 // ---------------------------------------------------------------- k_batch
 // Persistent batch: each workgroup runs its list of jobs in order.  A job
-// is a whole problem held in LDS (gang size 1, M <= tile bits), or one
+// is a whole problem held in registers (gang size 1, M < tile bits), or one
 // member's share of a problem run as tiled passes by a gang of G
 // workgroups that meet at a counter after every pass.  The host orders all
 // job lists consistently (a global order of gang start times), so every
@@ -1847,8 +1847,9 @@ __device__ __forceinline__ bool gang_barrier(int* counter, uint32_t target, int*
     return ok_s != 0;
 }
 
-// HALF: gangs run half-tile passes and two workgroups share a CU, so
-// problems held in LDS are limited to half a tile.
+// HALF: gangs run half-tile passes and two workgroups share a CU.  One-workgroup
+// problems are at most half a tile either way, what the registers hold beside
+// the gangs' tiles.
 template <typename T, int R, int NT, bool HALF>
 __global__ __launch_bounds__(NT, HALF ? 2 * NT / 256 : 1) void k_batch(const BatchProblem* __restrict__ probs,
                                               const BatchJob* __restrict__ jobs,

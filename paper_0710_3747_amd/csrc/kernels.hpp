@@ -28,7 +28,7 @@ struct BatchProblem {
     double* P;
     double* N;
     uint64_t seed;
-    int32_t M, polarized, init, gsize;   // gsize 1 with M <= tile bits: held in LDS
+    int32_t M, polarized, init, gsize;   // gsize 1 with M < tile bits: one workgroup's
     // one workgroup's: stage ranges as ResidentJob
     int32_t obs_stage0, pro_stage0, pro_nstage, step_stage0, step_nstage, last_stage0;
     // gang: pass templates, launch list (template, step offset), tiles
@@ -94,9 +94,9 @@ hipError_t launch_pass(const PassShape& sh, void* psi, const DevPass* passes,
                        int ch, hipStream_t st);
 // Persistent batch launch over `nslots` workgroups (all resident at once);
 // sync: kSyncGangs + ngangs integers; a gang-barrier time-out is or-ed into
-// `*status`.  half:
-// gangs run half-tile passes (two workgroups per CU) and problems held in
-// LDS have at most tile bits - 1 sites.  Launch shape: batch_shape.
+// `*status`.  half: gangs run half-tile passes (two workgroups per CU).
+// One-workgroup problems have at most tile bits - 1 sites.  Launch shape:
+// batch_shape.
 template <typename T>
 hipError_t launch_batch(int nslots, bool half, const BatchProblem* probs, const BatchJob* jobs,
                         const int* job_start, const DevPass* passes, const DevStage* stages,

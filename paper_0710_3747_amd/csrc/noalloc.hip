@@ -14,7 +14,8 @@
 namespace spinqp {
 
 // 1 MiB of FP64 partial sums: 2 values per workgroup per step slot, enough
-// for 1024 workgroups x 64 step slots.  Each GPU holds its own copy for the
+// for the 4 steps that one launch can measure with the most workgroups there
+// are, 2^14 (64 step slots with 1024).  Each GPU holds its own copy for the
 // life of the process.
 constexpr size_t kNoAllocScratchDoubles = size_t(1) << 17;
 static_assert(kNoAllocScratchDoubles * sizeof(double) == SPIN_NOALLOC_SCRATCH_BYTES,
