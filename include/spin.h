@@ -278,10 +278,10 @@ enum {
  * used since, and calls with other states, seeds or outputs reuse the tables
  * of their couplings).  Problems larger than one workgroup's
  * tile run as gangs of workgroups that meet at bounded device-wide barriers,
- * so batched launches with such problems run one after the other on a device
- * (others overlap as their streams allow); if a
- * barrier times out, the problem's P is set to NaN and spin_batch_status
- * reports it.  Errors as spin_trotter_evolve (plus SPIN_EINVAL for a bad
+ * so a batched launch with such problems runs beside no other batched launch
+ * on a device, whatever their streams (launches without such problems overlap
+ * each other); if a barrier times out, the problem's P is set to NaN and
+ * spin_batch_status reports it.  Errors as spin_trotter_evolve (plus SPIN_EINVAL for a bad
  * init or a basis index >= 2^M), reported for the first offending problem.
  */
 int spin_trotter_evolve_batch(const spin_problem *probs, int32_t n, const spin_coupling *J_all,

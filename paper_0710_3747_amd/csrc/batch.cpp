@@ -44,10 +44,13 @@ struct BatchCache {
     hipStream_t side = nullptr;
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
+    hipEvent_t end = nullptr;   // of the latest launch, if it has no gangs
+    bool awaited = false;       // listed in g_gangless
     size_t bytes = 0;
     ~BatchCache() {
         // its latest launch may still run
         if (side) (void)hipStreamSynchronize(side);
+        if (end) (void)hipEventDestroy(end);
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
         if (side) (void)hipStreamDestroy(side);
@@ -83,12 +86,15 @@ static std::list<std::pair<std::vector<double>, std::shared_ptr<const BatchTable
 // Per device: sticky status word of the persistent launches (non-zero once a
 // gang barrier has timed out), read and cleared by spin_batch_status.
 static std::map<int, int*> g_status;
-// Per device: the end of the latest persistent launch with gangs.  A gang waits
-// for its members, so the launch's workgroups must all find a slot: such launches
-// on several streams run one after the other.  Launches without gangs end by
-// themselves and are not chained.
+// Per device: the end of the latest persistent launch with gangs, and the calls
+// whose launches without gangs no later one with gangs waits for yet.  A gang
+// waits for its members, so the launch's workgroups must all find a slot: it
+// runs beside no other persistent launch of any stream (one that held some of
+// the slots for long would look like a gang that stands still).  Launches without
+// gangs overlap each other.
 static std::mutex g_launch_mu;
 static std::map<int, hipEvent_t> g_last_launch;
+static std::map<int, std::vector<std::weak_ptr<BatchCache>>> g_gangless;
 
 static int status_word(int dev, int** out) {
     std::lock_guard<std::mutex> lk(g_bmu);
@@ -117,6 +123,7 @@ void release_batch_caches() {
         for (auto& kv : g_last_launch)
             if (kv.second) (void)hipEventDestroy(kv.second);
         g_last_launch.clear();
+        g_gangless.clear();
     }
     for (auto& kv : g_status)
         if (kv.second) (void)hipFree(kv.second);
@@ -519,12 +526,35 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
                                bc->tables->ngangs, status, n_steps, s);
     };
     std::lock_guard<std::mutex> launch_lock(g_launch_mu);
-    hipEvent_t unchained = nullptr;
     const bool gangs = bc->tables->ngangs > 0;
-    hipEvent_t& last = gangs ? g_last_launch[dev] : unchained;
+    hipEvent_t& last = g_last_launch[dev];
+    hipEvent_t& end = gangs ? last : bc->end;
     const bool first = last == nullptr;
-    if (gangs && first && hipEventCreateWithFlags(&last, hipEventDisableTiming) != hipSuccess)
+    if (!end && hipEventCreateWithFlags(&end, hipEventDisableTiming) != hipSuccess)
         return fail(SPIN_EHIP, "event create failed");
+    std::vector<std::weak_ptr<BatchCache>>& gangless = g_gangless[dev];
+    // the launches that this one waits for
+    auto chain = [&](hipStream_t s) {
+        hipError_t e = first ? hipSuccess : hipStreamWaitEvent(s, last, 0);
+        if (!gangs) return e;
+        for (const std::weak_ptr<BatchCache>& w : gangless)
+            if (const std::shared_ptr<BatchCache> other = w.lock()) {     // else it has ended
+                if (e == hipSuccess) e = hipStreamWaitEvent(s, other->end, 0);
+                other->awaited = false;
+            }
+        gangless.clear();
+        return e;
+    };
+    auto launched = [&](hipStream_t s) {
+        if (!gangs && !bc->awaited) {
+            if (gangless.size() >= 2 * kCallsKept)
+                gangless.erase(std::remove_if(gangless.begin(), gangless.end(), [](auto& w) { return w.expired(); }),
+                               gangless.end());
+            gangless.push_back(bc);
+            bc->awaited = true;
+        }
+        return hipEventRecord(end, s);
+    };
     hipError_t e = hipSuccess;
     if (use_graph) {
         // capture on a library stream ordered after the caller's stream
@@ -545,16 +575,16 @@ static int batch_persistent(const spin_problem* probs, const std::vector<int>& s
             return fail(SPIN_EHIP, "event create failed");
         e = hipEventRecord(ev, st);
         if (e == hipSuccess) e = hipStreamWaitEvent(bc->side, ev, 0);
-        if (e == hipSuccess && !first) e = hipStreamWaitEvent(bc->side, last, 0);
+        if (e == hipSuccess) e = chain(bc->side);
         if (e == hipSuccess) e = hipGraphLaunch(bc->exec, bc->side);
-        if (e == hipSuccess && gangs) e = hipEventRecord(last, bc->side);
+        if (e == hipSuccess) e = launched(bc->side);
         if (e == hipSuccess) e = hipEventRecord(ev, bc->side);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, ev, 0);
         (void)hipEventDestroy(ev);
     } else {
-        if (!first) e = hipStreamWaitEvent(st, last, 0);
+        e = chain(st);
         if (e == hipSuccess) e = enqueue(st);
-        if (e == hipSuccess && gangs) e = hipEventRecord(last, st);
+        if (e == hipSuccess) e = launched(st);
     }
     if (e != hipSuccess) return fail(SPIN_EHIP, std::string("batch launch: ") + hipGetErrorString(e));
     return SPIN_OK;

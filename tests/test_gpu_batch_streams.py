@@ -93,6 +93,29 @@ def test_batches_without_gangs_overlap(M):
     assert running
 
 
+@pytest.mark.parametrize("gangs_first", [False, True])
+def test_gangs_run_beside_no_other_batch(gangs_first):
+    """A gang's launch needs all its slots: it starts after a call without gangs
+    that another stream runs, and such a call starts after it."""
+    import torch
+    note("gangs and others", gangs_first)
+    dt = 0.01
+    M, long_steps = (15, 10000) if gangs_first else (10, 100000)      # about a third of a second
+    J = workloads.chain(M)
+    long, short = problems(C64, [M], long_steps, J), problems(C64, [10 if gangs_first else 15], 3)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    spq.spin_trotter_evolve_batch(short, C64, dt, 3, stream=b.cuda_stream)
+    spq.spin_trotter_evolve_batch(long, C64, dt, long_steps, stream=a.cuda_stream)
+    torch.cuda.synchronize()
+    spq.spin_trotter_evolve_batch(long, C64, dt, long_steps, stream=a.cuda_stream)
+    assert not a.query()
+    spq.spin_trotter_evolve_batch(short, C64, dt, 3, stream=b.cuda_stream)
+    b.synchronize()
+    assert a.query()
+    assert spq.spin_batch_status() == 0
+    check_against_single_runs(C64, short, dt, 3)
+
+
 def test_problems_without_couplings_share_the_slots():
     """512 problems of 11 sites without couplings take less time than with a chain."""
     import torch
